@@ -69,6 +69,10 @@ constexpr int kAlg2 = 0, kMixedOrders = 1, kWithinJoin = 2, kLinestrings = 3;
 constexpr uint32_t kSideS = 0x80000000u;   // resident-object key: the object is from S
 constexpr uint32_t kNone = 0xffffffffu;    // no resident object / no upper key bound
 
+// Most pairs a wave takes at a time when they are screened (the offsets of
+// the open ones are kept as bytes).
+constexpr uint32_t kScreenGrab = 256;
+
 struct BatchArgs {
     FilterArgs f;
     unsigned int *xhead;         // pairs taken from XCD k's range: xhead[k * kCtrStride]
@@ -82,6 +86,7 @@ struct BatchArgs {
     // workgroup bin (Alg. 2 only): pairs whose shorter object spans at least
     // wg_min intervals in a list (kNone: no workgroup bin)
     uint32_t wg_min;
+    uint32_t screened;           // only pairs whose verdict is kPending are open
     uint32_t qcap;               // queue entries per XCD range
     unsigned int *qfill;         // big pairs binned into XCD k's queue: qfill[k * kCtrStride]
     unsigned int *qhead;         // queue entries taken by workgroups: qhead[k * kCtrStride]
@@ -108,7 +113,7 @@ struct BatchArgs {
 // range (the range holding the pair) and marks their verdict bytes; a pair
 // that finds its queue full is marked for the wave bin instead.
 constexpr uint8_t kQueued = 0xFE;     // verdict byte of a pair in a workgroup queue
-constexpr uint8_t kOverflow = 0xFD;   // verdict byte of a workgroup-bin pair left to the wave bin
+constexpr uint8_t kOverflow = kPending;   // of a workgroup-bin pair left to the wave bin (screened: of every pair left)
 
 __device__ __forceinline__ bool wg_bin(uint32_t mr, uint32_t ms, uint32_t tile, uint32_t wg_min) {
     return mr >= tile && ms >= tile && min(mr, ms) >= wg_min;
@@ -132,7 +137,7 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
          base += stride) {
         const uint64_t p = base + lane;
         bool big = false;
-        if (p < a.n_pairs) {
+        if (p < a.n_pairs && (!b.screened || a.verdict[p] == kPending)) {
             const uint32_t r = a.r[p], s = a.s[p];
             if ((r < a.n_r) & (s < a.n_s)) {
                 const uint32_t mr = uint32_t(max(a.Ar.off[r + 1] - a.Ar.off[r], a.Fr.off[r + 1] - a.Fr.off[r]));
@@ -998,6 +1003,7 @@ void k_batched(BatchArgs b) {
     uint32_t cached = kNone;   // resident object id | side bit
     uint32_t pcached = kNone;  // object whose piece is resident (512-interval Alg. 2 instance)
     __shared__ uint32_t piece_words[kWavesPerBlock][8];
+    __shared__ uint8_t open_at[kWavesPerBlock][kScreenGrab];
 
     // ---- pairs in input order: each XCD drains its own contiguous range,
     // then helps the others
@@ -1025,7 +1031,29 @@ void k_batched(BatchArgs b) {
             if (g0 >= hi) break;
             const uint64_t g1 = min(hi, g0 + grab);
             if (hi - g1 < pb->tail_pairs) grab = pb->tail_grab;
-            const uint64_t p = g0 + lane;
+            // Screened: the grab's open pairs (few of them) are collected first, as
+            // offsets from g0, so that a round of the loop below has a pair for
+            // most lanes.
+            uint32_t n_open = uint32_t(g1 - g0);
+            if (MODE == kAlg2 && pb->screened) {
+                const uint8_t __attribute__((address_space(1))) *vb =
+                    (const uint8_t __attribute__((address_space(1))) *)a.verdict + g0;
+                uint32_t cnt = 0;
+                wave_lds_sync();
+#pragma unroll
+                for (uint32_t q = 0; q < kScreenGrab; q += 64) {
+                    const bool open = q + lane < n_open && vb[q + lane] == kPending;
+                    const uint64_t m = __ballot(open);
+                    if (open) open_at[w][cnt + uint32_t(__popcll(m & ((1ull << lane) - 1)))] = uint8_t(q + lane);
+                    cnt += uint32_t(__popcll(m));
+                }
+                wave_lds_sync();
+                n_open = cnt;
+            }
+            for (uint32_t o0 = 0; o0 < n_open; o0 += 64) {
+            const bool in = o0 + lane < n_open;
+            uint64_t p = g0 + o0 + lane;
+            if (MODE == kAlg2 && pb->screened) p = g0 + (in ? open_at[w][o0 + lane] : 0u);
             bool seq = false, wave = false;
             // lane k's verdict for pair g0 + k, stored once per grab (a
             // store per pair would make each pair wait for the last one's)
@@ -1033,8 +1061,8 @@ void k_batched(BatchArgs b) {
             // lane k's pair: its lists with X the object to keep resident
             PairLists m{};
             uint32_t key = kNone;
-            bool mine = p < g1;   // false for a pair the workgroup bin answers
-            if (p < g1) {
+            bool mine = in;   // false for a pair the workgroup bin answers
+            if (in) {
                 const uint32_t r = gload32(a.r, p), s = gload32(a.s, p);
                 if ((r < a.n_r) & (s < a.n_s)) {
                     const uint64_t ar0 = gload64(a.Ar.off, r), fr0 = gload64(a.Fr.off, r);
@@ -1044,7 +1072,7 @@ void k_batched(BatchArgs b) {
                     const uint32_t nas = uint32_t(gload64(a.As.off, s + 1) - as0);
                     const uint32_t nfs = uint32_t(gload64(a.Fs.off, s + 1) - fs0);
                     const uint32_t mr = max(nar, nfr), ms = max(nas, nfs);
-                    if (MODE == kAlg2 && wg_bin(mr, ms, TILE, pb->wg_min) &&
+                    if (MODE == kAlg2 && !pb->screened && wg_bin(mr, ms, TILE, pb->wg_min) &&
                         ((const uint8_t __attribute__((address_space(1))) *)a.verdict)[p] != kOverflow)
                         mine = false;
                     // R resident when its lists fit a tile; else S when its
@@ -1097,6 +1125,7 @@ void k_batched(BatchArgs b) {
                 c_th += vv == APRIL_TH;
                 c_ind += vv == APRIL_INDECISIVE;
             }
+            }
         }
     }
 
@@ -1126,9 +1155,15 @@ int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
     const int dflt = TILE >= 512 ? 4 : per_cu;
     uint64_t blocks = uint64_t(cus) * std::min(per_cu, dflt);
     if (waves) blocks = std::max<uint64_t>(1, (waves + kWavesPerBlock - 1) / kWavesPerBlock);
-    // a range is near its end once its waves have about two full grabs each left
     BatchArgs bb = b;
-    bb.tail_pairs = 2ull * b.grab * kWavesPerBlock * ((blocks + b.xcds - 1) / b.xcds);
+    if (b.screened) {
+        // about one pair in fifteen is open: larger grabs, but two or more per wave
+        const uint64_t per_wave = b.f.n_pairs / (2 * blocks * kWavesPerBlock);
+        bb.grab = uint32_t(std::min<uint64_t>(kScreenGrab, std::max<uint64_t>(8, per_wave)));
+        bb.tail_grab = std::max(8u, bb.grab / 4);
+    }
+    // a range is near its end once its waves have about two full grabs each left
+    bb.tail_pairs = 2ull * bb.grab * kWavesPerBlock * ((blocks + b.xcds - 1) / b.xcds);
     if (MODE == kAlg2 && b.wg_min != kNone) {
         const uint64_t bin_blocks = std::min<uint64_t>((b.f.n_pairs + 255) / 256, uint64_t(cus) * 8);
         k_bin<<<dim3(uint32_t(bin_blocks)), dim3(256), 0, stream>>>(bb, TILE);
@@ -1237,10 +1272,11 @@ static void set_wg_bin(BatchArgs &b, uint32_t wg_min, void *workspace) {
     b.queue = reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + kCtrBytes + kQueueCtrBytes);
     b.qcap = uint32_t(kBigQueueCap / b.xcds);
     b.times = nullptr;
+    b.screened = 0;
 }
 
 int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, void *workspace,
-                   hipStream_t stream) {
+                   hipStream_t stream, const april_lists_t *R, const april_lists_t *S) {
     const uint32_t tile = o.tile ? o.tile : 256;
     // default chunk: 2 elements per lane per step (with chunk skipping, also
     // the best for 512-interval tiles: skewed workload 61.5 against 64.5 ms
@@ -1272,6 +1308,12 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
     if (wg_min != kNone || b.times) {
         k_zero_queue_ctrs<<<1, 2 * kMaxCtrs, 0, stream>>>(b.qfill);
         APRIL_HIP_TRY(hipGetLastError());
+    }
+    if (tile != 128 && tile != 256 && tile != 512) return fail(APRIL_E_INVALID, "tile must be 128, 256 or 512");
+    if (chunk != 1 && chunk != 2 && chunk != 4) return fail(APRIL_E_INVALID, "chunk must be 1, 2 or 4");
+    if (R && S && can_screen(R, S, a.n_pairs)) {
+        if (int rc = launch_screen(R, S, a, cus, workspace, stream)) return rc;
+        b.screened = 1;
     }
     switch (tile) {
         case 128: return launch_t<128>(b, chunk, cus, o.waves, stream);

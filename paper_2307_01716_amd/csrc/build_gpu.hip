@@ -633,18 +633,19 @@ extern "C" int april_build_lists_gpu(const april_grid_t *grid, const double *xy,
     L->d.start_f = reinterpret_cast<uint32_t *>(p); p += b_f;
     L->d.end_f = reinterpret_cast<uint32_t *>(p);
     L->d.bytes = total;
-    unsigned int *d_bad_slot = reinterpret_cast<unsigned int *>(d_small + 4);
-    e = hipMemsetAsync(d_bad_slot, 0, 4, s);
+    unsigned int *d_bad_slot = reinterpret_cast<unsigned int *>(d_small + 4);   // then: longest list, long A-lists
+    e = hipMemsetAsync(d_bad_slot, 0, 24, s);
     if (e == hipSuccess) {
         k_scatter<<<blocks_for(ne), kThreads, 0, s>>>(ca, cls, ne, na, ai, nf, fi, n, d_tot, n_a, n_f, L->d.off_a,
                                                       L->d.off_f, L->d.start_a, L->d.end_a, L->d.start_f,
                                                       L->d.end_f, d_bad_slot);
         e = hipGetLastError();
     }
-    unsigned int bad_slot = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&bad_slot, d_bad_slot, 4, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess && launch_list_stats(L->d.off_a, L->d.off_f, n, d_small + 5, s)) e = hipErrorUnknown;
+    uint64_t last[3] = {0, 0, 0};   // bad_slot, longest list, A-lists that need a coarse table
+    if (e == hipSuccess) e = hipMemcpyAsync(last, d_bad_slot, 24, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);   // the scratch is released after this call
-    if (e != hipSuccess || bad_slot) {
+    if (e != hipSuccess || last[0]) {
         (void)hipFree(L->d.block);
         delete L;
         return e != hipSuccess ? fail(APRIL_E_HIP, std::string("build: ") + hipGetErrorString(e))
@@ -657,6 +658,15 @@ extern "C" int april_build_lists_gpu(const april_grid_t *grid, const double *xy,
     L->n_f = n_f;
     L->device = dev;
     L->codec = APRIL_CODEC_RAW;
+    L->max_len = uint32_t(std::min<uint64_t>(last[1], 0xfffffffeull));
+    if (int rc = launch_summaries(L, last[2], L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)) {
+        april_lists_free(L);
+        return rc;
+    }
+    if (e = hipStreamSynchronize(s); e != hipSuccess) {   // complete on return, for any stream
+        april_lists_free(L);
+        return fail(APRIL_E_HIP, std::string("build: ") + hipGetErrorString(e));
+    }
     *out = L;
     return APRIL_OK;
 }

@@ -40,6 +40,8 @@ struct CArgs {
     unsigned long long *counts;
     unsigned int *xhead;
     uint32_t xcds;
+    uint32_t screened;    // only pairs whose verdict is kPending are open
+    uint32_t grab;        // pairs taken at a time (at most 64)
     uint32_t search_min;
     uint32_t first_cap;   // X intervals decoded before a join's first test (at most TILE)
     // decode cache: per wave, R's A and F lists of up to cache_cap intervals
@@ -298,12 +300,14 @@ __global__ __launch_bounds__(kBlock) void k_filter_vbyte(CArgs a) {
         if (k > 0 && range_drained(a.xhead, seg, lo, hi, lane)) continue;
         for (;;) {
             unsigned int got = 0;
-            if (lane == 0) got = atomicAdd(&a.xhead[seg * kCtrStride], 64u);
+            if (lane == 0) got = atomicAdd(&a.xhead[seg * kCtrStride], a.grab);
             const uint64_t g0 = lo + uniform(__shfl(got, 0));
             if (g0 >= hi) break;
-            const uint32_t cnt = uint32_t(min<uint64_t>(64, hi - g0));
-            for (uint32_t i = 0; i < cnt; i++) {
-                const uint64_t p = g0 + i;
+            const uint32_t cnt = uint32_t(min<uint64_t>(a.grab, hi - g0));
+            uint64_t todo = __ballot(lane < cnt && (!a.screened || a.verdict[g0 + lane] == kPending));
+            while (todo) {
+                const uint64_t p = g0 + uint32_t(__builtin_ctzll(todo));
+                todo &= todo - 1;
                 // the list arrays are read from the argument segment through a
                 // pointer the compiler cannot see through, so they hold no
                 // scalar registers between their uses
@@ -536,6 +540,23 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
     // (one by default: most joins of overlapping objects end within it)
     a.first_cap = std::min<uint32_t>(tile, 130u * (o.chunk ? o.chunk : 1u));
     const uint64_t blocks = uint64_t(cus) * kVbyteBlocksPerCu;
+    a.grab = 64;
+    a.screened = 0;
+    if ((tile == 256 || tile == 512 || tile == 1024) && can_screen(R, S, n_pairs)) {
+        FilterArgs f{};
+        f.Ar = {R->d.off_a, nullptr, nullptr};
+        f.r = d_r;
+        f.s = d_s;
+        f.n_pairs = n_pairs;
+        f.n_r = R->n;
+        f.n_s = S->n;
+        f.verdict = d_verdict;
+        f.counts = counts;
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream)) return rc;
+        a.screened = 1;
+        // few pairs are left: four grabs per wave where there are enough
+        a.grab = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(8, n_pairs / (4 * blocks * kWavesPerBlock))));
+    }
     // decode cache: cache_cap intervals per list for every wave of the grid,
     // from the caller's workspace (APRIL_WS_DECODE_CACHE) or stream-ordered;
     // without one (allocation refused) every pair decodes both objects

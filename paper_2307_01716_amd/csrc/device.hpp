@@ -61,6 +61,9 @@ constexpr uint64_t kBigQueueCap = 1ull << 20;
 // at-scale one (longest list 3,588 intervals) 4096 leaves the bin empty, so
 // the binning pass is skipped.
 constexpr uint32_t kDefaultWgMin = 4096;
+// Verdict byte of a pair that screening left to the join kernels, and that no
+// queue has taken.
+constexpr uint8_t kPending = 0xFD;
 // Workspace part of the static scratch (april_filter_pairs_static): enough
 // for any filter call's scratch on raw lists.
 constexpr uint64_t kStaticWorkspaceBytes = (4ull << 20) + (64ull << 10);
@@ -123,8 +126,18 @@ struct BatchedShape {
 void batched_defaults(april_filter_opts_t &o, const BatchedShape &shape);
 // XCDs of a device with `cus` compute units (32 CUs each on gfx950)
 int xcd_count(int cus);
+// R, S: screen the pairs first (null: lists without summaries)
 int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, void *workspace,
-                   hipStream_t stream);
+                   hipStream_t stream, const april_lists_t *R, const april_lists_t *S);
+
+// Screening (screen.hip): worth it, and possible, for a call's lists?
+bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs);
+// Decide what the lists' summaries decide: verdicts of all pairs (kPending
+// where the join kernels have to look), and the decided pairs' counts into the
+// slots at `counters` (already cleared) when f.counts is set.  Of f only the
+// pairs, the verdicts and R's raw A-lists are read.
+int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
+                  hipStream_t stream);
 // Kernel arguments of a filter call on device lists R and S (raw codec).
 FilterArgs make_args(const april_lists_t *R, const april_lists_t *S, const uint32_t *d_r, const uint32_t *d_s,
                      uint64_t n_pairs, uint8_t *d_verdict, unsigned long long *counts);

@@ -126,6 +126,7 @@ struct PlainArgs {
     FilterArgs f;
     unsigned int *ctr;   // scratch slots that sum the counts
     uint32_t xcds;
+    uint32_t screened;   // only pairs whose verdict is kPending are open
 };
 
 // 80 SGPRs at most: the hardware allocates SGPRs in blocks of 16, and
@@ -143,7 +144,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void k
     const uint64_t lo = a.n_pairs * xcd / xcds, hi = a.n_pairs * (xcd + 1) / xcds;
     const uint64_t n_waves = uint64_t(nbx) * kWavesPerBlock;
     unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
-    for (uint64_t p = lo + uint64_t(bx) * kWavesPerBlock + w; p < hi; p += n_waves) {
+    // pair by pair, every n_waves-th; which of the wave's next 64 are open is
+    // read by its lanes at once
+    for (uint64_t p0 = lo + uint64_t(bx) * kWavesPerBlock + w; p0 < hi; p0 += 64 * n_waves) {
+    const uint64_t pl = p0 + lane * n_waves;
+    uint64_t todo = __ballot(pl < hi && (!pa.screened || a.verdict[pl] == kPending));
+    while (todo) {
+        const uint64_t p = p0 + uint64_t(__builtin_ctzll(todo)) * n_waves;
+        todo &= todo - 1;
         const uint32_t r = uniform(a.r[p]), s = uniform(a.s[p]);
         uint8_t v;
         if (r >= a.n_r || s >= a.n_s) {
@@ -171,6 +179,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void k
         c_tn += (v == APRIL_TN);
         c_th += (v == APRIL_TH);
         c_ind += (v == APRIL_INDECISIVE);
+    }
     }
     if (a.counts && lane == 0) {
         // the slot pointer is read from the kernel arguments only here, so
@@ -374,12 +383,12 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
         const uint64_t need = batched_workspace_bytes(n_pairs);
         if (o.d_workspace) {
             if (o.workspace_bytes < need) return fail(APRIL_E_INVALID, "workspace too small");
-            return launch_batched(a, o, st->cus, o.d_workspace, stream);
+            return launch_batched(a, o, st->cus, o.d_workspace, stream, R, S);
         }
         void *ws = nullptr;
         hipError_t e = hipMallocAsync(&ws, need, stream);
         if (e != hipSuccess) return fail(APRIL_E_NOMEM, std::string("workspace: ") + hipGetErrorString(e));
-        const int rc = launch_batched(a, o, st->cus, ws, stream);
+        const int rc = launch_batched(a, o, st->cus, ws, stream, R, S);
         APRIL_HIP_TRY(hipFreeAsync(ws, stream));
         return rc;
     }
@@ -396,6 +405,14 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
         }
         k_zero_ctrs<<<1, 64, 0, stream>>>(static_cast<unsigned int *>(ws));
     }
+    uint32_t screened = 0;
+    if (can_screen(R, S, n_pairs)) {
+        if (int rc = launch_screen(R, S, a, st->cus, ws, stream)) {
+            if (ws && !o.d_workspace) (void)hipFreeAsync(ws, stream);
+            return rc;
+        }
+        screened = 1;
+    }
     static int per_cu = 0;   // resident workgroups per CU (same on every gfx950 device)
     if (!per_cu) {
         int q = 0;
@@ -409,7 +426,7 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
     const uint32_t xcds = uint32_t(xcd_count(st->cus));
     uint64_t blocks = std::max<uint64_t>(1, (waves + kWavesPerBlock - 1) / kWavesPerBlock);
     blocks = (blocks + xcds - 1) / xcds * xcds;   // every XCD gets the same number of workgroups
-    PlainArgs pa{a, static_cast<unsigned int *>(ws), xcds};
+    PlainArgs pa{a, static_cast<unsigned int *>(ws), xcds, screened};
     k_filter_plain<4><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(pa);
     hipError_t e = hipGetLastError();
     if (counts) {

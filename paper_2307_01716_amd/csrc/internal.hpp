@@ -47,8 +47,23 @@ struct DeviceArrays {
     uint32_t *bpos_a = nullptr, *bpos_f = nullptr;  // per block: byte offset within the list
     uint64_t n_bytes_a = 0, n_bytes_f = 0, n_blk_a = 0, n_blk_f = 0;
     void *block = nullptr;                          // one allocation holding all of the above
+    // summaries (screen.hip; null: none), in an allocation of their own
+    uint64_t *sum = nullptr;      // kSumEntries (start | end << 32) per object (compressed: per numbered object)
+    uint32_t *slot = nullptr;     // n: number of the object's coarse table (0xffffffff: none)
+    uint32_t *coarse = nullptr;   // the coarse tables
+    void *sum_block = nullptr;
     size_t bytes = 0;
 };
+
+// Entries of an object's summary (screen.hip).
+constexpr uint32_t kSumEntries = 64;
+// A-lists of fewer intervals are screened against as they are; longer ones
+// have a coarse table of 2 KiB, an eighth of such a list (A and F) at most.
+constexpr uint32_t kExact = 512;
+// Compressed lists: objects of fewer A-intervals have neither summary nor
+// table (2.5 KiB, about half of what such a list and its F-list take), so
+// that compression keeps what it saves.
+constexpr uint32_t kVbyteSummaryMin = 1024;
 
 // Encode one list (n intervals) into `out` (appended); block entries into
 // bval/bpos (appended).  Returns the number of bytes written.
@@ -161,6 +176,13 @@ uint64_t vbyte_cache_offset();
 int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const uint32_t *d_r, const uint32_t *d_s,
                         uint64_t n_pairs, uint8_t *d_verdict, unsigned long long *counts,
                         const april_filter_opts_t &o, int cus, void *workspace, hipStream_t stream);
+// Summaries of device lists for screening, see screen.hip.
+int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, const uint32_t *ae, const uint32_t *fs,
+                     const uint32_t *fe, hipStream_t stream);
+// stats[0] = the most intervals in one list, stats[1] = A-lists of kExact intervals or more
+// (both zero before the call).
+int launch_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, unsigned long long *stats,
+                      hipStream_t stream);
 // Alg. 2's bytes per pair on compressed lists (april_alg2_bytes).
 int launch_alg2_vbyte_bytes(const april_lists_t *R, const april_lists_t *S, const uint32_t *d_r,
                             const uint32_t *d_s, uint64_t n_pairs, unsigned long long *d_bytes, int cus,

@@ -178,6 +178,31 @@ int check_lists(uint64_t n, const uint64_t *off_a, const uint32_t *start_a, cons
 
 using namespace april;
 
+// The summaries of an uploaded collection.  Compressed lists are decoded on
+// the device for it, into memory that is given back; without room for that
+// they have none.
+static int upload_summaries(const april_lists_t *h, april_lists_t *L, hipStream_t s) {
+    const bool raw = L->codec == APRIL_CODEC_RAW;
+    uint64_t longer = 0;
+    for (uint64_t k = 0; k < h->n; k++) longer += h->off_a[k + 1] - h->off_a[k] >= (raw ? kExact : kVbyteSummaryMin);
+    if (raw) return launch_summaries(L, longer, L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s);
+    if (!longer) return APRIL_OK;
+    const uint64_t na = std::max<uint64_t>(L->n_a, 1), nf = std::max<uint64_t>(L->n_f, 1);
+    void *tmp = nullptr;
+    if (hipMalloc(&tmp, 8 * (na + nf)) != hipSuccess) {
+        (void)hipGetLastError();
+        return APRIL_OK;
+    }
+    uint32_t *as = static_cast<uint32_t *>(tmp), *ae = as + na, *fs = ae + na, *fe = fs + nf;
+    int rc = launch_decode_lists(L, false, as, ae, s);
+    if (!rc) rc = launch_decode_lists(L, true, fs, fe, s);
+    if (!rc) rc = launch_summaries(L, longer, as, ae, fs, fe, s);
+    const hipError_t e = hipStreamSynchronize(s);
+    (void)hipFree(tmp);
+    if (!rc && e != hipSuccess) return fail(APRIL_E_HIP, std::string("summaries: ") + hipGetErrorString(e));
+    return rc;
+}
+
 extern "C" {
 
 const char *april_last_error(void) { return april::g_last_error.c_str(); }
@@ -365,6 +390,10 @@ int april_lists_to_device(const april_lists_t *h, uint32_t codec, void *stream,
         delete L;
         return fail(APRIL_E_HIP, std::string("upload: ") + hipGetErrorString(rc));
     }
+    if (int rs = upload_summaries(h, L, s)) {
+        april_lists_free(L);
+        return rs;
+    }
     *out = L;
     return APRIL_OK;
 }
@@ -432,6 +461,7 @@ void april_lists_free(april_lists_t *L) {
         (void)hipGetDevice(&cur);
         if (cur != L->device) (void)hipSetDevice(L->device);
         (void)hipFree(L->d.block);
+        if (L->d.sum_block) (void)hipFree(L->d.sum_block);
         if (cur != L->device) (void)hipSetDevice(cur);
     }
     delete L;

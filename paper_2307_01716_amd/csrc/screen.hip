@@ -1,0 +1,504 @@
+// Screening: most candidate pairs are decided from a summary of each object,
+// before any of the join kernels reads the object's lists.
+//
+// Every object of a device collection has a summary of 64 intervals, one per
+// lane of a wavefront, made once when the lists are uploaded or built:
+//   TF, lanes 0..31   its 32 longest F-intervals (those that lie inside an
+//                     A-interval, which APRIL's all do);
+//   H, lanes 32..63   its hull: the A-list with all but its 31 widest gaps
+//                     closed, so every A-interval lies in one of 32.
+// Against the A-list of the other object, X, these give two one-sided tests:
+//   - a TF interval that overlaps A(X): that is an AF overlap, and, as it lies
+//     in an A-interval, an AA overlap too: Alg. 2 answers true hit;
+//   - no H interval overlaps A(X): no A-interval does: true negative.
+// Anything else is left to the join kernels.  X's A-list is held in LDS; for an
+// A-list of more than kExact intervals a coarse table of X stands in for it:
+// its 127 longest A-intervals in the first test (a subset: an overlap with one
+// is an overlap with A(X)), its hull of 127 in the second (a superset).  A
+// wave keeps X while consecutive pairs share their R object; one search of the
+// table by all lanes makes both tests of a pair.
+//
+// The two tests decide 95% of the at-scale join's pairs (98% of its true hits,
+// 92% of its true negatives) and 93% of a partition's, whose lists are
+// fourteen times as long.  32 + 32 intervals, because a summary then is one
+// coalesced 512-byte load and a pair one search; 16 + 16 leave twice as many
+// pairs to the joins, each of which costs several times a screened pair.
+//
+// Measured on one MI355X, whole calls without and with screening: at scale
+// (200k x 200k, 4.5M pairs) 1.96 and 0.79 ms, of which this kernel 0.49; the
+// plain schedule at 100k x 100k 1.47 and 0.46 ms; a partition of 10k x 10k
+// objects of 2,250 A-intervals 2.50 and 0.57 ms raw, 8k x 8k 3.36 and 0.81 ms
+// compressed; 40k x 40k with 300 complex objects a side 1.98 and 0.91 ms.
+// Making the summaries takes 0.61 ms for 200k objects.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "device.hpp"
+#include "internal.hpp"
+
+namespace april {
+namespace {
+
+constexpr uint32_t kSumHalf = kSumEntries / 2;    // TF intervals; hull intervals
+constexpr uint32_t kCoarse = 128;                 // entries per coarse list, the last one padding
+constexpr uint32_t kNoSlot = 0xffffffffu;
+// longest list that a single wave summarizes; longer ones get 16 waves (a list
+// is read twice per selection, and the skewed workload has lists of 200,000)
+constexpr uint32_t kOneWave = 2048;
+
+struct SumBuild {
+    ListView A, F;
+    uint64_t n;
+    uint64_t *sum;
+    uint32_t *slot, *coarse, *taken;   // taken[0]: coarse tables given out; taken[1]: objects queued
+    uint32_t *queue;                   // objects with a longer list than kOneWave
+    uint32_t tables, queue_cap;
+    uint32_t by_slot, min_len;         // compressed lists: objects of min_len A-intervals or more have a summary,
+                                       // numbered like their coarse tables
+};
+
+// Value bins for the selection of the largest: the position of the leading
+// bit and the three bits below it, so a bin spans 12.5%.
+__device__ __forceinline__ uint32_t bin_of(uint32_t v) {
+    v = max(v, 1u);
+    const uint32_t b = 31u - uint32_t(__builtin_clz(v));
+    return b * 8 + (b >= 3 ? (v >> (b - 3)) & 7u : (v << (3 - b)) & 7u);
+}
+
+template <int W>
+__device__ __forceinline__ void group_sync() {
+    if (W == 1) wave_lds_sync();
+    else __syncthreads();
+}
+
+// Selection of the K largest of m values by bins: every value in a bin above
+// `tie`, and the first `take` (by position) of those in it.
+struct Cut {
+    uint32_t tie, take;
+};
+
+__device__ __forceinline__ Cut find_cut(const uint32_t *hist, uint32_t K, uint32_t lane) {
+    // lane l holds bins 255 - 4l ... 252 - 4l
+    uint32_t c[4], s = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++) s += c[i] = hist[255 - 4 * lane - i];
+    uint32_t before = s;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(before, d);
+        if (lane >= uint32_t(d)) before += o;
+    }
+    before -= s;
+    uint32_t tie = 0, take = 0;
+    bool mine = false;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        if (!mine && before <= K && before + c[i] > K) {
+            mine = true;
+            tie = 255 - 4 * lane - i;
+            take = K - before;
+        }
+        before += c[i];
+    }
+    const uint64_t at = __ballot(mine);
+    if (!at) return Cut{0, 0xffffffffu};   // at most K values: all of them
+    const int l = int(__builtin_ctzll(at));
+    return Cut{uniform(__shfl(tie, l)), uniform(__shfl(take, l))};
+}
+
+// The histogram of value(0 .. m).
+template <int W, class V>
+__device__ __forceinline__ void histogram(uint32_t *hist, uint32_t m, V value, uint32_t tid) {
+    group_sync<W>();
+    for (uint32_t i = tid; i < 256; i += 64 * W) hist[i] = 0;
+    group_sync<W>();
+    for (uint32_t j = tid; j < m; j += 64 * W) atomicAdd(&hist[bin_of(value(j))], 1u);
+    group_sync<W>();
+}
+
+// put(rank, j) for every selected j, ranks in the order of positions.  Wave w
+// takes a contiguous share of the positions.
+template <int W, class V, class P>
+__device__ __forceinline__ void select(Cut cut, uint32_t m, V value, P put, uint32_t (*part)[2], uint32_t w,
+                                       uint32_t lane) {
+    const uint32_t share = W == 1 ? m : ((m + W - 1) / W + 63) / 64 * 64;
+    const uint32_t j0 = min(m, w * share), j1 = min(m, j0 + share);
+    uint32_t above = 0, ties = 0;   // selected, tied, in the positions before
+    if (W > 1) {
+        uint32_t a = 0, t = 0;
+        for (uint32_t j = j0; j < j1; j += 64) {
+            const uint32_t b = j + lane < j1 ? bin_of(value(j + lane)) : 0u;
+            a += uint32_t(__popcll(__ballot(j + lane < j1 && b > cut.tie)));
+            t += uint32_t(__popcll(__ballot(j + lane < j1 && b == cut.tie)));
+        }
+        __syncthreads();
+        if (lane == 0) {
+            part[w][0] = a;
+            part[w][1] = t;
+        }
+        __syncthreads();
+        for (uint32_t k = 0; k < w; k++) {
+            above += part[k][0];
+            ties += part[k][1];
+        }
+    }
+    uint32_t rank = above + min(ties, cut.take);
+    const uint64_t below = (1ull << lane) - 1;
+    for (uint32_t j = j0; j < j1; j += 64) {
+        const bool in = j + lane < j1;
+        const uint32_t b = in ? bin_of(value(j + lane)) : 0u;
+        const bool tied = in && b == cut.tie;
+        const uint64_t mt = __ballot(tied);
+        const bool sel = in && (b > cut.tie || (tied && ties + uint32_t(__popcll(mt & below)) < cut.take));
+        const uint64_t ms = __ballot(sel);
+        if (sel) put(rank + uint32_t(__popcll(ms & below)), j + lane);
+        ties += uint32_t(__popcll(mt));
+        rank += uint32_t(__popcll(ms));
+    }
+}
+
+struct SumLds {
+    uint32_t hist[256];
+    uint32_t sum[2 * kSumEntries];   // (start, end) pairs
+    uint32_t coarse[4 * kCoarse];
+    uint32_t part[16][2];
+    uint32_t slot;
+};
+
+// The hull of X.A with K gaps kept: hull interval i ends at the i-th kept gap
+// and the next one starts behind it.  end/start: its arrays, `step` words
+// apart.
+template <int W>
+__device__ __forceinline__ void hull(const uint32_t *as, const uint32_t *ae, uint32_t na, Cut cut, uint32_t K,
+                                     uint32_t *start, uint32_t *end, uint32_t step, SumLds &l, uint32_t w,
+                                     uint32_t lane) {
+    auto gap = [&](uint32_t j) { return as[j + 1] - ae[j]; };
+    if (na == 0) return;
+    if (w == 0 && lane == 0) {
+        start[0] = as[0];
+        end[min(K, na - 1) * step] = ae[na - 1];
+    }
+    select<W>(cut, na - 1, gap, [&](uint32_t i, uint32_t j) {
+        end[i * step] = ae[j];
+        start[(i + 1) * step] = as[j + 1];
+    }, l.part, w, lane);
+}
+
+// One object's summary, and its coarse table when `slot` is given.  Entries
+// not used are empty on the summary's side (end 0) and beyond every key on the
+// table's (0xFFFFFFFF), as in the joins' LDS tiles.
+template <int W>
+__device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &l, uint32_t w, uint32_t lane) {
+    const uint32_t tid = w * 64 + lane;
+    const uint64_t a0 = b.A.off[k], f0 = b.F.off[k];
+    const uint32_t na = uint32_t(b.A.off[k + 1] - a0), nf = uint32_t(b.F.off[k + 1] - f0);
+    const uint32_t *as = b.A.s + a0, *ae = b.A.e + a0, *fs = b.F.s + f0, *fe = b.F.e + f0;
+    group_sync<W>();
+    for (uint32_t i = tid; i < 2 * kSumEntries; i += 64 * W) l.sum[i] = (i & 1) ? 0u : 0xffffffffu;
+    if (slot != kNoSlot)
+        for (uint32_t i = tid; i < 4 * kCoarse; i += 64 * W) l.coarse[i] = 0xffffffffu;
+    // TF
+    auto flen = [&](uint32_t j) { return fe[j] - fs[j]; };
+    histogram<W>(l.hist, nf, flen, tid);
+    select<W>(find_cut(l.hist, kSumHalf, lane), nf, flen, [&](uint32_t i, uint32_t j) {
+        l.sum[2 * i] = fs[j];
+        l.sum[2 * i + 1] = fe[j];
+    }, l.part, w, lane);
+    // H, and the coarse hull from the same histogram
+    auto gap = [&](uint32_t j) { return as[j + 1] - ae[j]; };
+    const uint32_t ng = na ? na - 1 : 0u;
+    histogram<W>(l.hist, ng, gap, tid);
+    hull<W>(as, ae, na, find_cut(l.hist, kSumHalf - 1, lane), kSumHalf - 1, l.sum + kSumEntries,
+            l.sum + kSumEntries + 1, 2, l, w, lane);
+    if (slot != kNoSlot) {
+        hull<W>(as, ae, na, find_cut(l.hist, kCoarse - 2, lane), kCoarse - 2, l.coarse + 3 * kCoarse,
+                l.coarse + kCoarse, 1, l, w, lane);
+        auto alen = [&](uint32_t j) { return ae[j] - as[j]; };
+        histogram<W>(l.hist, na, alen, tid);
+        select<W>(find_cut(l.hist, kCoarse - 1, lane), na, alen, [&](uint32_t i, uint32_t j) {
+            l.coarse[i] = ae[j];
+            l.coarse[2 * kCoarse + i] = as[j];
+        }, l.part, w, lane);
+    }
+    group_sync<W>();
+    // a TF interval counts only inside an A-interval (lists that were not
+    // validated may hold others): the first A-interval that ends above its start
+    if (w == 0) {
+        uint32_t s = l.sum[2 * lane], e = l.sum[2 * lane + 1];
+        if (lane < kSumHalf && e != 0) {
+            uint32_t lo = 0, hi = na;
+            while (lo < hi) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (ae[mid] > s) hi = mid;
+                else lo = mid + 1;
+            }
+            if (lo == na || as[lo] > s || ae[lo] < e) e = 0;
+        }
+        const uint64_t at = b.by_slot ? slot : k;
+        b.sum[at * kSumEntries + lane] = (uint64_t(e) << 32) | s;
+    }
+    if (slot != kNoSlot)
+        for (uint32_t i = tid; i < 4 * kCoarse; i += 64 * W) b.coarse[uint64_t(slot) * 4 * kCoarse + i] = l.coarse[i];
+}
+
+// Objects whose lists one wave summarizes; the others are queued.  Numbers
+// the coarse tables (in no particular order).
+__global__ __launch_bounds__(kBlock) void k_summaries(SumBuild b) {
+    __shared__ SumLds lds[kWavesPerBlock];
+    const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    const uint64_t waves = uint64_t(gridDim.x) * kWavesPerBlock;
+    for (uint64_t k = uint64_t(blockIdx.x) * kWavesPerBlock + w; k < b.n; k += waves) {
+        const uint32_t na = uint32_t(b.A.off[k + 1] - b.A.off[k]), nf = uint32_t(b.F.off[k + 1] - b.F.off[k]);
+        uint32_t slot = kNoSlot;
+        if (na >= (b.by_slot ? b.min_len : kExact)) {
+            if (lane == 0) slot = atomicAdd(&b.taken[0], 1u);
+            slot = uniform(__shfl(slot, 0));
+            if (slot >= b.tables) slot = kNoSlot;
+        }
+        if (lane == 0) b.slot[k] = slot;
+        if (b.by_slot && slot == kNoSlot) continue;
+        if (max(na, nf) > kOneWave) {
+            if (lane == 0) {
+                const uint32_t q = atomicAdd(&b.taken[1], 1u);
+                if (q < b.queue_cap) b.queue[q] = uint32_t(k);
+            }
+            continue;
+        }
+        summarize<1>(b, k, slot, lds[w], 0, lane);
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_summaries_long(SumBuild b) {
+    __shared__ SumLds lds;
+    const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    const uint32_t n = min(b.taken[1], b.queue_cap);
+    for (uint32_t q = blockIdx.x; q < n; q += gridDim.x) {
+        const uint32_t k = b.queue[q];
+        __syncthreads();
+        summarize<16>(b, k, b.slot[k], lds, w, lane);
+    }
+}
+
+__global__ void k_clear_taken(uint32_t *t) { t[threadIdx.x] = 0; }
+
+// ---------------------------------------------------------------- screening
+
+struct ScreenArgs {
+    FilterArgs f;
+    const uint64_t *sum;             // S's summaries
+    const uint32_t *s_slot;          // their numbers (compressed lists; else the S id)
+    const uint32_t *r_slot, *coarse; // R's coarse tables
+    unsigned int *ctr;
+    uint32_t xcds;
+    uint32_t raw;                    // R's A-lists can be read (not compressed)
+};
+
+template <int P2>
+__device__ __forceinline__ bool search(const uint32_t *ends, uint64_t y) {
+    const uint32_t s = uint32_t(y), e = uint32_t(y >> 32);
+    const uint32_t *p = ends;
+#pragma unroll
+    for (uint32_t S = P2 / 2; S > 0; S >>= 1) p = p[S - 1] <= s ? p + S : p;
+    return p[kExact] < e;   // the matching start
+}
+
+// A wave takes 64 pairs at a time from its XCD's range, a lane reading one
+// pair's ids and the bounds of its R list, then goes through them one by one;
+// the next pair's summary is loaded before the current one is searched.  Every
+// pair costs about the same, so the blocks are dealt out without counters.
+__global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
+    __shared__ uint32_t lds[kWavesPerBlock][2 * kExact];   // X: ends, then starts
+    const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    uint32_t *const t = lds[w];
+    const uint32_t *const half = t + (lane < kSumHalf ? 0u : kCoarse);   // the coarse list a lane searches
+    const uint32_t xcd = blockIdx.x % a.xcds, bx = blockIdx.x / a.xcds, nbx = gridDim.x / a.xcds;
+    const uint64_t lo = a.f.n_pairs * xcd / a.xcds, hi = a.f.n_pairs * (xcd + 1) / a.xcds;
+    unsigned long long c_tn = 0, c_th = 0;
+    uint32_t cached = kNoSlot, size = 0;   // the R object in t; its table's entries, a power of two (0: coarse)
+    for (uint64_t g0 = lo + 64ull * (bx * kWavesPerBlock + w); g0 < hi; g0 += 64ull * nbx * kWavesPerBlock) {
+        const uint64_t p = g0 + lane;
+        uint32_t r = 0, s_at = 0, nar = 0, slot = kNoSlot;
+        uint64_t ar0 = 0;
+        bool todo_me = false;
+        uint32_t vv = APRIL_BAD_PAIR;
+        if (p < hi) {
+            r = a.f.r[p];
+            const uint32_t s = a.f.s[p];
+            if ((r < a.f.n_r) & (s < a.f.n_s)) {
+                vv = kPending;
+                ar0 = a.f.Ar.off[r];
+                nar = uint32_t(a.f.Ar.off[r + 1] - ar0);
+                s_at = a.s_slot ? a.s_slot[s] : s;
+                const bool exact = a.raw && nar < kExact;
+                if (!exact) slot = a.r_slot[r];
+                todo_me = s_at != kNoSlot && (exact || slot != kNoSlot);
+            }
+        }
+        uint64_t todo = __ballot(todo_me);
+        uint32_t kn = todo ? uint32_t(__builtin_ctzll(todo)) : 0u;
+        uint64_t y_next = 0;
+        if (todo) y_next = a.sum[uint64_t(__builtin_amdgcn_readlane(s_at, kn)) * kSumEntries + lane];
+        while (todo) {
+            const uint32_t k = kn;
+            const uint64_t y = y_next;
+            todo &= todo - 1;
+            if (todo) {
+                kn = uint32_t(__builtin_ctzll(todo));
+                y_next = a.sum[uint64_t(__builtin_amdgcn_readlane(s_at, kn)) * kSumEntries + lane];
+            }
+            const uint32_t key = __builtin_amdgcn_readlane(r, k);
+            if (key != cached) {
+                cached = key;
+                const uint32_t sl = __builtin_amdgcn_readlane(slot, k);
+                wave_lds_sync();
+                if (sl == kNoSlot) {
+                    const uint32_t n = __builtin_amdgcn_readlane(nar, k);
+                    const uint64_t at = (uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0 >> 32), k))) << 32) |
+                                        uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0), k));
+                    const uint32_t *xs = a.f.Ar.s + at, *xe = a.f.Ar.e + at;
+                    size = n < 64 ? 64u : n < 128 ? 128u : n < 256 ? 256u : kExact;   // above n: a padding entry
+                    for (uint32_t i = lane; i < size; i += 64) {
+                        t[i] = i < n ? xe[i] : 0xffffffffu;
+                        t[kExact + i] = i < n ? xs[i] : 0xffffffffu;
+                    }
+                } else {
+                    const uint32_t *c = a.coarse + uint64_t(sl) * 4 * kCoarse;
+                    size = 0;
+#pragma unroll
+                    for (uint32_t i = 0; i < 2 * kCoarse; i += 64) {
+                        t[i + lane] = c[i + lane];
+                        t[kExact + i + lane] = c[2 * kCoarse + i + lane];
+                    }
+                }
+                wave_lds_sync();
+            }
+            bool hit;
+            if (size == 64) hit = search<64>(t, y);
+            else if (size == 128) hit = search<128>(t, y);
+            else if (size == 256) hit = search<256>(t, y);
+            else if (size == 0) hit = search<kCoarse>(half, y);
+            else hit = search<kExact>(t, y);
+            const uint64_t m = __ballot(hit);
+            const uint32_t v = uint32_t(m) ? APRIL_TH : uint32_t(m >> 32) ? kPending : APRIL_TN;
+            vv = lane == k ? v : vv;
+        }
+        if (p < hi) {
+            a.f.verdict[p] = uint8_t(vv);
+            c_tn += vv == APRIL_TN;
+            c_th += vv == APRIL_TH;
+        }
+    }
+    if (a.f.counts) {
+        for (int off = 32; off > 0; off >>= 1) {
+            c_tn += __shfl_down(c_tn, off);
+            c_th += __shfl_down(c_th, off);
+        }
+        const unsigned long long v[2] = {c_tn, c_th};
+        if (lane == 0) add_totals(a.ctr, blockIdx.x * kWavesPerBlock + w, v, 2);
+    }
+}
+
+__global__ void k_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, unsigned long long *stats) {
+    const uint32_t lane = threadIdx.x & 63;
+    unsigned long long longest = 0, longer = 0;
+    for (uint64_t k = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; k < n; k += uint64_t(gridDim.x) * blockDim.x) {
+        const unsigned long long na = off_a[k + 1] - off_a[k], nf = off_f[k + 1] - off_f[k];
+        longest = max(longest, max(na, nf));
+        longer += na >= kExact;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        longest = max(longest, (unsigned long long)__shfl_down(longest, off));
+        longer += __shfl_down(longer, off);
+    }
+    if (lane == 0) {
+        atomicMax(&stats[0], longest);
+        if (longer) atomicAdd(&stats[1], longer);
+    }
+}
+
+}  // namespace
+
+int launch_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, unsigned long long *stats,
+                      hipStream_t stream) {
+    k_list_stats<<<dim3(uint32_t(std::min<uint64_t>((n + 255) / 256, 256))), dim3(256), 0, stream>>>(off_a, off_f, n,
+                                                                                                   stats);
+    APRIL_HIP_TRY(hipGetLastError());
+    return APRIL_OK;
+}
+
+// Fewest pairs that are screened.
+constexpr uint64_t kScreenMin = 4096;
+
+bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs) {
+    return n_pairs >= kScreenMin && R->d.sum && S->d.sum;
+}
+
+int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
+                  hipStream_t stream) {
+    ScreenArgs a;
+    a.f = f;
+    a.sum = S->d.sum;
+    a.s_slot = S->codec == APRIL_CODEC_RAW ? nullptr : S->d.slot;
+    a.r_slot = R->d.slot;
+    a.coarse = R->d.coarse;
+    a.ctr = static_cast<unsigned int *>(counters);
+    a.xcds = uint32_t(xcd_count(cus));
+    a.raw = R->codec == APRIL_CODEC_RAW;
+    const uint64_t most = uint64_t(cus) * 8, want = (f.n_pairs + 64 * kWavesPerBlock - 1) / (64 * kWavesPerBlock);
+    uint64_t blocks = std::min(most, want);
+    blocks = (blocks + a.xcds - 1) / a.xcds * a.xcds;
+    k_screen<<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a);
+    APRIL_HIP_TRY(hipGetLastError());
+    return APRIL_OK;
+}
+
+// Summaries of device lists, on `stream`.  `longer`: objects whose A-list has
+// kExact intervals or more (compressed lists: kVbyteSummaryMin), the coarse
+// tables needed.  as/ae/fs/fe: the raw arrays (of compressed lists: decoded
+// copies).  Lists without summaries are joined without screening, so running
+// out of memory here is not an error.
+int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, const uint32_t *ae, const uint32_t *fs,
+                     const uint32_t *fe, hipStream_t stream) {
+    const bool raw = L->codec == APRIL_CODEC_RAW;
+    const uint64_t sums = raw ? L->n : longer;
+    if (sums == 0 || L->n >= 0x7fffffffull || longer >= 0x7fffffffull) return APRIL_OK;
+    auto up = [](uint64_t v) { return (v + 255) & ~uint64_t(255); };
+    const uint64_t queue = std::min<uint64_t>(L->n, (L->n_a + L->n_f) / kOneWave + 1);
+    const uint64_t b_sum = up(8 * kSumEntries * sums), b_coarse = up(16 * kCoarse * longer), b_slot = up(4 * L->n);
+    const uint64_t total = b_sum + b_coarse + b_slot + up(4 * queue) + 256;
+    void *block = nullptr;
+    if (hipMalloc(&block, total) != hipSuccess) {
+        (void)hipGetLastError();
+        return APRIL_OK;
+    }
+    char *p = static_cast<char *>(block);
+    SumBuild b;
+    b.A = {L->d.off_a, as, ae};
+    b.F = {L->d.off_f, fs, fe};
+    b.n = L->n;
+    b.sum = reinterpret_cast<uint64_t *>(p); p += b_sum;
+    b.coarse = reinterpret_cast<uint32_t *>(p); p += b_coarse;
+    b.slot = reinterpret_cast<uint32_t *>(p); p += b_slot;
+    b.taken = reinterpret_cast<uint32_t *>(p); p += 256;
+    b.queue = reinterpret_cast<uint32_t *>(p);
+    b.tables = uint32_t(longer);
+    b.queue_cap = uint32_t(queue);
+    b.by_slot = raw ? 0 : 1;
+    b.min_len = kVbyteSummaryMin;
+    k_clear_taken<<<1, 2, 0, stream>>>(b.taken);
+    k_summaries<<<dim3(uint32_t(std::min<uint64_t>((L->n + 3) / 4, 4096))), dim3(kBlock), 0, stream>>>(b);
+    if (L->n_a + L->n_f > kOneWave)
+        k_summaries_long<<<dim3(uint32_t(std::min<uint64_t>(queue, 512))), dim3(1024), 0, stream>>>(b);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) {
+        (void)hipFree(block);
+        return fail(APRIL_E_HIP, std::string("summaries: ") + hipGetErrorString(e));
+    }
+    L->d.sum_block = block;
+    L->d.sum = b.sum;
+    L->d.slot = b.slot;
+    L->d.coarse = b.coarse;
+    L->d.bytes += total;
+    return APRIL_OK;
+}
+
+}  // namespace april
