@@ -21,8 +21,8 @@
 // left corner of the MBRs' union: when both polygons span less than 2^31
 // lattice units, differences fit in 32 bits and cross products in 64.  The
 // ray-crossing counts that decide containment are taken in the same pass
-// over the edges.  Wider pairs are marked and left to a second kernel that
-// works in 128-bit arithmetic.
+// over the edges.  Wider pairs are marked and left to a second pass, in 128-bit
+// arithmetic, and so are pairs of many edges, which go through boxes of 64 of them.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -37,6 +37,9 @@ struct april_polys {
     void *mem = nullptr;            // one allocation: records, then vertices
     const int64_t *rec = nullptr;   // per polygon: vtx0, nv, xmin, ymin, xmax, ymax, x0, y0
     const int64_t *xy = nullptr;    // vertices, (x, y) interleaved
+    uint64_t most = 0;              // vertices of the polygon with most
+    int64_t lo[2] = {0, 0}, hi[2] = {0, 0};   // MBR of all
+    int64_t *box = nullptr;         // boxes of 64 consecutive edges (xmin, ymin, xmax, ymax), see box_at
 };
 
 namespace april {
@@ -45,9 +48,15 @@ namespace {
 constexpr int kRecWords = 8;
 
 struct PolyView {
-    const int64_t *rec, *xy;
+    const int64_t *rec, *xy, *box;
     uint64_t n;
 };
+
+// Edge boxes.  A polygon of more than 64 edges has a box for every 64
+// consecutive ones.  Polygon k with first vertex v keeps its boxes from
+// number v / 64 + k on: it has at most n / 64 + 1 of them, so the next
+// polygon's begin behind them and no table of offsets is needed.
+__device__ __forceinline__ uint64_t box_at(uint64_t v0, uint64_t k) { return (v0 >> 6) + k; }
 
 struct RefineArgs {
     PolyView R, S;
@@ -56,9 +65,11 @@ struct RefineArgs {
     uint8_t *out;
     unsigned long long *counts;
     unsigned int *xhead;
+    uint32_t *left;      // pairs left to the second pass
     uint64_t n_pairs;
     uint32_t xcds;
     uint32_t grab;   // pairs per grab, 4 .. 64
+    uint32_t grab_rest;   // of the second pass, 1 .. 64
 };
 
 typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
@@ -137,11 +148,24 @@ struct Pair {
 
 enum : uint32_t { kDisjoint = 0, kNarrow = 1, kWide = 2 };
 
-// workgroups of k_refine per CU: the residency its registers allow
-constexpr int kRefineBlocksPerCU = 5;
+// Pairs of more edge pairs (of one polygon's with the other's), or with a
+// polygon of more edges, go through the boxes.  7,200 pairs take about 0.1 ms
+// there, whatever their size; through the chunks they take 0.17 ms at 250 x
+// 250 edges, 0.36 ms at 400 x 400 and 0.17 ms at 1000 x 35, but 0.08 ms (the
+// boxes 0.09) at 400 x 35.
+constexpr uint64_t kManyEdgePairs = 1ull << 16;
+constexpr uint32_t kManyEdges = 768;
 
-// marks a pair left for the wide pass
-constexpr uint8_t kWidePending = 0xFE;
+// counter of the pairs that the first pass leaves to the second, and how many
+// of them its list holds (in the scratch, behind the counters)
+constexpr uint32_t kLeftCtr = kMaxCtrs - 1;
+constexpr uint32_t kLeftCap = 1u << 16;
+
+// workgroups of k_refine per CU: the residency its registers allow
+constexpr int kRefineBlocksPerCU = 5, kRestBlocksPerCU = 4;
+
+// mark pairs left for the second pass: wide ones, and those of many edges
+constexpr uint8_t kWidePending = 0xFE, kManyPending = 0xFD;
 
 __device__ __forceinline__ int4 rel_edge(const int64_t *xy, uint64_t p0, uint32_t e, uint32_t n, int64_t ox,
                                          int64_t oy) {
@@ -265,6 +289,121 @@ __device__ uint8_t refine_chunked(const RefineArgs &a, const Pair &q, int4 *ea, 
     return contained(q, cross_s, cross_r);
 }
 
+// ------------------------------------------------------- many edges
+//
+// Two polygons of thousands of edges have few edges near each other, but
+// testing the edges that meet B all-pairs is quadratic in them: 300 x 300
+// polygons of 1k-20k vertices, 7,020 pairs, took 294 ms (its slowest pairs
+// most of it; now 0.12 ms).  Edges that follow each other lie close together, so the boxes
+// of 64 of them stand for them first: the wave holds 64 of R's boxes, one per
+// lane, and goes over S's 64 at a time; only box pairs that meet have their
+// 64 + 64 edges read, culled to the two boxes' intersection (which holds
+// every point that they share) and tested.  The box tests are bounded by the
+// latency of the loads, so that a lane's box is also tested against the union
+// of R's 64 first, which drops most of S's at once.
+
+struct EdgeSide {
+    const int64_t *xy, *box;
+    uint64_t v0;
+    uint32_t n, boxes;
+};
+
+// box c, relative to the pair's origin, as (x0, y0, x1, y1); a polygon of at
+// most 64 edges has one, B itself
+__device__ __forceinline__ int4 side_box(const EdgeSide &d, const Pair &q, uint32_t c) {
+    if (d.n <= 64) return make_int4(q.bx0, q.by0, q.bx1, q.by1);
+    const i64x2 a = gl128(d.box, 2 * uint64_t(c)), b = gl128(d.box, 2 * uint64_t(c) + 1);
+    return make_int4(int32_t(a.x - q.ox), int32_t(a.y - q.oy), int32_t(b.x - q.ox), int32_t(b.y - q.oy));
+}
+
+__device__ __forceinline__ bool boxes_overlap(int4 u, int4 w) {
+    return u.x <= w.z && w.x <= u.z && u.y <= w.w && w.y <= u.w;
+}
+
+__device__ __forceinline__ int4 lane_box(int4 v, uint32_t k) {
+    return make_int4(__builtin_amdgcn_readlane(v.x, k), __builtin_amdgcn_readlane(v.y, k),
+                     __builtin_amdgcn_readlane(v.z, k), __builtin_amdgcn_readlane(v.w, k));
+}
+
+// the lane's edge of box c (an edge twice where there are fewer than 64)
+__device__ __forceinline__ int4 side_edge(const EdgeSide &d, const Pair &q, uint32_t c, uint32_t lane) {
+    return rel_edge(d.xy, d.v0, min(c * 64 + lane, d.n - 1), d.n, q.ox, q.oy);
+}
+
+__device__ __forceinline__ bool edge_in(int4 E, int4 b) {
+    return max(E.x, E.z) >= b.x && min(E.x, E.z) <= b.z && max(E.y, E.w) >= b.y && min(E.y, E.w) <= b.w;
+}
+
+// crossings of the ray from (px, py) to the right: only edges in boxes that
+// span the ray's height and reach beyond the point
+__device__ uint32_t ray_crossings(const EdgeSide &d, const Pair &q, int32_t px, int32_t py, uint32_t lane) {
+    uint32_t cross = 0;
+    for (uint32_t c0 = 0; c0 < d.boxes; c0 += 64) {
+        bool need = c0 + lane < d.boxes;
+        if (need && d.n > 64) {
+            const int4 b = side_box(d, q, c0 + lane);
+            need = b.y <= py && b.w > py && b.z >= px;
+        }
+        uint64_t todo = __ballot(need);
+        while (todo) {
+            const uint32_t c = c0 + uint32_t(__builtin_ctzll(todo));
+            todo &= todo - 1;
+            const int4 E = side_edge(d, q, c, lane);
+            cross += uint32_t(__popcll(__ballot(c * 64 + lane < d.n && crosses_right32(E, px, py))));
+        }
+    }
+    return cross;
+}
+
+__device__ uint8_t refine_boxes(const EdgeSide &R, const EdgeSide &S, const Pair &q, int4 *ea, int4 *eb,
+                                uint32_t lane) {
+    const int4 B = make_int4(q.bx0, q.by0, q.bx1, q.by1);
+    for (uint32_t g = 0; g < R.boxes; g += 64) {
+        int4 rb = make_int4(INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN);   // meets nothing
+        if (g + lane < R.boxes) {
+            const int4 b = side_box(R, q, g + lane);
+            if (boxes_overlap(b, B)) rb = b;
+        }
+        if (!__any(rb.x <= rb.z)) continue;
+        int4 U = rb;
+        for (int off = 32; off > 0; off >>= 1) {
+            U.x = min(U.x, __shfl_xor(U.x, off));
+            U.y = min(U.y, __shfl_xor(U.y, off));
+            U.z = max(U.z, __shfl_xor(U.z, off));
+            U.w = max(U.w, __shfl_xor(U.w, off));
+        }
+        for (uint32_t h = 0; h < S.boxes; h += 64) {
+            const bool vs = h + lane < S.boxes;
+            const int4 sb = side_box(S, q, vs ? h + lane : 0);
+            uint64_t todo_s = __ballot(vs && boxes_overlap(sb, U) && boxes_overlap(sb, B));
+            while (todo_s) {
+                const uint32_t cs = uint32_t(__builtin_ctzll(todo_s));
+                todo_s &= todo_s - 1;
+                const int4 sbox = lane_box(sb, cs);
+                uint64_t todo_r = __ballot(boxes_overlap(rb, sbox));
+                if (!todo_r) continue;
+                const int4 Es = side_edge(S, q, h + cs, lane);
+                while (todo_r) {
+                    const uint32_t cr = uint32_t(__builtin_ctzll(todo_r));
+                    todo_r &= todo_r - 1;
+                    const int4 rbox = lane_box(rb, cr);
+                    const int4 Er = side_edge(R, q, g + cr, lane);
+                    const int4 both = make_int4(max(rbox.x, sbox.x), max(rbox.y, sbox.y), min(rbox.z, sbox.z),
+                                                min(rbox.w, sbox.w));
+                    wave_lds_sync();
+                    const uint32_t kr = append(ea, 0, (g + cr) * 64 + lane < R.n && edge_in(Er, both), Er);
+                    const uint32_t ks = append(eb, 0, (h + cs) * 64 + lane < S.n && edge_in(Es, both), Es);
+                    wave_lds_sync();
+                    if (edges_meet(ea, kr, eb, ks, lane)) return 1;
+                }
+            }
+        }
+    }
+    const uint32_t cross_s = q.r_in_bs ? ray_crossings(S, q, q.rx, q.ry, lane) : 0;
+    const uint32_t cross_r = q.s_in_br ? ray_crossings(R, q, q.sx, q.sy, lane) : 0;
+    return contained(q, cross_s, cross_r);
+}
+
 // --------------------------------------------------------- wide pairs
 
 __device__ __forceinline__ bool in_box(const int64_t *rec, int64_t x, int64_t y) {
@@ -328,6 +467,39 @@ __device__ uint8_t refine_pair_wide(const RefineArgs &a, uint32_t r, uint32_t s,
     return in_box(br, bs[6], bs[7]) && inside_wide(a.R.xy, r0, nr, bs[6], bs[7], lane) ? 1 : 0;
 }
 
+// One wave per box number: find its polygon, reduce the box over the edges.
+__global__ __launch_bounds__(256) void k_edge_boxes(const int64_t *rec, const int64_t *xy, uint64_t n,
+                                                    uint64_t n_boxes, int64_t *box) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t waves = uint64_t(gridDim.x) * (blockDim.x / 64);
+    for (uint64_t b = uint64_t(blockIdx.x) * (blockDim.x / 64) + (threadIdx.x >> 6); b < n_boxes; b += waves) {
+        uint64_t lo = 0, hi = n;   // the last polygon whose boxes start at or before b
+        while (hi - lo > 1) {
+            const uint64_t mid = (lo + hi) / 2;
+            if (box_at(uint64_t(rec[kRecWords * mid]), mid) <= b) lo = mid;
+            else hi = mid;
+        }
+        const uint64_t v0 = uint64_t(rec[kRecWords * lo]), nv = uint64_t(rec[kRecWords * lo + 1]);
+        const uint64_t e = (b - box_at(v0, lo)) * 64 + lane;
+        if (nv <= 64 || e - lane >= nv) continue;
+        int64_t x0 = INT64_MAX, y0 = INT64_MAX, x1 = INT64_MIN, y1 = INT64_MIN;
+        if (e < nv) {
+            const i64x2 u = gl128(xy, v0 + e), w = gl128(xy, v0 + (e + 1 == nv ? 0 : e + 1));
+            x0 = min(u.x, w.x);
+            y0 = min(u.y, w.y);
+            x1 = max(u.x, w.x);
+            y1 = max(u.y, w.y);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            x0 = min(x0, (int64_t)__shfl_xor((long long)x0, off));
+            y0 = min(y0, (int64_t)__shfl_xor((long long)y0, off));
+            x1 = max(x1, (int64_t)__shfl_xor((long long)x1, off));
+            y1 = max(y1, (int64_t)__shfl_xor((long long)y1, off));
+        }
+        if (lane < 4) box[4 * b + lane] = lane == 0 ? x0 : lane == 1 ? y0 : lane == 2 ? x1 : y1;
+    }
+}
+
 // ------------------------------------------------------------- kernels
 
 __device__ __forceinline__ uint32_t rl32(uint32_t v, uint32_t k) { return uniform(__builtin_amdgcn_readlane(v, k)); }
@@ -336,30 +508,55 @@ __device__ __forceinline__ uint64_t rl64(uint64_t v, uint32_t k) {
     return uint64_t(rl32(uint32_t(v), k)) | (uint64_t(rl32(uint32_t(v >> 32), k)) << 32);
 }
 
+// First pass (REST false): every pair but those of polygons with many edges
+// and wide ones, which it marks; second pass (REST): those.  Two kernels: with
+// the box path in it the first needs more registers, and a 1.13M-pair call of
+// small polygons took 632 us, not 590.
+template <bool REST>
 __global__ __launch_bounds__(kBlock) void k_refine(RefineArgs a) {
     __shared__ int4 lds[kWavesPerBlock][2][kEdgeChunk];
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int4 *ea = lds[wave][0], *eb = lds[wave][1];
     unsigned long long c_hit = 0, c_tested = 0;
-    const uint32_t my_xcd = blockIdx.x % a.xcds, G = a.grab;
+    // second pass: pair by pair from the list, or, with more pairs than it
+    // holds, from the marks
+    const uint32_t n_left = REST ? uniform(a.xhead[kLeftCtr * kCtrStride]) : 0;
+    const bool listed = REST && n_left <= kLeftCap;
+    uint32_t next = blockIdx.x * kWavesPerBlock + wave;
+    if (listed && next >= n_left) return;
+    const uint32_t my_xcd = blockIdx.x % a.xcds, G = REST ? a.grab_rest : a.grab;
     for (uint32_t k = 0; k < a.xcds; k++) {
         const uint32_t seg = (my_xcd + k) % a.xcds;
         const uint64_t lo = a.n_pairs * seg / a.xcds, hi = a.n_pairs * (seg + 1) / a.xcds;
-        if (k > 0 && range_drained(a.xhead, seg, lo, hi, lane)) continue;
+        const uint32_t ctr = REST ? a.xcds + seg : seg;
+        if (!listed && k > 0 && range_drained(a.xhead, ctr, lo, hi, lane)) continue;
         for (;;) {
-            unsigned int got = 0;
-            if (lane == 0) got = atomicAdd(&a.xhead[seg * kCtrStride], G);
-            const uint64_t g0 = lo + uniform(__shfl(got, 0));
-            if (g0 >= hi) break;
+            uint64_t g0;
+            if (listed) {
+                if (next >= n_left) break;
+                g0 = uniform(a.left[next]);
+                next += gridDim.x * kWavesPerBlock;
+            } else {
+                unsigned int got = 0;
+                if (lane == 0) got = atomicAdd(&a.xhead[ctr * kCtrStride], G);
+                g0 = lo + uniform(__shfl(got, 0));
+                if (g0 >= hi) break;
+            }
             const uint64_t p = g0 + lane;
-            const bool mine = lane < G && p < hi;
+            bool mine = listed ? lane == 0 : lane < G && p < hi;
+            if (REST && mine) mine = a.out[p] == kWidePending || a.out[p] == kManyPending;
+            if (REST && !__any(mine)) continue;
             uint32_t out = APRIL_BAD_PAIR, kind = kDisjoint;
             bool test = false;
             // this lane's pair: ids, verdict, both records
             Pair m = {};
+            uint32_t r = 0, s = 0;
             if (mine) {
-                const uint32_t r = a.r[p], s = a.s[p];
-                if (r < a.R.n && s < a.S.n) {
+                r = a.r[p];
+                s = a.s[p];
+                if (REST) {
+                    test = true;
+                } else if (r < a.R.n && s < a.S.n) {
                     const uint8_t v = a.verdict ? a.verdict[p] : uint8_t(APRIL_INDECISIVE);
                     if (v == APRIL_TN) out = 0;
                     else if (v == APRIL_TH) out = 1;
@@ -399,11 +596,28 @@ __global__ __launch_bounds__(kBlock) void k_refine(RefineArgs a) {
                     }
                 }
             }
-            uint64_t todo = __ballot(test && kind == kNarrow);
-            if (test && kind != kNarrow) out = kind == kWide ? kWidePending : 0;
+            const bool many = uint64_t(m.nr) * m.ns > kManyEdgePairs || max(m.nr, m.ns) > kManyEdges;
+            uint64_t todo = __ballot(REST ? test : test && kind == kNarrow && !many);
+            if (!REST && test && kind != kNarrow) out = kind == kWide ? kWidePending : 0;
+            if (!REST && test && kind == kNarrow && many) out = kManyPending;
+            if (!REST) {
+                const bool mark = out == kWidePending || out == kManyPending;
+                const uint64_t left = __ballot(mark);
+                if (left) {
+                    unsigned int at = 0;
+                    if (lane == 0) at = atomicAdd(&a.xhead[kLeftCtr * kCtrStride], uint32_t(__popcll(left)));
+                    const uint64_t slot = uint64_t(__shfl(at, 0)) + uint32_t(__popcll(left & ((1ull << lane) - 1)));
+                    if (mark && slot < kLeftCap) a.left[slot] = uint32_t(p);
+                }
+            }
             while (todo) {
                 const uint32_t k2 = uint32_t(__builtin_ctzll(todo));
                 todo &= todo - 1;
+                if (REST && rl32(kind, k2) == kWide) {
+                    const uint32_t vw = refine_pair_wide(a, rl32(r, k2), rl32(s, k2), lane);
+                    out = lane == k2 ? vw : out;
+                    continue;
+                }
                 Pair q;
                 q.r0 = rl64(m.r0, k2);
                 q.s0 = rl64(m.s0, k2);
@@ -421,14 +635,21 @@ __global__ __launch_bounds__(kBlock) void k_refine(RefineArgs a) {
                 q.sy = rli(m.sy, k2);
                 q.r_in_bs = rl32(m.r_in_bs, k2) != 0;
                 q.s_in_br = rl32(m.s_in_br, k2) != 0;
-                const uint32_t v = q.nr <= 64 && q.ns <= 64 ? refine_small(a, q, ea, eb, lane)
-                                                           : refine_chunked(a, q, ea, eb, lane);
+                uint32_t v;
+                if (!REST) {
+                    v = q.nr <= 64 && q.ns <= 64 ? refine_small(a, q, ea, eb, lane)
+                                                 : refine_chunked(a, q, ea, eb, lane);
+                } else {
+                    const EdgeSide er{a.R.xy, a.R.box + 4 * box_at(q.r0, rl32(r, k2)), q.r0, q.nr, (q.nr + 63) / 64};
+                    const EdgeSide es{a.S.xy, a.S.box + 4 * box_at(q.s0, rl32(s, k2)), q.s0, q.ns, (q.ns + 63) / 64};
+                    v = refine_boxes(er, es, q, ea, eb, lane);
+                }
                 out = lane == k2 ? v : out;
             }
             if (mine) {
                 a.out[p] = uint8_t(out);
                 c_hit += out == 1;
-                c_tested += test;
+                c_tested += !REST && test;
             }
         }
     }
@@ -442,39 +663,14 @@ __global__ __launch_bounds__(kBlock) void k_refine(RefineArgs a) {
     }
 }
 
-// Second pass: the pairs k_refine left as kWidePending, in 128-bit
-// arithmetic.  Every wave scans its share of the outputs 64 at a time.
-__global__ __launch_bounds__(kBlock) void k_refine_wide(RefineArgs a) {
-    const uint32_t lane = threadIdx.x & 63;
-    const uint64_t wave = (uint64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6;
-    const uint64_t waves = (uint64_t(gridDim.x) * blockDim.x) >> 6;
-    unsigned long long c_hit = 0;
-    for (uint64_t g0 = wave * 64; g0 < a.n_pairs; g0 += waves * 64) {
-        const uint64_t p = g0 + lane;
-        const bool wide = p < a.n_pairs && a.out[p] == kWidePending;
-        uint64_t todo = __ballot(wide);
-        if (!todo) continue;
-        const uint32_t r = wide ? a.r[p] : 0, s = wide ? a.s[p] : 0;
-        uint32_t out = 0;
-        while (todo) {
-            const uint32_t k2 = uint32_t(__builtin_ctzll(todo));
-            todo &= todo - 1;
-            const uint32_t v = refine_pair_wide(a, rl32(r, k2), rl32(s, k2), lane);
-            out = lane == k2 ? v : out;
-        }
-        if (wide) {
-            a.out[p] = uint8_t(out);
-            c_hit += out;
-        }
-    }
-    if (a.counts) {
-        for (int off = 32; off > 0; off >>= 1) c_hit += __shfl_down(c_hit, off);
-        if (lane == 0) add_totals(a.xhead, uint32_t(wave), &c_hit, 1);
-    }
+// do the two collections together span 2^31 lattice units or more in x
+// (axis 0) or y?
+bool wider(const april_polys_t *R, const april_polys_t *S, int axis) {
+    const int64_t lo = std::min(R->lo[axis], S->lo[axis]), hi = std::max(R->hi[axis], S->hi[axis]);
+    return uint64_t(hi) - uint64_t(lo) >= (1ull << 31);
 }
 
-
-PolyView view(const april_polys_t *P) { return PolyView{P->rec, P->xy, P->n}; }
+PolyView view(const april_polys_t *P) { return PolyView{P->rec, P->xy, P->box, P->n}; }
 
 }  // namespace
 }  // namespace april
@@ -536,23 +732,39 @@ extern "C" int april_polys_to_device(const double *xy, const uint64_t *vtx_off, 
     auto *P = new (std::nothrow) april_polys;
     if (!P) return fail(APRIL_E_NOMEM, "out of host memory");
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipMalloc(&P->mem, words * sizeof(int64_t)) != hipSuccess) {
+    const uint64_t n_boxes = ((nv - vtx_off[0]) >> 6) + n;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipMalloc(&P->mem, (words + 4 * n_boxes) * sizeof(int64_t)) != hipSuccess) {
         delete P;
         return fail(APRIL_E_NOMEM, "device allocation of the polygons failed");
     }
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (hipMemcpyAsync(P->mem, h.data(), words * sizeof(int64_t), hipMemcpyHostToDevice, stream) != hipSuccess ||
-        hipStreamSynchronize(stream) != hipSuccess) {   // the staging buffer dies here
+    int64_t *d = static_cast<int64_t *>(P->mem);
+    P->rec = d;
+    P->xy = d + uint64_t(kRecWords) * n;
+    P->box = d + words;
+    bool ok = hipMemcpyAsync(P->mem, h.data(), words * sizeof(int64_t), hipMemcpyHostToDevice, stream) == hipSuccess;
+    if (ok) {
+        k_edge_boxes<<<dim3(uint32_t(std::min<uint64_t>((n_boxes + 3) / 4, 8192))), dim3(256), 0, stream>>>(
+            P->rec, P->xy, n, n_boxes, P->box);
+        ok = hipGetLastError() == hipSuccess;
+    }
+    if (hipStreamSynchronize(stream) != hipSuccess || !ok) {   // the staging buffer dies here
         (void)hipFree(P->mem);
         delete P;
         return fail(APRIL_E_HIP, "copy of the polygons to the device failed");
     }
-    int64_t *d = static_cast<int64_t *>(P->mem);
+    for (uint64_t k = 0; k < n; k++) {
+        const int64_t *o = rec + uint64_t(kRecWords) * k;
+        P->most = std::max(P->most, uint64_t(o[1]));
+        for (int c = 0; c < 2; c++) {
+            P->lo[c] = k ? std::min(P->lo[c], o[2 + c]) : o[2 + c];
+            P->hi[c] = k ? std::max(P->hi[c], o[4 + c]) : o[4 + c];
+        }
+    }
     P->n = n;
     P->nv = nv - vtx_off[0];
     P->device = dev;
-    P->rec = d;
-    P->xy = d + uint64_t(kRecWords) * n;
     *out = P;
     return APRIL_OK;
 }
@@ -585,24 +797,30 @@ extern "C" int april_refine_pairs(const april_polys_t *R, const april_polys_t *S
     a.out = d_out;
     a.counts = d_counts;
     a.n_pairs = n_pairs;
-    a.xcds = uint32_t(xcd_count(st->cus));
+    a.xcds = uint32_t(std::min(xcd_count(st->cus), int(kLeftCtr) / 2));   // two passes' counters
     // 64 pairs per grab, fewer when that would leave waves idle (about two
-    // grabs per wave), but at least 4: each grab costs an atomic
+    // grabs per wave), but at least 4: each grab costs an atomic (1,650 pairs
+    // of small polygons take 45 us with grabs of 1, 39 with 4).  The second
+    // pass's pairs cost more than that, so it goes down to 1.
     const uint64_t blocks = uint64_t(st->cus) * kRefineBlocksPerCU, waves = blocks * kWavesPerBlock;
-    a.grab = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(4, n_pairs / (waves * 2))));
-    // per-XCD range counters in a stream-ordered scratch, so calls on
-    // different streams never share them
+    a.grab_rest = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(1, n_pairs / (waves * 2))));
+    a.grab = std::max(4u, a.grab_rest);
+    // per-XCD range counters (and the second pass's list) in a stream-ordered
+    // scratch, so calls on different streams never share them
+    // (the second pass only where the collections can have pairs for it)
+    const bool rest = R->most > kManyEdgePairs / S->most || std::max(R->most, S->most) > kManyEdges || wider(R, S, 0) || wider(R, S, 1);
     void *ws = nullptr;
-    hipError_t e = hipMallocAsync(&ws, kCtrBytes, stream);
+    hipError_t e = hipMallocAsync(&ws, kCtrBytes + (rest ? 4ull * kLeftCap : 0), stream);
     if (e != hipSuccess) return fail(APRIL_E_NOMEM, std::string("refine scratch: ") + hipGetErrorString(e));
     a.xhead = static_cast<unsigned int *>(ws);
+    a.left = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + kCtrBytes);
     k_zero_ctrs<<<1, 64, 0, stream>>>(a.xhead);
     e = hipGetLastError();
     if (e == hipSuccess && n_pairs) {
-        k_refine<<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a);
+        k_refine<false><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a);
         e = hipGetLastError();
-        if (e == hipSuccess) {
-            k_refine_wide<<<dim3(uint32_t(st->cus)), dim3(kBlock), 0, stream>>>(a);
+        if (e == hipSuccess && rest) {
+            k_refine<true><<<dim3(uint32_t(st->cus * kRestBlocksPerCU)), dim3(kBlock), 0, stream>>>(a);
             e = hipGetLastError();
         }
     }
