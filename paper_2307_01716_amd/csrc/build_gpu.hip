@@ -1,30 +1,49 @@
 // GPU construction of APRIL A- and F-lists (Sec. 6), for a whole collection
 // at once.  The lists are identical to the host builder's (build.cpp): the
 // same exact edge traversal, the same centre-line crossing rule, the same
-// one-step intervalization -- reorganized as data-parallel passes:
+// classes.  No cell is ever sorted: an aligned block of 64 x 64 cells is one
+// contiguous range of Hilbert ids, so a polygon is rasterized block by block
+// into bit arrays that are laid out in Hilbert order, where an interval is a
+// run of ones.
 //
 //  1. one thread per vertex: lattice coordinates relative to the grid origin
-//     and the checks (lattice, grid ring);
-//  2. one thread per edge: how many (cell, row) entries it produces -- the
-//     cells whose closed square it meets, row by row (Sec. 6.1 traversal),
-//     and the centre lines of cell rows it crosses; exclusive scans give
-//     every edge its output range;
-//  3. one thread per edge writes its entries: key (polygon, Hilbert id,
-//     interior-crossed flag) for cells, key (polygon, row) and crossing x
-//     for centre lines;
-//  4. radix sorts: for each polygon the touched cells are then in Hilbert
-//     order, and each row's crossings contiguous and in x order;
-//  5. one thread per entry keeps the last entry of every (polygon, cell) run
-//     (its flag is the OR of the run's), and a scan compacts them;
-//  6. one thread per touched cell takes the class bits of Alg. 3 (centre of
-//     a border-only cell inside; first cell of the gap after it inside) from
-//     the parity of the crossings left of the centre in its row (two binary
-//     searches);
-//  7. one thread per touched cell decides which A- and F-interval ends it
-//     owns -- a run of A or F cells starts or stops only at a touched cell or
-//     at a gap next to it -- and scans give each end its slot.
+//     (in place) and the checks (lattice, grid ring);
+//  2. one wave per 64 consecutive edges: their box; one wave per polygon:
+//     its extent in cells, which gives its blocks;
+//  3. every block of every polygon is an item with the key (polygon, Hilbert
+//     id of the block); a radix sort of these keys is the lists' order;
+//  4. one wave per item rasterizes it and counts the interval starts in it;
+//     whether an interval runs on from the block before or into the next one
+//     is a bit at either end, which a pass over the items settles;
+//  5. scans give each item its place in the lists, and the items are
+//     rasterized again and written there (storing them would take more
+//     memory than the lists).
 //
-// Two host synchronizations read the sizes that the output buffers need.
+// An item, by one wave (k_items).  Edges that only pass left of the block
+// change the parity of whole rows, which two comparisons per edge (or per 64
+// edges: their first and last vertex tell) give as a 64-bit mask; edges to the
+// right or above or below change nothing.  The rows of the edges that meet the
+// block are dealt out to the lanes, one (edge, row) each, so that long and
+// short edges fill the wave alike; a lane sets the cells whose closed square
+// the edge meets in that row (T), those whose interior it crosses (C), and
+// toggles the parity behind the crossing of the row's centre line.  Then lane
+// l owns 64 cells in Hilbert order (8 x 8 of them): a cell that is not
+// touched is inside when its centre is, and all of a run of such cells are
+// alike, so one look at the parity per run and word decides (Alg. 3's gap
+// test), and one per cell touched only on its border.
+//
+// Against emitting a 64-bit key per touched cell, sorting and compacting
+// them, as this file did before: 50k polygons of the at-scale collection
+// (715 cells and 327 intervals each) took 12.6 ms of kernels and 3.1 GB of
+// scratch, whose mapping and unmapping took up to 80 ms more in a call; now they
+// take 2.0 ms and 55 MB, and the whole call with a filter call behind it 5.0
+// ms, not 20.7 to 98.  k_items takes 0.65 ms to count and 1.04 to write, at
+// 0.9 of the VALU issue peak (783 instructions per item, 1,270 with the
+// writing).  Blocks of 64 x 64 cells, because a wave then has one word of 64
+// cells per lane and one row of cells per lane; at scale a polygon has nine,
+// with 55 edge rows each, about one per lane.
+//
+// Two host synchronizations read the sizes that the buffers need.
 #include <hip/hip_runtime.h>
 #include <hipcub/hipcub.hpp>
 
@@ -91,8 +110,11 @@ __device__ void hilbert_xy(int order, uint32_t d, uint32_t &x, uint32_t &y) {
 struct Geo {
     double x0, y0;     // grid origin
     int64_t w;         // cell side, lattice units
+    double inv_w;      // 1 / w
+    float inv_wf, inv_2wf;
     int64_t cells;     // 2^order
     int order;
+    int border;        // order of the grid of blocks (0 when the grid is one block or less)
     uint32_t strict;
 };
 
@@ -102,22 +124,18 @@ struct Geo {
 enum : uint64_t { kErrGrid = 1, kErrLattice = 2, kErrDistinct = 3 };
 constexpr uint64_t kErrNoVertex = 0xffffff;
 
-__global__ void k_vertices(const double *xy, const uint64_t *voff, uint64_t n, uint64_t nv, Geo g, int64_t *X,
-                           int64_t *Y, uint32_t *poly, uint8_t *bad, unsigned long long *err) {
+typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
+
+// xy: float64 coordinates in, int64 lattice coordinates out (in place)
+__global__ void k_vertices(i64x2 *xy, const uint64_t *voff, uint64_t n, uint64_t nv, Geo g,
+                           unsigned long long *err) {
     const uint64_t v = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (v >= nv) return;
-    // polygon of vertex v: the last k with voff[k] <= v
-    uint64_t lo = 0, hi = n;   // voff[lo] <= v < voff[hi]
-    while (hi - lo > 1) {
-        const uint64_t mid = (lo + hi) / 2;
-        if (voff[mid] <= v) lo = mid;
-        else hi = mid;
-    }
-    poly[v] = uint32_t(lo);
+    const i64x2 in = xy[v];
     uint64_t code = 0;
     int64_t c[2] = {0, 0};
     for (int a = 0; a < 2 && !code; a++) {
-        const double q = (xy[2 * v + a] - (a ? g.y0 : g.x0)) * 1073741824.0;
+        const double q = (__longlong_as_double(a ? in.y : in.x) - (a ? g.y0 : g.x0)) * 1073741824.0;
         const double r = rint(q);
         if (!(fabs(r) < 4.0e15)) code = kErrGrid;
         else if (g.strict && r != q) code = kErrLattice;
@@ -126,21 +144,149 @@ __global__ void k_vertices(const double *xy, const uint64_t *voff, uint64_t n, u
     // the outer ring of cells must stay untouched
     if (!code && (c[0] <= g.w || c[1] <= g.w || c[0] >= (g.cells - 1) * g.w || c[1] >= (g.cells - 1) * g.w))
         code = kErrGrid;
-    X[v] = c[0];
-    Y[v] = c[1];
+    xy[v] = i64x2{c[0], c[1]};
     if (code) {
-        bad[lo] = 1;
+        uint64_t lo = 0, hi = n;   // polygon of vertex v: voff[lo] <= v < voff[hi]
+        while (hi - lo > 1) {
+            const uint64_t mid = (lo + hi) / 2;
+            if (voff[mid] <= v) lo = mid;
+            else hi = mid;
+        }
         const uint64_t vl = min<uint64_t>(v - voff[lo], kErrNoVertex - 1);
         atomicMin(err, (unsigned long long)((lo << 32) | (vl << 8) | code));
     }
 }
 
-// Cells met by the edge a-b (closed squares), row by row; with EMIT, their
-// keys.  T is the product type: int64 when the grid spans few enough lattice
-// units, else 128-bit.
-template <typename T, bool EMIT>
-__device__ uint64_t edge_cells(int64_t ax, int64_t ay, int64_t bx, int64_t by, const Geo &g, uint64_t key_hi,
-                               uint64_t *out) {
+// Boxes of 64 consecutive edges: polygon k keeps its boxes from number
+// voff[k] / 64 + k on (it has at most its vertices / 64 + 1 of them, so the
+// next polygon's begin behind them).
+struct EdgeBox {
+    int64_t x0, y0, x1, y1;
+};
+
+__device__ __forceinline__ uint64_t box_at(uint64_t v0, uint64_t k) { return (v0 >> 6) + k; }
+
+// the lane's edge of a polygon (vertices [v0, v0 + nv)): edge e from vertex e
+__device__ __forceinline__ void load_edge(const i64x2 *xy, uint64_t v0, uint64_t nv, uint64_t e, i64x2 &a, i64x2 &b) {
+    a = xy[v0 + e];
+    b = xy[v0 + (e + 1 == nv ? 0 : e + 1)];
+}
+
+struct PolyArgs {
+    const i64x2 *xy;
+    const uint64_t *voff;
+    uint64_t n, n_boxes;
+    EdgeBox *box;
+    uint32_t *distinct;        // per box: edges with two different ends
+    unsigned long long *bound; // upper bound of the cells that all edges meet
+    Geo g;
+};
+
+// The cells that an edge meets number at most its extent in x plus three per
+// row (a row's first and last cell are shared with its neighbours' or touched
+// at a corner only).
+__global__ __launch_bounds__(256) void k_edge_boxes(PolyArgs a) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t waves = uint64_t(gridDim.x) * (blockDim.x / 64);
+    unsigned long long cells = 0;
+    for (uint64_t b = uint64_t(blockIdx.x) * (blockDim.x / 64) + (threadIdx.x >> 6); b < a.n_boxes; b += waves) {
+        uint64_t lo = 0, hi = a.n;   // the last polygon whose boxes start at or before b
+        while (hi - lo > 1) {
+            const uint64_t mid = (lo + hi) / 2;
+            if (box_at(a.voff[mid], mid) <= b) lo = mid;
+            else hi = mid;
+        }
+        const uint64_t v0 = a.voff[lo], nv = a.voff[lo + 1] - v0;
+        const uint64_t e = (b - box_at(v0, lo)) * 64 + lane;
+        if (e - lane >= nv) continue;   // a number that no box has
+        EdgeBox x{INT64_MAX, INT64_MAX, INT64_MIN, INT64_MIN};
+        bool two = false;
+        if (e < nv) {
+            i64x2 u, v;
+            load_edge(a.xy, v0, nv, e, u, v);
+            x = EdgeBox{min(u.x, v.x), min(u.y, v.y), max(u.x, v.x), max(u.y, v.y)};
+            two = u.x != v.x || u.y != v.y;
+            cells += uint64_t(double(x.x1 - x.x0) * a.g.inv_w) + 3 * uint64_t(double(x.y1 - x.y0) * a.g.inv_w) + 16;
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            x.x0 = min(x.x0, (int64_t)__shfl_xor((long long)x.x0, off));
+            x.y0 = min(x.y0, (int64_t)__shfl_xor((long long)x.y0, off));
+            x.x1 = max(x.x1, (int64_t)__shfl_xor((long long)x.x1, off));
+            x.y1 = max(x.y1, (int64_t)__shfl_xor((long long)x.y1, off));
+        }
+        const uint32_t d = uint32_t(__popcll(__ballot(two)));
+        if (lane == 0) {
+            a.box[b] = x;
+            a.distinct[b] = d;
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) cells += __shfl_down(cells, off);
+    // one addition per workgroup: 65,536 waves adding to one word took 0.5 ms
+    __shared__ unsigned long long part[4];
+    if (lane == 0) part[threadIdx.x >> 6] = cells;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(a.bound, part[0] + part[1] + part[2] + part[3]);
+}
+
+// A polygon's blocks: x0, y0 of the first, and how many in x and y.
+struct Blocks {
+    uint16_t x0, y0, nx, ny;
+};
+
+__device__ __forceinline__ int64_t floor_w(int64_t v, const Geo &g) {   // floor(v / w), v >= 0
+    int64_t q = int64_t(double(v) * g.inv_w);
+    const int64_t r = v - q * g.w;
+    return r < 0 ? q - 1 : r >= g.w ? q + 1 : q;
+}
+
+// One wave per polygon; item count of polygon k in items[k] (items[n] = 0).
+__global__ __launch_bounds__(256) void k_polygons(PolyArgs a, Blocks *blocks, uint64_t *items,
+                                                  unsigned long long *err) {
+    const uint32_t lane = threadIdx.x & 63;
+    const uint64_t waves = uint64_t(gridDim.x) * (blockDim.x / 64);
+    for (uint64_t k = uint64_t(blockIdx.x) * (blockDim.x / 64) + (threadIdx.x >> 6); k < a.n; k += waves) {
+        const uint64_t v0 = a.voff[k], nv = a.voff[k + 1] - v0, b0 = box_at(v0, k), nb = (nv + 63) / 64;
+        EdgeBox x{INT64_MAX, INT64_MAX, INT64_MIN, INT64_MIN};
+        uint32_t d = 0;
+        for (uint64_t b = lane; b < nb; b += 64) {
+            const EdgeBox o = a.box[b0 + b];
+            x = EdgeBox{min(x.x0, o.x0), min(x.y0, o.y0), max(x.x1, o.x1), max(x.y1, o.y1)};
+            d = min(3u, d + a.distinct[b0 + b]);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            x.x0 = min(x.x0, (int64_t)__shfl_xor((long long)x.x0, off));
+            x.y0 = min(x.y0, (int64_t)__shfl_xor((long long)x.y0, off));
+            x.x1 = max(x.x1, (int64_t)__shfl_xor((long long)x.x1, off));
+            x.y1 = max(x.y1, (int64_t)__shfl_xor((long long)x.y1, off));
+            d = min(3u, d + __shfl_xor(d, off));
+        }
+        if (lane == 0) {
+            if (d < 3) atomicMin(err, (unsigned long long)((k << 32) | (kErrNoVertex << 8) | kErrDistinct));
+            // cells whose closed square the box meets; inside the grid's outer
+            // ring unless a vertex was in error, when the call ends before the
+            // blocks are used
+            const int64_t top = a.g.cells - 1;
+            const int64_t i0 = min(top, max<int64_t>(0, floor_w(x.x0 + a.g.w - 1, a.g) - 1));
+            const int64_t j0 = min(top, max<int64_t>(0, floor_w(x.y0 + a.g.w - 1, a.g) - 1));
+            const int64_t i1 = max(i0, min(top, floor_w(x.x1, a.g))), j1 = max(j0, min(top, floor_w(x.y1, a.g)));
+            Blocks c;
+            c.x0 = uint16_t(i0 >> 6);
+            c.y0 = uint16_t(j0 >> 6);
+            c.nx = uint16_t((i1 >> 6) - (i0 >> 6) + 1);
+            c.ny = uint16_t((j1 >> 6) - (j0 >> 6) + 1);
+            blocks[k] = c;
+            items[k] = uint64_t(c.nx) * c.ny;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) items[a.n] = 0;
+}
+
+// Cells met by the edge a-b (closed squares), row by row.  T is the product
+// type: int64 when the grid spans few enough lattice units, else 128-bit.
+// Only counted when the bound above leaves it open whether a call has more
+// than it takes.
+template <typename T>
+__device__ uint64_t edge_cells(int64_t ax, int64_t ay, int64_t bx, int64_t by, const Geo &g) {
     const int64_t w = g.w;
     if (ay > by) {
         const int64_t tx = ax, ty = ay;
@@ -163,313 +309,541 @@ __device__ uint64_t edge_cells(int64_t ax, int64_t ay, int64_t bx, int64_t by, c
             n1 = u < v ? v : u;
         }
         const T Dw = D * T(w);
-        const int64_t i0 = cdiv<T>(n0, Dw) - 1, i1 = fdiv(n1, Dw);
-        if (EMIT) {
-            const bool open_row = horiz ? (j * w < ay && ay < (j + 1) * w) : (ylo < yhi);
-            int64_t o0 = 1, o1 = 0;
-            if (open_row) {
-                o0 = fdiv(n0, Dw);
-                o1 = cdiv<T>(n1, Dw) - 1;
-            }
-            for (int64_t i = i0; i <= i1; i++) {
-                const uint64_t d = hilbert_d(g.order, uint32_t(i), uint32_t(j));
-                out[cnt + uint64_t(i - i0)] = key_hi | (d << 1) | uint64_t(i >= o0 && i <= o1);
-            }
-        }
-        cnt += uint64_t(i1 - i0 + 1);
+        cnt += uint64_t(fdiv(n1, Dw) - (cdiv<T>(n0, Dw) - 1) + 1);
     }
     return cnt;
 }
 
-// Crossings of the edge a-b with the centre lines of cell rows (half-open:
-// y = c is crossed iff exactly one endpoint lies above c); with EMIT, the
-// floor of each crossing's doubled x.
-template <typename T, bool EMIT>
-__device__ uint64_t edge_crossings(int64_t ax, int64_t ay, int64_t bx, int64_t by, const Geo &g, uint64_t key_hi,
-                                   uint64_t *okey, int64_t *ox) {
-    if (ay == by) return 0;
-    if (ay > by) {
-        const int64_t tx = ax, ty = ay;
-        ax = bx; ay = by; bx = tx; by = ty;
-    }
-    const int64_t w = g.w;
-    const int64_t j0 = cdiv<int64_t>(2 * ay - w, 2 * w), j1 = cdiv<int64_t>(2 * by - w, 2 * w) - 1;
-    if (j1 < j0) return 0;
-    if (EMIT) {
-        const T D = T(by - ay);
-        for (int64_t j = j0; j <= j1; j++) {
-            const T c = T(2 * j + 1) * T(w);
-            const T N = T(2) * T(ax) * D + (c - T(2) * T(ay)) * T(bx - ax);
-            okey[j - j0] = key_hi | uint64_t(j);
-            ox[j - j0] = fdiv(N, D);
+__global__ void k_count_cells(const i64x2 *xy, const uint64_t *voff, uint64_t n, uint64_t nv, Geo g, uint32_t wide,
+                              unsigned long long *total) {
+    unsigned long long c = 0;
+    for (uint64_t v = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; v < nv; v += uint64_t(gridDim.x) * blockDim.x) {
+        uint64_t lo = 0, hi = n;
+        while (hi - lo > 1) {
+            const uint64_t mid = (lo + hi) / 2;
+            if (voff[mid] <= v) lo = mid;
+            else hi = mid;
         }
+        i64x2 a, b;
+        load_edge(xy, voff[lo], voff[lo + 1] - voff[lo], v - voff[lo], a, b);
+        c += wide ? edge_cells<__int128>(a.x, a.y, b.x, b.y, g) : edge_cells<int64_t>(a.x, a.y, b.x, b.y, g);
     }
-    return uint64_t(j1 - j0 + 1);
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off);
+    if ((threadIdx.x & 63) == 0) atomicAdd(total, c);
 }
 
-struct EdgeArgs {
-    const int64_t *X, *Y;
-    const uint32_t *poly;
+// ------------------------------------------------------------------ items
+
+struct ItemArgs {
+    const i64x2 *xy;
     const uint64_t *voff;
-    const uint8_t *bad;
-    uint64_t nv;
+    const EdgeBox *box;
+    const Blocks *blocks;
+    const uint64_t *base;      // first item of polygon k (of all polygons)
+    uint64_t first_poly, n_polys, item0, n_items;   // the group of polygons at work
+    uint64_t *key;             // (polygon - first_poly) << 2 border | Hilbert id of the block
+    uint32_t *place;           // the block: x | y << 12 | state of the curve in it << 24
+    uint32_t *info;
     Geo g;
-    uint32_t wide;
+    // where the intervals go
+    uint64_t n;
+    const uint64_t *ai, *fi;   // slots of the items' first starts, from a0 / f0 on
+    uint64_t a0, f0, n_a, n_f;
+    uint64_t *off_a, *off_f;
+    uint32_t *sa, *ea, *sf, *ef;
+    unsigned int *bad_slot;
 };
 
-__device__ __forceinline__ uint64_t next_vertex(const EdgeArgs &a, uint64_t v, uint32_t k) {
-    return v + 1 == a.voff[k + 1] ? a.voff[k] : v + 1;
-}
-
-__global__ void k_edges_count(EdgeArgs a, uint64_t *ccount, uint64_t *xcount, uint32_t *ndistinct) {
-    const uint64_t v = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const uint32_t lane = threadIdx.x & 63;
-    const bool valid = v < a.nv;
-    const uint32_t k = valid ? a.poly[v] : 0xffffffffu;
-    bool distinct = false;
-    uint64_t cc = 0, xc = 0;
-    if (valid && !a.bad[k]) {
-        const uint64_t v2 = next_vertex(a, v, k);
-        const int64_t ax = a.X[v], ay = a.Y[v], bx = a.X[v2], by = a.Y[v2];
-        distinct = ax != bx || ay != by;
-        if (a.wide) {
-            cc = edge_cells<__int128, false>(ax, ay, bx, by, a.g, 0, nullptr);
-            xc = edge_crossings<__int128, false>(ax, ay, bx, by, a.g, 0, nullptr, nullptr);
-        } else {
-            cc = edge_cells<int64_t, false>(ax, ay, bx, by, a.g, 0, nullptr);
-            xc = edge_crossings<int64_t, false>(ax, ay, bx, by, a.g, 0, nullptr, nullptr);
-        }
-    }
-    if (valid) {
-        ccount[v] = cc;
-        xcount[v] = xc;
-    }
-    // distinct edges per polygon, one atomic per run of equal polygon ids in
-    // the wave (ids are non-decreasing in v; a polygon of 10^5 vertices would
-    // otherwise take 10^5 atomics on one word)
-    const uint32_t kp = __shfl_up(k, 1);
-    const bool head = lane == 0 || kp != k;
-    const uint64_t heads = __ballot(head), flags = __ballot(distinct);
-    if (head && k != 0xffffffffu) {
-        const uint64_t above = lane == 63 ? 0 : heads & ~((2ull << lane) - 1);
-        const uint32_t next = above ? uint32_t(__builtin_ctzll(above)) : 64u;
-        const uint64_t upto = next == 64 ? ~0ull : (1ull << next) - 1;
-        const uint32_t c = uint32_t(__popcll(flags & upto & ~((1ull << lane) - 1)));
-        if (c) atomicAdd(&ndistinct[k], c);
-    }
-}
-
-__global__ void k_check_distinct(const uint32_t *ndistinct, uint64_t n, unsigned long long *err) {
-    const uint64_t k = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k < n && ndistinct[k] < 3) atomicMin(err, (unsigned long long)((k << 32) | (kErrNoVertex << 8) | kErrDistinct));
-}
-
-// Each edge writes exactly the entries it counted (same loops), inside its
-// scanned range [coff[v], coff[v] + ccount[v]); the range is checked against
-// the totals first.
-__global__ void k_edges_emit(EdgeArgs a, const uint64_t *coff, const uint64_t *ccount, const uint64_t *xoff,
-                             const uint64_t *xcount, uint64_t ne, uint64_t nx, uint64_t *ckey, uint64_t *xkey,
-                             int64_t *xval) {
-    const uint64_t v = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (v >= a.nv) return;
-    const uint32_t k = a.poly[v];
-    if (a.bad[k] || coff[v] + ccount[v] > ne || xoff[v] + xcount[v] > nx) return;
-    const uint64_t v2 = next_vertex(a, v, k);
-    const int64_t ax = a.X[v], ay = a.Y[v], bx = a.X[v2], by = a.Y[v2];
-    const uint64_t chi = uint64_t(k) << 33, xhi = uint64_t(k) << 16;
-    if (a.wide) {
-        edge_cells<__int128, true>(ax, ay, bx, by, a.g, chi, ckey + coff[v]);
-        edge_crossings<__int128, true>(ax, ay, bx, by, a.g, xhi, xkey + xoff[v], xval + xoff[v]);
-    } else {
-        edge_cells<int64_t, true>(ax, ay, bx, by, a.g, chi, ckey + coff[v]);
-        edge_crossings<int64_t, true>(ax, ay, bx, by, a.g, xhi, xkey + xoff[v], xval + xoff[v]);
-    }
-}
-
-// keep the last entry of every (polygon, cell) run: its flag is the run's OR
-__global__ void k_keep(const uint64_t *key, uint64_t ne, uint64_t *keep) {
-    const uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= ne) return;
-    keep[i] = (i + 1 == ne || (key[i] >> 1) != (key[i + 1] >> 1)) ? 1 : 0;
-}
-
-__global__ void k_compact(const uint64_t *key, const uint64_t *keep, const uint64_t *pos, uint64_t ne,
-                          uint64_t *cell, unsigned long long *m_out) {
-    const uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= ne) return;
-    if (keep[i]) cell[pos[i]] = key[i];
-    if (i + 1 == ne) *m_out = pos[i] + keep[i];
-}
-
-// first touched cell of every polygon (each polygon has at least one)
-__global__ void k_first(const uint64_t *cell, const unsigned long long *m_in, uint64_t n, uint64_t *first) {
+__global__ void k_item_keys(ItemArgs a) {
     const uint64_t t = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const uint64_t m = *m_in;
-    if (t == 0) first[n] = m;
-    if (t >= m) return;
-    const uint64_t k = cell[t] >> 33;
-    if (t == 0 || (cell[t - 1] >> 33) != k) first[k] = t;
-}
-
-// Is the centre of cell (i, j) of polygon k inside?  Asked only for cells
-// whose interior no edge crosses, so the centre is not on the boundary: the
-// parity of the row's crossings left of it decides.
-__device__ bool centre_inside(const uint64_t *xkey, const int64_t *xval, uint64_t nx, uint64_t k, uint32_t i,
-                              uint32_t j, int64_t w) {
-    const uint64_t target = (k << 16) | j;
-    const int64_t Xc = (2 * int64_t(i) + 1) * w;
-    // crossings are sorted by (polygon, row), x ascending within a row: the
-    // count left of the centre is the distance between the row's first entry
-    // and the first entry at or right of the centre
-    uint64_t lo = 0, hi = nx;   // first index with key >= target
-    while (lo < hi) {
+    if (t >= a.n_items) return;
+    uint64_t lo = a.first_poly, hi = a.first_poly + a.n_polys;   // base[lo] <= item0 + t < base[hi]
+    while (hi - lo > 1) {
         const uint64_t mid = (lo + hi) / 2;
-        if (xkey[mid] < target) lo = mid + 1;
+        if (a.base[mid] <= a.item0 + t) lo = mid;
         else hi = mid;
     }
-    uint64_t a = lo, b = nx;    // first index with (key, x) >= (target, Xc)
-    while (a < b) {
-        const uint64_t mid = (a + b) / 2;
-        if (xkey[mid] == target && xval[mid] < Xc) a = mid + 1;
-        else b = mid;
-    }
-    return (a - lo) & 1u;
+    const Blocks c = a.blocks[lo];
+    const uint32_t i = uint32_t(a.item0 + t - a.base[lo]);
+    a.key[t] = ((lo - a.first_poly) << (2 * a.g.border)) |
+               hilbert_d(a.g.border, c.x0 + i % c.nx, c.y0 + i / c.nx);
 }
 
-struct CellArgs {
-    const uint64_t *cell, *first;
-    const unsigned long long *m;
-    const uint64_t *xkey;
-    const int64_t *xval;
-    uint64_t nx;
-    Geo g;
+// What an item tells its neighbours: starts behind the first cell (12 bits for
+// A, 12 for F), and whether the first and the last cell are in A and in F.
+constexpr uint32_t kFirstA = 1u << 24, kLastA = 1u << 25, kFirstF = 1u << 26, kLastF = 1u << 27;
+
+// Is item t + 1 the block that follows item t's on the curve, of the same polygon?
+__device__ __forceinline__ bool follows(const uint64_t *key, uint64_t t, const Geo &g) {
+    const uint64_t u = key[t], v = key[t + 1];
+    return v == u + 1 && (u >> (2 * g.border)) == (v >> (2 * g.border));
+}
+
+// Hilbert steps of three levels by table: (state, x, y) -> the six bits of the
+// id and the state below, and back.  (A state is one of four symmetries.)
+struct Curve {
+    uint8_t to_d[256];    // [state * 64 + x * 8 + y] = d | state << 6
+    uint8_t to_xy[256];   // [state * 64 + d] = x * 8 + y | state << 6
 };
 
-// class bits of Alg. 3: bit 0 the touched cell is Full (no edge crosses its
-// interior and its centre is inside), bit 1 the gap after it is inside
-__global__ void k_classify(CellArgs a, uint64_t bound, uint8_t *cls) {
-    const uint64_t t = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= bound || t >= *a.m) return;
-    const uint64_t key = a.cell[t], k = key >> 33;
-    const uint32_t d = uint32_t(key >> 1);
-    uint8_t c = 0;
-    uint32_t ci, cj;
-    if (!(key & 1)) {
-        hilbert_xy(a.g.order, d, ci, cj);
-        if (centre_inside(a.xkey, a.xval, a.nx, k, ci, cj, a.g.w)) c |= 1;
+__device__ __forceinline__ void curve_tables(Curve &c, uint32_t t) {   // t < 256
+    uint32_t state = t >> 6, d = 0;
+    const uint32_t x = (t >> 3) & 7, y = t & 7, s0 = state;
+    for (int lvl = 2; lvl >= 0; lvl--) {
+        uint32_t qx, qy;
+        sym(state, (x >> lvl) & 1u, (y >> lvl) & 1u, qx, qy);
+        const uint32_t digit = (qx * 3u) ^ qy;
+        d = (d << 2) | digit;
+        state ^= child(digit);
     }
-    if (t + 1 < a.first[k + 1] && t + 1 < *a.m && uint32_t(a.cell[t + 1] >> 1) != d + 1) {
-        hilbert_xy(a.g.order, d + 1, ci, cj);
-        if (centre_inside(a.xkey, a.xval, a.nx, k, ci, cj, a.g.w)) c |= 2;
-    }
-    cls[t] = c;
+    c.to_d[t] = uint8_t(d | (state << 6));
+    c.to_xy[s0 * 64 + d] = uint8_t((x << 3) | y | (state << 6));
 }
 
-// The interval ends a touched cell t owns (cells of its polygon in Hilbert
-// order, u = t's rank, m its count).  A-intervals: a run of touched cells
-// and inside gaps; it starts at the first cell or after an outside gap, and
-// ends at the last cell or before an outside gap.  F-intervals: maximal runs
-// of Full touched cells and inside gaps.
-struct Ends {
-    bool a_start, a_end;
-    bool f_start, f_end;     // at most one of each per cell
-    uint32_t f_start_at, f_end_at;
+// the state of the curve inside block `d` of a grid of blocks of the given order, and the block's place
+__device__ __forceinline__ uint32_t block_xy(int order, uint32_t d, uint32_t &x, uint32_t &y) {
+    uint32_t state = 0;
+    x = y = 0;
+    for (int lvl = order - 1; lvl >= 0; lvl--) {
+        const uint32_t digit = (d >> (2 * lvl)) & 3u;
+        uint32_t bx, by;
+        sym(state, digit >> 1, (digit ^ (digit >> 1)) & 1u, bx, by);
+        x = (x << 1) | bx;
+        y = (y << 1) | by;
+        state ^= child(digit);
+    }
+    return state;
+}
+
+// A sorted item's place, a thread each.
+__global__ void k_item_places(ItemArgs a) {
+    const uint64_t t = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t >= a.n_items) return;
+    uint32_t x, y;
+    const uint32_t state = block_xy(a.g.border, uint32_t(a.key[t] & ((1ull << (2 * a.g.border)) - 1)), x, y);
+    a.place[t] = x | (y << 12) | (state << 24);
+}
+
+// Arithmetic.  While the grid spans at most 1.25 * 2^30 lattice units,
+// coordinates fit in 32 bits and products in 64 (|products| <= 4 E^2 < 2^63);
+// else they take 64 and 128.  Quotients are numbers of cells, below 2^17, so
+// that a single-precision estimate (relative error below 2^-21) is off by
+// less than one, and the exact remainder corrects it.
+struct Narrow {
+    typedef int32_t C;
+    typedef int64_t P;
+};
+struct Wide {
+    typedef int64_t C;
+    typedef __int128 P;
 };
 
-__device__ __forceinline__ Ends cell_ends(const CellArgs &a, const uint8_t *cls, uint64_t t) {
-    const uint64_t key = a.cell[t], k = key >> 33;
-    const uint32_t d = uint32_t(key >> 1);
-    const uint64_t f0 = a.first[k], f1 = a.first[k + 1];
-    const bool has_prev = t > f0, has_next = t + 1 < f1 && t + 1 < *a.m;
-    const uint32_t dp = has_prev ? uint32_t(a.cell[t - 1] >> 1) : 0, dn = has_next ? uint32_t(a.cell[t + 1] >> 1) : 0;
-    const uint8_t c = cls[t], cp = has_prev ? cls[t - 1] : 0, cn = has_next ? cls[t + 1] : 0;
-    const bool gap_before = has_prev && dp + 1 != d, gap_after = has_next && dn != d + 1;
-    Ends e;
-    e.a_start = !has_prev || (gap_before && !(cp & 2));
-    e.a_end = !has_next || (gap_after && !(c & 2));
-    const bool full = c & 1;
-    const bool prev_f = has_prev && (gap_before ? (cp & 2) : (cp & 1));
-    const bool next_f = has_next && (gap_after ? (c & 2) : (cn & 1));
-    const bool gap_in = gap_after && (c & 2);
-    e.f_start = false;
-    e.f_end = false;
-    e.f_start_at = e.f_end_at = 0;
-    if (full && !prev_f) { e.f_start = true; e.f_start_at = d; }
-    if (gap_in && !full) { e.f_start = true; e.f_start_at = d + 1; }
-    if (full && !next_f) { e.f_end = true; e.f_end_at = d + 1; }
-    if (gap_in && !(cn & 1)) { e.f_end = true; e.f_end_at = dn; }
-    return e;
+struct QR {
+    int32_t q;
+    bool zero;   // no remainder
+};
+
+__device__ __forceinline__ float to_float(int64_t v) {
+    return __builtin_fmaf(float(int32_t(v >> 32)), 4294967296.0f, float(uint32_t(v)));
 }
 
-__global__ void k_count_ends(CellArgs a, const uint8_t *cls, uint64_t bound, uint64_t *na, uint64_t *nf) {
+__device__ __forceinline__ QR div_cells(int64_t n, int64_t d, float inv) {   // n >= 0
+    int32_t q = int32_t(to_float(n) * inv);
+    int64_t r = n - int64_t(q) * d;
+    if (r < 0) {
+        q--;
+        r += d;
+    } else if (r >= d) {
+        q++;
+        r -= d;
+    }
+    return {q, r == 0};
+}
+__device__ __forceinline__ QR div_cells(__int128 n, __int128 d, float) {
+    const __int128 q = n / d;
+    return {int32_t(q), n == q * d};
+}
+
+// floor(v / w) and, for the centre lines, floor(v / 2 w); v >= 0
+__device__ __forceinline__ int32_t cell_of(int64_t v, const Geo &g) { return div_cells(v, g.w, g.inv_wf).q; }
+__device__ __forceinline__ int32_t half_of(int64_t v, const Geo &g) { return div_cells(v, 2 * g.w, g.inv_2wf).q; }
+
+template <class M>
+struct Edge {   // the lower end first
+    typename M::C ux, uy, vx, vy;
+};
+
+template <class M>
+struct ItemLds {
+    Edge<M> edge[64];           // edges that meet the block
+    uint32_t upto[64];          // rows of the edges up to each
+    int32_t row0[64];           // an edge's first row, less the rows before it
+    uint32_t touched[128], crossed[128];   // in Hilbert order
+    uint32_t parity[128];       // per row of cells: two words
+};
+
+template <class M>
+struct Block {
+    int32_t cx, cy;             // first cell
+    typename M::C x0, y0, x1, y1;   // closed, lattice units
+    uint32_t state;
+    int32_t size;               // cells a side
+};
+
+// rows of the block (bits) whose centre line lies below y, as the half-open
+// crossing rule has it: an edge crosses the line when exactly one of its ends
+// is above.  Row j's centre, doubled, is (2 j + 1) w < 2 y for the rows
+// j < ceil((2 y - w) / 2 w).
+template <class M>
+__device__ __forceinline__ uint64_t rows_below(typename M::C y, const Block<M> &b, const Geo &g) {
+    const int32_t c = half_of(2 * int64_t(y) + g.w - 1, g) - b.cy;
+    return c <= 0 ? 0ull : c >= 64 ? ~0ull : (1ull << c) - 1;
+}
+
+// The cells of row j that the edge meets.
+template <class M>
+__device__ __forceinline__ void raster_row(const Edge<M> &e, int32_t j, const Block<M> &b, const Geo &g,
+                                           ItemLds<M> &l, const Curve &cv) {
+    typedef typename M::C C;
+    typedef typename M::P P;
+    const C w = C(g.w);
+    const bool horiz = e.uy == e.vy;
+    const C D = horiz ? C(1) : e.vy - e.uy, dx = e.vx - e.ux;
+    const P Dw = P(D) * P(w), x0 = P(e.ux) * P(D);
+    const float inv = __builtin_amdgcn_rcpf(float(D) * float(w));
+    const C y0 = C(j) * w, y1 = y0 + w, ylo = max(e.uy, y0), yhi = min(e.vy, y1);
+    const P p = x0 + P(ylo - e.uy) * P(dx), q = horiz ? P(e.vx) : x0 + P(yhi - e.uy) * P(dx);
+    const QR q0 = div_cells(p < q ? p : q, Dw, inv), q1 = div_cells(p < q ? q : p, Dw, inv);
+    const int32_t row = j - b.cy;
+    const int32_t i0 = max(q0.q - (q0.zero ? 1 : 0), b.cx), i1 = min(q1.q, b.cx + b.size - 1);
+    const bool open_row = horiz ? (y0 < e.uy && e.uy < y1) : ylo < yhi;
+    const int32_t o0 = open_row ? q0.q : 1, o1 = open_row ? q1.q - (q1.zero ? 1 : 0) : 0;
+    const uint32_t y = uint32_t(row);
+    for (int32_t i = i0; i <= i1; i++) {
+        const uint32_t x = uint32_t(i - b.cx);
+        uint32_t d;
+        if (b.size == 64) {
+            const uint32_t hi = cv.to_d[b.state * 64 + (x >> 3) * 8 + (y >> 3)];
+            d = ((hi & 63u) << 6) | (cv.to_d[(hi >> 6) * 64 + (x & 7) * 8 + (y & 7)] & 63u);
+        } else {
+            d = hilbert_d(g.order, x, y);   // the grid is smaller than a block
+        }
+        atomicOr(&l.touched[d >> 5], 1u << (d & 31));
+        if (i >= o0 && i <= o1) atomicOr(&l.crossed[d >> 5], 1u << (d & 31));
+    }
+    // the crossing of the row's centre line: at x = N / D (doubled), it lies
+    // left of the centres of the cells i with (2 i + 1) w > floor(x), the first
+    // of which is floor((N + w D) / 2 w D)
+    const P c = P(2 * int64_t(j) + 1) * P(w), c0 = c - P(2) * P(e.uy);
+    if (!horiz && c0 >= 0 && c < P(2) * P(e.vy)) {
+        const P N = P(2) * x0 + c0 * P(dx);
+        const int32_t im = max(div_cells(N + Dw, Dw + Dw, 0.5f * inv).q, b.cx) - b.cx;
+        if (im < b.size) atomicXor(&l.parity[2 * row + (im >> 5)], 1u << (im & 31));
+    }
+}
+
+__device__ __forceinline__ uint64_t shfl_xor64(uint64_t v, int mask) {
+    return uint64_t(uint32_t(__shfl_xor(int(uint32_t(v)), mask))) |
+           (uint64_t(uint32_t(__shfl_xor(int(uint32_t(v >> 32)), mask))) << 32);
+}
+
+// The item's A and F cells in Hilbert order, 64 a lane.
+template <class M>
+__device__ __forceinline__ void raster_item(const ItemArgs &a, uint64_t poly, const Block<M> &b, ItemLds<M> &l,
+                                            const Curve &cv, uint32_t lane, uint64_t &A, uint64_t &F) {
+    typedef typename M::C C;
+    const uint64_t v0 = a.voff[poly], nv = a.voff[poly + 1] - v0;
+    const EdgeBox *boxes = a.box + box_at(v0, poly);
+    const uint32_t nb = uint32_t((nv + 63) / 64);
+    uint64_t left = 0;   // rows whose parity the lane's passing edges change
+    bool any = false;
+    for (uint32_t c0 = 0; c0 < nb; c0 += 64) {
+        // boxes of 64 edges, one a lane: beside the block, left of it, or to be looked into
+        bool into = c0 + lane < nb;
+        if (into && nb > 1) {
+            const uint32_t c = c0 + lane;
+            const EdgeBox x = boxes[c];
+            const bool beside = x.y1 < b.y0 || x.y0 > b.y1 || x.x0 > b.x1;
+            if (!beside && x.x1 < b.x0) {
+                const uint64_t e1 = min<uint64_t>(nv, 64ull * c + 64);
+                left ^= rows_below<M>(C(a.xy[v0 + 64ull * c].y), b, a.g) ^
+                        rows_below<M>(C(a.xy[v0 + (e1 == nv ? 0 : e1)].y), b, a.g);
+            }
+            into = !beside && x.x1 >= b.x0;
+        }
+        uint64_t todo = __ballot(into);
+        while (todo) {
+            const uint32_t c = c0 + uint32_t(__builtin_ctzll(todo));
+            todo &= todo - 1;
+            const uint64_t k = 64ull * c + lane;
+            Edge<M> e{};
+            bool in = false, pass = false;
+            if (k < nv) {
+                i64x2 u, v;
+                load_edge(a.xy, v0, nv, k, u, v);
+                const bool up = u.y <= v.y;
+                e = up ? Edge<M>{C(u.x), C(u.y), C(v.x), C(v.y)} : Edge<M>{C(v.x), C(v.y), C(u.x), C(u.y)};
+                const bool beside = e.vy < b.y0 || e.uy > b.y1 || min(e.ux, e.vx) > b.x1;
+                in = !beside && max(e.ux, e.vx) >= b.x0;
+                pass = !beside && !in;
+            }
+            if (pass) left ^= rows_below<M>(e.uy, b, a.g) ^ rows_below<M>(e.vy, b, a.g);
+            if (!__any(in)) continue;
+            if (!any) {
+                // the first edge here: clear the bit arrays
+                any = true;
+                wave_lds_sync();
+#pragma unroll
+                for (uint32_t i = 0; i < 128; i += 64)
+                    l.touched[i + lane] = l.crossed[i + lane] = l.parity[i + lane] = 0;
+            }
+            // the edges' rows one after another; lane i takes the i-th next
+            int32_t j0 = 0, rows = 0;
+            if (in) {
+                j0 = max(b.cy, cell_of(int64_t(e.uy) + a.g.w - 1, a.g) - 1);
+                rows = min(b.cy + b.size - 1, cell_of(e.vy, a.g)) - j0 + 1;
+            }
+            uint32_t upto = uint32_t(rows);
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t o = __shfl_up(upto, d);
+                if (lane >= uint32_t(d)) upto += o;
+            }
+            const uint32_t total = __builtin_amdgcn_readlane(upto, 63);
+            wave_lds_sync();
+            l.edge[lane] = e;
+            l.upto[lane] = upto;
+            l.row0[lane] = j0 - int32_t(upto - uint32_t(rows));
+            wave_lds_sync();
+            for (uint32_t t0 = 0; t0 < total; t0 += 64) {
+                const uint32_t t = t0 + lane;
+                if (t >= total) continue;
+                uint32_t i = 0;   // the first edge with upto > t
+#pragma unroll
+                for (uint32_t s = 32; s > 0; s >>= 1) i += l.upto[i + s - 1] <= t ? s : 0;
+                raster_row<M>(l.edge[i], l.row0[i] + int32_t(t), b, a.g, l, cv);
+            }
+        }
+    }
+    if (__any(left != 0))
+        for (int off = 32; off > 0; off >>= 1) left ^= shfl_xor64(left, off);
+    if (!any) {   // no edge here: all cells alike
+        A = F = (left & 1) && b.size == 64 ? ~0ull : 0ull;
+        return;
+    }
+    wave_lds_sync();
+    // parity to the left of each centre, row by row (a lane per row)
+    uint64_t p = uint64_t(l.parity[2 * lane]) | (uint64_t(l.parity[2 * lane + 1]) << 32);
+    p ^= (left >> lane) & 1;
+    for (int s = 1; s < 64; s <<= 1) p ^= p << s;
+    wave_lds_sync();
+    l.parity[2 * lane] = uint32_t(p);
+    l.parity[2 * lane + 1] = uint32_t(p >> 32);
+    const uint64_t T64 = uint64_t(l.touched[2 * lane]) | (uint64_t(l.touched[2 * lane + 1]) << 32);
+    const uint64_t C64 = uint64_t(l.crossed[2 * lane]) | (uint64_t(l.crossed[2 * lane + 1]) << 32);
+    wave_lds_sync();
+    // the lane's 64 cells: one 8 x 8 square
+    const uint32_t hi = b.size == 64 ? cv.to_xy[b.state * 64 + lane] : 0u;
+    auto inside = [&](uint32_t bit) {
+        uint32_t x, y;
+        if (b.size == 64) {
+            const uint32_t lo = cv.to_xy[(hi >> 6) * 64 + bit];
+            x = ((hi >> 3) & 7) * 8 + ((lo >> 3) & 7);
+            y = (hi & 7) * 8 + (lo & 7);
+        } else {
+            hilbert_xy(a.g.order, lane * 64 + bit, x, y);
+        }
+        return (l.parity[2 * y + (x >> 5)] >> (x & 31)) & 1u;
+    };
+    uint64_t valid = ~0ull;
+    if (b.size < 64) {
+        const uint32_t cells = uint32_t(b.size) * uint32_t(b.size);
+        valid = lane * 64 >= cells ? 0ull : cells - lane * 64 >= 64 ? ~0ull : (1ull << (cells - lane * 64)) - 1;
+    }
+    const uint64_t Z = ~T64 & valid;
+    uint64_t runs = Z & ~(Z << 1), G = 0;
+    while (runs) {
+        const uint32_t bit = uint32_t(__builtin_ctzll(runs));
+        runs &= runs - 1;
+        G |= uint64_t(inside(bit)) << bit;
+    }
+    // a run whose first bit is in G: adding G carries through it
+    const uint64_t gap = Z & ~(Z + G);
+    uint64_t border = T64 & ~C64, full = 0;
+    while (border) {
+        const uint32_t bit = uint32_t(__builtin_ctzll(border));
+        border &= border - 1;
+        full |= uint64_t(inside(bit)) << bit;
+    }
+    A = T64 | gap;
+    F = full | gap;
+}
+
+// Interval ends of one kind in an item: `cells` of the lane, `before` and
+// `after`: is the cell before the item's first, behind its last one in it?
+__device__ __forceinline__ void run_ends(uint64_t cells, bool before, bool after, uint32_t lane, uint64_t &starts,
+                                         uint64_t &stops) {
+    const uint32_t top = __shfl_up(uint32_t(cells >> 63), 1), low = __shfl_down(uint32_t(cells & 1), 1);
+    const uint64_t cin = lane == 0 ? uint64_t(before) : uint64_t(top);
+    const uint64_t cout = lane == 63 ? uint64_t(after) : uint64_t(low);
+    starts = cells & ~((cells << 1) | cin);
+    stops = cells & ~((cells >> 1) | (cout << 63));
+}
+
+// the sums of v over the lanes before this one
+__device__ __forceinline__ uint32_t wave_before(uint32_t v, uint32_t lane) {
+    uint32_t s = v;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(s, d);
+        if (lane >= uint32_t(d)) s += o;
+    }
+    return s - v;
+}
+
+// Where one kind's intervals of a lane go: its starts to s[at ...], its stops
+// to e[stop_at ...].  A lane's first stop is its first start's, unless the
+// interval runs into the lane: then it belongs to the start before.
+struct Runs {
+    uint64_t starts, stops, at, stop_at;
+};
+
+__device__ __forceinline__ Runs lane_runs(uint64_t cells, bool before, bool after, uint32_t lane) {
+    Runs r;
+    run_ends(cells, before, after, lane, r.starts, r.stops);
+    r.at = 0;
+    r.stop_at = (cells & 1) && !(r.starts & 1) ? ~0ull : 0ull;
+    return r;
+}
+
+// the next interval ends, checked against the sizes that were allocated (which
+// consistent items never exceed; below zero wraps past every bound)
+__device__ __forceinline__ bool write_next(Runs &r, uint32_t d0, uint64_t n, uint32_t *s, uint32_t *e) {
+    bool ok = true;
+    if (r.starts) {
+        if (r.at < n) s[r.at] = d0 + uint32_t(__builtin_ctzll(r.starts));
+        else ok = false;
+        r.at++;
+        r.starts &= r.starts - 1;
+    }
+    if (r.stops) {
+        if (r.stop_at < n) e[r.stop_at] = d0 + uint32_t(__builtin_ctzll(r.stops)) + 1;
+        else ok = false;
+        r.stop_at++;
+        r.stops &= r.stops - 1;
+    }
+    return ok;
+}
+
+template <class M, bool WRITE>
+__global__ __launch_bounds__(kBlock) void k_items(ItemArgs a) {
+    __shared__ ItemLds<M> lds[kWavesPerBlock];
+    __shared__ Curve cv;
+    const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    curve_tables(cv, threadIdx.x);
+    __syncthreads();
+    const uint64_t waves = uint64_t(gridDim.x) * kWavesPerBlock;
+    for (uint64_t t = uint64_t(blockIdx.x) * kWavesPerBlock + w; t < a.n_items; t += waves) {
+        const uint64_t key = a.key[t];
+        const uint64_t poly = a.first_poly + (key >> (2 * a.g.border));
+        const uint32_t place = uniform(a.place[t]);
+        typedef typename M::C C;
+        Block<M> b;
+        b.state = place >> 24;
+        b.size = int32_t(min<int64_t>(64, a.g.cells));
+        b.cx = int32_t(place & 0xfffu) * 64;
+        b.cy = int32_t((place >> 12) & 0xfffu) * 64;
+        b.x0 = C(b.cx) * C(a.g.w);
+        b.y0 = C(b.cy) * C(a.g.w);
+        b.x1 = C(b.cx + b.size) * C(a.g.w);
+        b.y1 = C(b.cy + b.size) * C(a.g.w);
+        uint64_t A, F;
+        raster_item<M>(a, poly, b, lds[w], cv, lane, A, F);
+        if (!WRITE) {
+            uint64_t s, f, e;
+            run_ends(A, true, true, lane, s, e);   // (a start at the first cell is not counted here)
+            run_ends(F, true, true, lane, f, e);
+            uint32_t c = uint32_t(__popcll(s)) | (uint32_t(__popcll(f)) << 12);
+            for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+            const uint32_t a0 = __builtin_amdgcn_readlane(uint32_t(A), 0), f0 = __builtin_amdgcn_readlane(uint32_t(F), 0);
+            const uint32_t a1 = __builtin_amdgcn_readlane(uint32_t(A >> 32), 63);
+            const uint32_t f1 = __builtin_amdgcn_readlane(uint32_t(F >> 32), 63);
+            c |= (a0 & 1 ? kFirstA : 0) | (f0 & 1 ? kFirstF : 0) | (a1 >> 31 ? kLastA : 0) | (f1 >> 31 ? kLastF : 0);
+            if (lane == 0) a.info[t] = c;
+        } else {
+            const bool prev = t > 0 && follows(a.key, t - 1, a.g), next = t + 1 < a.n_items && follows(a.key, t, a.g);
+            const uint32_t ip = prev ? a.info[t - 1] : 0u, in = next ? a.info[t + 1] : 0u;
+            const uint64_t at = a.a0 + a.ai[t], ft = a.f0 + a.fi[t];
+            const uint32_t d0 = (uint32_t(key & ((1ull << (2 * a.g.border)) - 1)) << 12) + lane * 64;
+            if (__any(A != 0)) {   // (F lies in A)
+                Runs ra = lane_runs(A, ip & kLastA, in & kFirstA, lane), rf = lane_runs(F, ip & kLastF, in & kFirstF, lane);
+                // starts of A (at most 2,048 an item) and of F in the lanes before
+                const uint32_t n = wave_before(uint32_t(__popcll(ra.starts)) | (uint32_t(__popcll(rf.starts)) << 16), lane);
+                ra.at += at + (n & 0xffffu);
+                ra.stop_at += at + (n & 0xffffu);
+                rf.at += ft + (n >> 16);
+                rf.stop_at += ft + (n >> 16);
+                bool ok = true;
+                while (ra.starts | ra.stops | rf.starts | rf.stops) {
+                    ok &= write_next(ra, d0, a.n_a, a.sa, a.ea);
+                    ok &= write_next(rf, d0, a.n_f, a.sf, a.ef);
+                }
+                if (!ok) atomicOr(a.bad_slot, 1u);
+            }
+            if (lane == 0 && (t == 0 || (a.key[t - 1] >> (2 * a.g.border)) != (key >> (2 * a.g.border)))) {
+                a.off_a[poly] = at;
+                a.off_f[poly] = ft;
+            }
+        }
+    }
+    if (WRITE && blockIdx.x == 0 && threadIdx.x == 0 && a.first_poly + a.n_polys == a.n) {
+        a.off_a[a.n] = a.n_a;
+        a.off_f[a.n] = a.n_f;
+    }
+}
+
+// starts of each item, with the one at its first cell unless the block before
+// it on the curve ends in the same interval; zero behind the last item
+__global__ void k_item_starts(ItemArgs a, uint64_t *na, uint64_t *nf) {
     const uint64_t t = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t >= bound) return;
-    if (t >= *a.m) {
+    if (t > a.n_items) return;
+    if (t == a.n_items) {
         na[t] = nf[t] = 0;
         return;
     }
-    const Ends e = cell_ends(a, cls, t);
-    na[t] = e.a_start;
-    nf[t] = e.f_start;
-}
-
-__global__ void k_totals(const uint64_t *na, const uint64_t *ai, const uint64_t *nf, const uint64_t *fi,
-                         uint64_t bound, unsigned long long *tot) {
-    tot[0] = ai[bound - 1] + na[bound - 1];
-    tot[1] = fi[bound - 1] + nf[bound - 1];
-}
-
-// Every slot is checked against the sizes the host allocated; a slot out of
-// range (which consistent class bits never give) sets *bad_slot instead.
-__global__ void k_scatter(CellArgs a, const uint8_t *cls, uint64_t bound, const uint64_t *na, const uint64_t *ai,
-                          const uint64_t *nf, const uint64_t *fi, uint64_t n, const unsigned long long *tot,
-                          uint64_t n_a, uint64_t n_f, uint64_t *off_a, uint64_t *off_f, uint32_t *sa, uint32_t *ea,
-                          uint32_t *sf, uint32_t *ef, unsigned int *bad_slot) {
-    const uint64_t t = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (t == 0) {
-        off_a[n] = tot[0];
-        off_f[n] = tot[1];
-    }
-    if (t >= bound || t >= *a.m) return;
-    const uint64_t key = a.cell[t], k = key >> 33;
-    const uint32_t d = uint32_t(key >> 1);
-    if (t == a.first[k]) {
-        off_a[k] = ai[t];
-        off_f[k] = fi[t];
-    }
-    const Ends e = cell_ends(a, cls, t);
-    // slots as unsigned: "- 1" below zero wraps past every bound
-    const uint64_t s_a = ai[t], e_a = ai[t] + na[t] - 1, s_f = fi[t], e_f = fi[t] + nf[t] - 1;
-    if ((e.a_start && s_a >= n_a) || (e.a_end && e_a >= n_a) || (e.f_start && s_f >= n_f) ||
-        (e.f_end && e_f >= n_f)) {
-        atomicOr(bad_slot, 1u);
-        return;
-    }
-    if (e.a_start) sa[s_a] = d;
-    if (e.a_end) ea[e_a] = d + 1;
-    if (e.f_start) sf[s_f] = e.f_start_at;
-    if (e.f_end) ef[e_f] = e.f_end_at;
+    const uint32_t i = a.info[t], p = t > 0 && follows(a.key, t - 1, a.g) ? a.info[t - 1] : 0u;
+    na[t] = (i & 0xfffu) + ((i & kFirstA) && !(p & kLastA) ? 1 : 0);
+    nf[t] = ((i >> 12) & 0xfffu) + ((i & kFirstF) && !(p & kLastF) ? 1 : 0);
 }
 
 uint32_t blocks_for(uint64_t n) { return uint32_t(std::max<uint64_t>(1, (n + kThreads - 1) / kThreads)); }
 
-// Stream-ordered scratch, freed when the call returns (in stream order).
+// Stream-ordered scratch, freed when the call returns (in stream order): a
+// block at a time, cut into arrays.
 struct Scratch {
     hipStream_t s;
     std::vector<void *> held;
-    hipError_t err = hipSuccess;
+    char *at = nullptr;
+    bool reserve(uint64_t bytes) {
+        void *p = nullptr;
+        if (hipMallocAsync(&p, std::max<uint64_t>(bytes, 256), s) != hipSuccess) return false;
+        held.push_back(p);
+        at = static_cast<char *>(p);
+        return true;
+    }
+    static uint64_t up(uint64_t b) { return (b + 255) & ~uint64_t(255); }
     template <typename T>
     T *get(uint64_t count) {
-        void *p = nullptr;
-        if (err == hipSuccess) err = hipMallocAsync(&p, std::max<uint64_t>(count, 1) * sizeof(T), s);
-        if (err != hipSuccess) return nullptr;
-        held.push_back(p);
-        return static_cast<T *>(p);
+        T *p = reinterpret_cast<T *>(at);
+        at += up(count * sizeof(T));
+        return p;
     }
     ~Scratch() {
         for (void *p : held) (void)hipFreeAsync(p, s);
     }
 };
+
+// Most items worked on at once (about 40 bytes of scratch each); a call with
+// more goes through its polygons in groups.
+constexpr uint64_t kGroupItems = 1ull << 26;
 
 }  // namespace
 }  // namespace april
@@ -500,48 +874,43 @@ extern "C" int april_build_lists_gpu(const april_grid_t *grid, const double *xy,
     BG_TRY(hipGetDevice(&dev));
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
 
-    Geo g{lg.x0, lg.y0, lg.w, lg.cells, lg.order, (flags & APRIL_STRICT) ? 1u : 0u};
-    // 64-bit products are exact while the grid spans at most 1.25 * 2^30
-    // lattice units (|products| <= 4 E^2 < 2^63)
+    Geo g{lg.x0, lg.y0, lg.w, 1.0 / double(lg.w), float(1.0 / double(lg.w)), float(0.5 / double(lg.w)), lg.cells, lg.order, std::max(0, lg.order - 6),
+          (flags & APRIL_STRICT) ? 1u : 0u};
+    // narrow arithmetic is exact while the grid spans at most 1.25 * 2^30 lattice units
     const uint32_t wide = double(lg.w) * double(lg.cells) > 1.25 * 1073741824.0 ? 1u : 0u;
 
-    Scratch sc{s};
-    double *d_xy = sc.get<double>(2 * nv);
-    uint64_t *d_voff = sc.get<uint64_t>(n + 1);
-    int64_t *d_X = sc.get<int64_t>(nv), *d_Y = sc.get<int64_t>(nv);
-    uint32_t *d_poly = sc.get<uint32_t>(nv), *d_ndist = sc.get<uint32_t>(n);
-    uint8_t *d_bad = sc.get<uint8_t>(n);
-    uint64_t *d_cc = sc.get<uint64_t>(nv), *d_xc = sc.get<uint64_t>(nv);
-    uint64_t *d_coff = sc.get<uint64_t>(nv), *d_xoff = sc.get<uint64_t>(nv);
-    unsigned long long *d_small = sc.get<unsigned long long>(8);   // err, m, totals
-    if (sc.err != hipSuccess) return fail(APRIL_E_NOMEM, std::string("build scratch: ") + hipGetErrorString(sc.err));
+    // 1-2: vertices, boxes, blocks
+    const uint64_t n_boxes = (nv >> 6) + n;
+    size_t scan_bytes = 0;
+    BG_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, (uint64_t *)nullptr, (uint64_t *)nullptr, n + 1, s));
+    Scratch sc{s, {}};
+    auto pad = Scratch::up;
+    if (!sc.reserve(pad(16 * nv) + 3 * pad(8 * (n + 1)) + pad(32 * n_boxes) + pad(4 * n_boxes) + pad(8 * n) + pad(64) +
+                    pad(scan_bytes)))
+        return fail(APRIL_E_NOMEM, "build scratch");
+    i64x2 *d_xy = sc.get<i64x2>(nv);
+    uint64_t *d_voff = sc.get<uint64_t>(n + 1), *d_items = sc.get<uint64_t>(n + 1), *d_base = sc.get<uint64_t>(n + 1);
+    EdgeBox *d_box = sc.get<EdgeBox>(n_boxes);
+    uint32_t *d_distinct = sc.get<uint32_t>(n_boxes);
+    Blocks *d_blocks = sc.get<Blocks>(n);
+    // err; bound of the cells; bad slot, longest list, long A-lists
+    unsigned long long *d_small = sc.get<unsigned long long>(8);
+    void *d_scan = sc.get<char>(scan_bytes);
     std::vector<uint64_t> voff_rel(n + 1);
     for (uint64_t k = 0; k <= n; k++) voff_rel[k] = vtx_off[k] - vtx_off[0];
     BG_TRY(hipMemcpyAsync(d_xy, xy + 2 * vtx_off[0], 16 * nv, hipMemcpyHostToDevice, s));
     BG_TRY(hipMemcpyAsync(d_voff, voff_rel.data(), 8 * (n + 1), hipMemcpyHostToDevice, s));
-    BG_TRY(hipMemsetAsync(d_ndist, 0, 4 * n, s));
-    BG_TRY(hipMemsetAsync(d_bad, 0, n, s));
     BG_TRY(hipMemsetAsync(d_small, 0xff, 8, s));   // err = none
-
-    // 1-2: vertices, then per-edge counts and their scans
-    k_vertices<<<blocks_for(nv), kThreads, 0, s>>>(d_xy, d_voff, n, nv, g, d_X, d_Y, d_poly, d_bad, d_small);
-    EdgeArgs ea{d_X, d_Y, d_poly, d_voff, d_bad, nv, g, wide};
-    k_edges_count<<<blocks_for(nv), kThreads, 0, s>>>(ea, d_cc, d_xc, d_ndist);
-    k_check_distinct<<<blocks_for(n), kThreads, 0, s>>>(d_ndist, n, d_small);
+    BG_TRY(hipMemsetAsync(d_small + 1, 0, 56, s));
+    k_vertices<<<blocks_for(nv), kThreads, 0, s>>>(d_xy, d_voff, n, nv, g, d_small);
+    PolyArgs pa{d_xy, d_voff, n, n_boxes, d_box, d_distinct, d_small + 1, g};
+    k_edge_boxes<<<uint32_t(std::min<uint64_t>((n_boxes + 3) / 4, uint64_t(st->cus) * 8)), 256, 0, s>>>(pa);
+    k_polygons<<<uint32_t(std::min<uint64_t>((n + 3) / 4, 16384)), 256, 0, s>>>(pa, d_blocks, d_items, d_small);
     BG_TRY(hipGetLastError());
-    size_t tmp_bytes = 0, need = 0;
-    BG_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, need, d_cc, d_coff, nv, s));
-    tmp_bytes = std::max(tmp_bytes, need);
-    void *d_tmp = sc.get<char>(tmp_bytes);
-    if (!d_tmp) return fail(APRIL_E_NOMEM, "build scratch");
-    BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_tmp, tmp_bytes, d_cc, d_coff, nv, s));
-    BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_tmp, tmp_bytes, d_xc, d_xoff, nv, s));
-    uint64_t h[5] = {0, 0, 0, 0, 0};   // err, last coff, last cc, last xoff, last xc
-    BG_TRY(hipMemcpyAsync(&h[0], d_small, 8, hipMemcpyDeviceToHost, s));
-    BG_TRY(hipMemcpyAsync(&h[1], d_coff + nv - 1, 8, hipMemcpyDeviceToHost, s));
-    BG_TRY(hipMemcpyAsync(&h[2], d_cc + nv - 1, 8, hipMemcpyDeviceToHost, s));
-    BG_TRY(hipMemcpyAsync(&h[3], d_xoff + nv - 1, 8, hipMemcpyDeviceToHost, s));
-    BG_TRY(hipMemcpyAsync(&h[4], d_xc + nv - 1, 8, hipMemcpyDeviceToHost, s));
+    BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_scan, scan_bytes, d_items, d_base, n + 1, s));
+    uint64_t h[2] = {0, 0}, items = 0;   // err, bound; items
+    BG_TRY(hipMemcpyAsync(h, d_small, 16, hipMemcpyDeviceToHost, s));
+    BG_TRY(hipMemcpyAsync(&items, d_base + n, 8, hipMemcpyDeviceToHost, s));
     BG_TRY(hipStreamSynchronize(s));
     if (h[0] != ~0ull) {
         const uint64_t k = h[0] >> 32, code = h[0] & 0xff;
@@ -550,69 +919,93 @@ extern "C" int april_build_lists_gpu(const april_grid_t *grid, const double *xy,
                         (code == kErrGrid ? " reaches the outer cell ring or leaves the grid"
                                           : " has a non-lattice coordinate or < 3 distinct vertices"));
     }
-    const uint64_t ne = h[1] + h[2], nx = h[3] + h[4];
-    if (ne == 0) return fail(APRIL_E_INVALID, "no boundary cells");
-    if (ne >= (1ull << 32) || nx >= (1ull << 32))
-        return fail(APRIL_E_NOMEM, "more than 2^32 boundary-cell entries in one call: split the collection");
-
-    // 3-4: emit, then sort both key sets
-    uint64_t *d_ck = sc.get<uint64_t>(ne), *d_ck2 = sc.get<uint64_t>(ne);
-    uint64_t *d_xk = sc.get<uint64_t>(nx), *d_xk2 = sc.get<uint64_t>(nx);
-    int64_t *d_xv = sc.get<int64_t>(nx), *d_xv2 = sc.get<int64_t>(nx);
-    if (sc.err != hipSuccess) return fail(APRIL_E_NOMEM, std::string("build scratch: ") + hipGetErrorString(sc.err));
-    k_edges_emit<<<blocks_for(nv), kThreads, 0, s>>>(ea, d_coff, d_cc, d_xoff, d_xc, ne, nx, d_ck, d_xk, d_xv);
-    BG_TRY(hipGetLastError());
-    int kbits = 1;
-    while (kbits < 31 && (1ull << kbits) < n) kbits++;
-    need = 0;
-    BG_TRY(hipcub::DeviceRadixSort::SortKeys(nullptr, need, d_ck, d_ck2, ne, 0, 33 + kbits, s));
-    size_t need2 = 0;
-    BG_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, need2, d_xk2, d_xk, reinterpret_cast<uint64_t *>(d_xv2),
-                                              reinterpret_cast<uint64_t *>(d_xv), nx, 0, 16 + kbits, s));
-    size_t need3 = 0;
-    BG_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, need3, d_ck, d_ck2, ne, s));
-    // doubled crossing x < 2 * cells * w
-    int xbits = 1;
-    while (xbits < 64 && double(uint64_t(1) << xbits) <= 2.0 * double(lg.cells) * double(lg.w)) xbits++;
-    size_t need4 = 0;
-    BG_TRY(hipcub::DeviceRadixSort::SortPairs(nullptr, need4, reinterpret_cast<uint64_t *>(d_xv),
-                                              reinterpret_cast<uint64_t *>(d_xv2), d_xk, d_xk2, nx, 0, xbits, s));
-    const size_t tmp2 = std::max({need, need2, need3, need4});
-    void *d_tmp2 = sc.get<char>(tmp2);
-    if (!d_tmp2) return fail(APRIL_E_NOMEM, "build scratch");
-    if (ne) BG_TRY(hipcub::DeviceRadixSort::SortKeys(d_tmp2, need, d_ck, d_ck2, ne, 0, 33 + kbits, s));
-    // crossings: by x first, then (stable) by (polygon, row), so that x is
-    // ascending within a row; x >= 0 (relative coordinates are positive)
-    if (nx) {
-        uint64_t *xv = reinterpret_cast<uint64_t *>(d_xv), *xv2 = reinterpret_cast<uint64_t *>(d_xv2);
-        BG_TRY(hipcub::DeviceRadixSort::SortPairs(d_tmp2, need4, xv, xv2, d_xk, d_xk2, nx, 0, xbits, s));
-        BG_TRY(hipcub::DeviceRadixSort::SortPairs(d_tmp2, need2, d_xk2, d_xk, xv2, xv, nx, 0, 16 + kbits, s));
+    if (h[1] >= (1ull << 32)) {   // (few calls: then the cells themselves are counted)
+        BG_TRY(hipMemsetAsync(d_small + 1, 0, 8, s));
+        k_count_cells<<<uint32_t(st->cus) * 8, 256, 0, s>>>(d_xy, d_voff, n, nv, g, wide, d_small + 1);
+        BG_TRY(hipGetLastError());
+        BG_TRY(hipMemcpyAsync(h, d_small, 16, hipMemcpyDeviceToHost, s));
+        BG_TRY(hipStreamSynchronize(s));
+        if (h[1] >= (1ull << 32))
+            return fail(APRIL_E_NOMEM, "more than 2^32 boundary-cell entries in one call: split the collection");
     }
 
-    // 5: one entry per (polygon, cell); d_ck is free again and holds the flags
-    uint64_t *keep = d_ck, *pos = sc.get<uint64_t>(ne), *cell = sc.get<uint64_t>(ne);
-    uint64_t *first = sc.get<uint64_t>(n + 1);
-    uint8_t *cls = sc.get<uint8_t>(ne);
-    uint64_t *na = sc.get<uint64_t>(ne), *ai = sc.get<uint64_t>(ne), *nf = sc.get<uint64_t>(ne), *fi = sc.get<uint64_t>(ne);
-    if (sc.err != hipSuccess) return fail(APRIL_E_NOMEM, std::string("build scratch: ") + hipGetErrorString(sc.err));
-    unsigned long long *d_m = d_small + 1, *d_tot = d_small + 2;
-    k_keep<<<blocks_for(ne), kThreads, 0, s>>>(d_ck2, ne, keep);
-    BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_tmp2, need3, keep, pos, ne, s));
-    k_compact<<<blocks_for(ne), kThreads, 0, s>>>(d_ck2, keep, pos, ne, cell, d_m);
-    k_first<<<blocks_for(ne), kThreads, 0, s>>>(cell, d_m, n, first);
-    // 6-7: classes, interval ends and their slots
-    CellArgs ca{cell, first, d_m, d_xk, d_xv, nx, g};
-    k_classify<<<blocks_for(ne), kThreads, 0, s>>>(ca, ne, cls);
-    k_count_ends<<<blocks_for(ne), kThreads, 0, s>>>(ca, cls, ne, na, nf);
-    BG_TRY(hipGetLastError());
-    BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_tmp2, need3, na, ai, ne, s));
-    BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_tmp2, need3, nf, fi, ne, s));
-    k_totals<<<1, 1, 0, s>>>(na, ai, nf, fi, ne, d_tot);
-    BG_TRY(hipGetLastError());
-    uint64_t tot[2] = {0, 0};
-    BG_TRY(hipMemcpyAsync(tot, d_tot, 16, hipMemcpyDeviceToHost, s));
-    BG_TRY(hipStreamSynchronize(s));
-    const uint64_t n_a = tot[0], n_f = tot[1];
+    // groups of polygons, one where they have few enough items
+    std::vector<uint64_t> base{0, items}, first{0, n};
+    if (items > kGroupItems) {
+        std::vector<uint64_t> all(n + 1);
+        BG_TRY(hipMemcpyAsync(all.data(), d_base, 8 * (n + 1), hipMemcpyDeviceToHost, s));
+        BG_TRY(hipStreamSynchronize(s));
+        base.assign(1, 0);
+        first.assign(1, 0);
+        for (uint64_t k = 1; k <= n; k++)
+            if (k == n || all[k + 1] - base.back() > kGroupItems) {
+                base.push_back(all[k]);
+                first.push_back(k);
+            }
+    }
+    uint64_t most = 0, most_polys = 0;
+    for (size_t q = 0; q + 1 < base.size(); q++) {
+        most = std::max(most, base[q + 1] - base[q]);
+        most_polys = std::max(most_polys, first[q + 1] - first[q]);
+    }
+    int kbits = 2 * g.border;
+    while (kbits < 64 && (1ull << (kbits - 2 * g.border)) < most_polys) kbits++;
+    size_t sort_bytes = 0, scan2_bytes = 0;
+    BG_TRY(hipcub::DeviceRadixSort::SortKeys(nullptr, sort_bytes, (uint64_t *)nullptr, (uint64_t *)nullptr, most, 0,
+                                             std::max(kbits, 1), s));
+    BG_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, scan2_bytes, (uint64_t *)nullptr, (uint64_t *)nullptr, most + 1, s));
+    const size_t tmp_bytes = std::max(sort_bytes, scan2_bytes);
+    if (!sc.reserve(4 * pad(8 * (most + 1)) + 2 * pad(4 * most) + pad(tmp_bytes))) return fail(APRIL_E_NOMEM, "build scratch");
+    // the unsorted keys and the starts share an array each with the scans' results
+    uint64_t *d_key = sc.get<uint64_t>(most + 1), *d_k0 = sc.get<uint64_t>(most + 1);
+    uint64_t *d_na = d_k0, *d_ai = sc.get<uint64_t>(most + 1), *d_nf = sc.get<uint64_t>(most + 1), *d_fi = d_nf;
+    uint32_t *d_info = sc.get<uint32_t>(most), *d_place = sc.get<uint32_t>(most);
+    void *d_tmp = sc.get<char>(tmp_bytes);
+    ItemArgs ia{};
+    ia.xy = d_xy;
+    ia.voff = d_voff;
+    ia.box = d_box;
+    ia.blocks = d_blocks;
+    ia.base = d_base;
+    ia.info = d_info;
+    ia.place = d_place;
+    ia.g = g;
+    ia.n = n;
+    ia.ai = d_ai;
+    ia.fi = d_fi;
+    // 3-4 and the scans of 5 for one group
+    auto count_group = [&](size_t q) -> int {
+        ia.first_poly = first[q];
+        ia.n_polys = first[q + 1] - first[q];
+        ia.item0 = base[q];
+        ia.n_items = base[q + 1] - base[q];
+        ia.key = d_k0;
+        k_item_keys<<<blocks_for(ia.n_items), kThreads, 0, s>>>(ia);
+        BG_TRY(hipGetLastError());
+        BG_TRY(hipcub::DeviceRadixSort::SortKeys(d_tmp, sort_bytes, d_k0, d_key, ia.n_items, 0, std::max(kbits, 1), s));
+        ia.key = d_key;
+        const uint32_t nb = uint32_t(std::min<uint64_t>((ia.n_items + 3) / 4, uint64_t(st->cus) * 64));
+        k_item_places<<<blocks_for(ia.n_items), kThreads, 0, s>>>(ia);
+        if (wide) k_items<Wide, false><<<nb, kBlock, 0, s>>>(ia);
+        else k_items<Narrow, false><<<nb, kBlock, 0, s>>>(ia);
+        k_item_starts<<<blocks_for(ia.n_items + 1), kThreads, 0, s>>>(ia, d_na, d_nf);
+        BG_TRY(hipGetLastError());
+        BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_tmp, scan2_bytes, d_na, d_ai, ia.n_items + 1, s));
+        BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_tmp, scan2_bytes, d_nf, d_fi, ia.n_items + 1, s));
+        return APRIL_OK;
+    };
+    const size_t groups = base.size() - 1;
+    std::vector<uint64_t> ga(groups + 1, 0), gf(groups + 1, 0);   // intervals before each group
+    for (size_t q = 0; q < groups; q++) {
+        if (int rc = count_group(q)) return rc;
+        uint64_t tot[2] = {0, 0};
+        BG_TRY(hipMemcpyAsync(&tot[0], d_ai + ia.n_items, 8, hipMemcpyDeviceToHost, s));
+        BG_TRY(hipMemcpyAsync(&tot[1], d_fi + ia.n_items, 8, hipMemcpyDeviceToHost, s));
+        BG_TRY(hipStreamSynchronize(s));
+        ga[q + 1] = ga[q] + tot[0];
+        gf[q + 1] = gf[q] + tot[1];
+    }
+    const uint64_t n_a = ga[groups], n_f = gf[groups];
 
     // the lists, in the layout april_lists_to_device gives raw lists
     auto *L = new (std::nothrow) april_lists;
@@ -633,15 +1026,29 @@ extern "C" int april_build_lists_gpu(const april_grid_t *grid, const double *xy,
     L->d.start_f = reinterpret_cast<uint32_t *>(p); p += b_f;
     L->d.end_f = reinterpret_cast<uint32_t *>(p);
     L->d.bytes = total;
-    unsigned int *d_bad_slot = reinterpret_cast<unsigned int *>(d_small + 4);   // then: longest list, long A-lists
-    e = hipMemsetAsync(d_bad_slot, 0, 24, s);
-    if (e == hipSuccess) {
-        k_scatter<<<blocks_for(ne), kThreads, 0, s>>>(ca, cls, ne, na, ai, nf, fi, n, d_tot, n_a, n_f, L->d.off_a,
-                                                      L->d.off_f, L->d.start_a, L->d.end_a, L->d.start_f,
-                                                      L->d.end_f, d_bad_slot);
+    unsigned int *d_bad_slot = reinterpret_cast<unsigned int *>(d_small + 2);   // then: longest list, long A-lists
+    ia.off_a = L->d.off_a;
+    ia.off_f = L->d.off_f;
+    ia.sa = L->d.start_a;
+    ia.ea = L->d.end_a;
+    ia.sf = L->d.start_f;
+    ia.ef = L->d.end_f;
+    ia.n_a = n_a;
+    ia.n_f = n_f;
+    ia.bad_slot = d_bad_slot;
+    for (size_t q = 0; q < groups && e == hipSuccess; q++) {
+        if (groups > 1 && count_group(q)) {   // (one group: its arrays are still there)
+            e = hipErrorUnknown;
+            break;
+        }
+        ia.a0 = ga[q];
+        ia.f0 = gf[q];
+        const uint32_t nb = uint32_t(std::min<uint64_t>((ia.n_items + 3) / 4, uint64_t(st->cus) * 64));
+        if (wide) k_items<Wide, true><<<nb, kBlock, 0, s>>>(ia);
+        else k_items<Narrow, true><<<nb, kBlock, 0, s>>>(ia);
         e = hipGetLastError();
     }
-    if (e == hipSuccess && launch_list_stats(L->d.off_a, L->d.off_f, n, d_small + 5, s)) e = hipErrorUnknown;
+    if (e == hipSuccess && launch_list_stats(L->d.off_a, L->d.off_f, n, d_small + 3, s)) e = hipErrorUnknown;
     uint64_t last[3] = {0, 0, 0};   // bad_slot, longest list, A-lists that need a coarse table
     if (e == hipSuccess) e = hipMemcpyAsync(last, d_bad_slot, 24, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);   // the scratch is released after this call
