@@ -274,9 +274,9 @@ int april_filter_workspace_size(uint64_t n_pairs, const april_filter_opts_t *opt
  * Screening.  Device lists carry a summary of every object, made at upload
  * (512 bytes; 2 KiB more for an A-list of 512 intervals or more; compressed
  * lists: 2.5 KiB for an A-list of 1,024 or more, none for shorter ones).  Calls
- * of 4,096 pairs or more first decide from the summaries what they can (most
- * pairs of overlapping or clearly separate objects); the schedule then
- * takes the pairs that are left.
+ * of 8,192 pairs or more, and all calls on long lists, first decide from the
+ * summaries what they can (most pairs of overlapping or clearly separate
+ * objects); the schedule then takes the pairs that are left.
  *
  * Schedules (the verdicts are identical):
  *   APRIL_SCHED_PLAIN    one wavefront per pair; the three joins run as

@@ -87,6 +87,8 @@ struct BatchArgs {
     // wg_min intervals in a list (kNone: no workgroup bin)
     uint32_t wg_min;
     uint32_t screened;           // only pairs whose verdict is kPending are open
+    uint32_t fixed;              // small calls: wave k of an XCD takes the k-th `fixed` pairs of its range
+                                 // and no more (0: waves take pairs as they come free)
     uint32_t qcap;               // queue entries per XCD range
     unsigned int *qfill;         // big pairs binned into XCD k's queue: qfill[k * kCtrStride]
     unsigned int *qhead;         // queue entries taken by workgroups: qhead[k * kCtrStride]
@@ -1015,6 +1017,7 @@ void k_batched(BatchArgs b) {
             typedef const __attribute__((address_space(4))) BatchArgs *KArgs;
             KArgs pb = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
             asm volatile("" : "+s"(pb));
+            if (pb->fixed) break;
             if (range_drained(pb->xhead, seg, lo, hi, lane)) continue;
         }
         for (;;) {
@@ -1026,11 +1029,18 @@ void k_batched(BatchArgs b) {
             asm volatile("" : "+s"(pb));
             const __attribute__((address_space(4))) FilterArgs &a = pb->f;
             unsigned int got = 0;
-            if (lane == 0) got = atomicAdd(&pb->xhead[seg * kCtrStride], grab);
-            const uint64_t g0 = lo + uniform(__shfl(got, 0));
+            if (pb->fixed) {
+                if (grab == 0) break;   // its pairs are done
+                got = (blockIdx.x / xcds * kWavesPerBlock + w) * pb->fixed;
+            } else {
+                if (lane == 0) got = atomicAdd(&pb->xhead[seg * kCtrStride], grab);
+                got = uniform(__shfl(got, 0));
+            }
+            const uint64_t g0 = lo + got;
             if (g0 >= hi) break;
             const uint64_t g1 = min(hi, g0 + grab);
-            if (hi - g1 < pb->tail_pairs) grab = pb->tail_grab;
+            if (pb->fixed) grab = 0;
+            else if (hi - g1 < pb->tail_pairs) grab = pb->tail_grab;
             // Screened: the grab's open pairs (few of them) are collected first, as
             // offsets from g0, so that a round of the loop below has a pair for
             // most lanes.
@@ -1156,7 +1166,15 @@ int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
     uint64_t blocks = uint64_t(cus) * std::min(per_cu, dflt);
     if (waves) blocks = std::max<uint64_t>(1, (waves + kWavesPerBlock - 1) / kWavesPerBlock);
     BatchArgs bb = b;
-    if (b.screened) {
+    if (b.fixed) {
+        // (at most kSmallCall pairs, so at most 8 or so a wave)
+        const uint64_t range = (b.f.n_pairs + b.xcds - 1) / b.xcds, per_xcd = std::max<uint64_t>(1, blocks / b.xcds);
+        bb.fixed = uint32_t(std::max<uint64_t>(1, (range + per_xcd * kWavesPerBlock - 1) / (per_xcd * kWavesPerBlock)));
+        const uint64_t per_block = uint64_t(bb.fixed) * kWavesPerBlock;
+        blocks = b.xcds * std::max<uint64_t>(1, (range + per_block - 1) / per_block);
+        bb.grab = bb.fixed;
+        bb.f.counts = nullptr;
+    } else if (b.screened) {
         // about one pair in fifteen is open: larger grabs, but two or more per wave
         const uint64_t per_wave = b.f.n_pairs / (2 * blocks * kWavesPerBlock);
         bb.grab = uint32_t(std::min<uint64_t>(kScreenGrab, std::max<uint64_t>(8, per_wave)));
@@ -1179,6 +1197,7 @@ int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
     }
     k_batched<TILE, C, MODE><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(bb);
     APRIL_HIP_TRY(hipGetLastError());
+    if (b.f.counts && b.fixed) return launch_count_verdicts(b.f.verdict, b.f.n_pairs, b.f.counts, stream);
     if (b.f.counts) {
         k_sum_totals<<<1, 64, 0, stream>>>(b.xhead, b.f.counts, 3);
         APRIL_HIP_TRY(hipGetLastError());
@@ -1265,14 +1284,24 @@ void batched_defaults(april_filter_opts_t &o, const BatchedShape &shape) {
 // Workgroup-bin fields of the arguments: off (kNone) or on, with the queues
 // in the workspace after the counters.
 static void set_wg_bin(BatchArgs &b, uint32_t wg_min, void *workspace) {
-    unsigned int *qctr = reinterpret_cast<unsigned int *>(static_cast<char *>(workspace) + kCtrBytes);
     b.wg_min = wg_min;
+    b.times = nullptr;
+    b.screened = b.fixed = 0;
+    b.qfill = b.qhead = nullptr;
+    b.queue = nullptr;
+    b.qcap = 0;
+    if (!workspace) return;
+    unsigned int *qctr = reinterpret_cast<unsigned int *>(static_cast<char *>(workspace) + kCtrBytes);
     b.qfill = qctr;
     b.qhead = qctr + kMaxCtrs * kCtrStride;
     b.queue = reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + kCtrBytes + kQueueCtrBytes);
     b.qcap = uint32_t(kBigQueueCap / b.xcds);
-    b.times = nullptr;
-    b.screened = 0;
+}
+
+// Small calls deal their pairs out beforehand and need no scratch, unless they
+// have a workgroup bin, wave times or a set number of waves.
+bool batched_needs_scratch(uint64_t n_pairs, const april_filter_opts_t &o) {
+    return n_pairs > kSmallCall || o.wg_min != kNone || o.waves || (o.flags & APRIL_WAVE_TIMES);
 }
 
 int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, void *workspace,
@@ -1301,8 +1330,11 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
     b.tail_grab = 8;
     b.shift_r = b.shift_s = 0;
     if (b.thread_max >= tile) return fail(APRIL_E_INVALID, "thread_max must be below tile");
-    k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
-    APRIL_HIP_TRY(hipGetLastError());
+    b.fixed = !batched_needs_scratch(a.n_pairs, o);
+    if (!b.fixed) {
+        k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
+        APRIL_HIP_TRY(hipGetLastError());
+    }
     if (o.flags & APRIL_WAVE_TIMES)
         b.times = reinterpret_cast<unsigned long long *>(static_cast<char *>(workspace) + kTimesOffset);
     if (wg_min != kNone || b.times) {
@@ -1312,7 +1344,9 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
     if (tile != 128 && tile != 256 && tile != 512) return fail(APRIL_E_INVALID, "tile must be 128, 256 or 512");
     if (chunk != 1 && chunk != 2 && chunk != 4) return fail(APRIL_E_INVALID, "chunk must be 1, 2 or 4");
     if (R && S && can_screen(R, S, a.n_pairs)) {
-        if (int rc = launch_screen(R, S, a, cus, workspace, stream)) return rc;
+        FilterArgs f = a;
+        if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream)) return rc;
         b.screened = 1;
     }
     switch (tile) {
@@ -1337,8 +1371,11 @@ int launch_batched_mixed(const FilterArgs &a, uint32_t shift_r, uint32_t shift_s
     b.shift_r = shift_r;
     b.shift_s = shift_s;
     set_wg_bin(b, kNone, workspace);
-    k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
-    APRIL_HIP_TRY(hipGetLastError());
+    b.fixed = a.n_pairs <= kSmallCall;
+    if (!b.fixed) {
+        k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
+        APRIL_HIP_TRY(hipGetLastError());
+    }
     return launch_tc<256, 2, kMixedOrders>(b, cus, 0, stream);
 }
 
@@ -1353,8 +1390,11 @@ int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStre
     b.tail_grab = 8;
     b.shift_r = b.shift_s = 0;
     set_wg_bin(b, kNone, workspace);
-    k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
-    APRIL_HIP_TRY(hipGetLastError());
+    b.fixed = a.n_pairs <= kSmallCall;
+    if (!b.fixed) {
+        k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
+        APRIL_HIP_TRY(hipGetLastError());
+    }
     return launch_tc<256, 2, kWithinJoin>(b, cus, 0, stream);
 }
 
@@ -1369,8 +1409,11 @@ int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hi
     b.tail_grab = 8;
     b.shift_r = b.shift_s = 0;
     set_wg_bin(b, kNone, workspace);
-    k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
-    APRIL_HIP_TRY(hipGetLastError());
+    b.fixed = a.n_pairs <= kSmallCall;
+    if (!b.fixed) {
+        k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
+        APRIL_HIP_TRY(hipGetLastError());
+    }
     return launch_tc<256, 2, kLinestrings>(b, cus, 0, stream);
 }
 

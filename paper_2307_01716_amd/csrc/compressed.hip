@@ -559,7 +559,11 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
     }
     // decode cache: cache_cap intervals per list for every wave of the grid,
     // from the caller's workspace (APRIL_WS_DECODE_CACHE) or stream-ordered;
-    // without one (allocation refused) every pair decodes both objects
+    // without one (allocation refused) every pair decodes both objects.  Screened
+    // calls go without: two or three pairs of an R object are left, most of
+    // which end in its first tiles, and the 512 MiB are mapped anew after each
+    // synchronization (a partition of 8k x 8k objects: 0.77 ms a call, with
+    // the cache 0.88, and 1.22 when the host waits for each call)
     a.cache_cap = kCacheCap;
     a.cache = nullptr;
     const uint64_t cache_bytes = vbyte_cache_bytes(cus);
@@ -567,10 +571,11 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
     if (o.flags & APRIL_WS_DECODE_CACHE) {
         if (!o.d_workspace || o.workspace_bytes < vbyte_cache_offset() + cache_bytes)
             return fail(APRIL_E_INVALID, "workspace too small for the decode cache");
-        a.cache = reinterpret_cast<uint32_t *>(static_cast<char *>(o.d_workspace) + vbyte_cache_offset());
-    } else if (hipMallocAsync(reinterpret_cast<void **>(&a.cache), cache_bytes, stream) == hipSuccess) {
+        if (!a.screened)
+            a.cache = reinterpret_cast<uint32_t *>(static_cast<char *>(o.d_workspace) + vbyte_cache_offset());
+    } else if (!a.screened && hipMallocAsync(reinterpret_cast<void **>(&a.cache), cache_bytes, stream) == hipSuccess) {
         own_cache = true;
-    } else {
+    } else if (!a.screened) {
         (void)hipGetLastError();
         a.cache = nullptr;
     }

@@ -68,6 +68,14 @@ constexpr uint8_t kPending = 0xFD;
 // for any filter call's scratch on raw lists.
 constexpr uint64_t kStaticWorkspaceBytes = (4ull << 20) + (64ull << 10);
 
+// Calls of at most this many pairs use neither: their pairs are dealt out to
+// the waves beforehand and their verdicts counted by one workgroup
+// (launch_count_verdicts), so that no scratch has to be allocated, cleared and
+// freed.  (hipFreeAsync alone takes 15 us of host time, half of a call of
+// 1,650 pairs, which now takes 10 us and not 31; the batched schedule's waves
+// queueing at the work counters made a call of 452 pairs 146 us, now 15.)
+constexpr uint64_t kSmallCall = 1ull << 16;
+
 // zero both regions
 __global__ void k_zero_ctrs(unsigned int *ctr);
 // totals[0 .. n) = sums over the slots (n <= 3)
@@ -114,6 +122,9 @@ __device__ inline bool seq_join(const uint32_t *__restrict__ xs, const uint32_t 
 }
 
 
+// counts[0 .. 3) = how many of the n verdicts are APRIL_TN, APRIL_TH, APRIL_INDECISIVE
+int launch_count_verdicts(const uint8_t *verdict, uint64_t n, unsigned long long *counts, hipStream_t stream);
+
 // Batched schedule (batched.hip): scratch bytes for n_pairs, the library's
 // default settings for a call (filled into the zero fields of `o`), and the
 // launch of its binning and persistent kernels on `workspace`.
@@ -126,7 +137,9 @@ struct BatchedShape {
 void batched_defaults(april_filter_opts_t &o, const BatchedShape &shape);
 // XCDs of a device with `cus` compute units (32 CUs each on gfx950)
 int xcd_count(int cus);
-// R, S: screen the pairs first (null: lists without summaries)
+// R, S: screen the pairs first (null: lists without summaries).  workspace may
+// be null when batched_needs_scratch says so.
+bool batched_needs_scratch(uint64_t n_pairs, const april_filter_opts_t &o);
 int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, void *workspace,
                    hipStream_t stream, const april_lists_t *R, const april_lists_t *S);
 

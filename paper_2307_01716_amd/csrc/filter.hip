@@ -230,6 +230,49 @@ __global__ void k_alg2_bytes(FilterArgs a, unsigned long long *bytes) {
     }
 }
 
+// One workgroup: the verdicts' counts, plain stores.  Verdict bytes are 0, 1, 2
+// or APRIL_BAD_PAIR (both low bits), so each kind is a bit pattern of the low
+// two bits, counted four bytes at a time.
+__global__ __launch_bounds__(1024) void k_count_verdicts(const uint8_t *v, uint32_t n, unsigned long long *counts) {
+    const uint32_t head = min(n, uint32_t(-reinterpret_cast<uintptr_t>(v) & 15u)), quads = (n - head) / 16;
+    const uint32_t t = threadIdx.x, lane = t & 63;
+    uint32_t c[3] = {0, 0, 0};
+    auto one = [&](uint32_t x) {
+        c[0] += x == APRIL_TN;
+        c[1] += x == APRIL_TH;
+        c[2] += x == APRIL_INDECISIVE;
+    };
+    auto four = [&](uint32_t x) {
+        const uint32_t lo = x & 0x01010101u, hi = (x >> 1) & 0x01010101u;
+        c[0] += uint32_t(__popc(~(lo | hi) & 0x01010101u));
+        c[1] += uint32_t(__popc(lo & ~hi));
+        c[2] += uint32_t(__popc(hi & ~lo));
+    };
+    const uint4 *q = reinterpret_cast<const uint4 *>(v + head);
+#pragma unroll 4
+    for (uint32_t i = t; i < quads; i += 1024) {
+        const uint4 x = q[i];
+        four(x.x);
+        four(x.y);
+        four(x.z);
+        four(x.w);
+    }
+    const uint32_t rest = head + quads * 16;
+    if (t < head) one(v[t]);
+    if (rest + t < n) one(v[rest + t]);   // fewer than 16
+    __shared__ uint32_t part[16][3];
+    for (int k = 0; k < 3; k++) {
+        for (int off = 32; off > 0; off >>= 1) c[k] += __shfl_down(c[k], off);
+        if (lane == 0) part[t >> 6][k] = c[k];
+    }
+    __syncthreads();
+    if (t < 3) {
+        unsigned long long s = 0;
+        for (int w = 0; w < 16; w++) s += part[w][t];
+        counts[t] = s;
+    }
+}
+
 __global__ void k_zero_counts(unsigned long long *c) {
     if (threadIdx.x < 3) c[threadIdx.x] = 0;
 }
@@ -244,6 +287,12 @@ __global__ void k_check_pairs(const uint32_t *r, const uint32_t *s, uint64_t n, 
 }
 
 }  // namespace
+
+int launch_count_verdicts(const uint8_t *verdict, uint64_t n, unsigned long long *counts, hipStream_t stream) {
+    k_count_verdicts<<<1, 1024, 0, stream>>>(verdict, uint32_t(n), counts);
+    APRIL_HIP_TRY(hipGetLastError());
+    return APRIL_OK;
+}
 
 int device_state(DeviceState **out) {
     static DeviceState states[64];
@@ -385,6 +434,7 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
             if (o.workspace_bytes < need) return fail(APRIL_E_INVALID, "workspace too small");
             return launch_batched(a, o, st->cus, o.d_workspace, stream, R, S);
         }
+        if (!batched_needs_scratch(n_pairs, o)) return launch_batched(a, o, st->cus, nullptr, stream, R, S);
         void *ws = nullptr;
         hipError_t e = hipMallocAsync(&ws, need, stream);
         if (e != hipSuccess) return fail(APRIL_E_NOMEM, std::string("workspace: ") + hipGetErrorString(e));
@@ -395,9 +445,11 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
     // the counts are summed through the scratch slots (the caller's
     // workspace, else a stream-ordered allocation)
     void *ws = nullptr;
-    if (counts) {
+    if (counts && o.d_workspace && o.workspace_bytes < kCtrBytes) return fail(APRIL_E_INVALID, "workspace too small");
+    const bool small = n_pairs <= kSmallCall;
+    if (small) a.counts = nullptr;
+    if (counts && !small) {
         if (o.d_workspace) {
-            if (o.workspace_bytes < kCtrBytes) return fail(APRIL_E_INVALID, "workspace too small");
             ws = o.d_workspace;
         } else {
             hipError_t e = hipMallocAsync(&ws, kCtrBytes, stream);
@@ -429,7 +481,9 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
     PlainArgs pa{a, static_cast<unsigned int *>(ws), xcds, screened};
     k_filter_plain<4><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(pa);
     hipError_t e = hipGetLastError();
-    if (counts) {
+    if (counts && small) {
+        if (e == hipSuccess) return launch_count_verdicts(d_verdict, n_pairs, counts, stream);
+    } else if (counts) {
         if (e == hipSuccess) {
             k_sum_totals<<<1, 64, 0, stream>>>(static_cast<unsigned int *>(ws), counts, 3);
             e = hipGetLastError();

@@ -51,6 +51,7 @@ struct DeviceArrays {
     uint64_t *sum = nullptr;      // kSumEntries (start | end << 32) per object (compressed: per numbered object)
     uint32_t *slot = nullptr;     // n: number of the object's coarse table (0xffffffff: none)
     uint32_t *coarse = nullptr;   // the coarse tables
+    uint64_t n_sums = 0;          // objects that have a summary
     void *sum_block = nullptr;
     size_t bytes = 0;
 };

@@ -290,6 +290,7 @@ struct ScreenArgs {
     const uint32_t *r_slot, *coarse; // R's coarse tables
     unsigned int *ctr;
     uint32_t xcds;
+    uint32_t take;                   // pairs a wave takes at a time (at most 64)
     uint32_t raw;                    // R's A-lists can be read (not compressed)
 };
 
@@ -302,7 +303,7 @@ __device__ __forceinline__ bool search(const uint32_t *ends, uint64_t y) {
     return p[kExact] < e;   // the matching start
 }
 
-// A wave takes 64 pairs at a time from its XCD's range, a lane reading one
+// A wave takes up to 64 pairs at a time from its XCD's range, a lane reading one
 // pair's ids and the bounds of its R list, then goes through them one by one;
 // the next pair's summary is loaded before the current one is searched.  Every
 // pair costs about the same, so the blocks are dealt out without counters.
@@ -315,13 +316,15 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
     const uint64_t lo = a.f.n_pairs * xcd / a.xcds, hi = a.f.n_pairs * (xcd + 1) / a.xcds;
     unsigned long long c_tn = 0, c_th = 0;
     uint32_t cached = kNoSlot, size = 0;   // the R object in t; its table's entries, a power of two (0: coarse)
-    for (uint64_t g0 = lo + 64ull * (bx * kWavesPerBlock + w); g0 < hi; g0 += 64ull * nbx * kWavesPerBlock) {
+    for (uint64_t g0 = lo + uint64_t(a.take) * (bx * kWavesPerBlock + w); g0 < hi;
+         g0 += uint64_t(a.take) * nbx * kWavesPerBlock) {
         const uint64_t p = g0 + lane;
         uint32_t r = 0, s_at = 0, nar = 0, slot = kNoSlot;
         uint64_t ar0 = 0;
         bool todo_me = false;
         uint32_t vv = APRIL_BAD_PAIR;
-        if (p < hi) {
+        const bool mine = lane < a.take && p < hi;
+        if (mine) {
             r = a.f.r[p];
             const uint32_t s = a.f.s[p];
             if ((r < a.f.n_r) & (s < a.f.n_s)) {
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
             const uint32_t v = uint32_t(m) ? APRIL_TH : uint32_t(m >> 32) ? kPending : APRIL_TN;
             vv = lane == k ? v : vv;
         }
-        if (p < hi) {
+        if (mine) {
             a.f.verdict[p] = uint8_t(vv);
             c_tn += vv == APRIL_TN;
             c_th += vv == APRIL_TH;
@@ -426,11 +429,24 @@ int launch_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, 
     return APRIL_OK;
 }
 
-// Fewest pairs that are screened.
-constexpr uint64_t kScreenMin = 4096;
+// Fewest pairs that are screened: in smaller calls each wave has one pair
+// anyway, and screening only comes before its join.  Measured, without and with:
+// at-scale objects, plain schedule, 4,204 pairs 30 and 34 us, 16,272 pairs 58
+// and 40 us; batched, 4,204 pairs 20 and 21 us, 16,272 pairs 33 and 31 us,
+// 65,088 pairs 93 and 55 us.  Long lists, whose joins take far longer, are always
+// worth it: 486 pairs of objects of 2,250 A-intervals 293 and 134 us raw, 1384
+// and 210 us compressed; 2,804 pairs with some complex objects 442 and 131 us.
+constexpr uint64_t kScreenMin = 8192;
+constexpr uint64_t kLongMean = 512, kLongMost = 4096;
+
+static bool long_lists(const april_lists_t *L) {
+    return L->n_a >= kLongMean * L->n || (L->max_len >= kLongMost && L->max_len != 0xffffffffu);
+}
 
 bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs) {
-    return n_pairs >= kScreenMin && R->d.sum && S->d.sum;
+    if (n_pairs < kScreenMin && !long_lists(R) && !long_lists(S)) return false;
+    // (compressed lists: where most objects are long enough to have a summary)
+    return R->d.sum && S->d.sum && 2 * R->d.n_sums >= R->n && 2 * S->d.n_sums >= S->n;
 }
 
 int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
@@ -444,8 +460,12 @@ int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterAr
     a.ctr = static_cast<unsigned int *>(counters);
     a.xcds = uint32_t(xcd_count(cus));
     a.raw = R->codec == APRIL_CODEC_RAW;
-    const uint64_t most = uint64_t(cus) * 8, want = (f.n_pairs + 64 * kWavesPerBlock - 1) / (64 * kWavesPerBlock);
-    uint64_t blocks = std::min(most, want);
+    // 64 pairs at a time, or what gives every wave some: a pair takes half a
+    // microsecond and more after another (16,272 pairs with 64 at a time: 93 us
+    // a call, so 31)
+    const uint64_t most = uint64_t(cus) * 8, waves = most * kWavesPerBlock;
+    a.take = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(1, (f.n_pairs + waves - 1) / waves)));
+    uint64_t blocks = std::min(most, (f.n_pairs + a.take * kWavesPerBlock - 1) / (a.take * kWavesPerBlock));
     blocks = (blocks + a.xcds - 1) / a.xcds * a.xcds;
     k_screen<<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a);
     APRIL_HIP_TRY(hipGetLastError());
@@ -497,6 +517,7 @@ int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, cons
     L->d.sum = b.sum;
     L->d.slot = b.slot;
     L->d.coarse = b.coarse;
+    L->d.n_sums = sums;
     L->d.bytes += total;
     return APRIL_OK;
 }

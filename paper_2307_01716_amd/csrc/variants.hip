@@ -41,6 +41,11 @@ int run_batched(const FilterArgs &fa, int device, Variant v, uint32_t shift_r, u
     APRIL_HIP_TRY(hipGetDevice(&cur));
     if (cur != device) return fail(APRIL_E_INVALID, "current device does not hold the lists");
     void *ws = nullptr;
+    if (fa.n_pairs <= kSmallCall) {   // no scratch (and nothing to launch without pairs but the counts)
+        return v == Variant::kWithin        ? launch_batched_within(fa, st->cus, ws, stream)
+               : v == Variant::kLinestrings ? launch_batched_linestrings(fa, st->cus, ws, stream)
+                                            : launch_batched_mixed(fa, shift_r, shift_s, st->cus, ws, stream);
+    }
     hipError_t e = hipMallocAsync(&ws, batched_workspace_bytes(fa.n_pairs), stream);
     if (e != hipSuccess) return fail(APRIL_E_NOMEM, std::string("workspace: ") + hipGetErrorString(e));
     const int rc = v == Variant::kWithin        ? launch_batched_within(fa, st->cus, ws, stream)

@@ -17,7 +17,7 @@ torch = pytest.importorskip("torch")
 from paper_2307_01716_amd import april  # noqa: E402
 
 GRID = (0.0, 0.0, float(1 << 16) * 2.0 ** -30 * (1 << 16), 16)
-PAIRS = 6000     # enough to be screened
+PAIRS = 9000     # enough to be screened
 SIZES = {
     "summary": [0, 1, 2, 31, 32, 33, 34, 63, 64, 65],
     "tables": [62, 63, 64, 126, 127, 128, 129, 255, 256, 257],
