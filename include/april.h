@@ -272,8 +272,8 @@ int april_filter_workspace_size(uint64_t n_pairs, const april_filter_opts_t *opt
  * The intermediate filter (Sec. 4.2, Alg. 2) on n_pairs candidate pairs.
  *
  * Screening.  Device lists carry a summary of every object, made at upload
- * (512 bytes; 2 KiB more for an A-list of 512 intervals or more; compressed
- * lists: 2.5 KiB for an A-list of 1,024 or more, none for shorter ones).  Calls
+ * (512 bytes; 3 KiB more for an A-list of 512 intervals or more; compressed
+ * lists: 3.5 KiB for an A-list of 1,024 or more, none for shorter ones).  Calls
  * of 8,192 pairs or more, and all calls on long lists, first decide from the
  * summaries what they can (most pairs of overlapping or clearly separate
  * objects); the schedule then takes the pairs that are left.

@@ -59,10 +59,10 @@ struct DeviceArrays {
 // Entries of an object's summary (screen.hip).
 constexpr uint32_t kSumEntries = 64;
 // A-lists of fewer intervals are screened against as they are; longer ones
-// have a coarse table of 2 KiB, an eighth of such a list (A and F) at most.
+// have a coarse table of 3 KiB, three eighths of such lists (A and F) at most.
 constexpr uint32_t kExact = 512;
 // Compressed lists: objects of fewer A-intervals have neither summary nor
-// table (2.5 KiB, about half of what such a list and its F-list take), so
+// table (3.5 KiB; such a list and its F-list take about 4.8 KiB), so
 // that compression keeps what it saves.
 constexpr uint32_t kVbyteSummaryMin = 1024;
 

@@ -12,11 +12,13 @@
 //     in an A-interval, an AA overlap too: Alg. 2 answers true hit;
 //   - no H interval overlaps A(X): no A-interval does: true negative.
 // Anything else is left to the join kernels.  X's A-list is held in LDS; for an
-// A-list of more than kExact intervals a coarse table of X stands in for it:
-// its 127 longest A-intervals in the first test (a subset: an overlap with one
-// is an overlap with A(X)), its hull of 127 in the second (a superset).  A
-// wave keeps X while consecutive pairs share their R object; one search of the
-// table by all lanes makes both tests of a pair.
+// A-list of kExact intervals or more a coarse table of X stands in for it: its
+// 127 longest A-intervals in the first test (a subset: an overlap with one is
+// an overlap with A(X)), its hull of 127 in the second (a superset).  A wave
+// keeps X while consecutive pairs share their R object; one search of the table
+// by all lanes makes both tests of a pair.  Where the other object has a
+// coarse table too, a pair that is still open is tested once more with that
+// table's 127 longest F-intervals and its hull of 127.
 //
 // The two tests decide 95% of the at-scale join's pairs (98% of its true hits,
 // 92% of its true negatives) and 93% of a partition's, whose lists are
@@ -25,11 +27,13 @@
 // pairs to the joins, each of which costs several times a screened pair.
 //
 // Measured on one MI355X, whole calls without and with screening: at scale
-// (200k x 200k, 4.5M pairs) 1.96 and 0.79 ms, of which this kernel 0.49; the
-// plain schedule at 100k x 100k 1.47 and 0.46 ms; a partition of 10k x 10k
-// objects of 2,250 A-intervals 2.50 and 0.57 ms raw, 8k x 8k 3.36 and 0.81 ms
-// compressed; 40k x 40k with 300 complex objects a side 1.98 and 0.91 ms.
-// Making the summaries takes 0.61 ms for 200k objects.
+// (200k x 200k, 4.5M pairs) 1.96 and 0.72 ms, of which this kernel 0.40; the
+// plain schedule at 100k x 100k 1.50 and 0.40 ms; a partition of 10k x 10k
+// objects of 2,250 A-intervals 2.49 and 0.41 ms raw, 8k x 8k 3.45 and 0.72 ms
+// compressed; 40k x 40k with 300 complex objects a side 2.00 and 0.82 ms.
+// Making the summaries takes 0.65 ms for 200k objects.  The kernel issues 38
+// vector instructions per pair, 0.7 of the issue peak; two pairs' searches
+// side by side gained nothing at scale (0.42 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,6 +46,9 @@ namespace {
 
 constexpr uint32_t kSumHalf = kSumEntries / 2;    // TF intervals; hull intervals
 constexpr uint32_t kCoarse = 128;                 // entries per coarse list, the last one padding
+// a coarse table: ends of the longest A-intervals, ends of the hull, starts of
+// both, then ends and starts of the longest F-intervals
+constexpr uint32_t kTable = 6 * kCoarse;
 constexpr uint32_t kNoSlot = 0xffffffffu;
 // longest list that a single wave summarizes; longer ones get 16 waves (a list
 // is read twice per selection, and the skewed workload has lists of 200,000)
@@ -160,7 +167,7 @@ __device__ __forceinline__ void select(Cut cut, uint32_t m, V value, P put, uint
 struct SumLds {
     uint32_t hist[256];
     uint32_t sum[2 * kSumEntries];   // (start, end) pairs
-    uint32_t coarse[4 * kCoarse];
+    uint32_t coarse[kTable];
     uint32_t part[16][2];
     uint32_t slot;
 };
@@ -196,7 +203,7 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
     group_sync<W>();
     for (uint32_t i = tid; i < 2 * kSumEntries; i += 64 * W) l.sum[i] = (i & 1) ? 0u : 0xffffffffu;
     if (slot != kNoSlot)
-        for (uint32_t i = tid; i < 4 * kCoarse; i += 64 * W) l.coarse[i] = 0xffffffffu;
+        for (uint32_t i = tid; i < kTable; i += 64 * W) l.coarse[i] = 0xffffffffu;
     // TF
     auto flen = [&](uint32_t j) { return fe[j] - fs[j]; };
     histogram<W>(l.hist, nf, flen, tid);
@@ -204,6 +211,11 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
         l.sum[2 * i] = fs[j];
         l.sum[2 * i + 1] = fe[j];
     }, l.part, w, lane);
+    if (slot != kNoSlot)
+        select<W>(find_cut(l.hist, kCoarse - 1, lane), nf, flen, [&](uint32_t i, uint32_t j) {
+            l.coarse[4 * kCoarse + i] = fe[j];
+            l.coarse[5 * kCoarse + i] = fs[j];
+        }, l.part, w, lane);
     // H, and the coarse hull from the same histogram
     auto gap = [&](uint32_t j) { return as[j + 1] - ae[j]; };
     const uint32_t ng = na ? na - 1 : 0u;
@@ -221,24 +233,31 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
         }, l.part, w, lane);
     }
     group_sync<W>();
-    // a TF interval counts only inside an A-interval (lists that were not
+    // an F-interval counts only inside an A-interval (lists that were not
     // validated may hold others): the first A-interval that ends above its start
+    auto in_a = [&](uint32_t s, uint32_t e) {
+        uint32_t lo = 0, hi = na;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (ae[mid] > s) hi = mid;
+            else lo = mid + 1;
+        }
+        return lo < na && as[lo] <= s && ae[lo] >= e;
+    };
     if (w == 0) {
         uint32_t s = l.sum[2 * lane], e = l.sum[2 * lane + 1];
-        if (lane < kSumHalf && e != 0) {
-            uint32_t lo = 0, hi = na;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (ae[mid] > s) hi = mid;
-                else lo = mid + 1;
-            }
-            if (lo == na || as[lo] > s || ae[lo] < e) e = 0;
-        }
+        if (lane < kSumHalf && e != 0 && !in_a(s, e)) e = 0;
         const uint64_t at = b.by_slot ? slot : k;
         b.sum[at * kSumEntries + lane] = (uint64_t(e) << 32) | s;
     }
-    if (slot != kNoSlot)
-        for (uint32_t i = tid; i < 4 * kCoarse; i += 64 * W) b.coarse[uint64_t(slot) * 4 * kCoarse + i] = l.coarse[i];
+    if (slot != kNoSlot) {
+        if (w == 0)
+            for (uint32_t i = 4 * kCoarse + lane; i < 5 * kCoarse; i += 64)
+                if (l.coarse[i] != 0xffffffffu && !in_a(l.coarse[i + kCoarse], l.coarse[i]))
+                    l.coarse[i] = l.coarse[i + kCoarse] = 0xffffffffu;
+        group_sync<W>();
+        for (uint32_t i = tid; i < kTable; i += 64 * W) b.coarse[uint64_t(slot) * kTable + i] = l.coarse[i];
+    }
 }
 
 // Objects whose lists one wave summarizes; the others are queued.  Numbers
@@ -287,20 +306,43 @@ struct ScreenArgs {
     FilterArgs f;
     const uint64_t *sum;             // S's summaries
     const uint32_t *s_slot;          // their numbers (compressed lists; else the S id)
-    const uint32_t *r_slot, *coarse; // R's coarse tables
+    const uint32_t *r_slot, *coarse;      // R's coarse tables
+    const uint32_t *s_table, *s_coarse;   // and S's
     unsigned int *ctr;
     uint32_t xcds;
     uint32_t take;                   // pairs a wave takes at a time (at most 64)
     uint32_t raw;                    // R's A-lists can be read (not compressed)
 };
 
+// LDS place of a table's entry i: a word is left out after every 64.  The
+// entries that a round of the search compares lie a power of two apart, which
+// without that is the same bank for up to four of them in most rounds
+// (1.7 conflict cycles per LDS instruction).
+__device__ __forceinline__ constexpr uint32_t padded(uint32_t i) { return i + (i >> 6); }
+constexpr uint32_t kStarts = kExact + kExact / 64;   // from an end to its start
+
+// Does [s, e) overlap an interval of the table (P2 entries, the last ones
+// padding)?
 template <int P2>
-__device__ __forceinline__ bool search(const uint32_t *ends, uint64_t y) {
-    const uint32_t s = uint32_t(y), e = uint32_t(y >> 32);
+__device__ __forceinline__ bool search(const uint32_t *ends, uint32_t s, uint32_t e) {
     const uint32_t *p = ends;
 #pragma unroll
-    for (uint32_t S = P2 / 2; S > 0; S >>= 1) p = p[S - 1] <= s ? p + S : p;
-    return p[kExact] < e;   // the matching start
+    for (uint32_t S = P2 / 2; S > 0; S >>= 1) p = p[padded(S - 1)] <= s ? p + padded(S) : p;
+    return p[kStarts] < e;   // the first interval that ends above s starts below e
+}
+
+// (size: a power of two, 0 for a coarse table)
+__device__ __forceinline__ bool search_any(const uint32_t *ends, uint32_t size, uint32_t s, uint32_t e) {
+    if (size == 64) return search<64>(ends, s, e);
+    if (size == 128 || size == 0) return search<128>(ends, s, e);
+    if (size == 256) return search<256>(ends, s, e);
+    return search<kExact>(ends, s, e);
+}
+static_assert(kCoarse == 128, "search_any");
+
+// One word per active lane from global memory straight into LDS, lane l's at dst[l].
+__device__ __forceinline__ void lds_dma(const uint32_t *src, uint32_t *dst) {
+    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)dst, 4, 0, 0);
 }
 
 // A wave takes up to 64 pairs at a time from its XCD's range, a lane reading one
@@ -308,10 +350,11 @@ __device__ __forceinline__ bool search(const uint32_t *ends, uint64_t y) {
 // the next pair's summary is loaded before the current one is searched.  Every
 // pair costs about the same, so the blocks are dealt out without counters.
 __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
-    __shared__ uint32_t lds[kWavesPerBlock][2 * kExact];   // X: ends, then starts
+    __shared__ uint32_t lds[kWavesPerBlock][2 * kStarts];   // X: ends, then starts
     const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
     uint32_t *const t = lds[w];
-    const uint32_t *const half = t + (lane < kSumHalf ? 0u : kCoarse);   // the coarse list a lane searches
+    const uint32_t *const hull = t + padded(kCoarse);               // a coarse table's second list
+    const uint32_t *const half = lane < kSumHalf ? t : hull;        // the coarse list a lane searches
     const uint32_t xcd = blockIdx.x % a.xcds, bx = blockIdx.x / a.xcds, nbx = gridDim.x / a.xcds;
     const uint64_t lo = a.f.n_pairs * xcd / a.xcds, hi = a.f.n_pairs * (xcd + 1) / a.xcds;
     unsigned long long c_tn = 0, c_th = 0;
@@ -319,7 +362,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
     for (uint64_t g0 = lo + uint64_t(a.take) * (bx * kWavesPerBlock + w); g0 < hi;
          g0 += uint64_t(a.take) * nbx * kWavesPerBlock) {
         const uint64_t p = g0 + lane;
-        uint32_t r = 0, s_at = 0, nar = 0, slot = kNoSlot;
+        uint32_t r = 0, s_at = 0, nar = 0, slot = kNoSlot, s_tab = kNoSlot;
         uint64_t ar0 = 0;
         bool todo_me = false;
         uint32_t vv = APRIL_BAD_PAIR;
@@ -331,12 +374,48 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
                 vv = kPending;
                 ar0 = a.f.Ar.off[r];
                 nar = uint32_t(a.f.Ar.off[r + 1] - ar0);
-                s_at = a.s_slot ? a.s_slot[s] : s;
+                s_tab = a.s_table[s];
+                s_at = a.s_slot ? s_tab : s;
                 const bool exact = a.raw && nar < kExact;
                 if (!exact) slot = a.r_slot[r];
                 todo_me = s_at != kNoSlot && (exact || slot != kNoSlot);
             }
         }
+        // pair k's R object into LDS, unless it is there
+        auto load_x = [&](uint32_t k) {
+            const uint32_t key = __builtin_amdgcn_readlane(r, k);
+            if (key == cached) return;
+            cached = key;
+            const uint32_t sl = __builtin_amdgcn_readlane(slot, k);
+            wave_lds_sync();
+            if (sl == kNoSlot) {
+                const uint32_t n = __builtin_amdgcn_readlane(nar, k);
+                const uint64_t at = (uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0 >> 32), k))) << 32) |
+                                    uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0), k));
+                const uint32_t *xs = a.f.Ar.s + at, *xe = a.f.Ar.e + at;
+                size = n < 64 ? 64u : n < 128 ? 128u : n < 256 ? 256u : kExact;   // above n: a padding entry
+#pragma unroll 1
+                for (uint32_t i = 0; i < size; i += 64) {
+                    if (i + lane < n) {
+                        lds_dma(xe + i + lane, t + padded(i));
+                        lds_dma(xs + i + lane, t + kStarts + padded(i));
+                    } else {
+                        t[padded(i) + lane] = 0xffffffffu;
+                        t[kStarts + padded(i) + lane] = 0xffffffffu;
+                    }
+                }
+            } else {
+                const uint32_t *c = a.coarse + uint64_t(sl) * kTable;
+                size = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < 2 * kCoarse; i += 64) {
+                    lds_dma(c + i + lane, t + padded(i));
+                    lds_dma(c + 2 * kCoarse + i + lane, t + kStarts + padded(i));
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(0);   // the copies, all under way at once, have landed
+            wave_lds_sync();
+        };
         uint64_t todo = __ballot(todo_me);
         uint32_t kn = todo ? uint32_t(__builtin_ctzll(todo)) : 0u;
         uint64_t y_next = 0;
@@ -349,40 +428,34 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
                 kn = uint32_t(__builtin_ctzll(todo));
                 y_next = a.sum[uint64_t(__builtin_amdgcn_readlane(s_at, kn)) * kSumEntries + lane];
             }
-            const uint32_t key = __builtin_amdgcn_readlane(r, k);
-            if (key != cached) {
-                cached = key;
-                const uint32_t sl = __builtin_amdgcn_readlane(slot, k);
-                wave_lds_sync();
-                if (sl == kNoSlot) {
-                    const uint32_t n = __builtin_amdgcn_readlane(nar, k);
-                    const uint64_t at = (uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0 >> 32), k))) << 32) |
-                                        uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0), k));
-                    const uint32_t *xs = a.f.Ar.s + at, *xe = a.f.Ar.e + at;
-                    size = n < 64 ? 64u : n < 128 ? 128u : n < 256 ? 256u : kExact;   // above n: a padding entry
-                    for (uint32_t i = lane; i < size; i += 64) {
-                        t[i] = i < n ? xe[i] : 0xffffffffu;
-                        t[kExact + i] = i < n ? xs[i] : 0xffffffffu;
-                    }
-                } else {
-                    const uint32_t *c = a.coarse + uint64_t(sl) * 4 * kCoarse;
-                    size = 0;
-#pragma unroll
-                    for (uint32_t i = 0; i < 2 * kCoarse; i += 64) {
-                        t[i + lane] = c[i + lane];
-                        t[kExact + i + lane] = c[2 * kCoarse + i + lane];
-                    }
-                }
-                wave_lds_sync();
-            }
-            bool hit;
-            if (size == 64) hit = search<64>(t, y);
-            else if (size == 128) hit = search<128>(t, y);
-            else if (size == 256) hit = search<256>(t, y);
-            else if (size == 0) hit = search<kCoarse>(half, y);
-            else hit = search<kExact>(t, y);
-            const uint64_t m = __ballot(hit);
+            load_x(k);
+            const uint64_t m = __ballot(search_any(size ? t : half, size, uint32_t(y), uint32_t(y >> 32)));
             const uint32_t v = uint32_t(m) ? APRIL_TH : uint32_t(m >> 32) ? kPending : APRIL_TN;
+            vv = lane == k ? v : vv;
+        }
+        // once more, with S's coarse table where it has one (padding entries
+        // overlap nothing); apart from the loop above, which it would slow down
+        todo = __ballot(todo_me && vv == kPending && s_tab != kNoSlot);
+        while (todo) {
+            const uint32_t k = uint32_t(__builtin_ctzll(todo));
+            todo &= todo - 1;
+            const uint32_t *c = a.s_coarse + uint64_t(__builtin_amdgcn_readlane(s_tab, k)) * kTable;
+            uint32_t fs[2], fe[2], hs[2], he[2];
+#pragma unroll
+            for (uint32_t i = 0; i < 2; i++) {
+                fe[i] = c[4 * kCoarse + 64 * i + lane];
+                fs[i] = c[5 * kCoarse + 64 * i + lane];
+                he[i] = c[kCoarse + 64 * i + lane];
+                hs[i] = c[3 * kCoarse + 64 * i + lane];
+            }
+            load_x(k);
+            bool f = false, h = false;
+#pragma unroll
+            for (uint32_t i = 0; i < 2; i++) {
+                f |= search_any(t, size, fs[i], fe[i]);
+                h |= search_any(size ? t : hull, size, hs[i], he[i]);
+            }
+            const uint32_t v = __any(f) ? APRIL_TH : __any(h) ? kPending : APRIL_TN;
             vv = lane == k ? v : vv;
         }
         if (mine) {
@@ -457,6 +530,8 @@ int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterAr
     a.s_slot = S->codec == APRIL_CODEC_RAW ? nullptr : S->d.slot;
     a.r_slot = R->d.slot;
     a.coarse = R->d.coarse;
+    a.s_table = S->d.slot;
+    a.s_coarse = S->d.coarse;
     a.ctr = static_cast<unsigned int *>(counters);
     a.xcds = uint32_t(xcd_count(cus));
     a.raw = R->codec == APRIL_CODEC_RAW;
@@ -484,7 +559,7 @@ int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, cons
     if (sums == 0 || L->n >= 0x7fffffffull || longer >= 0x7fffffffull) return APRIL_OK;
     auto up = [](uint64_t v) { return (v + 255) & ~uint64_t(255); };
     const uint64_t queue = std::min<uint64_t>(L->n, (L->n_a + L->n_f) / kOneWave + 1);
-    const uint64_t b_sum = up(8 * kSumEntries * sums), b_coarse = up(16 * kCoarse * longer), b_slot = up(4 * L->n);
+    const uint64_t b_sum = up(8 * kSumEntries * sums), b_coarse = up(4 * kTable * longer), b_slot = up(4 * L->n);
     const uint64_t total = b_sum + b_coarse + b_slot + up(4 * queue) + 256;
     void *block = nullptr;
     if (hipMalloc(&block, total) != hipSuccess) {
