@@ -114,6 +114,7 @@ struct BatchArgs {
 // The binning pass appends the workgroup bin's pairs to one queue per XCD
 // range (the range holding the pair) and marks their verdict bytes; a pair
 // that finds its queue full is marked for the wave bin instead.
+constexpr uint32_t kTilesCtr = kMaxCtrs / 2;   // qhead counters from here on: sums of `tiles` over the queues
 constexpr uint8_t kQueued = 0xFE;     // verdict byte of a pair in a workgroup queue
 constexpr uint8_t kOverflow = kPending;   // of a workgroup-bin pair left to the wave bin (screened: of every pair left)
 
@@ -139,12 +140,15 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
          base += stride) {
         const uint64_t p = base + lane;
         bool big = false;
+        uint32_t tiles = 0;   // workgroup tiles that the shorter object's A-list fills
         if (p < a.n_pairs && (!b.screened || a.verdict[p] == kPending)) {
             const uint32_t r = a.r[p], s = a.s[p];
             if ((r < a.n_r) & (s < a.n_s)) {
-                const uint32_t mr = uint32_t(max(a.Ar.off[r + 1] - a.Ar.off[r], a.Fr.off[r + 1] - a.Fr.off[r]));
-                const uint32_t ms = uint32_t(max(a.As.off[s + 1] - a.As.off[s], a.Fs.off[s + 1] - a.Fs.off[s]));
+                const uint32_t nar = uint32_t(a.Ar.off[r + 1] - a.Ar.off[r]), nas = uint32_t(a.As.off[s + 1] - a.As.off[s]);
+                const uint32_t mr = max(nar, uint32_t(a.Fr.off[r + 1] - a.Fr.off[r]));
+                const uint32_t ms = max(nas, uint32_t(a.Fs.off[s + 1] - a.Fs.off[s]));
                 big = wg_bin(mr, ms, tile, b.wg_min);
+                tiles = (ms < mr ? nas : nar) / (kWavesPerBlock * tile);
             }
         }
         const uint32_t k = p < a.n_pairs ? range_of(p, a.n_pairs, b.xcds) : 0u;
@@ -154,6 +158,9 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
             const uint32_t k0 = uniform(__shfl(k, int(__builtin_ctzll(todo))));
             const uint64_t mine = __ballot(big && k == k0) & todo;
             todo &= ~mine;
+            uint32_t sum = (mine >> lane) & 1 ? tiles : 0u;
+            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+            if (lane == 0) atomicAdd(&b.qhead[(kTilesCtr + k0) * kCtrStride], sum);
             unsigned int got = 0;
             if (lane == uint32_t(__builtin_ctzll(mine)))
                 got = atomicAdd(&b.qfill[k0 * kCtrStride], uint32_t(__popcll(mine)));
@@ -162,6 +169,8 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
                 const uint32_t slot = got + uint32_t(__popcll(mine & ((1ull << lane) - 1)));
                 if (slot < b.qcap) {
                     b.queue[uint64_t(k0) * b.qcap + slot] = uint32_t(p);
+                    // its parts' answers, from the queue's end
+                    if (slot < b.qcap / 2) b.queue[uint64_t(k0 + 1) * b.qcap - 1 - slot] = 0;
                     a.verdict[p] = kQueued;
                 } else {
                     a.verdict[p] = kOverflow;
@@ -672,13 +681,40 @@ __device__ uint32_t wave_pair(Resident &res, uint32_t &cached, uint32_t key, con
 // the LDS search compares it with real intervals of X.)
 
 struct WgShared {
-    uint32_t grab;      // queue entry taken by the workgroup
+    uint32_t grab;      // queue entry (part) taken by the workgroup
     uint32_t bits;      // this pass: 1 = overlap with X.A, 2 = true hit
     uint32_t cstop;     // this pass: smallest stop chunk over the waves
-    uint32_t pad;
+    uint32_t known;     // another part of the pair has found a true hit
 };
 
 constexpr uint32_t kHitAA = 1, kHitTH = 2;
+
+// Parts.  With fewer queued pairs than would fill the chip, each is cut into
+// parts: contiguous shares of X's A-list with the F-intervals inside them
+// (every F-interval lies in an A-interval), each joined with all of Y by a
+// workgroup of its own.  An overlap is in one of them, so the pair's answer is
+// the highest of theirs: they are or-ed into a word at the queue's end, which
+// counts the parts done in its upper bits; the last one writes the verdict.
+// A part is as many tiles of X as give every workgroup of the XCD about
+// kPartsPerBlock parts, but kPartTiles of them at least: a part searches its
+// place in Y anew, costs some 25 us however short it is, and does not stop at
+// another's true hit.  Screening leaves few pairs of two long objects, and
+// those that need whole merges: of 40k x 40k objects with 300 complex ones a
+// side (230 pairs of 25 tiles) the kernel took 462 us, and takes 169 with parts
+// of 4 tiles (the call 0.51 ms; 0.52, 0.55 and 0.60 with 3, 6 and 10).  Cut
+// down to one tile, a partition's pairs (2 tiles each) took 149 us, not 57.
+constexpr uint32_t kMaxParts = 32, kPartsPerBlock = 2, kPartTiles = 4;
+
+// (tiles: the sum over the nq queued pairs)
+struct Parts {
+    uint32_t most, tiles;   // parts per pair; least tiles of one
+};
+
+__device__ __forceinline__ Parts wg_parts(uint32_t nq, uint32_t tiles, uint32_t qcap, uint32_t blocks) {
+    if (nq == 0 || nq > qcap / 2) return Parts{1, 1};
+    const uint32_t each = max(kPartTiles, tiles / (kPartsPerBlock * blocks));
+    return Parts{max(1u, min(kMaxParts, tiles / nq / each)), each};
+}
 
 // One chunk of a workgroup pass (see wg_stream), from Y[j]: true when the
 // wave's pass ends there (the end of Y, a chunk starting at or after
@@ -940,12 +976,23 @@ __global__ __launch_bounds__(kBlock) void k_wg(BatchArgs b) {
             // the grab is one thread's, passed on through LDS, so that all
             // four waves take the same branches and reach every barrier)
             const uint32_t nq = uniform(min(pb->qfill[seg * kCtrStride], pb->qcap));
+            const Parts cut =
+                wg_parts(nq, uniform(pb->qhead[(kTilesCtr + seg) * kCtrStride]), pb->qcap, gridDim.x / xcds);
+            const uint32_t parts = cut.most;
             for (;;) {
                 __syncthreads();   // the last pair's shared words are no longer read
-                if (threadIdx.x == 0) wg_sh.grab = atomicAdd(&pb->qhead[seg * kCtrStride], 1u);
+                if (threadIdx.x == 0) {
+                    const uint32_t g = atomicAdd(&pb->qhead[seg * kCtrStride], 1u);
+                    wg_sh.grab = g;
+                    wg_sh.known = parts > 1 && g < nq * parts
+                                      ? __hip_atomic_load(&pb->queue[uint64_t(seg + 1) * pb->qcap - 1 - g / parts],
+                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kHitTH
+                                      : 0u;
+                }
                 __syncthreads();
-                const uint32_t q = uniform(wg_sh.grab);
-                if (q >= nq) break;
+                if (uniform(wg_sh.grab) >= nq * parts) break;
+                const uint32_t q = uniform(wg_sh.grab) / parts, part = uniform(wg_sh.grab) % parts;
+                const bool known = uniform(wg_sh.known) != 0;
                 const __attribute__((address_space(4))) FilterArgs &a = pb->f;
                 const uint64_t p = pb->queue[uint64_t(seg) * pb->qcap + q];
                 const uint32_t r = uniform(gload32(a.r, p)), s = uniform(gload32(a.s, p));
@@ -956,13 +1003,47 @@ __global__ __launch_bounds__(kBlock) void k_wg(BatchArgs b) {
                 const uint32_t nas = uint32_t(gload64(a.As.off, s + 1) - as0);
                 const uint32_t nfs = uint32_t(gload64(a.Fs.off, s + 1) - fs0);
                 const bool xs = max(nas, nfs) < max(nar, nfr);   // the shorter object is cut into pieces
-                const PairLists L = pair_lists(a, xs, ar0, nar, fr0, nfr, as0, nas, fs0, nfs);
-                const uint32_t v = wg_pair<TW, C>(wres, L, pb->search_min, w, lane, &wg_sh);
+                PairLists L = pair_lists(a, xs, ar0, nar, fr0, nfr, as0, nas, fs0, nfs);
+                // this part of X: all of it when the pair is not cut
+                const uint32_t of = min(parts, max(1u, L.nxa / (TW * cut.tiles)));
+                bool run = true;
+                if (of > 1 || part > 0) {
+                    run = part < of && !known;
+                    if (run) {
+                        const uint32_t i0 = uint32_t(uint64_t(L.nxa) * part / of);
+                        const uint32_t i1 = uint32_t(uint64_t(L.nxa) * (part + 1) / of);
+                        // F-intervals that end above the part's first key, up to the next part's
+                        const uint32_t f0 =
+                            part == 0 ? 0u : uniform(wave_first_above(L.xfe, L.nxf, uniform(gload(L.xas, i0)), lane));
+                        const uint32_t f1 =
+                            part + 1 == of ? L.nxf
+                                           : uniform(wave_first_above(L.xfe, L.nxf, uniform(gload(L.xas, i1)), lane));
+                        L.xas += i0;
+                        L.xae += i0;
+                        L.xfs += f0;
+                        L.xfe += f0;
+                        L.nxa = i1 - i0;
+                        L.nxf = f1 - f0;
+                    }
+                }
+                uint32_t v = APRIL_TN;
+                if (run) v = wg_pair<TW, C>(wres, L, pb->search_min, w, lane, &wg_sh);
                 if (threadIdx.x == 0) {
-                    pb->f.verdict[p] = uint8_t(v);
-                    c_tn += v == APRIL_TN;
-                    c_th += v == APRIL_TH;
-                    c_ind += v == APRIL_INDECISIVE;
+                    bool last = true;
+                    if (parts > 1) {
+                        uint32_t *word = pb->queue + uint64_t(seg + 1) * pb->qcap - 1 - q;
+                        if (v != APRIL_TN) atomicOr(word, v == APRIL_TH ? kHitAA | kHitTH : kHitAA);
+                        __threadfence();
+                        const uint32_t old = atomicAdd(word, 0x100u);
+                        last = (old >> 8) + 1 == parts;
+                        v = old & kHitTH ? APRIL_TH : old & kHitAA ? APRIL_INDECISIVE : APRIL_TN;
+                    }
+                    if (last) {
+                        pb->f.verdict[p] = uint8_t(v);
+                        c_tn += v == APRIL_TN;
+                        c_th += v == APRIL_TH;
+                        c_ind += v == APRIL_INDECISIVE;
+                    }
                 }
             }
         }
@@ -1245,7 +1326,8 @@ __global__ void k_zero_queue_ctrs(unsigned int *qctr) {
     }
 }
 
-int xcd_count(int cus) { return (cus >= 64 && cus % 32 == 0) ? std::min<int>(cus / 32, kMaxCtrs - 1) : 1; }
+// (below kTilesCtr: the queue counters' second halves hold the sums of tiles)
+int xcd_count(int cus) { return (cus >= 64 && cus % 32 == 0) ? std::min<int>(cus / 32, kTilesCtr - 1) : 1; }
 
 __global__ void k_zero_ctrs(unsigned int *ctr) {
     const uint32_t t = threadIdx.x;
