@@ -1126,7 +1126,7 @@ void k_batched(BatchArgs b) {
             // offsets from g0, so that a round of the loop below has a pair for
             // most lanes.
             uint32_t n_open = uint32_t(g1 - g0);
-            if (MODE == kAlg2 && pb->screened) {
+            if (MODE != kMixedOrders && pb->screened) {
                 const uint8_t __attribute__((address_space(1))) *vb =
                     (const uint8_t __attribute__((address_space(1))) *)a.verdict + g0;
                 uint32_t cnt = 0;
@@ -1144,7 +1144,7 @@ void k_batched(BatchArgs b) {
             for (uint32_t o0 = 0; o0 < n_open; o0 += 64) {
             const bool in = o0 + lane < n_open;
             uint64_t p = g0 + o0 + lane;
-            if (MODE == kAlg2 && pb->screened) p = g0 + (in ? open_at[w][o0 + lane] : 0u);
+            if (MODE != kMixedOrders && pb->screened) p = g0 + (in ? open_at[w][o0 + lane] : 0u);
             bool seq = false, wave = false;
             // lane k's verdict for pair g0 + k, stored once per grab (a
             // store per pair would make each pair wait for the last one's)
@@ -1461,7 +1461,8 @@ int launch_batched_mixed(const FilterArgs &a, uint32_t shift_r, uint32_t shift_s
     return launch_tc<256, 2, kMixedOrders>(b, cus, 0, stream);
 }
 
-int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStream_t stream) {
+int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStream_t stream, const april_lists_t *R,
+                          const april_lists_t *S) {
     BatchArgs b;
     b.f = a;
     b.xhead = static_cast<unsigned int *>(workspace);
@@ -1477,10 +1478,17 @@ int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStre
         k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
         APRIL_HIP_TRY(hipGetLastError());
     }
+    if (can_screen(R, S, a.n_pairs)) {
+        FilterArgs f = a;
+        if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream, true)) return rc;
+        b.screened = 1;
+    }
     return launch_tc<256, 2, kWithinJoin>(b, cus, 0, stream);
 }
 
-int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hipStream_t stream) {
+int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hipStream_t stream,
+                               const april_lists_t *P, const april_cells_t *L) {
     BatchArgs b;
     b.f = a;
     b.xhead = static_cast<unsigned int *>(workspace);
@@ -1495,6 +1503,12 @@ int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hi
     if (!b.fixed) {
         k_zero_ctrs<<<1, 64, 0, stream>>>(b.xhead);
         APRIL_HIP_TRY(hipGetLastError());
+    }
+    if (can_screen_lines(P, L, a.n_pairs)) {
+        FilterArgs f = a;
+        if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
+        if (int rc = launch_screen_lines(P, L, f, cus, workspace, stream)) return rc;
+        b.screened = 1;
     }
     return launch_tc<256, 2, kLinestrings>(b, cus, 0, stream);
 }

@@ -59,6 +59,10 @@ extern "C" int april_cells_to_device(const april_cells_t *h, void *hip_stream, a
         delete C;
         return fail(APRIL_E_HIP, std::string("cells upload: ") + hipGetErrorString(e));
     }
+    if (int rc = launch_line_summaries(C, s)) {
+        april_cells_free(C);
+        return rc;
+    }
     *out = C;
     return APRIL_OK;
 }
@@ -87,6 +91,7 @@ extern "C" void april_cells_free(april_cells_t *C) {
         (void)hipGetDevice(&cur);
         if (cur != C->device) (void)hipSetDevice(C->device);
         (void)hipFree(C->d_block);
+        if (C->sum_block) (void)hipFree(C->sum_block);
         if (cur != C->device) (void)hipSetDevice(cur);
     }
     delete C;

@@ -149,8 +149,13 @@ bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs
 // where the join kernels have to look), and the decided pairs' counts into the
 // slots at `counters` (already cleared) when f.counts is set.  Of f only the
 // pairs, the verdicts and R's raw A-lists are read.
+// within: for within joins.
 int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
-                  hipStream_t stream);
+                  hipStream_t stream, bool within = false);
+// The same for polygons (R of f) against linestrings.
+bool can_screen_lines(const april_lists_t *P, const april_cells_t *L, uint64_t n_pairs);
+int launch_screen_lines(const april_lists_t *P, const april_cells_t *L, const FilterArgs &f, int cus, void *counters,
+                        hipStream_t stream);
 // Kernel arguments of a filter call on device lists R and S (raw codec).
 FilterArgs make_args(const april_lists_t *R, const april_lists_t *S, const uint32_t *d_r, const uint32_t *d_s,
                      uint64_t n_pairs, uint8_t *d_verdict, unsigned long long *counts);
@@ -162,10 +167,13 @@ int launch_batched_mixed(const FilterArgs &a, uint32_t shift_r, uint32_t shift_s
                          hipStream_t stream);
 // The batched schedule for within joins (Sec. 4.3.2): s resident, A(r)
 // streamed for AA, then tested for lying inside F(s).
-int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStream_t stream);
+// R, S (and P, L below): as for launch_batched.
+int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStream_t stream, const april_lists_t *R,
+                          const april_lists_t *S);
 // The batched schedule for polygon-linestring joins (Sec. 4.3.3): R are the
 // polygons (resident), S the linestrings, As their cell ids as runs of
 // consecutive ids [start, end) (the F views are not read).
-int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hipStream_t stream);
+int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hipStream_t stream,
+                               const april_lists_t *P, const april_cells_t *L);
 
 }  // namespace april

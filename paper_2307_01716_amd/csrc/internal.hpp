@@ -104,6 +104,8 @@ struct april_cells {
     std::vector<uint64_t> run_off;
     std::vector<uint32_t> run_start, run_end;
     uint64_t n_runs = 0;
+    uint64_t *sum = nullptr;         // summaries for screening (screen.hip; null: none)
+    void *sum_block = nullptr;
     uint64_t *d_off = nullptr;
     uint32_t *d_start = nullptr, *d_end = nullptr;
     void *d_block = nullptr;
@@ -180,6 +182,7 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
 // Summaries of device lists for screening, see screen.hip.
 int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, const uint32_t *ae, const uint32_t *fs,
                      const uint32_t *fe, hipStream_t stream);
+int launch_line_summaries(april_cells_t *C, hipStream_t stream);
 // stats[0] = the most intervals in one list, stats[1] = A-lists of kExact intervals or more
 // (both zero before the call).
 int launch_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, unsigned long long *stats,

@@ -61,6 +61,7 @@ struct SumBuild {
     uint32_t *slot, *coarse, *taken;   // taken[0]: coarse tables given out; taken[1]: objects queued
     uint32_t *queue;                   // objects with a longer list than kOneWave
     uint32_t tables, queue_cap;
+    uint32_t sample;                   // no F-lists: TF are 32 of the A-list, evenly spaced (linestrings)
     uint32_t by_slot, min_len;         // compressed lists: objects of min_len A-intervals or more have a summary,
                                        // numbered like their coarse tables
 };
@@ -169,7 +170,7 @@ struct SumLds {
     uint32_t sum[2 * kSumEntries];   // (start, end) pairs
     uint32_t coarse[kTable];
     uint32_t part[16][2];
-    uint32_t slot;
+    uint32_t outside;                // some F-interval lies in no hull interval
 };
 
 // The hull of X.A with K gaps kept: hull interval i ends at the i-th kept gap
@@ -197,13 +198,21 @@ __device__ __forceinline__ void hull(const uint32_t *as, const uint32_t *ae, uin
 template <int W>
 __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &l, uint32_t w, uint32_t lane) {
     const uint32_t tid = w * 64 + lane;
-    const uint64_t a0 = b.A.off[k], f0 = b.F.off[k];
-    const uint32_t na = uint32_t(b.A.off[k + 1] - a0), nf = uint32_t(b.F.off[k + 1] - f0);
+    const uint64_t a0 = b.A.off[k], f0 = b.sample ? 0 : b.F.off[k];
+    const uint32_t na = uint32_t(b.A.off[k + 1] - a0), nf = b.sample ? 0u : uint32_t(b.F.off[k + 1] - f0);
     const uint32_t *as = b.A.s + a0, *ae = b.A.e + a0, *fs = b.F.s + f0, *fe = b.F.e + f0;
     group_sync<W>();
+    if (tid == 0) l.outside = 0;
     for (uint32_t i = tid; i < 2 * kSumEntries; i += 64 * W) l.sum[i] = (i & 1) ? 0u : 0xffffffffu;
     if (slot != kNoSlot)
         for (uint32_t i = tid; i < kTable; i += 64 * W) l.coarse[i] = 0xffffffffu;
+    if (b.sample) {
+        if (tid < min(na, kSumHalf)) {
+            const uint32_t j = na <= kSumHalf ? tid : uint32_t(uint64_t(na - 1) * tid / (kSumHalf - 1));
+            l.sum[2 * tid] = as[j];
+            l.sum[2 * tid + 1] = ae[j];
+        }
+    } else {
     // TF
     auto flen = [&](uint32_t j) { return fe[j] - fs[j]; };
     histogram<W>(l.hist, nf, flen, tid);
@@ -216,6 +225,7 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
             l.coarse[4 * kCoarse + i] = fe[j];
             l.coarse[5 * kCoarse + i] = fs[j];
         }, l.part, w, lane);
+    }
     // H, and the coarse hull from the same histogram
     auto gap = [&](uint32_t j) { return as[j + 1] - ae[j]; };
     const uint32_t ng = na ? na - 1 : 0u;
@@ -233,8 +243,23 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
         }, l.part, w, lane);
     }
     group_sync<W>();
-    // an F-interval counts only inside an A-interval (lists that were not
-    // validated may hold others): the first A-interval that ends above its start
+    // Within joins take an interval outside the hull for one outside F, so no
+    // F-interval may lie there (lists that were not validated may hold such):
+    // the last hull interval that starts at or below each one's start.
+    if (!b.sample) {
+        bool out = false;
+        for (uint32_t j = tid; j < nf; j += 64 * W) {
+            const uint32_t s = fs[j], *h = l.sum + kSumEntries;
+#pragma unroll
+            for (uint32_t step = kSumHalf / 2; step > 0; step >>= 1) h = h[2 * step] <= s ? h + 2 * step : h;
+            out |= h[0] > s || h[1] < fe[j];
+        }
+        if (__any(out) && lane == 0) l.outside = 1;
+        group_sync<W>();
+    }
+    const bool none = l.outside != 0;
+    // an F-interval counts only inside an A-interval (for the same reason): the
+    // first A-interval that ends above its start
     auto in_a = [&](uint32_t s, uint32_t e) {
         uint32_t lo = 0, hi = na;
         while (lo < hi) {
@@ -246,7 +271,7 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
     };
     if (w == 0) {
         uint32_t s = l.sum[2 * lane], e = l.sum[2 * lane + 1];
-        if (lane < kSumHalf && e != 0 && !in_a(s, e)) e = 0;
+        if (lane < kSumHalf && e != 0 && !b.sample && (none || !in_a(s, e))) e = 0;
         const uint64_t at = b.by_slot ? slot : k;
         b.sum[at * kSumEntries + lane] = (uint64_t(e) << 32) | s;
     }
@@ -267,9 +292,10 @@ __global__ __launch_bounds__(kBlock) void k_summaries(SumBuild b) {
     const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
     const uint64_t waves = uint64_t(gridDim.x) * kWavesPerBlock;
     for (uint64_t k = uint64_t(blockIdx.x) * kWavesPerBlock + w; k < b.n; k += waves) {
-        const uint32_t na = uint32_t(b.A.off[k + 1] - b.A.off[k]), nf = uint32_t(b.F.off[k + 1] - b.F.off[k]);
+        const uint32_t na = uint32_t(b.A.off[k + 1] - b.A.off[k]);
+        const uint32_t nf = b.sample ? 0u : uint32_t(b.F.off[k + 1] - b.F.off[k]);
         uint32_t slot = kNoSlot;
-        if (na >= (b.by_slot ? b.min_len : kExact)) {
+        if (b.tables && na >= (b.by_slot ? b.min_len : kExact)) {
             if (lane == 0) slot = atomicAdd(&b.taken[0], 1u);
             slot = uniform(__shfl(slot, 0));
             if (slot >= b.tables) slot = kNoSlot;
@@ -321,24 +347,51 @@ struct ScreenArgs {
 __device__ __forceinline__ constexpr uint32_t padded(uint32_t i) { return i + (i >> 6); }
 constexpr uint32_t kStarts = kExact + kExact / 64;   // from an end to its start
 
-// Does [s, e) overlap an interval of the table (P2 entries, the last ones
-// padding)?
+// The first entry of a table (P2 entries, the last ones padding) that ends above `key`.
 template <int P2>
-__device__ __forceinline__ bool search(const uint32_t *ends, uint32_t s, uint32_t e) {
+__device__ __forceinline__ const uint32_t *find(const uint32_t *ends, uint32_t key) {
     const uint32_t *p = ends;
 #pragma unroll
-    for (uint32_t S = P2 / 2; S > 0; S >>= 1) p = p[padded(S - 1)] <= s ? p + padded(S) : p;
-    return p[kStarts] < e;   // the first interval that ends above s starts below e
+    for (uint32_t S = P2 / 2; S > 0; S >>= 1) p = p[padded(S - 1)] <= key ? p + padded(S) : p;
+    return p;
 }
 
 // (size: a power of two, 0 for a coarse table)
-__device__ __forceinline__ bool search_any(const uint32_t *ends, uint32_t size, uint32_t s, uint32_t e) {
-    if (size == 64) return search<64>(ends, s, e);
-    if (size == 128 || size == 0) return search<128>(ends, s, e);
-    if (size == 256) return search<256>(ends, s, e);
-    return search<kExact>(ends, s, e);
+__device__ __forceinline__ const uint32_t *find_any(const uint32_t *ends, uint32_t size, uint32_t key) {
+    if (size == 64) return find<64>(ends, key);
+    if (size == 128 || size == 0) return find<128>(ends, key);
+    if (size == 256) return find<256>(ends, key);
+    return find<kExact>(ends, key);
 }
-static_assert(kCoarse == 128, "search_any");
+static_assert(kCoarse == 128, "find_any");
+
+// Does [s, e) overlap an interval of the table?  (The first one that ends
+// above s has to start below e.)
+__device__ __forceinline__ bool search_any(const uint32_t *ends, uint32_t size, uint32_t s, uint32_t e) {
+    return find_any(ends, size, s)[kStarts] < e;
+}
+
+// A table place's entry number (places step over one word in 65).
+__device__ __forceinline__ uint32_t entry_at(const uint32_t *ends, const uint32_t *p) {
+    const uint32_t q = uint32_t(p - ends);
+    return q - ((q * 1009) >> 16);   // q / 65 for q < 520
+}
+
+// What is screened for.  Alg. 2; within joins (is r within s?); polygons
+// against linestrings, whose runs of cells stand for A-lists and, 32 of them
+// evenly spaced, for TF.
+//
+// Within joins: no H interval of s overlapping A(r) is a true negative as
+// before.  A TF interval of s that overlaps A(r) is an overlap of the A-lists;
+// if then some A-interval of r lies in no hull interval of s, it lies in no
+// F-interval either: indecisive.  (The hull intervals are disjoint, so the
+// A-intervals inside them are counted by two searches each.)  Decides 90% of
+// the at-scale pairs.
+//
+// Linestrings: a run that overlaps F(p) is a true hit, no hull interval of the
+// runs overlapping A(p) a true negative; 94% of the pairs.  Both lists of the
+// polygon are in LDS (or its coarse table's longest F-intervals and hull).
+constexpr int kAlg2 = 0, kWithin = 1, kLines = 2;
 
 // One word per active lane from global memory straight into LDS, lane l's at dst[l].
 __device__ __forceinline__ void lds_dma(const uint32_t *src, uint32_t *dst) {
@@ -349,21 +402,26 @@ __device__ __forceinline__ void lds_dma(const uint32_t *src, uint32_t *dst) {
 // pair's ids and the bounds of its R list, then goes through them one by one;
 // the next pair's summary is loaded before the current one is searched.  Every
 // pair costs about the same, so the blocks are dealt out without counters.
-__global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
-    __shared__ uint32_t lds[kWavesPerBlock][2 * kStarts];   // X: ends, then starts
+template <int MODE>
+__global__ __launch_bounds__(kBlock, MODE == kLines ? 4 : 8) void k_screen(ScreenArgs a) {
+    // X: ends, then starts (linestrings: of A, then of F)
+    constexpr uint32_t kF = MODE == kLines ? 2 * kStarts : 0;
+    __shared__ uint32_t lds[kWavesPerBlock][kF + 2 * kStarts];
     const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
     uint32_t *const t = lds[w];
     const uint32_t *const hull = t + padded(kCoarse);               // a coarse table's second list
     const uint32_t *const half = lane < kSumHalf ? t : hull;        // the coarse list a lane searches
+    const uint32_t *const whole = MODE == kLines && lane < kSumHalf ? t + kF : t;   // and the exact one
     const uint32_t xcd = blockIdx.x % a.xcds, bx = blockIdx.x / a.xcds, nbx = gridDim.x / a.xcds;
     const uint64_t lo = a.f.n_pairs * xcd / a.xcds, hi = a.f.n_pairs * (xcd + 1) / a.xcds;
-    unsigned long long c_tn = 0, c_th = 0;
+    unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
     uint32_t cached = kNoSlot, size = 0;   // the R object in t; its table's entries, a power of two (0: coarse)
     for (uint64_t g0 = lo + uint64_t(a.take) * (bx * kWavesPerBlock + w); g0 < hi;
          g0 += uint64_t(a.take) * nbx * kWavesPerBlock) {
         const uint64_t p = g0 + lane;
         uint32_t r = 0, s_at = 0, nar = 0, slot = kNoSlot, s_tab = kNoSlot;
-        uint64_t ar0 = 0;
+        uint64_t ar0 = 0, fr0 = 0;
+        uint32_t nfr = 0;
         bool todo_me = false;
         uint32_t vv = APRIL_BAD_PAIR;
         const bool mine = lane < a.take && p < hi;
@@ -374,9 +432,14 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
                 vv = kPending;
                 ar0 = a.f.Ar.off[r];
                 nar = uint32_t(a.f.Ar.off[r + 1] - ar0);
-                s_tab = a.s_table[s];
+                if (MODE == kLines) {
+                    fr0 = a.f.Fr.off[r];
+                    nfr = uint32_t(a.f.Fr.off[r + 1] - fr0);
+                } else {
+                    s_tab = a.s_table[s];
+                }
                 s_at = a.s_slot ? s_tab : s;
-                const bool exact = a.raw && nar < kExact;
+                const bool exact = a.raw && max(nar, nfr) < kExact;
                 if (!exact) slot = a.r_slot[r];
                 todo_me = s_at != kNoSlot && (exact || slot != kNoSlot);
             }
@@ -390,27 +453,41 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
             wave_lds_sync();
             if (sl == kNoSlot) {
                 const uint32_t n = __builtin_amdgcn_readlane(nar, k);
-                const uint64_t at = (uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0 >> 32), k))) << 32) |
-                                    uint32_t(__builtin_amdgcn_readlane(uint32_t(ar0), k));
-                const uint32_t *xs = a.f.Ar.s + at, *xe = a.f.Ar.e + at;
-                size = n < 64 ? 64u : n < 128 ? 128u : n < 256 ? 256u : kExact;   // above n: a padding entry
+                const uint32_t nf = MODE == kLines ? __builtin_amdgcn_readlane(nfr, k) : 0u, nm = max(n, nf);
+                auto copy = [&](const uint32_t *xs, const uint32_t *xe, uint32_t m, uint32_t *to) {
 #pragma unroll 1
-                for (uint32_t i = 0; i < size; i += 64) {
-                    if (i + lane < n) {
-                        lds_dma(xe + i + lane, t + padded(i));
-                        lds_dma(xs + i + lane, t + kStarts + padded(i));
-                    } else {
-                        t[padded(i) + lane] = 0xffffffffu;
-                        t[kStarts + padded(i) + lane] = 0xffffffffu;
+                    for (uint32_t i = 0; i < size; i += 64) {
+                        if (i + lane < m) {
+                            lds_dma(xe + i + lane, to + padded(i));
+                            lds_dma(xs + i + lane, to + kStarts + padded(i));
+                        } else {
+                            to[padded(i) + lane] = 0xffffffffu;
+                            to[kStarts + padded(i) + lane] = 0xffffffffu;
+                        }
                     }
+                };
+                auto lane64 = [&](uint64_t v) {
+                    return (uint64_t(uint32_t(__builtin_amdgcn_readlane(uint32_t(v >> 32), k))) << 32) |
+                           uint32_t(__builtin_amdgcn_readlane(uint32_t(v), k));
+                };
+                size = nm < 64 ? 64u : nm < 128 ? 128u : nm < 256 ? 256u : kExact;   // above nm: a padding entry
+                const uint64_t at = lane64(ar0);
+                copy(a.f.Ar.s + at, a.f.Ar.e + at, n, t);
+                if (MODE == kLines) {
+                    const uint64_t ft = lane64(fr0);
+                    copy(a.f.Fr.s + ft, a.f.Fr.e + ft, nf, t + kF);
                 }
             } else {
-                const uint32_t *c = a.coarse + uint64_t(sl) * kTable;
+                // (linestrings: the longest F-intervals in the place of the longest A-intervals)
+                const uint32_t *c = a.coarse + uint64_t(sl) * kTable, *first = c + (MODE == kLines ? 4 * kCoarse : 0);
+                const uint32_t to_start = MODE == kLines ? kCoarse : 2 * kCoarse;
                 size = 0;
 #pragma unroll
-                for (uint32_t i = 0; i < 2 * kCoarse; i += 64) {
-                    lds_dma(c + i + lane, t + padded(i));
-                    lds_dma(c + 2 * kCoarse + i + lane, t + kStarts + padded(i));
+                for (uint32_t i = 0; i < kCoarse; i += 64) {
+                    lds_dma(first + i + lane, t + padded(i));
+                    lds_dma(first + to_start + i + lane, t + kStarts + padded(i));
+                    lds_dma(c + kCoarse + i + lane, t + padded(kCoarse + i));
+                    lds_dma(c + 3 * kCoarse + i + lane, t + kStarts + padded(kCoarse + i));
                 }
             }
             __builtin_amdgcn_s_waitcnt(0);   // the copies, all under way at once, have landed
@@ -429,13 +506,28 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
                 y_next = a.sum[uint64_t(__builtin_amdgcn_readlane(s_at, kn)) * kSumEntries + lane];
             }
             load_x(k);
-            const uint64_t m = __ballot(search_any(size ? t : half, size, uint32_t(y), uint32_t(y >> 32)));
-            const uint32_t v = uint32_t(m) ? APRIL_TH : uint32_t(m >> 32) ? kPending : APRIL_TN;
+            const uint32_t ys = uint32_t(y), ye = uint32_t(y >> 32);
+            const uint64_t m = __ballot(search_any(size ? whole : half, size, ys, ye));
+            uint32_t v;
+            if (MODE == kWithin) {
+                v = uint32_t(m >> 32) ? kPending : APRIL_TN;
+                if (uint32_t(m) && v == kPending) {
+                    // the A-intervals (of a coarse table: its longest) inside each hull interval
+                    const uint32_t *p0 = find_any(t, size, ys), *p1 = find_any(t, size, ye);
+                    const uint32_t i0 = entry_at(t, p0) + (p0[kStarts] < ys ? 1u : 0u), i1 = entry_at(t, p1);
+                    uint32_t in = lane >= kSumHalf && ye != 0 && i1 > i0 ? i1 - i0 : 0u;
+                    for (int off = 32; off > 0; off >>= 1) in += __shfl_xor(in, off);
+                    const uint32_t n = size ? __builtin_amdgcn_readlane(nar, k) : kCoarse - 1;
+                    if (in < n) v = APRIL_INDECISIVE;
+                }
+            } else {
+                v = uint32_t(m) ? APRIL_TH : uint32_t(m >> 32) ? kPending : APRIL_TN;
+            }
             vv = lane == k ? v : vv;
         }
         // once more, with S's coarse table where it has one (padding entries
         // overlap nothing); apart from the loop above, which it would slow down
-        todo = __ballot(todo_me && vv == kPending && s_tab != kNoSlot);
+        todo = MODE == kAlg2 ? __ballot(todo_me && vv == kPending && s_tab != kNoSlot) : 0;
         while (todo) {
             const uint32_t k = uint32_t(__builtin_ctzll(todo));
             todo &= todo - 1;
@@ -462,15 +554,17 @@ __global__ __launch_bounds__(kBlock, 8) void k_screen(ScreenArgs a) {
             a.f.verdict[p] = uint8_t(vv);
             c_tn += vv == APRIL_TN;
             c_th += vv == APRIL_TH;
+            if (MODE == kWithin) c_ind += vv == APRIL_INDECISIVE;
         }
     }
     if (a.f.counts) {
         for (int off = 32; off > 0; off >>= 1) {
             c_tn += __shfl_down(c_tn, off);
             c_th += __shfl_down(c_th, off);
+            if (MODE == kWithin) c_ind += __shfl_down(c_ind, off);
         }
-        const unsigned long long v[2] = {c_tn, c_th};
-        if (lane == 0) add_totals(a.ctr, blockIdx.x * kWavesPerBlock + w, v, 2);
+        const unsigned long long v[3] = {c_tn, c_th, c_ind};
+        if (lane == 0) add_totals(a.ctr, blockIdx.x * kWavesPerBlock + w, v, 3);
     }
 }
 
@@ -522,44 +616,68 @@ bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs
     return R->d.sum && S->d.sum && 2 * R->d.n_sums >= R->n && 2 * S->d.n_sums >= S->n;
 }
 
-int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
-                  hipStream_t stream) {
-    ScreenArgs a;
-    a.f = f;
-    a.sum = S->d.sum;
-    a.s_slot = S->codec == APRIL_CODEC_RAW ? nullptr : S->d.slot;
+bool can_screen_lines(const april_lists_t *P, const april_cells_t *L, uint64_t n_pairs) {
+    return (n_pairs >= kScreenMin || long_lists(P)) && P->d.sum && L->sum;
+}
+
+template <int MODE>
+static int screen(ScreenArgs &a, const april_lists_t *R, int cus, void *counters, hipStream_t stream) {
     a.r_slot = R->d.slot;
     a.coarse = R->d.coarse;
-    a.s_table = S->d.slot;
-    a.s_coarse = S->d.coarse;
+    a.raw = R->codec == APRIL_CODEC_RAW;
     a.ctr = static_cast<unsigned int *>(counters);
     a.xcds = uint32_t(xcd_count(cus));
-    a.raw = R->codec == APRIL_CODEC_RAW;
     // 64 pairs at a time, or what gives every wave some: a pair takes half a
     // microsecond and more after another (16,272 pairs with 64 at a time: 93 us
     // a call, so 31)
-    const uint64_t most = uint64_t(cus) * 8, waves = most * kWavesPerBlock;
-    a.take = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(1, (f.n_pairs + waves - 1) / waves)));
-    uint64_t blocks = std::min(most, (f.n_pairs + a.take * kWavesPerBlock - 1) / (a.take * kWavesPerBlock));
+    const uint64_t most = uint64_t(cus) * (MODE == kLines ? 4 : 8), waves = most * kWavesPerBlock;
+    a.take = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(1, (a.f.n_pairs + waves - 1) / waves)));
+    uint64_t blocks = std::min(most, (a.f.n_pairs + a.take * kWavesPerBlock - 1) / (a.take * kWavesPerBlock));
     blocks = (blocks + a.xcds - 1) / a.xcds * a.xcds;
-    k_screen<<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a);
+    k_screen<MODE><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a);
     APRIL_HIP_TRY(hipGetLastError());
     return APRIL_OK;
 }
 
-// Summaries of device lists, on `stream`.  `longer`: objects whose A-list has
-// kExact intervals or more (compressed lists: kVbyteSummaryMin), the coarse
-// tables needed.  as/ae/fs/fe: the raw arrays (of compressed lists: decoded
-// copies).  Lists without summaries are joined without screening, so running
-// out of memory here is not an error.
-int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, const uint32_t *ae, const uint32_t *fs,
-                     const uint32_t *fe, hipStream_t stream) {
-    const bool raw = L->codec == APRIL_CODEC_RAW;
-    const uint64_t sums = raw ? L->n : longer;
-    if (sums == 0 || L->n >= 0x7fffffffull || longer >= 0x7fffffffull) return APRIL_OK;
+int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
+                  hipStream_t stream, bool within) {
+    ScreenArgs a{};
+    a.f = f;
+    a.sum = S->d.sum;
+    a.s_slot = S->codec == APRIL_CODEC_RAW ? nullptr : S->d.slot;
+    a.s_table = S->d.slot;
+    a.s_coarse = S->d.coarse;
+    return within ? screen<kWithin>(a, R, cus, counters, stream) : screen<kAlg2>(a, R, cus, counters, stream);
+}
+
+int launch_screen_lines(const april_lists_t *P, const april_cells_t *L, const FilterArgs &f, int cus, void *counters,
+                        hipStream_t stream) {
+    ScreenArgs a{};
+    a.f = f;
+    a.sum = L->sum;
+    return screen<kLines>(a, P, cus, counters, stream);
+}
+
+namespace {
+
+// Summaries of n lists on `stream` into an allocation of their own (null when
+// there is no memory for it: lists without summaries are joined without
+// screening).  `tables`: coarse tables needed.
+struct Made {
+    void *block;
+    uint64_t *sum;
+    uint32_t *slot, *coarse;
+    uint64_t sums, bytes;
+};
+
+int make_summaries(ListView A, ListView F, uint64_t n, uint64_t intervals, uint64_t tables, bool by_slot, bool sample,
+                   hipStream_t stream, Made *out) {
+    *out = Made{};
+    const uint64_t sums = by_slot ? tables : n;
+    if (sums == 0 || n >= 0x7fffffffull || tables >= 0x7fffffffull) return APRIL_OK;
     auto up = [](uint64_t v) { return (v + 255) & ~uint64_t(255); };
-    const uint64_t queue = std::min<uint64_t>(L->n, (L->n_a + L->n_f) / kOneWave + 1);
-    const uint64_t b_sum = up(8 * kSumEntries * sums), b_coarse = up(4 * kTable * longer), b_slot = up(4 * L->n);
+    const uint64_t queue = std::min<uint64_t>(n, intervals / kOneWave + 1);
+    const uint64_t b_sum = up(8 * kSumEntries * sums), b_coarse = up(4 * kTable * tables), b_slot = up(4 * n);
     const uint64_t total = b_sum + b_coarse + b_slot + up(4 * queue) + 256;
     void *block = nullptr;
     if (hipMalloc(&block, total) != hipSuccess) {
@@ -568,32 +686,57 @@ int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, cons
     }
     char *p = static_cast<char *>(block);
     SumBuild b;
-    b.A = {L->d.off_a, as, ae};
-    b.F = {L->d.off_f, fs, fe};
-    b.n = L->n;
+    b.A = A;
+    b.F = F;
+    b.n = n;
     b.sum = reinterpret_cast<uint64_t *>(p); p += b_sum;
     b.coarse = reinterpret_cast<uint32_t *>(p); p += b_coarse;
     b.slot = reinterpret_cast<uint32_t *>(p); p += b_slot;
     b.taken = reinterpret_cast<uint32_t *>(p); p += 256;
     b.queue = reinterpret_cast<uint32_t *>(p);
-    b.tables = uint32_t(longer);
+    b.tables = uint32_t(tables);
     b.queue_cap = uint32_t(queue);
-    b.by_slot = raw ? 0 : 1;
+    b.sample = sample ? 1 : 0;
+    b.by_slot = by_slot ? 1 : 0;
     b.min_len = kVbyteSummaryMin;
     k_clear_taken<<<1, 2, 0, stream>>>(b.taken);
-    k_summaries<<<dim3(uint32_t(std::min<uint64_t>((L->n + 3) / 4, 4096))), dim3(kBlock), 0, stream>>>(b);
-    if (L->n_a + L->n_f > kOneWave)
+    k_summaries<<<dim3(uint32_t(std::min<uint64_t>((n + 3) / 4, 4096))), dim3(kBlock), 0, stream>>>(b);
+    if (intervals > kOneWave)
         k_summaries_long<<<dim3(uint32_t(std::min<uint64_t>(queue, 512))), dim3(1024), 0, stream>>>(b);
     if (const hipError_t e = hipGetLastError(); e != hipSuccess) {
         (void)hipFree(block);
         return fail(APRIL_E_HIP, std::string("summaries: ") + hipGetErrorString(e));
     }
-    L->d.sum_block = block;
-    L->d.sum = b.sum;
-    L->d.slot = b.slot;
-    L->d.coarse = b.coarse;
-    L->d.n_sums = sums;
-    L->d.bytes += total;
+    *out = Made{block, b.sum, b.slot, b.coarse, sums, total};
+    return APRIL_OK;
+}
+
+}  // namespace
+
+// `longer`: objects whose A-list has kExact intervals or more (compressed
+// lists: kVbyteSummaryMin).  as/ae/fs/fe: the raw arrays (of compressed lists:
+// decoded copies).
+int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, const uint32_t *ae, const uint32_t *fs,
+                     const uint32_t *fe, hipStream_t stream) {
+    Made m;
+    if (int rc = make_summaries({L->d.off_a, as, ae}, {L->d.off_f, fs, fe}, L->n, L->n_a + L->n_f, longer,
+                                L->codec != APRIL_CODEC_RAW, false, stream, &m))
+        return rc;
+    L->d.sum_block = m.block;
+    L->d.sum = m.sum;
+    L->d.slot = m.slot;
+    L->d.coarse = m.coarse;
+    L->d.n_sums = m.sums;
+    L->d.bytes += m.bytes;
+    return APRIL_OK;
+}
+
+int launch_line_summaries(april_cells_t *C, hipStream_t stream) {
+    Made m;
+    const ListView runs{C->d_off, C->d_start, C->d_end};
+    if (int rc = make_summaries(runs, runs, C->n, C->n_runs, 0, false, true, stream, &m)) return rc;
+    C->sum_block = m.block;
+    C->sum = m.sum;
     return APRIL_OK;
 }
 

@@ -32,25 +32,27 @@ int check_device(const april_lists_t *L) {
 enum class Variant { kWithin, kLinestrings, kMixed };
 
 // A variant on the filter's batched kernel, with a stream-ordered workspace.
-int run_batched(const FilterArgs &fa, int device, Variant v, uint32_t shift_r, uint32_t shift_s,
-                hipStream_t stream) {
+int run_batched(const FilterArgs &fa, Variant v, const april_lists_t *R, const april_lists_t *S,
+                const april_cells_t *L, uint32_t shift_r, uint32_t shift_s, hipStream_t stream) {
     if (fa.n_pairs >= (1ull << 32)) return fail(APRIL_E_INVALID, "fewer than 2^32 pairs per call");
     DeviceState *st = nullptr;
     if (int rc = device_state(&st)) return rc;
     int cur = 0;
     APRIL_HIP_TRY(hipGetDevice(&cur));
-    if (cur != device) return fail(APRIL_E_INVALID, "current device does not hold the lists");
+    if (cur != R->device) return fail(APRIL_E_INVALID, "current device does not hold the lists");
     void *ws = nullptr;
-    if (fa.n_pairs <= kSmallCall) {   // no scratch (and nothing to launch without pairs but the counts)
-        return v == Variant::kWithin        ? launch_batched_within(fa, st->cus, ws, stream)
-               : v == Variant::kLinestrings ? launch_batched_linestrings(fa, st->cus, ws, stream)
-                                            : launch_batched_mixed(fa, shift_r, shift_s, st->cus, ws, stream);
-    }
+    auto launch = [&]() -> int {
+        switch (v) {
+            case Variant::kWithin: return launch_batched_within(fa, st->cus, ws, stream, R, S);
+            case Variant::kLinestrings: return launch_batched_linestrings(fa, st->cus, ws, stream, R, L);
+            case Variant::kMixed: break;
+        }
+        return launch_batched_mixed(fa, shift_r, shift_s, st->cus, ws, stream);
+    };
+    if (fa.n_pairs <= kSmallCall) return launch();   // without scratch
     hipError_t e = hipMallocAsync(&ws, batched_workspace_bytes(fa.n_pairs), stream);
     if (e != hipSuccess) return fail(APRIL_E_NOMEM, std::string("workspace: ") + hipGetErrorString(e));
-    const int rc = v == Variant::kWithin        ? launch_batched_within(fa, st->cus, ws, stream)
-                   : v == Variant::kLinestrings ? launch_batched_linestrings(fa, st->cus, ws, stream)
-                                                : launch_batched_mixed(fa, shift_r, shift_s, st->cus, ws, stream);
+    const int rc = launch();
     APRIL_HIP_TRY(hipFreeAsync(ws, stream));
     return rc;
 }
@@ -72,7 +74,7 @@ extern "C" int april_filter_within(const april_lists_t *R, const april_lists_t *
     if (n_pairs && (!d_r || !d_s || !d_verdict)) return fail(APRIL_E_INVALID, "NULL pair/verdict array");
     const FilterArgs fa =
         make_args(R, S, d_r, d_s, n_pairs, d_verdict, reinterpret_cast<unsigned long long *>(d_counts));
-    return run_batched(fa, R->device, Variant::kWithin, 0, 0, static_cast<hipStream_t>(hip_stream));
+    return run_batched(fa, Variant::kWithin, R, S, nullptr, 0, 0, static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int april_filter_linestrings(const april_lists_t *P, const april_cells_t *L, const uint32_t *d_p,
@@ -90,7 +92,7 @@ extern "C" int april_filter_linestrings(const april_lists_t *P, const april_cell
     fa.As = {L->d_off, L->d_start, L->d_end};
     fa.Fs = fa.As;
     fa.n_s = L->n;
-    return run_batched(fa, P->device, Variant::kLinestrings, 0, 0, static_cast<hipStream_t>(hip_stream));
+    return run_batched(fa, Variant::kLinestrings, P, P, L, 0, 0, static_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int april_filter_mixed(const april_lists_t *R, const april_lists_t *S, const uint32_t *d_r,
@@ -114,5 +116,5 @@ extern "C" int april_filter_mixed(const april_lists_t *R, const april_lists_t *S
     }
     const FilterArgs fa =
         make_args(R, S, d_r, d_s, n_pairs, d_verdict, reinterpret_cast<unsigned long long *>(d_counts));
-    return run_batched(fa, R->device, Variant::kMixed, shift_r, shift_s, static_cast<hipStream_t>(hip_stream));
+    return run_batched(fa, Variant::kMixed, R, S, nullptr, shift_r, shift_s, static_cast<hipStream_t>(hip_stream));
 }

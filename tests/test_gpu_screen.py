@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 
 import oracle
+from synth.grid import Grid
 from synth.intervals import ListSet, random_lists, sub_lists
 
 pytestmark = pytest.mark.gpu
@@ -104,3 +105,108 @@ def test_bad_pairs_are_not_counted():
         got = v.cpu().numpy()
         assert np.array_equal(got, np.where(bad, april.BAD_PAIR, want))
         assert np.array_equal(c.cpu().numpy(), np.bincount(want[~bad], minlength=3))
+
+
+# ------------------------------------------------- within joins, linestrings
+
+def run(fn, *args):
+    r, s = args[2:]
+    v = torch.full((len(r),), 77, dtype=torch.uint8, device="cuda")
+    c = torch.full((3,), -1, dtype=torch.int64, device="cuda")
+    fn(args[0], args[1], torch.from_numpy(r.view(np.int32)).cuda(), torch.from_numpy(s.view(np.int32)).cuda(), v, c)
+    torch.cuda.synchronize()
+    return v.cpu().numpy(), c.cpu().numpy()
+
+
+def inside(rng, fs, fe, n, kind):
+    """Up to n intervals, each inside an F-interval; kind 1: and one beyond the
+    last, kind 2: and the first one grown over its F-interval's start."""
+    take = np.sort(rng.choice(len(fs), min(n, len(fs)), replace=False))
+    s, e = fs[take].copy(), fe[take].copy()
+    cut = rng.integers(0, e - s)
+    keep_end = rng.random(len(s)) < 0.5
+    s += np.where(keep_end, cut, 0).astype(np.uint32)
+    e -= np.where(keep_end, 0, cut).astype(np.uint32)
+    if len(s) and kind == 1:
+        s, e = np.append(s, fe[-1] + np.uint32(5)), np.append(e, fe[-1] + np.uint32(6))
+    if len(s) and kind == 2:
+        s[0] = fs[take[0]] - np.uint32(1)
+    return s.astype(np.uint32), e.astype(np.uint32)
+
+
+def contained(rng, LS, sizes):
+    """One object for each of LS: inside its F-intervals, almost so, or not."""
+    A, F = [], []
+    for k in range(len(LS.offA) - 1):
+        f = slice(int(LS.offF[k]), int(LS.offF[k + 1]))
+        a = inside(rng, LS.sF[f], LS.eF[f], int(sizes[k % len(sizes)]), k % 3)
+        A.append(a)
+        F.append(sub_lists(rng, *a, p=0.5))
+    a, f = ListSet.from_lists(A), ListSet.from_lists(F)
+    return oracle.Lists(a.off, a.start, a.end, f.off, f.start, f.end)
+
+
+@pytest.mark.parametrize("sizes", list(SIZES))
+def test_within(sizes):
+    rng = np.random.default_rng(20 + len(sizes))
+    print(f"[screen] within {sizes}", flush=True)
+    n = 48 if sizes == "long" else 120
+    LS = lists_of(rng, SIZES[sizes], n, False)
+    LR = contained(rng, LS, SIZES[sizes])
+    r = rng.integers(0, n, PAIRS).astype(np.uint32)
+    r.sort()
+    s = np.where(rng.random(PAIRS) < 0.7, r, rng.integers(0, n, PAIRS)).astype(np.uint32)
+    R, S = upload(LR, april.CODEC_RAW), upload(LS, april.CODEC_RAW)
+    want = oracle.filter_within(LR, LS, r, s)
+    assert set(np.unique(want)) == {0, 1, 2}
+    got, counts = run(april.april_filter_within, R, S, r, s)
+    assert np.array_equal(got, want)
+    assert np.array_equal(counts, np.bincount(want, minlength=3))
+
+
+def test_within_f_outside_a():
+    """Lists whose F-intervals lie outside A: as without screening, which
+    calls of few pairs go without."""
+    rng = np.random.default_rng(31)
+    LR, LS = (lists_of(rng, [5, 40, 200, 600], 40, False, outside=o) for o in (False, True))
+    R, S = upload(LR, april.CODEC_RAW), upload(LS, april.CODEC_RAW, False)
+    r, s = (rng.integers(0, 40, PAIRS).astype(np.uint32) for _ in range(2))
+    parts = [run(april.april_filter_within, R, S, r[i:i + 4500], s[i:i + 4500]) for i in (0, 4500)]
+    got, counts = run(april.april_filter_within, R, S, r, s)
+    assert np.array_equal(got, np.concatenate([p[0] for p in parts]))
+    assert np.array_equal(counts, sum(p[1] for p in parts))
+
+
+@pytest.mark.parametrize("sizes", list(SIZES))
+def test_linestrings(sizes):
+    rng = np.random.default_rng(40 + len(sizes))
+    print(f"[screen] linestrings {sizes}", flush=True)
+    g = Grid(0.0, 0.0, 1.0, 10)
+    n, ids = (24 if sizes == "long" else 60), 1 << 20
+    A, F = [], []
+    for k in range(n):
+        m = int(SIZES[sizes][k % len(SIZES[sizes])])
+        hi = ids if k % 2 else max(16 * m, ids >> 6)
+        lo = int(rng.integers(0, ids - hi + 1)) if hi < ids else 0
+        a = random_lists(rng, m, lo, lo + min(hi, ids))
+        A.append(a)
+        F.append(sub_lists(rng, *a, p=0.3 * float(rng.random())))
+    a, f = ListSet.from_lists(A), ListSet.from_lists(F)
+    LP = oracle.Lists(a.off, a.start, a.end, f.off, f.start, f.end)
+    steps = [1, 2, 20, 40, 60, 100, 300, 4000]
+    lines = []
+    for k in range(n):
+        walk = rng.random(2) + np.cumsum(rng.normal(0, 2.0 ** -9, (steps[k % len(steps)] + 1, 2)), axis=0)
+        lines.append(np.round(np.clip(walk, 0.01, 0.99) * 2.0 ** 30) * 2.0 ** -30)
+    xy, voff = np.concatenate(lines), np.concatenate([[0], np.cumsum([len(x) for x in lines])]).astype(np.uint64)
+    C = april.april_build_cells(g, xy, voff, april.STRICT)
+    off, cells = C.export()
+    p, l = (rng.integers(0, n, PAIRS).astype(np.uint32) for _ in range(2))
+    p.sort()
+    want = oracle.filter_linestrings(LP, oracle.Cells(off, cells), p, l)
+    assert set(np.unique(want)) == {0, 1, 2}
+    h = april.april_lists_from_arrays(g, LP.offA, LP.sA, LP.eA, LP.offF, LP.sF, LP.eF)
+    got, counts = run(april.april_filter_linestrings, april.april_lists_to_device(h),
+                      april.april_cells_to_device(C), p, l)
+    assert np.array_equal(got, want)
+    assert np.array_equal(counts, np.bincount(want, minlength=3))
