@@ -73,6 +73,9 @@ constexpr uint32_t kNone = 0xffffffffu;    // no resident object / no upper key 
 // the open ones are kept as bytes).
 constexpr uint32_t kScreenGrab = 256;
 
+// Turns of a wave, about, in a list of open pairs; most pairs a turn.
+constexpr uint32_t kListGrabs = 4, kListGrab = 16;
+
 struct BatchArgs {
     FilterArgs f;
     unsigned int *xhead;         // pairs taken from XCD k's range: xhead[k * kCtrStride]
@@ -93,6 +96,7 @@ struct BatchArgs {
     unsigned int *qfill;         // big pairs binned into XCD k's queue: qfill[k * kCtrStride]
     unsigned int *qhead;         // queue entries taken by workgroups: qhead[k * kCtrStride]
     uint32_t *queue;             // XCD k's queue: queue[k * qcap ...]
+    OpenLists open;              // screened: the open pairs (pairs null: found by a scan)
     unsigned long long *times;   // APRIL_WAVE_TIMES: call start; first, last end of the wave
                                  // kernel; first, last end of the workgroup kernel (or null)
 };
@@ -114,7 +118,7 @@ struct BatchArgs {
 // The binning pass appends the workgroup bin's pairs to one queue per XCD
 // range (the range holding the pair) and marks their verdict bytes; a pair
 // that finds its queue full is marked for the wave bin instead.
-constexpr uint32_t kTilesCtr = kMaxCtrs / 2;   // qhead counters from here on: sums of `tiles` over the queues
+// (qhead counters from kTilesCtr on: sums of `tiles` over the queues)
 constexpr uint8_t kQueued = 0xFE;     // verdict byte of a pair in a workgroup queue
 constexpr uint8_t kOverflow = kPending;   // of a workgroup-bin pair left to the wave bin (screened: of every pair left)
 
@@ -467,6 +471,16 @@ struct PairLists {
     const uint32_t *yas, *yae, *yfs, *yfe;
     uint32_t nxa, nxf, nya, nyf;
 };
+
+// Alg. 2 by one lane.
+__device__ __forceinline__ uint32_t seq_pair(const PairLists &m) {
+    uint32_t x, y;
+    if (!seq_join(m.xas, m.xae, m.nxa, m.yas, m.yae, m.nya, &x, &y)) return APRIL_TN;
+    return seq_join(m.xas, m.xae, m.nxa, m.yfs, m.yfe, m.nyf, &x, &y) ||
+                   seq_join(m.xfs, m.xfe, m.nxf, m.yas, m.yae, m.nya, &x, &y)
+               ? APRIL_TH
+               : APRIL_INDECISIVE;
+}
 
 // Probe join, for a resident object X of few intervals spread over a wide
 // key range (its Hilbert key range crosses a large part of the curve) and a
@@ -1072,11 +1086,14 @@ void k_batched(BatchArgs b) {
     __shared__ uint32_t lds_words[kWavesPerBlock * 4 * TILE];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t w = uniform(threadIdx.x >> 6);
+    if (MODE != kMixedOrders && b.open.pairs) {
+        // the open pairs have been joined, unless a list was full
+        const uint32_t fill = (lane & (kTilesCtr - 1)) < b.xcds ? b.open.fill[lane * kCtrStride] : 0u;
+        if (!__any(fill > (lane >= kTilesCtr ? b.open.long_cap : b.open.cap))) return;
+    }
     unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
     const uint32_t xcds = b.xcds;
     const uint32_t my_xcd = blockIdx.x % xcds;
-
-
     Resident res;
     res.ae = lds_words + w * 4 * TILE;   // layout: A.end, A.start, F.end, F.start
     res.as = res.ae + TILE;
@@ -1199,16 +1216,7 @@ void k_batched(BatchArgs b) {
             // (X and Y stand for R and S in either order; the verdict is
             // symmetric)
             if (seq) {
-                uint32_t x, y;
-                uint32_t v;
-                if (!seq_join(m.xas, m.xae, m.nxa, m.yas, m.yae, m.nya, &x, &y))
-                    v = APRIL_TN;
-                else if (seq_join(m.xas, m.xae, m.nxa, m.yfs, m.yfe, m.nyf, &x, &y) ||
-                         seq_join(m.xfs, m.xfe, m.nxf, m.yas, m.yae, m.nya, &x, &y))
-                    v = APRIL_TH;
-                else
-                    v = APRIL_INDECISIVE;
-                vv = v;
+                vv = seq_pair(m);
             }
             if (mine) {
                 pb->f.verdict[p] = uint8_t(vv);
@@ -1232,6 +1240,123 @@ void k_batched(BatchArgs b) {
     if (b.times && lane == 0) wave_ended(b.times + 1);
 }
 
+
+// The pairs that screening left open, from its lists, the long ones first.
+// XCD k's workgroups take the k-th part of all the lists laid end to end (most
+// of it their own list, whatever the lists' lengths), dealt out to them in turn,
+// and a workgroup's waves take its turns from a counter in LDS.  Counters in
+// memory bound this kernel while it used them: with one a list, a grab waits
+// for those of the XCD's 1,024 waves before it (at scale 420 us, as many as the
+// joins take now; 100k polygons x 100k lines 300 against 110 us).  It is a
+// kernel of its own as the one above has no registers to spare for it.
+template <int TILE, int C, int MODE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8), amdgpu_num_sgpr(80)))
+void k_open(BatchArgs b) {
+    __shared__ uint32_t lds_words[kWavesPerBlock * 4 * TILE];
+    __shared__ uint32_t piece_words[kWavesPerBlock][8];
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t w = uniform(threadIdx.x >> 6);
+    unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
+    // (a grid of fewer workgroups than XCDs: a part for each)
+    const uint32_t xcds = b.xcds, parts = min(xcds, gridDim.x), part = blockIdx.x % parts;
+    const uint32_t blocks = (gridDim.x - part + parts - 1) / parts;   // of this part, at least one
+    Resident res;
+    res.ae = lds_words + w * 4 * TILE;   // layout: A.end, A.start, F.end, F.start
+    res.as = res.ae + TILE;
+    res.fe = res.as + TILE;
+    res.fs = res.fe + TILE;
+    res.na = res.nf = 0;
+    uint32_t cached = kNone, pcached = kNone;
+    __shared__ uint32_t turns[2];
+    if (threadIdx.x < 2) turns[threadIdx.x] = 0;
+    __syncthreads();
+    // the long pairs' lists, then the others
+    for (uint32_t half = 0; half < 2; half++) {
+        uint32_t first, hi, grab, before;   // this part of all lists end to end; lane k: entries before XCD k's list
+        {
+            typedef const __attribute__((address_space(4))) BatchArgs *KArgs;
+            KArgs pb = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(pb));
+            const uint32_t n = lane < xcds ? min(pb->open.fill[((half ? 0u : kTilesCtr) + lane) * kCtrStride],
+                                                 half ? pb->open.cap : pb->open.long_cap)
+                                           : 0u;
+            before = n;
+            for (uint32_t d = 1; d < kTilesCtr; d <<= 1) {
+                const uint32_t o = __shfl_up(before, d);
+                before += lane >= d ? o : 0u;
+            }
+            const uint64_t all = uniform(__shfl(before, kTilesCtr - 1));
+            before -= n;
+            first = uint32_t(all * part / parts);
+            hi = uint32_t(all * (part + 1) / parts);
+            grab = min((hi - first) / (kListGrabs * kWavesPerBlock * blocks) + 1, kListGrab);
+        }
+        for (;;) {
+            typedef const __attribute__((address_space(4))) BatchArgs *KArgs;
+            KArgs pb = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(pb));
+            const __attribute__((address_space(4))) FilterArgs &a = pb->f;
+            uint32_t turn = 0;
+            if (lane == 0) turn = atomicAdd(&turns[half], 1u);
+            // (grab and blocks are at least 1: every wave gets beyond `hi`, by less than 2^16)
+            const uint32_t got = first + (uniform(__shfl(turn, 0)) * blocks + blockIdx.x / parts) * grab;
+            if (got >= hi) break;
+            uint32_t vv = 0, key = kNone, p = 0;
+            PairLists m{};
+            bool seq = false;
+            const bool in = lane < grab && got + lane < hi;
+            uint32_t seg = 0, at = got + lane;   // entry `at`: of which list, and where
+            for (uint32_t k = 1; k < xcds; k++) seg = at >= lane_val(before, k) ? k : seg;
+            at -= __shfl(before, seg);
+            if (in) {
+                const uint32_t cap = pb->open.cap;
+                p = gload(pb->open.pairs + uint64_t(seg) * (cap + pb->open.long_cap) + (half ? 0u : cap), at);
+                const uint32_t r = gload32(a.r, p), s = gload32(a.s, p);
+                const uint64_t ar0 = gload64(a.Ar.off, r), fr0 = gload64(a.Fr.off, r);
+                const uint64_t as0 = gload64(a.As.off, s), fs0 = gload64(a.Fs.off, s);
+                const uint32_t nar = uint32_t(gload64(a.Ar.off, r + 1) - ar0);
+                const uint32_t nfr = uint32_t(gload64(a.Fr.off, r + 1) - fr0);
+                const uint32_t nas = uint32_t(gload64(a.As.off, s + 1) - as0);
+                const uint32_t nfs = uint32_t(gload64(a.Fs.off, s + 1) - fs0);
+                const uint32_t mr = max(nar, nfr), ms = max(nas, nfs);
+                // (the resident side: as above)
+                const bool xs = MODE == kWithinJoin     ? true
+                                : MODE == kLinestrings ? false
+                                                       : !(mr < TILE) && (ms < TILE || ms < mr);
+                seq = MODE == kAlg2 && max(mr, ms) <= pb->thread_max;
+                m = pair_lists(a, xs, ar0, nar, fr0, nfr, as0, nas, fs0, nfs);
+                key = (xs ? s : r) | (xs ? kSideS : 0u);
+            }
+            uint64_t todo = __ballot(in && !seq);
+            const uint32_t search_min = pb->search_min;
+            while (todo) {
+                const uint32_t k = uint32_t(__builtin_ctzll(todo));
+                todo &= todo - 1;
+                const PairLists L = lane_pair(m, k);
+                const uint32_t v = wave_pair<TILE, C, MODE>(res, cached, lane_val(key, k), L, search_min, lane, 0,
+                                                            pcached, piece_words[w]);
+                vv = lane == k ? v : vv;
+            }
+            if (seq) vv = seq_pair(m);
+            if (in) {
+                pb->f.verdict[p] = uint8_t(vv);
+                c_tn += vv == APRIL_TN;
+                c_th += vv == APRIL_TH;
+                c_ind += vv == APRIL_INDECISIVE;
+            }
+        }
+    }
+    if (b.f.counts) {
+        for (int off = 32; off > 0; off >>= 1) {
+            c_tn += __shfl_down(c_tn, off);
+            c_th += __shfl_down(c_th, off);
+            c_ind += __shfl_down(c_ind, off);
+        }
+        const unsigned long long v[3] = {c_tn, c_th, c_ind};
+        if (lane == 0) add_totals(b.xhead, blockIdx.x * kWavesPerBlock + w, v, 3);
+    }
+    if (b.times && lane == 0) wave_ended(b.times + 1);
+}
 
 template <int TILE, int C, int MODE = kAlg2>
 int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
@@ -1276,8 +1401,18 @@ int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
         k_wg<TILE, C><<<dim3(uint32_t(uint64_t(cus) * wg_per_cu)), dim3(kBlock), 0, stream>>>(bb);
         APRIL_HIP_TRY(hipGetLastError());
     }
-    k_batched<TILE, C, MODE><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(bb);
-    APRIL_HIP_TRY(hipGetLastError());
+    bool scan = true;   // (lists that hold a whole range are never full)
+    if constexpr (MODE != kMixedOrders) {
+        if (b.open.pairs) {
+            k_open<TILE, C, MODE><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(bb);
+            APRIL_HIP_TRY(hipGetLastError());
+            scan = b.f.n_pairs / b.xcds + 1 > b.open.long_cap;
+        }
+    }
+    if (scan) {
+        k_batched<TILE, C, MODE><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(bb);
+        APRIL_HIP_TRY(hipGetLastError());
+    }
     if (b.f.counts && b.fixed) return launch_count_verdicts(b.f.verdict, b.f.n_pairs, b.f.counts, stream);
     if (b.f.counts) {
         k_sum_totals<<<1, 64, 0, stream>>>(b.xhead, b.f.counts, 3);
@@ -1303,6 +1438,7 @@ int launch_t(const BatchArgs &b, uint32_t chunk, int cus, uint32_t waves, hipStr
 // kMaxCtrs slots, 128 bytes apart), then the queues: kBigQueueCap pair
 // indices shared evenly by the XCD ranges.
 constexpr uint64_t kQueueCtrBytes = 2ull * kMaxCtrs * kCtrStride * sizeof(unsigned int);
+static_assert(kTilesCtr == 32, "k_open: one counter per lane");
 static_assert(kCtrBytes + kQueueCtrBytes + 4ull * kBigQueueCap <= kStaticWorkspaceBytes,
               "the static scratch holds a batched workspace");
 
@@ -1369,6 +1505,7 @@ static void set_wg_bin(BatchArgs &b, uint32_t wg_min, void *workspace) {
     b.wg_min = wg_min;
     b.times = nullptr;
     b.screened = b.fixed = 0;
+    b.open = {};
     b.qfill = b.qhead = nullptr;
     b.queue = nullptr;
     b.qcap = 0;
@@ -1378,6 +1515,21 @@ static void set_wg_bin(BatchArgs &b, uint32_t wg_min, void *workspace) {
     b.qhead = qctr + kMaxCtrs * kCtrStride;
     b.queue = reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + kCtrBytes + kQueueCtrBytes);
     b.qcap = uint32_t(kBigQueueCap / b.xcds);
+}
+
+// The lists of open pairs for screening, in the place of the workgroup bin's
+// queues (null counters and lists when that is on, and for small calls).
+static int open_lists(BatchArgs &b, void *workspace, hipStream_t stream) {
+    if (b.fixed || b.wg_min != kNone || b.f.n_pairs >= (1ull << 32)) return APRIL_OK;
+    b.open.fill = b.qfill;
+    b.open.pairs = b.queue;
+    b.open.long_cap = b.qcap / 4;
+    b.open.cap = b.qcap - b.open.long_cap;
+    if (!b.times) {   // (else zeroed already)
+        k_zero_queue_ctrs<<<1, 2 * kMaxCtrs, 0, stream>>>(b.qfill);
+        APRIL_HIP_TRY(hipGetLastError());
+    }
+    return APRIL_OK;
 }
 
 // Small calls deal their pairs out beforehand and need no scratch, unless they
@@ -1428,7 +1580,8 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
     if (R && S && can_screen(R, S, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        if (int rc = launch_screen(R, S, f, cus, workspace, stream)) return rc;
+        if (int rc = open_lists(b, workspace, stream)) return rc;
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream, false, b.open)) return rc;
         b.screened = 1;
     }
     switch (tile) {
@@ -1481,7 +1634,8 @@ int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStre
     if (can_screen(R, S, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        if (int rc = launch_screen(R, S, f, cus, workspace, stream, true)) return rc;
+        if (int rc = open_lists(b, workspace, stream)) return rc;
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream, true, b.open)) return rc;
         b.screened = 1;
     }
     return launch_tc<256, 2, kWithinJoin>(b, cus, 0, stream);
@@ -1507,7 +1661,8 @@ int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hi
     if (can_screen_lines(P, L, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        if (int rc = launch_screen_lines(P, L, f, cus, workspace, stream)) return rc;
+        if (int rc = open_lists(b, workspace, stream)) return rc;
+        if (int rc = launch_screen_lines(P, L, f, cus, workspace, stream, b.open)) return rc;
         b.screened = 1;
     }
     return launch_tc<256, 2, kLinestrings>(b, cus, 0, stream);

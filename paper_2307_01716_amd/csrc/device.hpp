@@ -149,13 +149,24 @@ bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs
 // where the join kernels have to look), and the decided pairs' counts into the
 // slots at `counters` (already cleared) when f.counts is set.  Of f only the
 // pairs, the verdicts and R's raw A-lists are read.
+// The pairs that screening leaves open, listed for the join kernel: one list
+// per XCD range for pairs of which neither object has a coarse table, one for
+// the others ("long").  A listed pair's verdict byte is kListed; a pair that
+// finds its list full keeps kPending.
+struct OpenLists {
+    unsigned int *fill;      // pairs put into XCD k's lists: fill[k * kCtrStride]; of long ones at kTilesCtr + k
+    uint32_t *pairs;         // XCD k's: pairs[k * (cap + long_cap) ...], the long ones behind the others (null: no lists)
+    uint32_t cap, long_cap;
+};
+constexpr uint8_t kListed = 0xFE;
+constexpr uint32_t kTilesCtr = kMaxCtrs / 2;   // a counter region's second half
 // within: for within joins.
 int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
-                  hipStream_t stream, bool within = false);
+                  hipStream_t stream, bool within = false, const OpenLists &open = {});
 // The same for polygons (R of f) against linestrings.
 bool can_screen_lines(const april_lists_t *P, const april_cells_t *L, uint64_t n_pairs);
 int launch_screen_lines(const april_lists_t *P, const april_cells_t *L, const FilterArgs &f, int cus, void *counters,
-                        hipStream_t stream);
+                        hipStream_t stream, const OpenLists &open = {});
 // Kernel arguments of a filter call on device lists R and S (raw codec).
 FilterArgs make_args(const april_lists_t *R, const april_lists_t *S, const uint32_t *d_r, const uint32_t *d_s,
                      uint64_t n_pairs, uint8_t *d_verdict, unsigned long long *counts);

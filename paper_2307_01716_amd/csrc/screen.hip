@@ -338,6 +338,7 @@ struct ScreenArgs {
     uint32_t xcds;
     uint32_t take;                   // pairs a wave takes at a time (at most 64)
     uint32_t raw;                    // R's A-lists can be read (not compressed)
+    OpenLists open;
 };
 
 // LDS place of a table's entry i: a word is left out after every 64.  The
@@ -550,6 +551,20 @@ __global__ __launch_bounds__(kBlock, MODE == kLines ? 4 : 8) void k_screen(Scree
             const uint32_t v = __any(f) ? APRIL_TH : __any(h) ? kPending : APRIL_TN;
             vv = lane == k ? v : vv;
         }
+        if (a.open.pairs) {
+            const bool open = mine && vv == kPending, big = slot != kNoSlot || s_tab != kNoSlot;
+            uint32_t *const list = a.open.pairs + uint64_t(xcd) * (a.open.cap + a.open.long_cap);
+            const uint64_t few = __ballot(open && !big), lng = __ballot(open && big);
+            uint32_t at = 0;   // lane 0: of the others, lane 1: of the long ones
+            if (lane < 2 && (lane ? lng : few))
+                at = atomicAdd(&a.open.fill[(lane * kTilesCtr + xcd) * kCtrStride], uint32_t(__popcll(lane ? lng : few)));
+            const uint32_t at_few = __shfl(at, 0), at_lng = __shfl(at, 1);
+            at = (big ? at_lng : at_few) + uint32_t(__popcll((big ? lng : few) & ((1ull << lane) - 1)));
+            if (open && at < (big ? a.open.long_cap : a.open.cap)) {
+                list[(big ? a.open.cap : 0u) + at] = uint32_t(p);
+                vv = kListed;
+            }
+        }
         if (mine) {
             a.f.verdict[p] = uint8_t(vv);
             c_tn += vv == APRIL_TN;
@@ -640,9 +655,10 @@ static int screen(ScreenArgs &a, const april_lists_t *R, int cus, void *counters
 }
 
 int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterArgs &f, int cus, void *counters,
-                  hipStream_t stream, bool within) {
+                  hipStream_t stream, bool within, const OpenLists &open) {
     ScreenArgs a{};
     a.f = f;
+    a.open = open;
     a.sum = S->d.sum;
     a.s_slot = S->codec == APRIL_CODEC_RAW ? nullptr : S->d.slot;
     a.s_table = S->d.slot;
@@ -651,9 +667,10 @@ int launch_screen(const april_lists_t *R, const april_lists_t *S, const FilterAr
 }
 
 int launch_screen_lines(const april_lists_t *P, const april_cells_t *L, const FilterArgs &f, int cus, void *counters,
-                        hipStream_t stream) {
+                        hipStream_t stream, const OpenLists &open) {
     ScreenArgs a{};
     a.f = f;
+    a.open = open;
     a.sum = L->sum;
     return screen<kLines>(a, P, cus, counters, stream);
 }

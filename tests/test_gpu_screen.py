@@ -210,3 +210,32 @@ def test_linestrings(sizes):
                       april.april_cells_to_device(C), p, l)
     assert np.array_equal(got, want)
     assert np.array_equal(counts, np.bincount(want, minlength=3))
+
+
+# ----------------------------------------------------- lists of open pairs
+
+@pytest.mark.parametrize("sizes, n", [([3, 40], 70_000), ([3], 900_000), ([600], 300_000), ([3, 600], 1_000_000)])
+def test_open_lists(sizes, n):
+    """Every pair is left open (F-lists empty, A-lists that meet): lists that
+    hold them all, and lists of either kind that overflow; grids of fewer
+    workgroups than there are lists, and of no multiple of them."""
+    rng = np.random.default_rng(n)
+    print(f"[screen] open {sizes} {n}", flush=True)
+    A = [random_lists(rng, sizes[k % len(sizes)], 100, 100 + 16 * sizes[k % len(sizes)]) for k in range(40)]
+    a = ListSet.from_lists([(np.append(np.uint32(50), s), np.append(np.uint32(60), e)) for s, e in A])
+    off = np.zeros(41, np.uint64)
+    none = np.zeros(0, np.uint32)
+    L = oracle.Lists(a.off, a.start, a.end, off, none, none)
+    D = upload(L, april.CODEC_RAW)
+    r, s = (rng.integers(0, 40, n).astype(np.uint32) for _ in range(2))
+    rt, st = (torch.from_numpy(k.view(np.int32)).cuda() for k in (r, s))
+    calls = [lambda v, c, w=w: april.april_filter_pairs(D, D, rt, st, v, c, schedule=april.SCHED_BATCHED, waves=w)
+             for w in (0, 4, 12, 52)]
+    calls.append(lambda v, c: april.april_filter_within(D, D, rt, st, v, c))
+    for k, call in enumerate(calls):
+        v = torch.full((n,), 77, dtype=torch.uint8, device="cuda")
+        c = torch.full((3,), -1, dtype=torch.int64, device="cuda")
+        call(v, c)
+        torch.cuda.synchronize()
+        assert int((v != april.INDECISIVE).sum()) == 0, k
+        assert c.tolist() == [0, 0, n], k
