@@ -122,6 +122,11 @@ struct BatchArgs {
 constexpr uint8_t kQueued = 0xFE;     // verdict byte of a pair in a workgroup queue
 constexpr uint8_t kOverflow = kPending;   // of a workgroup-bin pair left to the wave bin (screened: of every pair left)
 
+// An XCD's queue of qcap words: its last words hold the answers of the first
+// pairs' parts (few pairs are cut into parts), the others queued pairs.
+__device__ __forceinline__ uint32_t wg_words(uint32_t qcap) { return qcap / 8; }
+__device__ __forceinline__ uint32_t wg_slots(uint32_t qcap) { return qcap - wg_words(qcap); }
+
 __device__ __forceinline__ bool wg_bin(uint32_t mr, uint32_t ms, uint32_t tile, uint32_t wg_min) {
     return mr >= tile && ms >= tile && min(mr, ms) >= wg_min;
 }
@@ -171,10 +176,10 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
             got = __shfl(got, int(__builtin_ctzll(mine)));
             if ((mine >> lane) & 1) {
                 const uint32_t slot = got + uint32_t(__popcll(mine & ((1ull << lane) - 1)));
-                if (slot < b.qcap) {
+                if (slot < wg_slots(b.qcap)) {
                     b.queue[uint64_t(k0) * b.qcap + slot] = uint32_t(p);
                     // its parts' answers, from the queue's end
-                    if (slot < b.qcap / 2) b.queue[uint64_t(k0 + 1) * b.qcap - 1 - slot] = 0;
+                    if (slot < wg_words(b.qcap)) b.queue[uint64_t(k0 + 1) * b.qcap - 1 - slot] = 0;
                     a.verdict[p] = kQueued;
                 } else {
                     a.verdict[p] = kOverflow;
@@ -725,7 +730,7 @@ struct Parts {
 };
 
 __device__ __forceinline__ Parts wg_parts(uint32_t nq, uint32_t tiles, uint32_t qcap, uint32_t blocks) {
-    if (nq == 0 || nq > qcap / 2) return Parts{1, 1};
+    if (nq == 0 || nq > wg_words(qcap)) return Parts{1, 1};
     const uint32_t each = max(kPartTiles, tiles / (kPartsPerBlock * blocks));
     return Parts{max(1u, min(kMaxParts, tiles / nq / each)), each};
 }
@@ -989,7 +994,7 @@ __global__ __launch_bounds__(kBlock) void k_wg(BatchArgs b) {
             // (every wave reads the same count: the binning pass has ended;
             // the grab is one thread's, passed on through LDS, so that all
             // four waves take the same branches and reach every barrier)
-            const uint32_t nq = uniform(min(pb->qfill[seg * kCtrStride], pb->qcap));
+            const uint32_t nq = uniform(min(pb->qfill[seg * kCtrStride], wg_slots(pb->qcap)));
             const Parts cut =
                 wg_parts(nq, uniform(pb->qhead[(kTilesCtr + seg) * kCtrStride]), pb->qcap, gridDim.x / xcds);
             const uint32_t parts = cut.most;

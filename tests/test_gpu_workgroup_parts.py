@@ -58,3 +58,24 @@ def test_planted_overlaps(n):
             assert np.array_equal(v.cpu().numpy(), want)
             assert np.array_equal(c.cpu().numpy(), np.bincount(want, minlength=3))
             assert len(np.unique(want)) >= 2
+
+
+@pytest.mark.parametrize("n", [120_000, 140_000, 600_000, 1_000_000, 1_200_000])
+def test_full_queues(n):
+    """Every pair is queued: queues without and with room for the parts'
+    answers, and ones that overflow."""
+    rng = np.random.default_rng(n)
+    print(f"[parts] {n} pairs", flush=True)
+    none = (np.zeros(0, np.uint32), np.zeros(0, np.uint32))
+    A = []
+    for _ in range(20):
+        s, e = random_lists(rng, 130, 100, 2000)
+        A.append((np.append(np.uint32(50), s), np.append(np.uint32(60), e)))
+    _, D = lists(A, [none] * 20)
+    r, s = (torch.from_numpy(rng.integers(0, 20, n).astype(np.int32)).cuda() for _ in range(2))
+    v = torch.full((n,), 77, dtype=torch.uint8, device="cuda")
+    c = torch.full((3,), -1, dtype=torch.int64, device="cuda")
+    april.april_filter_pairs(D, D, r, s, v, c, schedule=april.SCHED_BATCHED, tile=128, wg_min=1)
+    torch.cuda.synchronize()
+    assert int((v != april.INDECISIVE).sum()) == 0
+    assert c.tolist() == [0, 0, n]
