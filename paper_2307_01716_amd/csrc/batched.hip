@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
     for (uint64_t base = uint64_t(blockIdx.x) * blockDim.x + (threadIdx.x & ~63u); base < a.n_pairs;
          base += stride) {
         const uint64_t p = base + lane;
-        bool big = false;
+        bool big = false, open = false;   // (open: for the list of the pairs that screening left)
         uint32_t tiles = 0;   // workgroup tiles that the shorter object's A-list fills
         if (p < a.n_pairs && (!b.screened || a.verdict[p] == kPending)) {
             const uint32_t r = a.r[p], s = a.s[p];
@@ -157,6 +157,7 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
                 const uint32_t mr = max(nar, uint32_t(a.Fr.off[r + 1] - a.Fr.off[r]));
                 const uint32_t ms = max(nas, uint32_t(a.Fs.off[s + 1] - a.Fs.off[s]));
                 big = wg_bin(mr, ms, tile, b.wg_min);
+                open = !big;
                 tiles = (ms < mr ? nas : nar) / (kWavesPerBlock * tile);
             }
         }
@@ -183,7 +184,23 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
                     a.verdict[p] = kQueued;
                 } else {
                     a.verdict[p] = kOverflow;
+                    open = true;
                 }
+            }
+        }
+        todo = b.open.pairs ? __ballot(open) : 0;
+        while (todo) {
+            const int l0 = int(__builtin_ctzll(todo));
+            const uint32_t k0 = uniform(__shfl(k, l0));
+            const uint64_t mine = __ballot(open && k == k0) & todo;
+            todo &= ~mine;
+            unsigned int got = 0;
+            if (lane == uint32_t(l0))
+                got = atomicAdd(&b.open.fill[(kTilesCtr + k0) * kCtrStride], uint32_t(__popcll(mine)));
+            got = __shfl(got, l0) + uint32_t(__popcll(mine & ((1ull << lane) - 1)));
+            if (((mine >> lane) & 1) && got < b.open.long_cap) {
+                b.open.pairs[uint64_t(k0) * b.open.long_cap + got] = uint32_t(p);
+                a.verdict[p] = kListed;
             }
         }
     }
@@ -1523,9 +1540,18 @@ static void set_wg_bin(BatchArgs &b, uint32_t wg_min, void *workspace) {
 }
 
 // The lists of open pairs for screening, in the place of the workgroup bin's
-// queues (null counters and lists when that is on, and for small calls).
-static int open_lists(BatchArgs &b, void *workspace, hipStream_t stream) {
-    if (b.fixed || b.wg_min != kNone || b.f.n_pairs >= (1ull << 32)) return APRIL_OK;
+// queues; with the workgroup bin, one list per range behind the queues, half of
+// the space each, which the binning pass fills with the pairs that it does not
+// queue (its counters are the upper halves of the ranges').  None for small calls.
+static int open_lists(BatchArgs &b, hipStream_t stream, OpenLists *of_screen) {
+    if (b.fixed || b.f.n_pairs >= (1ull << 32)) return APRIL_OK;
+    if (b.wg_min != kNone) {
+        b.qcap /= 2;
+        b.open.fill = b.xhead;
+        b.open.pairs = b.queue + uint64_t(b.xcds) * b.qcap;
+        b.open.long_cap = b.qcap;
+        return APRIL_OK;
+    }
     b.open.fill = b.qfill;
     b.open.pairs = b.queue;
     b.open.long_cap = b.qcap / 4;
@@ -1534,6 +1560,7 @@ static int open_lists(BatchArgs &b, void *workspace, hipStream_t stream) {
         k_zero_queue_ctrs<<<1, 2 * kMaxCtrs, 0, stream>>>(b.qfill);
         APRIL_HIP_TRY(hipGetLastError());
     }
+    *of_screen = b.open;
     return APRIL_OK;
 }
 
@@ -1585,8 +1612,9 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
     if (R && S && can_screen(R, S, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        if (int rc = open_lists(b, workspace, stream)) return rc;
-        if (int rc = launch_screen(R, S, f, cus, workspace, stream, false, b.open)) return rc;
+        OpenLists open{};
+        if (int rc = open_lists(b, stream, &open)) return rc;
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream, false, open)) return rc;
         b.screened = 1;
     }
     switch (tile) {
@@ -1639,8 +1667,9 @@ int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStre
     if (can_screen(R, S, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        if (int rc = open_lists(b, workspace, stream)) return rc;
-        if (int rc = launch_screen(R, S, f, cus, workspace, stream, true, b.open)) return rc;
+        OpenLists open{};
+        if (int rc = open_lists(b, stream, &open)) return rc;
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream, true, open)) return rc;
         b.screened = 1;
     }
     return launch_tc<256, 2, kWithinJoin>(b, cus, 0, stream);
@@ -1666,8 +1695,9 @@ int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hi
     if (can_screen_lines(P, L, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        if (int rc = open_lists(b, workspace, stream)) return rc;
-        if (int rc = launch_screen_lines(P, L, f, cus, workspace, stream, b.open)) return rc;
+        OpenLists open{};
+        if (int rc = open_lists(b, stream, &open)) return rc;
+        if (int rc = launch_screen_lines(P, L, f, cus, workspace, stream, open)) return rc;
         b.screened = 1;
     }
     return launch_tc<256, 2, kLinestrings>(b, cus, 0, stream);

@@ -214,7 +214,8 @@ def test_linestrings(sizes):
 
 # ----------------------------------------------------- lists of open pairs
 
-@pytest.mark.parametrize("sizes, n", [([3, 40], 70_000), ([3], 900_000), ([600], 300_000), ([3, 600], 1_000_000)])
+@pytest.mark.parametrize("sizes, n", [([3, 40], 70_000), ([3], 900_000), ([600], 300_000), ([600], 600_000),
+                                      ([3, 600], 1_000_000)])
 def test_open_lists(sizes, n):
     """Every pair is left open (F-lists empty, A-lists that meet): lists that
     hold them all, and lists of either kind that overflow; grids of fewer
@@ -231,6 +232,8 @@ def test_open_lists(sizes, n):
     rt, st = (torch.from_numpy(k.view(np.int32)).cuda() for k in (r, s))
     calls = [lambda v, c, w=w: april.april_filter_pairs(D, D, rt, st, v, c, schedule=april.SCHED_BATCHED, waves=w)
              for w in (0, 4, 12, 52)]
+    calls += [lambda v, c, m=m: april.april_filter_pairs(D, D, rt, st, v, c, schedule=april.SCHED_BATCHED, wg_min=m)
+              for m in (1, 0xFFFFFFFF)]   # every pair that can be in the workgroup bin, none
     calls.append(lambda v, c: april.april_filter_within(D, D, rt, st, v, c))
     for k, call in enumerate(calls):
         v = torch.full((n,), 77, dtype=torch.uint8, device="cuda")
