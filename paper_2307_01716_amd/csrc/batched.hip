@@ -139,6 +139,44 @@ __device__ __forceinline__ uint32_t range_of(uint64_t p, uint64_t n, uint32_t xc
     return k;
 }
 
+// What the binning passes need to know of a pair: whether it belongs into the
+// workgroup bin, and the workgroup tiles that its shorter object's A-list fills.
+struct Binned {
+    bool big;
+    uint32_t tiles;
+};
+
+__device__ __forceinline__ Binned bin_pair(const BatchArgs &b, uint64_t p, uint32_t tile) {
+    const FilterArgs &a = b.f;
+    const uint32_t r = a.r[p], s = a.s[p];
+    if (!((r < a.n_r) & (s < a.n_s))) return Binned{false, 0};
+    const uint32_t nar = uint32_t(a.Ar.off[r + 1] - a.Ar.off[r]), nas = uint32_t(a.As.off[s + 1] - a.As.off[s]);
+    const uint32_t mr = max(nar, uint32_t(a.Fr.off[r + 1] - a.Fr.off[r]));
+    const uint32_t ms = max(nas, uint32_t(a.Fs.off[s + 1] - a.Fs.off[s]));
+    return Binned{wg_bin(mr, ms, tile, b.wg_min), (ms < mr ? nas : nar) / (kWavesPerBlock * tile)};
+}
+
+// The lanes of `mine` put their pairs into range k0's queue; false for one that
+// finds it full.
+__device__ __forceinline__ bool enqueue(const BatchArgs &b, uint32_t k0, uint64_t mine, uint64_t p, uint32_t tiles,
+                                        uint32_t lane) {
+    const int l0 = int(__builtin_ctzll(mine));
+    const bool me = (mine >> lane) & 1;
+    uint32_t sum = me ? tiles : 0u;
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    unsigned int got = 0;
+    if (lane == uint32_t(l0)) {
+        atomicAdd(&b.qhead[(kTilesCtr + k0) * kCtrStride], sum);
+        got = atomicAdd(&b.qfill[k0 * kCtrStride], uint32_t(__popcll(mine)));
+    }
+    const uint32_t slot = __shfl(got, l0) + uint32_t(__popcll(mine & ((1ull << lane) - 1)));
+    if (!me || slot >= wg_slots(b.qcap)) return false;
+    b.queue[uint64_t(k0) * b.qcap + slot] = uint32_t(p);
+    // its parts' answers, from the queue's end
+    if (slot < wg_words(b.qcap)) b.queue[uint64_t(k0 + 1) * b.qcap - 1 - slot] = 0;
+    return true;
+}
+
 // The binning pass: a thread per pair (grid-stride), one atomic per run of
 // same-range queued lanes in a wave.
 __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
@@ -148,64 +186,36 @@ __global__ __launch_bounds__(256) void k_bin(BatchArgs b, uint32_t tile) {
     for (uint64_t base = uint64_t(blockIdx.x) * blockDim.x + (threadIdx.x & ~63u); base < a.n_pairs;
          base += stride) {
         const uint64_t p = base + lane;
-        bool big = false, open = false;   // (open: for the list of the pairs that screening left)
-        uint32_t tiles = 0;   // workgroup tiles that the shorter object's A-list fills
-        if (p < a.n_pairs && (!b.screened || a.verdict[p] == kPending)) {
-            const uint32_t r = a.r[p], s = a.s[p];
-            if ((r < a.n_r) & (s < a.n_s)) {
-                const uint32_t nar = uint32_t(a.Ar.off[r + 1] - a.Ar.off[r]), nas = uint32_t(a.As.off[s + 1] - a.As.off[s]);
-                const uint32_t mr = max(nar, uint32_t(a.Fr.off[r + 1] - a.Fr.off[r]));
-                const uint32_t ms = max(nas, uint32_t(a.Fs.off[s + 1] - a.Fs.off[s]));
-                big = wg_bin(mr, ms, tile, b.wg_min);
-                open = !big;
-                tiles = (ms < mr ? nas : nar) / (kWavesPerBlock * tile);
-            }
-        }
+        Binned q{false, 0};
+        if (p < a.n_pairs && (!b.screened || a.verdict[p] == kPending)) q = bin_pair(b, p, tile);
         const uint32_t k = p < a.n_pairs ? range_of(p, a.n_pairs, b.xcds) : 0u;
-        uint64_t todo = __ballot(big);
+        uint64_t todo = __ballot(q.big);
         while (todo) {
             // lanes of the first pending lane's range
             const uint32_t k0 = uniform(__shfl(k, int(__builtin_ctzll(todo))));
-            const uint64_t mine = __ballot(big && k == k0) & todo;
+            const uint64_t mine = __ballot(q.big && k == k0) & todo;
             todo &= ~mine;
-            uint32_t sum = (mine >> lane) & 1 ? tiles : 0u;
-            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-            if (lane == 0) atomicAdd(&b.qhead[(kTilesCtr + k0) * kCtrStride], sum);
-            unsigned int got = 0;
-            if (lane == uint32_t(__builtin_ctzll(mine)))
-                got = atomicAdd(&b.qfill[k0 * kCtrStride], uint32_t(__popcll(mine)));
-            got = __shfl(got, int(__builtin_ctzll(mine)));
-            if ((mine >> lane) & 1) {
-                const uint32_t slot = got + uint32_t(__popcll(mine & ((1ull << lane) - 1)));
-                if (slot < wg_slots(b.qcap)) {
-                    b.queue[uint64_t(k0) * b.qcap + slot] = uint32_t(p);
-                    // its parts' answers, from the queue's end
-                    if (slot < wg_words(b.qcap)) b.queue[uint64_t(k0 + 1) * b.qcap - 1 - slot] = 0;
-                    a.verdict[p] = kQueued;
-                } else {
-                    a.verdict[p] = kOverflow;
-                    open = true;
-                }
-            }
-        }
-        todo = b.open.pairs ? __ballot(open) : 0;
-        while (todo) {
-            const int l0 = int(__builtin_ctzll(todo));
-            const uint32_t k0 = uniform(__shfl(k, l0));
-            const uint64_t mine = __ballot(open && k == k0) & todo;
-            todo &= ~mine;
-            unsigned int got = 0;
-            if (lane == uint32_t(l0))
-                got = atomicAdd(&b.open.fill[(kTilesCtr + k0) * kCtrStride], uint32_t(__popcll(mine)));
-            got = __shfl(got, l0) + uint32_t(__popcll(mine & ((1ull << lane) - 1)));
-            if (((mine >> lane) & 1) && got < b.open.long_cap) {
-                b.open.pairs[uint64_t(k0) * b.open.long_cap + got] = uint32_t(p);
-                a.verdict[p] = kListed;
-            }
+            const bool in = enqueue(b, k0, mine, p, q.tiles, lane);
+            if ((mine >> lane) & 1) a.verdict[p] = in ? kQueued : kOverflow;
         }
     }
 }
 
+// The same where screening has listed the open pairs: moves those for the
+// workgroup bin from the lists of long ones to the queues.  blockIdx.y: the
+// XCD range.
+__global__ __launch_bounds__(256) void k_bin_open(BatchArgs b, uint32_t tile) {
+    const uint32_t lane = threadIdx.x & 63, k = blockIdx.y;
+    const uint32_t n = min(b.open.long_fill[k * kCtrStride], b.open.long_cap);
+    uint32_t *const list = b.open.pairs + uint64_t(k) * (b.open.cap + b.open.long_cap) + b.open.cap;
+    for (uint32_t i0 = blockIdx.x * 256 + (threadIdx.x & ~63u); i0 < n; i0 += gridDim.x * 256) {
+        const uint32_t i = i0 + lane, p = i < n ? list[i] : 0u;
+        Binned q{false, 0};
+        if (i < n) q = bin_pair(b, p, tile);
+        const uint64_t mine = __ballot(q.big);
+        if (mine && enqueue(b, k, mine, p, q.tiles, lane)) list[i] = kNone;
+    }
+}
 
 // ------------------------------------------------------------ join pieces
 
@@ -1110,8 +1120,10 @@ void k_batched(BatchArgs b) {
     const uint32_t w = uniform(threadIdx.x >> 6);
     if (MODE != kMixedOrders && b.open.pairs) {
         // the open pairs have been joined, unless a list was full
-        const uint32_t fill = (lane & (kTilesCtr - 1)) < b.xcds ? b.open.fill[lane * kCtrStride] : 0u;
-        if (!__any(fill > (lane >= kTilesCtr ? b.open.long_cap : b.open.cap))) return;
+        const bool lng = lane >= kTilesCtr;
+        const uint32_t k = lane & (kTilesCtr - 1);
+        const uint32_t fill = k < b.xcds ? (lng ? b.open.long_fill : b.open.fill)[k * kCtrStride] : 0u;
+        if (!__any(fill > (lng ? b.open.long_cap : b.open.cap))) return;
     }
     unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
     const uint32_t xcds = b.xcds;
@@ -1299,7 +1311,7 @@ void k_open(BatchArgs b) {
             typedef const __attribute__((address_space(4))) BatchArgs *KArgs;
             KArgs pb = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
             asm volatile("" : "+s"(pb));
-            const uint32_t n = lane < xcds ? min(pb->open.fill[((half ? 0u : kTilesCtr) + lane) * kCtrStride],
+            const uint32_t n = lane < xcds ? min((half ? pb->open.fill : pb->open.long_fill)[lane * kCtrStride],
                                                  half ? pb->open.cap : pb->open.long_cap)
                                            : 0u;
             before = n;
@@ -1326,13 +1338,16 @@ void k_open(BatchArgs b) {
             uint32_t vv = 0, key = kNone, p = 0;
             PairLists m{};
             bool seq = false;
-            const bool in = lane < grab && got + lane < hi;
+            bool in = lane < grab && got + lane < hi;
             uint32_t seg = 0, at = got + lane;   // entry `at`: of which list, and where
             for (uint32_t k = 1; k < xcds; k++) seg = at >= lane_val(before, k) ? k : seg;
             at -= __shfl(before, seg);
             if (in) {
                 const uint32_t cap = pb->open.cap;
                 p = gload(pb->open.pairs + uint64_t(seg) * (cap + pb->open.long_cap) + (half ? 0u : cap), at);
+                in = p != kNone;   // (kNone: moved to the workgroup bin)
+            }
+            if (in) {
                 const uint32_t r = gload32(a.r, p), s = gload32(a.s, p);
                 const uint64_t ar0 = gload64(a.Ar.off, r), fr0 = gload64(a.Fr.off, r);
                 const uint64_t as0 = gload64(a.As.off, s), fs0 = gload64(a.Fs.off, s);
@@ -1412,7 +1427,8 @@ int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
     bb.tail_pairs = 2ull * bb.grab * kWavesPerBlock * ((blocks + b.xcds - 1) / b.xcds);
     if (MODE == kAlg2 && b.wg_min != kNone) {
         const uint64_t bin_blocks = std::min<uint64_t>((b.f.n_pairs + 255) / 256, uint64_t(cus) * 8);
-        k_bin<<<dim3(uint32_t(bin_blocks)), dim3(256), 0, stream>>>(bb, TILE);
+        if (b.open.pairs) k_bin_open<<<dim3(32, b.xcds), dim3(256), 0, stream>>>(bb, TILE);
+        else k_bin<<<dim3(uint32_t(bin_blocks)), dim3(256), 0, stream>>>(bb, TILE);
         APRIL_HIP_TRY(hipGetLastError());
         static int wg_per_cu = 0;   // resident workgroups per CU
         if (!wg_per_cu) {
@@ -1460,7 +1476,7 @@ int launch_t(const BatchArgs &b, uint32_t chunk, int cus, uint32_t waves, hipStr
 // kMaxCtrs slots, 128 bytes apart), then the queues: kBigQueueCap pair
 // indices shared evenly by the XCD ranges.
 constexpr uint64_t kQueueCtrBytes = 2ull * kMaxCtrs * kCtrStride * sizeof(unsigned int);
-static_assert(kTilesCtr == 32, "k_open: one counter per lane");
+static_assert(kTilesCtr == 32, "k_batched: a lane for each list");
 static_assert(kCtrBytes + kQueueCtrBytes + 4ull * kBigQueueCap <= kStaticWorkspaceBytes,
               "the static scratch holds a batched workspace");
 
@@ -1540,27 +1556,23 @@ static void set_wg_bin(BatchArgs &b, uint32_t wg_min, void *workspace) {
 }
 
 // The lists of open pairs for screening, in the place of the workgroup bin's
-// queues; with the workgroup bin, one list per range behind the queues, half of
-// the space each, which the binning pass fills with the pairs that it does not
-// queue (its counters are the upper halves of the ranges').  None for small calls.
-static int open_lists(BatchArgs &b, hipStream_t stream, OpenLists *of_screen) {
+// queues, or behind them in half the space (none for small calls).
+static int open_lists(BatchArgs &b, hipStream_t stream) {
     if (b.fixed || b.f.n_pairs >= (1ull << 32)) return APRIL_OK;
-    if (b.wg_min != kNone) {
-        b.qcap /= 2;
-        b.open.fill = b.xhead;
-        b.open.pairs = b.queue + uint64_t(b.xcds) * b.qcap;
-        b.open.long_cap = b.qcap;
-        return APRIL_OK;
-    }
-    b.open.fill = b.qfill;
+    uint32_t cap = b.qcap;
     b.open.pairs = b.queue;
-    b.open.long_cap = b.qcap / 4;
-    b.open.cap = b.qcap - b.open.long_cap;
-    if (!b.times) {   // (else zeroed already)
+    if (b.wg_min != kNone) {
+        cap = b.qcap /= 2;
+        b.open.pairs += uint64_t(b.xcds) * cap;
+    }
+    b.open.fill = b.qfill + kTilesCtr * kCtrStride;
+    b.open.long_fill = b.xhead + kTilesCtr * kCtrStride;
+    b.open.long_cap = cap / 4;
+    b.open.cap = cap - b.open.long_cap;
+    if (b.wg_min == kNone && !b.times) {   // (else zeroed already)
         k_zero_queue_ctrs<<<1, 2 * kMaxCtrs, 0, stream>>>(b.qfill);
         APRIL_HIP_TRY(hipGetLastError());
     }
-    *of_screen = b.open;
     return APRIL_OK;
 }
 
@@ -1612,9 +1624,8 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
     if (R && S && can_screen(R, S, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        OpenLists open{};
-        if (int rc = open_lists(b, stream, &open)) return rc;
-        if (int rc = launch_screen(R, S, f, cus, workspace, stream, false, open)) return rc;
+        if (int rc = open_lists(b, stream)) return rc;
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream, false, b.open)) return rc;
         b.screened = 1;
     }
     switch (tile) {
@@ -1667,9 +1678,8 @@ int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStre
     if (can_screen(R, S, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        OpenLists open{};
-        if (int rc = open_lists(b, stream, &open)) return rc;
-        if (int rc = launch_screen(R, S, f, cus, workspace, stream, true, open)) return rc;
+        if (int rc = open_lists(b, stream)) return rc;
+        if (int rc = launch_screen(R, S, f, cus, workspace, stream, true, b.open)) return rc;
         b.screened = 1;
     }
     return launch_tc<256, 2, kWithinJoin>(b, cus, 0, stream);
@@ -1695,9 +1705,8 @@ int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hi
     if (can_screen_lines(P, L, a.n_pairs)) {
         FilterArgs f = a;
         if (b.fixed) f.counts = nullptr;   // counted from the verdicts at the end
-        OpenLists open{};
-        if (int rc = open_lists(b, stream, &open)) return rc;
-        if (int rc = launch_screen_lines(P, L, f, cus, workspace, stream, open)) return rc;
+        if (int rc = open_lists(b, stream)) return rc;
+        if (int rc = launch_screen_lines(P, L, f, cus, workspace, stream, b.open)) return rc;
         b.screened = 1;
     }
     return launch_tc<256, 2, kLinestrings>(b, cus, 0, stream);

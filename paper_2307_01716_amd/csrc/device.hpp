@@ -154,7 +154,7 @@ bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs
 // the others ("long").  A listed pair's verdict byte is kListed; a pair that
 // finds its list full keeps kPending.
 struct OpenLists {
-    unsigned int *fill;      // pairs put into XCD k's lists: fill[k * kCtrStride]; of long ones at kTilesCtr + k
+    unsigned int *fill, *long_fill;   // pairs put into XCD k's lists: fill[k * kCtrStride]
     uint32_t *pairs;         // XCD k's: pairs[k * (cap + long_cap) ...], the long ones behind the others (null: no lists)
     uint32_t cap, long_cap;
 };

@@ -557,7 +557,8 @@ __global__ __launch_bounds__(kBlock, MODE == kLines ? 4 : 8) void k_screen(Scree
             const uint64_t few = __ballot(open && !big), lng = __ballot(open && big);
             uint32_t at = 0;   // lane 0: of the others, lane 1: of the long ones
             if (lane < 2 && (lane ? lng : few))
-                at = atomicAdd(&a.open.fill[(lane * kTilesCtr + xcd) * kCtrStride], uint32_t(__popcll(lane ? lng : few)));
+                at = atomicAdd(&(lane ? a.open.long_fill : a.open.fill)[xcd * kCtrStride],
+                               uint32_t(__popcll(lane ? lng : few)));
             const uint32_t at_few = __shfl(at, 0), at_lng = __shfl(at, 1);
             at = (big ? at_lng : at_few) + uint32_t(__popcll((big ? lng : few) & ((1ull << lane) - 1)));
             if (open && at < (big ? a.open.long_cap : a.open.cap)) {

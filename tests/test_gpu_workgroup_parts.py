@@ -69,7 +69,7 @@ def test_full_queues(n):
     none = (np.zeros(0, np.uint32), np.zeros(0, np.uint32))
     A = []
     for _ in range(20):
-        s, e = random_lists(rng, 130, 100, 2000)
+        s, e = random_lists(rng, 520, 100, 8000)
         A.append((np.append(np.uint32(50), s), np.append(np.uint32(60), e)))
     _, D = lists(A, [none] * 20)
     r, s = (torch.from_numpy(rng.integers(0, 20, n).astype(np.int32)).cuda() for _ in range(2))
