@@ -400,7 +400,7 @@ def serve_bench(args):
            "config": {"workload": f"served: S = {len(S)} star polygons device-resident, grid 2^16; "
                                   "queries 10..10^4 vertices, radius 5e-4..0.05 (log-uniform)",
                       "slots": st["slots"], "cap_pairs": st["cap_pairs"],
-                      "gpu_build_cells": args.gpu_build_cells or (1 << 18)},
+                      "gpu_build_cells": args.gpu_build_cells or (1 << 14)},
            "served": {"saturation_qps": sat_qps, "saturation_pairs_per_s": sat_pairs / t_sat,
                       "levels": levels}}
     print(json.dumps(out), flush=True)

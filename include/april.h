@@ -402,7 +402,10 @@ typedef struct {
                                    or more has its lists built on the GPU
                                    (april_build_lists_gpu; one thread builds all such
                                    queries waiting at once in one call), the others on
-                                   the host (0 = 2^18, 0xFFFFFFFF = never) */
+                                   the host (0 = 2^14, 0xFFFFFFFF = never); lists
+                                   built on the GPU stay there until the query's
+                                   batch is done, up to a quarter of mem_budget
+                                   beside the slots */
     uint32_t reserved;      /* must be 0 */
     april_filter_opts_t filter;   /* batched-filter tuning (schedule/workspace ignored) */
 } april_serve_opts_t;

@@ -858,6 +858,11 @@ using namespace april;
 
 extern "C" int april_build_lists_gpu(const april_grid_t *grid, const double *xy, const uint64_t *vtx_off,
                                      uint64_t n, uint32_t flags, void *hip_stream, april_lists_t **out) {
+    return build_lists_gpu(grid, xy, vtx_off, n, flags, hip_stream, true, out);
+}
+
+int april::build_lists_gpu(const april_grid_t *grid, const double *xy, const uint64_t *vtx_off, uint64_t n,
+                           uint32_t flags, void *hip_stream, bool summaries, april_lists_t **out) {
     clear_error();
     if (!xy || !vtx_off || !out) return fail(APRIL_E_INVALID, "NULL argument");
     if (n == 0) return fail(APRIL_E_INVALID, "no polygons");
@@ -1066,7 +1071,8 @@ extern "C" int april_build_lists_gpu(const april_grid_t *grid, const double *xy,
     L->device = dev;
     L->codec = APRIL_CODEC_RAW;
     L->max_len = uint32_t(std::min<uint64_t>(last[1], 0xfffffffeull));
-    if (int rc = launch_summaries(L, last[2], L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)) {
+    if (int rc = summaries ? launch_summaries(L, last[2], L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)
+                           : APRIL_OK) {
         april_lists_free(L);
         return rc;
     }

@@ -162,6 +162,20 @@ struct DeviceState {
 };
 int device_state(DeviceState **out);
 
+// april_build_lists_gpu, with summaries for screening or without (lists that
+// are not filtered themselves).
+int build_lists_gpu(const april_grid_t *grid, const double *xy, const uint64_t *vtx_off, uint64_t n, uint32_t flags,
+                    void *hip_stream, bool summaries, april_lists_t **out);
+
+// A served query's lists on the device, to be copied into its batch's: na and
+// nf intervals to a0 and f0 (na = 0: nothing to copy).
+struct QueryLists {
+    const uint32_t *as, *ae, *fs, *fe;
+    uint64_t na, nf, a0, f0;
+};
+int launch_gather(const QueryLists *d_lists, uint64_t n, uint32_t *as, uint32_t *ae, uint32_t *fs, uint32_t *fe,
+                  hipStream_t stream);
+
 // One query of a served batch: its MBR and the grid cells the MBR covers.
 struct ProbeQuery {
     double x0, y0, x1, y1;

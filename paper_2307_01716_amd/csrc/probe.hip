@@ -12,6 +12,8 @@
 // per wavefront.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -69,7 +71,40 @@ __global__ __launch_bounds__(256) void k_probe(const ProbeQuery *__restrict__ q,
     }
 }
 
+// blockIdx.y: the query; its workgroups copy its lists, 16 bytes a thread and
+// turn where both sides allow it.
+__device__ __forceinline__ void copy_list(const uint32_t *__restrict__ from, uint32_t *__restrict__ to, uint64_t n) {
+    const uint64_t t = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x, stride = uint64_t(gridDim.x) * blockDim.x;
+    uint64_t done = 0;
+    if (((reinterpret_cast<uintptr_t>(from) | reinterpret_cast<uintptr_t>(to)) & 15) == 0) {
+        const uint64_t n4 = n / 4;
+        for (uint64_t i = t; i < n4; i += stride)
+            reinterpret_cast<uint4 *>(to)[i] = reinterpret_cast<const uint4 *>(from)[i];
+        done = 4 * n4;
+    }
+    for (uint64_t i = done + t; i < n; i += stride) to[i] = from[i];
+}
+
+__global__ __launch_bounds__(256) void k_gather(const QueryLists *__restrict__ lists, uint32_t *as, uint32_t *ae,
+                                                uint32_t *fs, uint32_t *fe) {
+    const QueryLists q = lists[blockIdx.y];
+    copy_list(q.as, as + q.a0, q.na);
+    copy_list(q.ae, ae + q.a0, q.na);
+    copy_list(q.fs, fs + q.f0, q.nf);
+    copy_list(q.fe, fe + q.f0, q.nf);
+}
+
 }  // namespace
+
+int launch_gather(const QueryLists *d_lists, uint64_t n, uint32_t *as, uint32_t *ae, uint32_t *fs, uint32_t *fe,
+                  hipStream_t stream) {
+    for (uint64_t k = 0; k < n; k += 65535) {   // (gridDim.y has 16 bits)
+        k_gather<<<dim3(16, uint32_t(std::min<uint64_t>(n - k, 65535))), dim3(256), 0, stream>>>(d_lists + k, as, ae, fs,
+                                                                                             fe);
+        APRIL_HIP_TRY(hipGetLastError());
+    }
+    return APRIL_OK;
+}
 
 int launch_probe(const ProbeQuery *d_q, uint32_t n_q, const uint32_t *cell_off, const uint32_t *cell_ids,
                  const double *boxes, const uint16_t *cells, uint32_t G, uint32_t *pr, uint32_t *ps,

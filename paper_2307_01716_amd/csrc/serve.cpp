@@ -7,11 +7,12 @@
 //
 //   submit -> builder threads (lists, MBR cell range, pair upper bound;
 //             large queries: one device thread builds all those queued in
-//             one call)
+//             one call, and their lists stay on the device)
 //          -> dispatcher: packs ready requests into the next free slot while
 //             the slot's device memory (pairs, intervals, queries) suffices
-//             -> slot phase A on its stream: H2D of the batch's lists and MBRs,
-//                probe kernel, D2H of the pair count
+//             -> slot phase A on its stream: H2D of the batch's host-built
+//                lists and MBRs, a copy of its device-built lists, probe
+//                kernel, D2H of the pair count
 //             -> slot phase B: filter (batched schedule, slot workspace), D2H
 //                of pairs and verdicts
 //          -> results split per request, sorted by S id, ticket ready.
@@ -21,6 +22,7 @@
 // and their work overlaps on the device.  A request whose lists or pair
 // bound alone exceed a slot's capacity fails with APRIL_E_NOMEM.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -41,6 +43,20 @@ double now_s() {
 
 enum ReqState { RQ_QUEUED, RQ_BUILT, RQ_RUNNING, RQ_DONE, RQ_FAILED };
 
+// Lists that the device builder has built in one call, held by the requests
+// they belong to; `held` is the server's sum of such bytes.
+struct DeviceLists {
+    april_lists_t *L;
+    std::atomic<uint64_t> *held;
+    DeviceLists(april_lists_t *lists, std::atomic<uint64_t> *sum) : L(lists), held(sum) { held->fetch_add(L->d.bytes); }
+    DeviceLists(const DeviceLists &) = delete;
+    DeviceLists &operator=(const DeviceLists &) = delete;
+    ~DeviceLists() {
+        held->fetch_sub(L->d.bytes);
+        april_lists_free(L);
+    }
+};
+
 // A request is shared by whoever holds it: the ticket table, a queue, a
 // builder thread, a slot's batch, and callers blocked in april_serve_wait.
 // It is freed with the last of them, so a cancel or a release never frees a
@@ -51,7 +67,9 @@ struct Req {
     uint64_t ticket = 0;
     std::vector<double> xy;
     april::ProbeQuery q{};
-    april_lists_t *lists = nullptr;   // host lists of the query (1 object)
+    april_lists_t *lists = nullptr;   // host lists of the query (1 object), or
+    std::shared_ptr<DeviceLists> dev;   // device lists: intervals a0 .. a0 + n_a and f0 .. f0 + n_f of them
+    uint64_t n_a = 0, n_f = 0, a0 = 0, f0 = 0;
     uint64_t pair_bound = 0;
     int state = RQ_QUEUED;
     int rc = APRIL_OK;
@@ -81,6 +99,7 @@ struct Slot {
     uint8_t *d_v = nullptr;
     uint64_t *d_counts = nullptr;
     unsigned int *d_n = nullptr;
+    april::QueryLists *d_from = nullptr;
     void *d_ws = nullptr;
     uint64_t ws_bytes = 0;
     april_lists Q;   // device view of the batch's query lists (no ownership)
@@ -92,6 +111,7 @@ struct Slot {
     uint32_t *h_pr = nullptr, *h_ps = nullptr;
     uint8_t *h_v = nullptr;
     unsigned int *h_n = nullptr;
+    april::QueryLists *h_from = nullptr;
 };
 
 }  // namespace
@@ -112,6 +132,12 @@ struct april_server {
     uint16_t *d_cells = nullptr;
     // slot capacities
     uint64_t cap_pairs = 0, cap_intervals = 0, cap_queries = 0;
+    // bytes of lists kept on the device for requests, and the most of them
+    // (batches beyond it are read back); lists no request needs any more,
+    // freed by the device builder thread
+    std::atomic<uint64_t> held{0};
+    uint64_t held_most = 0;
+    std::vector<std::shared_ptr<DeviceLists>> spent;
     std::vector<Slot> slots;
     // requests
     std::mutex mu;
@@ -155,10 +181,14 @@ double est_cells(const april_server *sv, const std::vector<double> &xy) {
     return cells;
 }
 
-// A query's lists are built (rc, L): its MBR and grid-cell range, the
-// upper bound of its pairs, the capacity checks, then ready for a slot (or
-// failed).  Takes the server's mutex.
+// A query's lists are built (rc; L, or q's device lists): its MBR and
+// grid-cell range, the upper bound of its pairs, the capacity checks, then
+// ready for a slot (or failed).  Takes the server's mutex.
 void finish_build(april_server *sv, const ReqPtr &q, april_lists_t *L, int rc) {
+    if (L) {
+        q->n_a = L->n_a;
+        q->n_f = L->n_f;
+    }
     const uint64_t nv = q->xy.size() / 2;
     if (rc == APRIL_OK) {
         double b[4] = {q->xy[0], q->xy[1], q->xy[0], q->xy[1]};
@@ -171,7 +201,7 @@ void finish_build(april_server *sv, const ReqPtr &q, april_lists_t *L, int rc) {
         q->q = april::ProbeQuery{b[0], b[1], b[2], b[3], cell_of(sv, b[0], 0), cell_of(sv, b[1], 1),
                                  cell_of(sv, b[2], 0), cell_of(sv, b[3], 1)};
         q->pair_bound = sat_sum(sv, q->q.cx0, q->q.cy0, q->q.cx1, q->q.cy1);
-        if (L->n_a + L->n_f > sv->cap_intervals || q->pair_bound > sv->cap_pairs) rc = APRIL_E_NOMEM;
+        if (q->n_a + q->n_f > sv->cap_intervals || q->pair_bound > sv->cap_pairs) rc = APRIL_E_NOMEM;
     }
     std::lock_guard<std::mutex> lk(sv->mu);
     q->lists = L;
@@ -217,11 +247,14 @@ void builder_main(april_server *sv) {
     }
 }
 
-// The lists of the queued large queries, built on the device in one call
-// (all of them at once, so the call's synchronizations and launches are
-// shared), read back, split per query.  On error the batch's queries are
-// built one by one on the host, so that each gets its own result.
+// The lists of the queued large queries, built on the device in one call (all
+// of them at once, so the call's synchronizations and launches are shared).
+// They stay there for their slots to copy (read back, split per query and
+// staged again, 400 queries of 11 million intervals took 25 ms); where too many
+// bytes are held already, they are read back and split.  On error the batch's
+// queries go to the host builders, so that each gets its own result.
 void gpu_build_batch(april_server *sv, std::vector<ReqPtr> &batch, hipStream_t stream) {
+    const size_t n = batch.size();
     std::vector<double> xy;
     std::vector<uint64_t> off(1, 0);
     for (const ReqPtr &q : batch) {
@@ -229,24 +262,48 @@ void gpu_build_batch(april_server *sv, std::vector<ReqPtr> &batch, hipStream_t s
         off.push_back(off.back() + q->xy.size() / 2);
     }
     april_lists_t *Ld = nullptr, *L = nullptr;
-    int rc = april_build_lists_gpu(&sv->S->grid, xy.data(), off.data(), batch.size(), 0, stream, &Ld);
+    int rc = april::build_lists_gpu(&sv->S->grid, xy.data(), off.data(), n, 0, stream, false, &Ld);
+    if (rc == APRIL_OK && sv->held.load() + Ld->d.bytes <= sv->held_most) {
+        std::vector<uint64_t> oa(n + 1), of(n + 1);
+        hipError_t e = hipMemcpyAsync(oa.data(), Ld->d.off_a, 8 * (n + 1), hipMemcpyDeviceToHost, stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(of.data(), Ld->d.off_f, 8 * (n + 1), hipMemcpyDeviceToHost, stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(stream);   // and the lists are complete, for any stream
+        if (e == hipSuccess) {
+            const auto dev = std::make_shared<DeviceLists>(Ld, &sv->held);
+            for (size_t k = 0; k < n; k++) {
+                Req &q = *batch[k];
+                q.dev = dev;
+                q.a0 = oa[k];
+                q.n_a = oa[k + 1] - oa[k];
+                q.f0 = of[k];
+                q.n_f = of[k + 1] - of[k];
+                finish_build(sv, batch[k], nullptr, APRIL_OK);
+            }
+            return;
+        }
+        rc = APRIL_E_HIP;
+    }
     if (rc == APRIL_OK) rc = april_lists_download(Ld, stream, &L);
     if (Ld) april_lists_free(Ld);
-    for (size_t k = 0; k < batch.size(); k++) {
-        april_lists_t *Lq = nullptr;
-        int rq = rc;
-        if (rc == APRIL_OK) {
-            const uint64_t a0 = L->off_a[k], a1 = L->off_a[k + 1], f0 = L->off_f[k], f1 = L->off_f[k + 1];
-            const uint64_t oa[2] = {0, a1 - a0}, of[2] = {0, f1 - f0};
-            rq = april_lists_from_arrays(&sv->S->grid, 1, oa, L->start_a.data() + a0, L->end_a.data() + a0, of,
-                                         L->start_f.data() + f0, L->end_f.data() + f0, 0, &Lq);
-        } else {
-            const uint64_t o1[2] = {0, batch[k]->xy.size() / 2};
-            rq = april::build_lists_threads(&sv->S->grid, batch[k]->xy.data(), o1, 1, 0, 1, &Lq);
+    if (rc != APRIL_OK) {
+        std::lock_guard<std::mutex> lk(sv->mu);
+        for (const ReqPtr &q : batch) {
+            if (q->cancelled) continue;
+            q->state = RQ_QUEUED;
+            sv->to_build.push_back(q);
         }
+        sv->cv_build.notify_all();
+        return;
+    }
+    for (size_t k = 0; k < n; k++) {
+        april_lists_t *Lq = nullptr;
+        const uint64_t a0 = L->off_a[k], a1 = L->off_a[k + 1], f0 = L->off_f[k], f1 = L->off_f[k + 1];
+        const uint64_t oa[2] = {0, a1 - a0}, of[2] = {0, f1 - f0};
+        const int rq = april_lists_from_arrays(&sv->S->grid, 1, oa, L->start_a.data() + a0, L->end_a.data() + a0, of,
+                                               L->start_f.data() + f0, L->end_f.data() + f0, 0, &Lq);
         finish_build(sv, batch[k], Lq, rq);
     }
-    if (L) april_lists_free(L);
+    april_lists_free(L);
 }
 
 // The device builder thread: takes every large query queued (up to
@@ -256,6 +313,13 @@ void gpu_build_batch(april_server *sv, std::vector<ReqPtr> &batch, hipStream_t s
 // bound the build rate.)
 constexpr uint64_t kGpuBuildVertices = 4u << 20;
 
+// Default of gpu_build_cells.  A device call takes 1 to 2 ms, whatever its
+// queries, and a host thread about 35 ns a cell: at 16,384 cells a lone query
+// costs the same (p90 of single queries 1.3 ms with 2^14 and less, 2.0, 3.1 and
+// 3.5 with 2^15, 2^16 and 2^18), and 400 queries of up to 10^4 vertices, for
+// which 14 host threads took 84 ms with 2^18, are no faster below.
+constexpr double kGpuBuildCells = 16384.0;
+
 void gpu_builder_main(april_server *sv) {
     hipStream_t stream = nullptr;
     if (hipSetDevice(sv->device) != hipSuccess ||
@@ -263,9 +327,11 @@ void gpu_builder_main(april_server *sv) {
         stream = nullptr;
     for (;;) {
         std::vector<ReqPtr> batch;
+        std::vector<std::shared_ptr<DeviceLists>> spent;   // freed here, outside the lock
         {
             std::unique_lock<std::mutex> lk(sv->mu);
-            sv->cv_gpu.wait(lk, [&] { return sv->stop || !sv->to_gpu.empty(); });
+            sv->cv_gpu.wait(lk, [&] { return sv->stop || !sv->to_gpu.empty() || !sv->spent.empty(); });
+            spent.swap(sv->spent);
             if (sv->stop) break;
             uint64_t nv = 0;
             while (!sv->to_gpu.empty() &&
@@ -276,6 +342,7 @@ void gpu_builder_main(april_server *sv) {
                 nv += batch.back()->xy.size() / 2;
             }
         }
+        if (batch.empty()) continue;
         if (stream) {
             gpu_build_batch(sv, batch, stream);
         } else {
@@ -288,18 +355,32 @@ void gpu_builder_main(april_server *sv) {
 // Phase A: stage the batch, probe the MBR grid, read back the pair count.
 int slot_phase_a(april_server *sv, Slot &sl) {
     const uint64_t nq = sl.batch.size();
-    uint64_t na = 0, nf = 0;
+    // the queries built on the host first: one copy brings all their lists
+    const uint64_t host = uint64_t(std::stable_partition(sl.batch.begin(), sl.batch.end(),
+                                                         [](const ReqPtr &q) { return q->lists != nullptr; }) -
+                                   sl.batch.begin());
+    uint64_t na = 0, nf = 0, host_a = 0, host_f = 0;
     for (uint64_t k = 0; k < nq; k++) {
-        const april_lists_t *L = sl.batch[k]->lists;
-        sl.h_q[k] = sl.batch[k]->q;
+        const Req &q = *sl.batch[k];
+        sl.h_q[k] = q.q;
         sl.h_offa[k] = na;
         sl.h_offf[k] = nf;
-        std::copy(L->start_a.begin(), L->start_a.end(), sl.h_sa + na);
-        std::copy(L->end_a.begin(), L->end_a.end(), sl.h_ea + na);
-        std::copy(L->start_f.begin(), L->start_f.end(), sl.h_sf + nf);
-        std::copy(L->end_f.begin(), L->end_f.end(), sl.h_ef + nf);
-        na += L->n_a;
-        nf += L->n_f;
+        if (const april_lists_t *L = q.lists) {
+            std::copy(L->start_a.begin(), L->start_a.end(), sl.h_sa + na);
+            std::copy(L->end_a.begin(), L->end_a.end(), sl.h_ea + na);
+            std::copy(L->start_f.begin(), L->start_f.end(), sl.h_sf + nf);
+            std::copy(L->end_f.begin(), L->end_f.end(), sl.h_ef + nf);
+        } else {
+            const auto &d = q.dev->L->d;
+            sl.h_from[k - host] = april::QueryLists{d.start_a + q.a0, d.end_a + q.a0, d.start_f + q.f0, d.end_f + q.f0,
+                                                    q.n_a, q.n_f, na, nf};
+        }
+        na += q.n_a;
+        nf += q.n_f;
+        if (k < host) {
+            host_a = na;
+            host_f = nf;
+        }
     }
     sl.h_offa[nq] = na;
     sl.h_offf[nq] = nf;
@@ -313,10 +394,16 @@ int slot_phase_a(april_server *sv, Slot &sl) {
     APRIL_HIP_TRY(h2d(sl.d_q, sl.h_q, sizeof(april::ProbeQuery) * nq));
     APRIL_HIP_TRY(h2d(Q.d.off_a, sl.h_offa, 8 * (nq + 1)));
     APRIL_HIP_TRY(h2d(Q.d.off_f, sl.h_offf, 8 * (nq + 1)));
-    APRIL_HIP_TRY(h2d(Q.d.start_a, sl.h_sa, 4 * na));
-    APRIL_HIP_TRY(h2d(Q.d.end_a, sl.h_ea, 4 * na));
-    APRIL_HIP_TRY(h2d(Q.d.start_f, sl.h_sf, 4 * nf));
-    APRIL_HIP_TRY(h2d(Q.d.end_f, sl.h_ef, 4 * nf));
+    APRIL_HIP_TRY(h2d(Q.d.start_a, sl.h_sa, 4 * host_a));
+    APRIL_HIP_TRY(h2d(Q.d.end_a, sl.h_ea, 4 * host_a));
+    APRIL_HIP_TRY(h2d(Q.d.start_f, sl.h_sf, 4 * host_f));
+    APRIL_HIP_TRY(h2d(Q.d.end_f, sl.h_ef, 4 * host_f));
+    if (host < nq) {
+        APRIL_HIP_TRY(h2d(sl.d_from, sl.h_from, sizeof(april::QueryLists) * (nq - host)));
+        if (int rc = april::launch_gather(sl.d_from, nq - host, Q.d.start_a, Q.d.end_a, Q.d.start_f, Q.d.end_f,
+                                          sl.stream))
+            return rc;
+    }
     APRIL_HIP_TRY(hipMemsetAsync(sl.d_n, 0, sizeof(unsigned int), sl.stream));
     if (int rc = april::launch_probe(sl.d_q, uint32_t(nq), sv->d_cell_off, sv->d_cell_ids, sv->d_boxes,
                                      sv->d_cells, sv->G, sl.d_pr, sl.d_ps, uint32_t(sv->cap_pairs), sl.d_n,
@@ -350,6 +437,19 @@ int slot_phase_b(april_server *sv, Slot &sl) {
     return APRIL_OK;
 }
 
+// A request's lists are not needed any more (under the server's mutex; freeing
+// device memory waits for the device, so the device builder thread does that).
+void drop_lists(april_server *sv, Req &q) {
+    if (q.lists) april_lists_free(q.lists);
+    q.lists = nullptr;
+    if (!q.dev) return;
+    if (q.dev.use_count() == 1) {
+        sv->spent.push_back(std::move(q.dev));
+        sv->cv_gpu.notify_one();
+    }
+    q.dev.reset();
+}
+
 // Split a finished batch into per-request results (sorted by S id).
 void slot_finish(april_server *sv, Slot &sl) {
     const uint64_t nq = sl.batch.size();
@@ -377,8 +477,7 @@ void slot_finish(april_server *sv, Slot &sl) {
             q->verdict[u] = sv_pairs[u].second;
             if (sv_pairs[u].second <= APRIL_INDECISIVE) q->counts[sv_pairs[u].second]++;
         }
-        april_lists_free(q->lists);
-        q->lists = nullptr;
+        drop_lists(sv, *q);
         q->state = RQ_DONE;
         q->t_done = t;
     }
@@ -393,7 +492,7 @@ void fail_batch(april_server *sv, Slot &sl, int rc) {
         q->rc = rc;
         q->state = RQ_FAILED;
         q->t_done = now_s();
-        if (q->lists) { april_lists_free(q->lists); q->lists = nullptr; }
+        drop_lists(sv, *q);
     }
     sl.batch.clear();
     sl.state = SL_FREE;
@@ -427,7 +526,7 @@ void dispatcher_main(april_server *sv) {
             while (!sv->ready.empty() && free_slot->batch.size() < sv->cap_queries) {
                 ReqPtr q = sv->ready.front();
                 if (q->cancelled) { sv->ready.pop_front(); continue; }
-                const uint64_t qi = q->lists->n_a + q->lists->n_f;
+                const uint64_t qi = q->n_a + q->n_f;
                 if (!free_slot->batch.empty() &&
                     (pairs + q->pair_bound > sv->cap_pairs || ivs + qi > sv->cap_intervals))
                     break;   // the slot is full: the request waits for the next one
@@ -468,8 +567,9 @@ int alloc_slot(april_server *sv, Slot &sl) {
     if (int rc = april_filter_workspace_size(P, &o, &sl.ws_bytes)) return rc;
     auto up = [](uint64_t b) { return (b + 255) & ~uint64_t(255); };
     const uint64_t b_q = up(sizeof(april::ProbeQuery) * NQ), b_off = up(8 * (NQ + 1)), b_i = up(4 * I),
-                   b_p = up(4 * P), b_v = up(P), b_c = up(24), b_n = up(4), b_ws = up(sl.ws_bytes);
-    const uint64_t dev_total = b_q + 2 * b_off + 4 * b_i + 2 * b_p + b_v + b_c + b_n + b_ws;
+                   b_p = up(4 * P), b_v = up(P), b_c = up(24), b_n = up(4), b_ws = up(sl.ws_bytes),
+                   b_from = up(sizeof(april::QueryLists) * NQ);
+    const uint64_t dev_total = b_q + 2 * b_off + 4 * b_i + 2 * b_p + b_v + b_c + b_n + b_from + b_ws;
     hipError_t e = hipMalloc(&sl.d_block, dev_total);
     if (e != hipSuccess) return fail(APRIL_E_NOMEM, "server slot: device memory");
     char *d = static_cast<char *>(sl.d_block);
@@ -485,12 +585,13 @@ int alloc_slot(april_server *sv, Slot &sl) {
     sl.d_v = reinterpret_cast<uint8_t *>(d); d += b_v;
     sl.d_counts = reinterpret_cast<uint64_t *>(d); d += b_c;
     sl.d_n = reinterpret_cast<unsigned int *>(d); d += b_n;
+    sl.d_from = reinterpret_cast<april::QueryLists *>(d); d += b_from;
     sl.d_ws = d;
     sl.Q.grid = sv->S->grid;
     sl.Q.device = sv->device;
     sl.Q.codec = APRIL_CODEC_RAW;
     sl.Q.d.block = nullptr;
-    const uint64_t host_total = b_q + 2 * b_off + 4 * b_i + 2 * b_p + b_v + b_n;
+    const uint64_t host_total = b_q + 2 * b_off + 4 * b_i + 2 * b_p + b_v + b_n + b_from;
     e = hipHostMalloc(&sl.h_block, host_total, hipHostMallocDefault);
     if (e != hipSuccess) return fail(APRIL_E_NOMEM, "server slot: pinned host memory");
     char *h = static_cast<char *>(sl.h_block);
@@ -504,7 +605,8 @@ int alloc_slot(april_server *sv, Slot &sl) {
     sl.h_pr = reinterpret_cast<uint32_t *>(h); h += b_p;
     sl.h_ps = reinterpret_cast<uint32_t *>(h); h += b_p;
     sl.h_v = reinterpret_cast<uint8_t *>(h); h += b_v;
-    sl.h_n = reinterpret_cast<unsigned int *>(h);
+    sl.h_n = reinterpret_cast<unsigned int *>(h); h += b_n;
+    sl.h_from = reinterpret_cast<april::QueryLists *>(h);
     APRIL_HIP_TRY(hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking));
     APRIL_HIP_TRY(hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming));
     return APRIL_OK;
@@ -565,7 +667,7 @@ int april_serve_create(const april_lists_t *S, const double *boxes, const april_
         }
         sv->cell_lattice = double(lg.w);
         sv->gpu_build_cells = o.gpu_build_cells == 0xFFFFFFFFu ? 1e300
-                              : o.gpu_build_cells ? double(o.gpu_build_cells) : 262144.0;
+                              : o.gpu_build_cells ? double(o.gpu_build_cells) : kGpuBuildCells;
     }
     if (o.reserved) {
         delete sv;
@@ -578,6 +680,7 @@ int april_serve_create(const april_lists_t *S, const double *boxes, const april_
     sv->cap_pairs = std::min<uint64_t>(sv->cap_pairs, 0x7fffffffull);
     sv->cap_intervals = std::max<uint64_t>(1024, per_slot * 3 / 10 / 8);
     sv->cap_queries = o.max_batch ? o.max_batch : 8192;
+    sv->held_most = budget / 4;
     // uniform MBR grid over S's extent
     const uint64_t n = S->n;
     double lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY};
