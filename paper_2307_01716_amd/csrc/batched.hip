@@ -1524,12 +1524,17 @@ __global__ void k_sum_totals(const unsigned int *ctr, unsigned long long *totals
 }
 
 void batched_defaults(april_filter_opts_t &o, const BatchedShape &shape) {
-    // default tile: 256 intervals when a typical A-list fits it (more waves
-    // per CU), else 512 (fewer pieces, and the probe join for short objects
-    // spread over a wide key range).  Measured: 6% faster at 256 on the
-    // at-scale join (mean 177 intervals); 11% faster at 512 on the skewed
-    // one (mean 990; 75.7 against 84.9 ms).
-    if (!o.tile) o.tile = shape.intervals_a <= 256 * shape.objects ? 256 : 512;
+    // default tile: 256 intervals when a typical A-list of either side fits it
+    // (more waves per CU), else 512 (fewer pieces, and, with few long objects
+    // against many short ones, the chunk skipping and the probe join for
+    // short objects spread over a wide key range).  Measured without
+    // screening: 6% faster at 256 on the at-scale join (mean 177 intervals);
+    // 11% faster at 512 on the skewed one (mean 990 on both sides); 8,000 pairs
+    // of query polygons with short objects (mean 70) 38 and 35 us at 256 and
+    // 512 with queries of 380 intervals, 55 and 46 of 730, 126 and 46 of 8,000,
+    // 932 and 57 of 78,000.
+    if (!o.tile)
+        o.tile = shape.intervals_r <= 256 * shape.objects_r && shape.intervals_s <= 256 * shape.objects_s ? 256 : 512;
     // the workgroup bin needs two objects of at least max(tile, wg_min)
     // intervals: without such objects on both sides, no binning pass
     if (!o.wg_min) o.wg_min = kDefaultWgMin;

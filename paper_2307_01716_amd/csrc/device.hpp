@@ -130,8 +130,8 @@ int launch_count_verdicts(const uint8_t *verdict, uint64_t n, unsigned long long
 // launch of its binning and persistent kernels on `workspace`.
 uint64_t batched_workspace_bytes(uint64_t n_pairs);
 struct BatchedShape {
-    uint64_t intervals_a;   // A-list intervals of both collections
-    uint64_t objects;       // objects of both collections
+    uint64_t intervals_r, intervals_s;   // A-list intervals
+    uint64_t objects_r, objects_s;
     uint32_t max_len_r, max_len_s;   // longest list of one object (0xffffffff: unknown)
 };
 void batched_defaults(april_filter_opts_t &o, const BatchedShape &shape);

@@ -428,7 +428,7 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
     }
     FilterArgs a = make_args(R, S, d_r, d_s, n_pairs, d_verdict, counts);
     if (o.schedule == APRIL_SCHED_BATCHED) {
-        batched_defaults(o, BatchedShape{R->n_a + S->n_a, R->n + S->n, R->max_len, S->max_len});
+        batched_defaults(o, BatchedShape{R->n_a, S->n_a, R->n, S->n, R->max_len, S->max_len});
         const uint64_t need = batched_workspace_bytes(n_pairs);
         if (o.d_workspace) {
             if (o.workspace_bytes < need) return fail(APRIL_E_INVALID, "workspace too small");

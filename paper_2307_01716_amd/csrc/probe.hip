@@ -8,8 +8,7 @@
 // MBR overlaps and reports (q, s) only from the cell holding the lower-left
 // corner of the two MBRs' intersection -- that cell is (max(qcx0, scx0),
 // max(qcy0, scy0)) because the cell map is monotone -- so each pair appears
-// exactly once.  One workgroup per query; pairs are appended with one atomic
-// per wavefront.
+// exactly once.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -20,54 +19,67 @@
 namespace april {
 namespace {
 
-__global__ __launch_bounds__(256) void k_probe(const ProbeQuery *__restrict__ q, uint32_t n_q,
+// Pairs a wave holds in LDS before it appends them (one atomic on the one
+// counter each time: per turn of 64 entries, those took longer than the rest).
+constexpr uint32_t kHeld = 256;
+
+// A query's rows of cells are dealt out to the waves of `parts` workgroups.
+// The entries of a row's cells lie next to each other, so a wave's lanes take
+// them side by side, whatever the cells hold; an entry is in its object's
+// reporting cell when its place lies between that cell's bounds.  (A thread per
+// cell took a large query 0.3 ms and more: its threads walked their cells'
+// entries one by one, those of the fullest cell deciding.)
+__global__ __launch_bounds__(256) void k_probe(const ProbeQuery *__restrict__ q, uint32_t n_q, uint32_t parts,
                                                const uint32_t *__restrict__ cell_off,
                                                const uint32_t *__restrict__ cell_ids,
                                                const double *__restrict__ boxes,
                                                const uint16_t *__restrict__ cells, uint32_t G,
                                                uint32_t *pr, uint32_t *ps, uint32_t cap,
                                                unsigned int *count) {
-    const uint32_t lane = threadIdx.x & 63;
-    for (uint32_t k = blockIdx.x; k < n_q; k += gridDim.x) {
+    __shared__ uint32_t held[4][kHeld];
+    const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    for (uint64_t item = blockIdx.x; item < uint64_t(n_q) * parts; item += gridDim.x) {
+        const uint32_t k = uint32_t(item / parts), part = uint32_t(item % parts);
         const ProbeQuery Q = q[k];
-        const uint32_t ncx = Q.cx1 - Q.cx0 + 1, ncy = Q.cy1 - Q.cy0 + 1;
-        const uint64_t ncell = uint64_t(ncx) * ncy;
-        // every thread walks cells; the entries of a cell are read by one thread
-        for (uint64_t c = threadIdx.x; c < ncell; c += blockDim.x) {
-            const uint32_t cx = Q.cx0 + uint32_t(c % ncx);
-            const uint32_t cy = Q.cy0 + uint32_t(c / ncx);
-            const uint32_t cell = cy * G + cx;
-            uint32_t b = cell_off[cell];
-            const uint32_t e = cell_off[cell + 1];
-            for (;;) {
+        uint32_t n = 0;
+        auto append = [&]() {
+            unsigned int pos = 0;
+            if (lane == 0) pos = atomicAdd(count, n);
+            pos = uniform(__shfl(pos, 0));
+            wave_lds_sync();
+            for (uint32_t i = lane; i < n; i += 64) {
+                if (pos + i < cap) {
+                    pr[pos + i] = k;
+                    ps[pos + i] = held[w][i];
+                }
+            }
+            wave_lds_sync();
+            n = 0;
+        };
+        for (uint32_t cy = Q.cy0 + part * 4 + w; cy <= Q.cy1; cy += 4 * parts) {
+            const uint32_t *const row = cell_off + uint64_t(cy) * G;
+            const uint32_t e = uniform(row[Q.cx1 + 1]);
+            for (uint32_t j0 = uniform(row[Q.cx0]); j0 < e; j0 += 64) {
+                const uint32_t j = j0 + lane;
                 bool emit = false;
                 uint32_t s = 0;
-                if (b < e) {
-                    s = cell_ids[b++];
+                if (j < e) {
+                    s = cell_ids[j];
                     const double *sb = boxes + 4 * uint64_t(s);
                     const uint16_t *sc = cells + 4 * uint64_t(s);
                     const bool meet = Q.x0 <= sb[2] && sb[0] <= Q.x1 && Q.y0 <= sb[3] && sb[1] <= Q.y1;
-                    const uint32_t rx = max(Q.cx0, uint32_t(sc[0])), ry = max(Q.cy0, uint32_t(sc[1]));
-                    emit = meet && rx == cx && ry == cy;
-                }
-                // ballot over the lanes still active in this loop
-                const uint64_t mask = __ballot(emit);
-                if (mask) {
-                    const uint32_t leader = __builtin_ctzll(mask);
-                    unsigned int pos = 0;
-                    if (lane == leader) pos = atomicAdd(count, unsigned(__popcll(mask)));
-                    pos = __shfl(pos, leader);
-                    const uint32_t at = pos + __builtin_amdgcn_mbcnt_hi(
-                                                  uint32_t(mask >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0u));
-                    if (emit && at < cap) {
-                        pr[at] = k;
-                        ps[at] = s;
+                    if (meet && max(Q.cy0, uint32_t(sc[1])) == cy) {
+                        const uint32_t rx = max(Q.cx0, uint32_t(sc[0]));
+                        emit = j >= row[rx] && j < row[rx + 1];
                     }
                 }
-                if (!__any(b < e)) break;
+                const uint64_t mask = __ballot(emit);
+                if (emit) held[w][n + uint32_t(__popcll(mask & ((1ull << lane) - 1)))] = s;
+                n += uint32_t(__popcll(mask));
+                if (n > kHeld - 64) append();
             }
         }
+        if (n) append();
     }
 }
 
@@ -110,9 +122,10 @@ int launch_probe(const ProbeQuery *d_q, uint32_t n_q, const uint32_t *cell_off, 
                  const double *boxes, const uint16_t *cells, uint32_t G, uint32_t *pr, uint32_t *ps,
                  uint32_t cap, unsigned int *count, hipStream_t stream) {
     if (n_q == 0) return APRIL_OK;
-    const uint32_t blocks = n_q < 4096 ? n_q : 4096;
-    k_probe<<<dim3(blocks), dim3(256), 0, stream>>>(d_q, n_q, cell_off, cell_ids, boxes, cells, G, pr, ps,
-                                                    cap, count);
+    // few queries: several workgroups each
+    const uint32_t parts = std::max(1u, std::min(8u, 4096 / n_q));
+    k_probe<<<dim3(uint32_t(std::min<uint64_t>(uint64_t(n_q) * parts, 4096))), dim3(256), 0, stream>>>(
+        d_q, n_q, parts, cell_off, cell_ids, boxes, cells, G, pr, ps, cap, count);
     APRIL_HIP_TRY(hipGetLastError());
     return APRIL_OK;
 }
