@@ -41,6 +41,7 @@ struct CArgs {
     unsigned int *xhead;
     uint32_t xcds;
     uint32_t screened;    // only pairs whose verdict is kPending are open
+    const uint32_t *slot_r, *slot_s, *coarse_r, *coarse_s;   // then: the objects' coarse tables
     uint32_t grab;        // pairs taken at a time (at most 64)
     uint32_t search_min;
     uint32_t first_cap;   // X intervals decoded before a join's first test (at most TILE)
@@ -199,21 +200,67 @@ __device__ __forceinline__ bool probe_tile(const uint32_t *ts, const uint32_t *t
     return false;
 }
 
+// May an interval in [lo, hi) overlap one of the object whose hull this is (a
+// coarse table's 127 intervals)?
+__device__ __forceinline__ bool near_hull(const uint32_t *table, uint32_t lo, uint32_t hi) {
+    const uint32_t *p = table + kCoarse;   // the hull's ends; its starts lie 2 * kCoarse further on
+#pragma unroll
+    for (uint32_t S = kCoarse / 2; S > 0; S >>= 1) p = p[S - 1] <= lo ? p + S : p;
+    return p[2 * kCoarse] < hi;
+}
+
 // Any overlap between list X (compressed, decoded tile by tile into LDS) and
-// list Y (compressed, streamed)?
+// list Y (compressed, streamed)?  With Y's coarse table, only the blocks of X
+// (64 intervals, all between its start and the next one's) that meet Y's hull
+// are decoded: pairs that screening leaves open mostly meet at their edges.
 template <int TILE>
-__device__ bool cjoin(const ListRef &X, const ListRef &Y, uint32_t *ts, uint32_t *te, uint32_t *ys,
-                      uint32_t *ye, uint32_t search_min, uint32_t first_cap, uint32_t lane) {
+__device__ bool cjoin(const ListRef &X, const ListRef &Y, const uint32_t *table, uint32_t *ts, uint32_t *te,
+                      uint32_t *ys, uint32_t *ye, uint32_t search_min, uint32_t first_cap, uint32_t lane) {
     if (X.n == 0 || Y.n == 0) return false;
-    VCursor cx = cursor_at(X);
+    const uint64_t xb0 = X.L->boff[X.obj], xb1 = X.L->boff[X.obj + 1], xblk = X.L->blk[X.obj];
+    const uint32_t nblk = uint32_t(X.L->blk[X.obj + 1] - xblk);
+    const uint32_t *bval = X.L->bval + xblk, *bpos = X.L->bpos + xblk;
+    VCursor cx = vcursor(X.L->bytes, xb0, xb1, X.n);
     uint32_t cap = first_cap;   // a short first tile: a join that ends early decodes less of X
-    while (cx.g < cx.nvals) {
-        // fill the tile window by window (a window completes at most 128
-        // intervals and may leave one start pending after them)
-        uint32_t nt = 0;
-        while (cx.g < cx.nvals && nt + 130 <= cap) {
-            wave_lds_sync();
-            nt += vdecode_window(cx, ts + nt, te + nt, false, lane);
+    uint32_t nt = 0;            // intervals in the tile; a pending start lies behind them
+    uint32_t bb = 0, bv = 0, bp = 0;   // blocks looked at; this lane's of the last 64: start, end's place
+    uint64_t mask = 0;                 // those of the last 64 still to be decoded
+    uint32_t gend = 0;                 // values up to the end of the block being decoded
+    bool started = false;
+    for (;;) {
+        bool more = true;
+        for (;;) {
+            if (cx.g < gend) {
+                // (a window completes at most 128 intervals and may leave a start behind them)
+                if (nt + 130 > cap) break;
+                wave_lds_sync();
+                nt += vdecode_window(cx, ts + nt, te + nt, false, lane);
+                continue;
+            }
+            for (; !mask && bb < nblk; bb += 64) {
+                const uint32_t b = bb + lane;
+                bool need = false;
+                if (b < nblk) {
+                    bv = bval[b];
+                    bp = bpos[b];
+                    need = !table || near_hull(table, bv, b + 1 < nblk ? bval[b + 1] : 0xffffffffu);
+                }
+                mask = __ballot(need);
+            }
+            if (!mask) {
+                more = false;
+                break;
+            }
+            const uint32_t jl = uint32_t(__builtin_ctzll(mask)), blk = bb - 64 + jl;
+            mask &= mask - 1;
+            gend = min(cx.nvals, 2 * kVbyteBlock * (blk + 1));
+            if (!started || cx.g < 2 * kVbyteBlock * blk) {   // (else an earlier window has reached it)
+                const uint32_t start = __builtin_amdgcn_readlane(bv, jl);
+                cx = vcursor_block(X.L->bytes, xb0, xb1, X.n, blk, start, __builtin_amdgcn_readlane(bp, jl));
+                started = true;
+                wave_lds_sync();
+                if (lane == 0) ts[nt] = start;
+            }
         }
         wave_lds_sync();
         // a start decoded after the tile's last full interval opens the next
@@ -223,13 +270,12 @@ __device__ bool cjoin(const ListRef &X, const ListRef &Y, uint32_t *ts, uint32_t
         pad_tile<TILE>(ts, te, nt, lane);
         wave_lds_sync();
         if (nt && probe_tile<TILE>(ts, te, nt, Y, ys, ye, search_min, lane)) return true;
+        if (!more) return false;
         cap = TILE;
-        if (cx.g & 1u) {
-            wave_lds_sync();
-            if (lane == 0) ts[0] = pend;
-        }
+        nt = 0;
+        wave_lds_sync();
+        if (lane == 0) ts[0] = pend;
     }
-    return false;
 }
 
 // Which tile of the cached R object the LDS tile holds: (first interval << 1)
@@ -364,11 +410,23 @@ __global__ __launch_bounds__(kBlock) void k_filter_vbyte(CArgs a) {
                 const ListRef YA{xs ? &pa->Ar : &pa->As, xs ? r : s, xs ? nar : nas};
                 const ListRef YF{xs ? &pa->Fr : &pa->Fs, xs ? r : s, xs ? nfr : nfs};
                 held = kNoTile;   // the decoding joins overwrite ts/te
-                if (!cjoin<TILE>(XA, YA, ts, te, ys, ye, a.search_min, a.first_cap, lane)) v = APRIL_TN;
-                else if (cjoin<TILE>(XA, YF, ts, te, ys, ye, a.search_min, a.first_cap, lane) ||
-                         cjoin<TILE>(XF, YA, ts, te, ys, ye, a.search_min, a.first_cap, lane))
-                    v = APRIL_TH;
-                else v = APRIL_INDECISIVE;
+                const uint32_t *table = nullptr;   // Y's
+                if (a.screened) {
+                    const uint32_t slot = uniform(xs ? pa->slot_r[r] : pa->slot_s[s]);
+                    if (slot != kNoSlot) table = (xs ? pa->coarse_r : pa->coarse_s) + uint64_t(slot) * kTable;
+                }
+                // AA, then AF and FA (in a loop: one copy of the join's code)
+                v = APRIL_INDECISIVE;
+#pragma unroll 1
+                for (uint32_t j = 0; j < 3; j++) {
+                    const ListRef X{j == 2 ? XF.L : XA.L, XA.obj, j == 2 ? XF.n : XA.n};
+                    const ListRef Y{j == 1 ? YF.L : YA.L, YA.obj, j == 1 ? YF.n : YA.n};
+                    const bool hit = cjoin<TILE>(X, Y, table, ts, te, ys, ye, a.search_min, a.first_cap, lane);
+                    if (hit != (j == 0)) {
+                        v = j == 0 ? APRIL_TN : APRIL_TH;
+                        break;
+                    }
+                }
                 if (lane == 0) {
                     a.verdict[p] = v;
                     c_tn += v == APRIL_TN;
@@ -554,6 +612,10 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
         f.counts = counts;
         if (int rc = launch_screen(R, S, f, cus, workspace, stream)) return rc;
         a.screened = 1;
+        a.slot_r = R->d.slot;
+        a.slot_s = S->d.slot;
+        a.coarse_r = R->d.coarse;
+        a.coarse_s = S->d.coarse;
         // few pairs are left: four grabs per wave where there are enough
         a.grab = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(8, n_pairs / (4 * blocks * kWavesPerBlock))));
     }

@@ -149,6 +149,12 @@ bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs
 // where the join kernels have to look), and the decided pairs' counts into the
 // slots at `counters` (already cleared) when f.counts is set.  Of f only the
 // pairs, the verdicts and R's raw A-lists are read.
+// A coarse table (screen.hip): ends of the longest A-intervals, ends of the
+// hull, starts of both, then ends and starts of the longest F-intervals.
+constexpr uint32_t kCoarse = 128;   // entries per list, the last one padding
+constexpr uint32_t kTable = 6 * kCoarse;
+constexpr uint32_t kNoSlot = 0xffffffffu;   // an object without one
+
 // The pairs that screening leaves open, listed for the join kernel: one list
 // per XCD range for pairs of which neither object has a coarse table, one for
 // the others ("long").  A listed pair's verdict byte is kListed; a pair that

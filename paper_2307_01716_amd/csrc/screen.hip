@@ -45,11 +45,6 @@ namespace april {
 namespace {
 
 constexpr uint32_t kSumHalf = kSumEntries / 2;    // TF intervals; hull intervals
-constexpr uint32_t kCoarse = 128;                 // entries per coarse list, the last one padding
-// a coarse table: ends of the longest A-intervals, ends of the hull, starts of
-// both, then ends and starts of the longest F-intervals
-constexpr uint32_t kTable = 6 * kCoarse;
-constexpr uint32_t kNoSlot = 0xffffffffu;
 // longest list that a single wave summarizes; longer ones get 16 waves (a list
 // is read twice per selection, and the skewed workload has lists of 200,000)
 constexpr uint32_t kOneWave = 2048;
@@ -282,6 +277,8 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
                     l.coarse[i] = l.coarse[i + kCoarse] = 0xffffffffu;
         group_sync<W>();
         for (uint32_t i = tid; i < kTable; i += 64 * W) b.coarse[uint64_t(slot) * kTable + i] = l.coarse[i];
+        // (the compressed join takes what lies outside the hull for outside F too)
+        if (none && b.by_slot && tid == 0) b.slot[k] = kNoSlot;
     }
 }
 

@@ -242,3 +242,52 @@ def test_open_lists(sizes, n):
         torch.cuda.synchronize()
         assert int((v != april.INDECISIVE).sum()) == 0, k
         assert c.tolist() == [0, 0, n], k
+
+
+# --------------------------------------------- compressed pairs left open
+
+@pytest.mark.parametrize("holes", [False, True])
+@pytest.mark.parametrize("n", [1024, 1025, 1087, 1088, 2049, 6000])
+def test_compressed_planted(n, holes):
+    """One overlap planted at the edges of blocks of 64 intervals (give or take
+    a decoding window) in lists that otherwise touch everywhere, as an AA, an
+    AF and an FA overlap.  `holes`: every 100 intervals the other side has 150
+    by itself, whose blocks meet nothing of the first one's hull."""
+    rng = np.random.default_rng(n + holes)
+    print(f"[screen] compressed {n} {holes}", flush=True)
+    X = random_lists(rng, n + 1, 0, 12 * n + 64)
+    C = X[1][:-1].copy(), X[0][1:].copy()   # the gaps of X
+    none = (np.zeros(0, np.uint32), np.zeros(0, np.uint32))
+    if holes:
+        far = (np.arange(n + 1, dtype=np.uint32) // np.uint32(100)) * np.uint32(400_000)
+        C = C[0] + far[:-1], C[1] + far[:-1]
+        own = [np.uint32(20 * n + 1000) + np.uint32(400_000) * np.uint32(k) + np.arange(0, 450, 3, dtype=np.uint32)
+               for k in range(n // 100 + 1)]
+        own = np.concatenate(own)
+        X = (np.concatenate([X[0] + far, own]), np.concatenate([X[1] + far, own + np.uint32(1)]))
+        o = np.argsort(X[0], kind="stable")
+        X = X[0][o].astype(np.uint32), X[1][o].astype(np.uint32)
+        keep = np.append(X[1][:-1] <= X[0][1:], True)
+        X = X[0][keep], X[1][keep]
+    at = sorted({k for b in (0, 64, 128, 192, 512, 1024, n // 2 // 64 * 64, n // 64 * 64, n)
+                 for k in (b - 131, b - 65, b - 2, b - 1, b, b + 1, b + 63, b + 129) if 0 <= k < n - 1})
+    A, F = [C, C], [none, C]
+    for t in at:
+        nxt = X[0][np.searchsorted(X[0], C[1][t])]   # the next interval of the other side
+        if nxt + 1 > C[0][t + 1]:
+            continue
+        end = C[1].copy()
+        end[t] = nxt + 1
+        A += [(C[0], end), (C[0], end)]
+        F += [none, (C[0][t:t + 1], end[t:t + 1])]
+    for XF in (none, X):
+        sides = []
+        for a, f in (([X], [XF]), (A, F)):
+            a, f = ListSet.from_lists(a), ListSet.from_lists(f)
+            L = oracle.Lists(a.off, a.start, a.end, f.off, f.start, f.end)
+            sides.append((L, upload(L, april.CODEC_VBYTE)))
+        r, s = np.zeros(len(A), np.uint32), np.arange(len(A), dtype=np.uint32)
+        assert len(set(oracle.filter_pairs(sides[0][0], sides[1][0], r, s))) > 1
+        for tile in (256, 512, 1024):
+            check(sides[0], sides[1], r, s, schedule=april.SCHED_BATCHED, tile=tile)
+            check(sides[1], sides[0], s, r, schedule=april.SCHED_BATCHED, tile=tile)
