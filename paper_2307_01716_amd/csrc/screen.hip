@@ -413,6 +413,7 @@ __global__ __launch_bounds__(kBlock, MODE == kLines ? 4 : 8) void k_screen(Scree
     const uint32_t xcd = blockIdx.x % a.xcds, bx = blockIdx.x / a.xcds, nbx = gridDim.x / a.xcds;
     const uint64_t lo = a.f.n_pairs * xcd / a.xcds, hi = a.f.n_pairs * (xcd + 1) / a.xcds;
     unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
+    uint32_t x_lo = 0, x_hi = 0;           // (within joins: its A-list's first start, last end)
     uint32_t cached = kNoSlot, size = 0;   // the R object in t; its table's entries, a power of two (0: coarse)
     for (uint64_t g0 = lo + uint64_t(a.take) * (bx * kWavesPerBlock + w); g0 < hi;
          g0 += uint64_t(a.take) * nbx * kWavesPerBlock) {
@@ -490,6 +491,12 @@ __global__ __launch_bounds__(kBlock, MODE == kLines ? 4 : 8) void k_screen(Scree
             }
             __builtin_amdgcn_s_waitcnt(0);   // the copies, all under way at once, have landed
             wave_lds_sync();
+            if (MODE == kWithin) {
+                const uint32_t n = size ? __builtin_amdgcn_readlane(nar, k) : kCoarse - 1;
+                const uint32_t at = size ? 0u : kCoarse;   // a coarse table's hull has the list's ends
+                x_lo = uniform(t[padded(at) + kStarts]);
+                x_hi = n ? uniform(t[padded(at + n - 1)]) : 0u;
+            }
         };
         uint64_t todo = __ballot(todo_me);
         uint32_t kn = todo ? uint32_t(__builtin_ctzll(todo)) : 0u;
@@ -509,7 +516,12 @@ __global__ __launch_bounds__(kBlock, MODE == kLines ? 4 : 8) void k_screen(Scree
             uint32_t v;
             if (MODE == kWithin) {
                 v = uint32_t(m >> 32) ? kPending : APRIL_TN;
-                if (uint32_t(m) && v == kPending) {
+                const uint64_t some = __ballot(ye != 0);
+                if (uint32_t(m) && v == kPending &&
+                    (x_lo < uint32_t(__builtin_amdgcn_readlane(ys, kSumHalf)) ||
+                     x_hi > uint32_t(__builtin_amdgcn_readlane(ye, 63 - __builtin_clzll(some))))) {
+                    v = APRIL_INDECISIVE;   // beyond the hull at one end
+                } else if (uint32_t(m) && v == kPending) {
                     // the A-intervals (of a coarse table: its longest) inside each hull interval
                     const uint32_t *p0 = find_any(t, size, ys), *p1 = find_any(t, size, ye);
                     const uint32_t i0 = entry_at(t, p0) + (p0[kStarts] < ys ? 1u : 0u), i1 = entry_at(t, p1);
