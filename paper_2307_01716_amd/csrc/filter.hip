@@ -129,6 +129,9 @@ struct PlainArgs {
     uint32_t screened;   // only pairs whose verdict is kPending are open
 };
 
+constexpr uint32_t kPlainList = 1024;   // pairs looked at for one list
+static_assert(kPlainList % kBlock == 0 && kPlainList <= 65536, "16-bit list entries, whole rounds");
+
 // 80 SGPRs at most: the hardware allocates SGPRs in blocks of 16, and
 // above 80 fewer than 8 waves per SIMD fit (at 81 SGPRs the kernel ran 1.6x
 // longer with a grid of 8 waves per SIMD: part of it ran as a second round).
@@ -144,14 +147,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void k
     const uint64_t lo = a.n_pairs * xcd / xcds, hi = a.n_pairs * (xcd + 1) / xcds;
     const uint64_t n_waves = uint64_t(nbx) * kWavesPerBlock;
     unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
-    // pair by pair, every n_waves-th; which of the wave's next 64 are open is
-    // read by its lanes at once
-    for (uint64_t p0 = lo + uint64_t(bx) * kWavesPerBlock + w; p0 < hi; p0 += 64 * n_waves) {
-    const uint64_t pl = p0 + lane * n_waves;
-    uint64_t todo = __ballot(pl < hi && (!pa.screened || a.verdict[pl] == kPending));
-    while (todo) {
-        const uint64_t p = p0 + uint64_t(__builtin_ctzll(todo)) * n_waves;
-        todo &= todo - 1;
+    // The workgroup's pairs are kWavesPerBlock next to each other out of every
+    // n_waves.  Its threads list the open ones of the next kPlainList, and its
+    // waves take them from the list in turn: an open pair takes a wave 10 us or so,
+    // some many times that, and a wave has about seven at 100k x 100k (dealt out
+    // to the waves beforehand: 227 us, so 174).
+    __shared__ uint16_t list[kPlainList];
+    __shared__ uint32_t listed, taken;
+    for (uint64_t p0 = lo + uint64_t(bx) * kWavesPerBlock; p0 < hi; p0 += kPlainList / kWavesPerBlock * n_waves) {
+    __syncthreads();
+    if (threadIdx.x == 0) listed = taken = 0;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < kPlainList; i += kBlock) {
+        const uint64_t pl = p0 + i % kWavesPerBlock + uint64_t(i / kWavesPerBlock) * n_waves;
+        if (pl < hi && (!pa.screened || a.verdict[pl] == kPending)) list[atomicAdd(&listed, 1u)] = uint16_t(i);
+    }
+    __syncthreads();
+    for (;;) {
+        uint32_t t = 0;
+        if (lane == 0) t = atomicAdd(&taken, 1u);
+        t = uniform(__shfl(t, 0));
+        if (t >= listed) break;
+        const uint32_t i = uniform(list[t]);
+        const uint64_t p = p0 + i % kWavesPerBlock + uint64_t(i / kWavesPerBlock) * n_waves;
         const uint32_t r = uniform(a.r[p]), s = uniform(a.s[p]);
         uint8_t v;
         if (r >= a.n_r || s >= a.n_s) {

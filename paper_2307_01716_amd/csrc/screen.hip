@@ -26,12 +26,13 @@
 // coalesced 512-byte load and a pair one search; 16 + 16 leave twice as many
 // pairs to the joins, each of which costs several times a screened pair.
 //
-// Measured on one MI355X, whole calls without and with screening: at scale
-// (200k x 200k, 4.5M pairs) 1.96 and 0.72 ms, of which this kernel 0.40; the
-// plain schedule at 100k x 100k 1.50 and 0.40 ms; a partition of 10k x 10k
-// objects of 2,250 A-intervals 2.49 and 0.41 ms raw, 8k x 8k 3.45 and 0.72 ms
-// compressed; 40k x 40k with 300 complex objects a side 2.00 and 0.82 ms.
-// Making the summaries takes 0.65 ms for 200k objects.  The kernel issues 38
+// Measured on one MI355X, whole calls without screening and now, with the open
+// pairs listed for k_open: at scale (200k x 200k, 4.5M pairs) 1.96 and 0.64 ms,
+// of which this kernel 0.40; the plain schedule at 100k x 100k 1.50 and 0.32 ms;
+// a partition of 10k x 10k objects of 2,250 A-intervals 2.51 and 0.37 ms raw,
+// 8k x 8k 3.37 and 0.53 ms compressed; 40k x 40k with 300 complex objects a side
+// 1.99 and 0.45 ms; 100k x 100k within joins 0.95 and 0.43 ms, linestrings 0.93
+// and 0.30.  Making the summaries takes 0.8 ms for 200k objects.  The kernel issues 38
 // vector instructions per pair, 0.7 of the issue peak; two pairs' searches
 // side by side gained nothing at scale (0.42 ms).
 #include <hip/hip_runtime.h>
