@@ -36,10 +36,11 @@ from collections import OrderedDict
 PKG = os.path.dirname(os.path.abspath(__file__))
 # sources that define each kernel's code and its launch defaults
 # (the batched schedule's defaults live in batched.hip, so a change to the
-# plain kernel in filter.hip leaves the batched records valid)
-KERNEL_SOURCES = {"k_batched": ["csrc/batched.hip", "csrc/device.hpp"],
-                  "k_filter_plain": ["csrc/filter.hip", "csrc/device.hpp"],
-                  "k_filter_vbyte": ["csrc/compressed.hip", "csrc/vbyte.hpp", "csrc/device.hpp"]}
+# plain kernel in filter.hip leaves the batched records valid; screening decides
+# which pairs each of them sees)
+KERNEL_SOURCES = {"k_batched": ["csrc/batched.hip", "csrc/device.hpp", "csrc/screen.hip"],
+                  "k_filter_plain": ["csrc/filter.hip", "csrc/device.hpp", "csrc/screen.hip"],
+                  "k_filter_vbyte": ["csrc/compressed.hip", "csrc/vbyte.hpp", "csrc/device.hpp", "csrc/screen.hip"]}
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 # Peak VALU issue rate of the device: 256 CUs x 4 SIMDs, each issuing one
 # wave64 VALU instruction every 4 cycles (16 lanes wide) at 2.4 GHz, i.e.

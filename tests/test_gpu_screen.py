@@ -107,6 +107,29 @@ def test_bad_pairs_are_not_counted():
         assert np.array_equal(c.cpu().numpy(), np.bincount(want[~bad], minlength=3))
 
 
+@pytest.mark.parametrize("sizes", ["tables", "long"])
+def test_in_parts(sizes):
+    """Calls of more pairs than are screened at a time: the same pairs over and
+    over, against one of them by itself."""
+    rng = np.random.default_rng(50)
+    print(f"[screen] parts {sizes}", flush=True)
+    LR, LS = (lists_of(rng, SIZES[sizes], 24, False) for _ in range(2))
+    R, S = upload(LR, april.CODEC_RAW), upload(LS, april.CODEC_RAW)
+    r, s = (rng.integers(0, 24, PAIRS + 1).astype(np.uint32) for _ in range(2))
+    r.sort()
+    for fn, want in ((april.april_filter_pairs, oracle.filter_pairs(LR, LS, r, s)),
+                     (april.april_filter_within, oracle.filter_within(LR, LS, r, s))):
+        times = (1 << 24) // len(r) + 7
+        rt, st = (torch.from_numpy(k.view(np.int32)).cuda().repeat(times) for k in (r, s))
+        v = torch.full((len(rt),), 77, dtype=torch.uint8, device="cuda")
+        c = torch.full((3,), -1, dtype=torch.int64, device="cuda")
+        kw = {"schedule": april.SCHED_BATCHED} if fn is april.april_filter_pairs else {}
+        fn(R, S, rt, st, v, c, **kw)
+        torch.cuda.synchronize()
+        assert bool((v.view(times, -1) == torch.from_numpy(want).cuda()).all())
+        assert c.tolist() == (np.bincount(want, minlength=3) * times).tolist()
+
+
 # ------------------------------------------------- within joins, linestrings
 
 def run(fn, *args):
