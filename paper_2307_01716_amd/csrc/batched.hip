@@ -1573,7 +1573,7 @@ static int open_lists(BatchArgs &b, hipStream_t stream) {
     }
     b.open.fill = b.qfill + kTilesCtr * kCtrStride;
     b.open.long_fill = b.xhead + kTilesCtr * kCtrStride;
-    b.open.long_cap = cap / 2;
+    b.open.long_cap = b.wg_min != kNone ? cap / 2 : cap / 4;   // (the collections with long objects)
     b.open.cap = cap - b.open.long_cap;
     if (b.wg_min == kNone && !b.times) {   // (else zeroed already)
         k_zero_queue_ctrs<<<1, 2 * kMaxCtrs, 0, stream>>>(b.qfill);
@@ -1584,9 +1584,10 @@ static int open_lists(BatchArgs &b, hipStream_t stream) {
 
 // Pairs screened and joined at a time where there are lists: of 2^23 pairs the
 // open ones fit them (at scale 5.3% are open; with complex objects 2.3% long
-// ones, and the lists are half as large beside the workgroup bin's queues).
-// Those that did not were most of a call: 30M pairs of 200k x 200k objects with
-// 2,000 complex ones a side 23.4 ms, of which the scan for them 19.7.
+// ones, and the lists are half as large beside the workgroup bin's queues); of
+// within pairs, 10% of which are open, 2^22.  Those that did not were most of a
+// call: 30M pairs of 200k x 200k objects with 2,000 complex ones a side 23.4 ms,
+// of which the scan for them 19.7 (9.1 now).
 constexpr uint64_t kChunkPairs = 1ull << 23;
 
 __global__ void k_zero_lists(unsigned int *xhead, unsigned int *qctr) {
@@ -1595,13 +1596,13 @@ __global__ void k_zero_lists(unsigned int *xhead, unsigned int *qctr) {
     if (t < 2 * kMaxCtrs && t != kMaxCtrs - 1) qctr[t * kCtrStride] = 0;   // (that one: the wave times)
 }
 
-// screen(b), then join(b), for each part of the pairs.
+// screen, then join, for each part (of `most` pairs at most) of the pairs.
 template <class S, class J>
-static int screened_join(BatchArgs b, hipStream_t stream, S screen, J join) {
+static int screened_join(BatchArgs b, hipStream_t stream, uint64_t most, S screen, J join) {
     if (int rc = open_lists(b, stream)) return rc;
     b.screened = 1;
     const FilterArgs a = b.f;
-    const uint64_t parts = b.open.pairs ? (a.n_pairs + kChunkPairs - 1) / kChunkPairs : 1;
+    const uint64_t parts = b.open.pairs ? (a.n_pairs + most - 1) / most : 1;
     for (uint64_t k = 0; k < parts; k++) {
         const uint64_t lo = a.n_pairs / parts * k, hi = k + 1 < parts ? a.n_pairs / parts * (k + 1) : a.n_pairs;
         b.f.r = a.r + lo;
@@ -1674,7 +1675,7 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
         return launch_t<512>(c, chunk, cus, o.waves, stream);
     };
     if (!R || !S || !can_screen(R, S, a.n_pairs)) return join(b);
-    return screened_join(b, stream, [&](const FilterArgs &f, const OpenLists &open) {
+    return screened_join(b, stream, kChunkPairs, [&](const FilterArgs &f, const OpenLists &open) {
         return launch_screen(R, S, f, cus, workspace, stream, false, open);
     }, join);
 }
@@ -1720,7 +1721,7 @@ int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStre
     }
     auto join = [&](const BatchArgs &c) { return launch_tc<256, 2, kWithinJoin>(c, cus, 0, stream); };
     if (!can_screen(R, S, a.n_pairs)) return join(b);
-    return screened_join(b, stream, [&](const FilterArgs &f, const OpenLists &open) {
+    return screened_join(b, stream, kChunkPairs / 2, [&](const FilterArgs &f, const OpenLists &open) {
         return launch_screen(R, S, f, cus, workspace, stream, true, open);
     }, join);
 }
@@ -1744,7 +1745,7 @@ int launch_batched_linestrings(const FilterArgs &a, int cus, void *workspace, hi
     }
     auto join = [&](const BatchArgs &c) { return launch_tc<256, 2, kLinestrings>(c, cus, 0, stream); };
     if (!can_screen_lines(P, L, a.n_pairs)) return join(b);
-    return screened_join(b, stream, [&](const FilterArgs &f, const OpenLists &open) {
+    return screened_join(b, stream, kChunkPairs, [&](const FilterArgs &f, const OpenLists &open) {
         return launch_screen_lines(P, L, f, cus, workspace, stream, open);
     }, join);
 }
