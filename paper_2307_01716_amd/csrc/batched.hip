@@ -1280,10 +1280,10 @@ void k_batched(BatchArgs b) {
 // XCD k's workgroups take the k-th part of all the lists laid end to end (most
 // of it their own list, whatever the lists' lengths), dealt out to them in turn,
 // and a workgroup's waves take its turns from a counter in LDS.  Counters in
-// memory bound this kernel while it used them: with one a list, a grab waits
-// for those of the XCD's 1,024 waves before it (at scale 420 us, as many as the
-// joins take now; 100k polygons x 100k lines 300 against 110 us).  It is a
-// kernel of its own as the one above has no registers to spare for it.
+// memory bound this kernel while it used them: with one a list, a grab waited
+// for those of the XCD's 1,024 waves before it (200k x 200k objects 425 us, now
+// 240; 100k polygons x 100k lines 300, now 93).  It is a kernel of its own as the
+// one above has no registers to spare for it.
 template <int TILE, int C, int MODE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8), amdgpu_num_sgpr(80)))
 void k_open(BatchArgs b) {
