@@ -122,6 +122,8 @@ __device__ inline bool seq_join(const uint32_t *__restrict__ xs, const uint32_t 
 }
 
 
+// counts[0 .. 3) = 0 (a call of no pairs)
+int launch_zero_counts(unsigned long long *counts, hipStream_t stream);
 // counts[0 .. 3) = how many of the n verdicts are APRIL_TN, APRIL_TH, APRIL_INDECISIVE
 int launch_count_verdicts(const uint8_t *verdict, uint64_t n, unsigned long long *counts, hipStream_t stream);
 

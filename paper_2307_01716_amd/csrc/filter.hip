@@ -306,6 +306,12 @@ __global__ void k_check_pairs(const uint32_t *r, const uint32_t *s, uint64_t n, 
 
 }  // namespace
 
+int launch_zero_counts(unsigned long long *counts, hipStream_t stream) {
+    k_zero_counts<<<1, 64, 0, stream>>>(counts);
+    APRIL_HIP_TRY(hipGetLastError());
+    return APRIL_OK;
+}
+
 int launch_count_verdicts(const uint8_t *verdict, uint64_t n, unsigned long long *counts, hipStream_t stream) {
     k_count_verdicts<<<1, 1024, 0, stream>>>(verdict, uint32_t(n), counts);
     APRIL_HIP_TRY(hipGetLastError());
@@ -411,13 +417,7 @@ extern "C" int april_filter_pairs(const april_lists_t *R, const april_lists_t *S
     if (int rc = device_state(&st)) return rc;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     auto *counts = reinterpret_cast<unsigned long long *>(d_counts);
-    if (n_pairs == 0) {
-        if (counts) {
-            k_zero_counts<<<1, 64, 0, stream>>>(counts);
-            APRIL_HIP_TRY(hipGetLastError());
-        }
-        return APRIL_OK;
-    }
+    if (n_pairs == 0) return counts ? launch_zero_counts(counts, stream) : APRIL_OK;
     if (o.flags & APRIL_VALIDATE) {
         k_clear_flag<<<1, 1, 0, stream>>>(st->flag);
         APRIL_HIP_TRY(hipGetLastError());

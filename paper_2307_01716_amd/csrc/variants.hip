@@ -40,6 +40,8 @@ int run_batched(const FilterArgs &fa, Variant v, const april_lists_t *R, const a
     int cur = 0;
     APRIL_HIP_TRY(hipGetDevice(&cur));
     if (cur != R->device) return fail(APRIL_E_INVALID, "current device does not hold the lists");
+    // (no grid of no workgroups: screening would launch one on long lists)
+    if (fa.n_pairs == 0) return fa.counts ? launch_zero_counts(fa.counts, stream) : APRIL_OK;
     void *ws = nullptr;
     auto launch = [&]() -> int {
         switch (v) {
