@@ -181,6 +181,19 @@ double est_cells(const april_server *sv, const std::vector<double> &xy) {
     return cells;
 }
 
+// A request's lists are not needed any more (under the server's mutex; freeing
+// device memory waits for the device, so the device builder thread does that).
+void drop_lists(april_server *sv, Req &q) {
+    if (q.lists) april_lists_free(q.lists);
+    q.lists = nullptr;
+    if (!q.dev) return;
+    if (q.dev.use_count() == 1) {
+        sv->spent.push_back(std::move(q.dev));
+        sv->cv_gpu.notify_one();
+    }
+    q.dev.reset();
+}
+
 // A query's lists are built (rc; L, or q's device lists): its MBR and
 // grid-cell range, the upper bound of its pairs, the capacity checks, then
 // ready for a slot (or failed).  Takes the server's mutex.
@@ -206,8 +219,12 @@ void finish_build(april_server *sv, const ReqPtr &q, april_lists_t *L, int rc) {
     std::lock_guard<std::mutex> lk(sv->mu);
     q->lists = L;
     q->t_built = now_s();
-    if (q->cancelled) return;   // cancelled while being built: dropped with the last holder
+    if (q->cancelled) {   // while being built: the rest of it goes with the last holder
+        drop_lists(sv, *q);
+        return;
+    }
     if (rc != APRIL_OK) {
+        drop_lists(sv, *q);   // (its ticket may stay unreleased for long)
         q->rc = rc;
         q->state = RQ_FAILED;
         q->t_done = q->t_built;
@@ -435,19 +452,6 @@ int slot_phase_b(april_server *sv, Slot &sl) {
     std::lock_guard<std::mutex> lk(sv->mu);
     sl.state = SL_FILTERING;
     return APRIL_OK;
-}
-
-// A request's lists are not needed any more (under the server's mutex; freeing
-// device memory waits for the device, so the device builder thread does that).
-void drop_lists(april_server *sv, Req &q) {
-    if (q.lists) april_lists_free(q.lists);
-    q.lists = nullptr;
-    if (!q.dev) return;
-    if (q.dev.use_count() == 1) {
-        sv->spent.push_back(std::move(q.dev));
-        sv->cv_gpu.notify_one();
-    }
-    q.dev.reset();
 }
 
 // Split a finished batch into per-request results (sorted by S id).
@@ -854,7 +858,9 @@ int april_serve_cancel(april_server_t *sv, uint64_t ticket) {
     q->cancelled = true;
     for (auto *dq : {&sv->to_build, &sv->to_gpu, &sv->ready}) {
         auto f = std::find(dq->begin(), dq->end(), q);
-        if (f != dq->end()) dq->erase(f);
+        if (f == dq->end()) continue;
+        dq->erase(f);
+        if (dq == &sv->ready) drop_lists(sv, *q);   // (a builder or a slot drops those it works on)
     }
     sv->reqs.erase(it);
     sv->cv_done.notify_all();
