@@ -171,10 +171,10 @@ int april_lists_export(const april_lists_t *lists, uint64_t *off_a, uint32_t *st
  * Upload host lists to the current HIP device in the layout the kernels
  * read (Sec. 4.1: per object a sorted interval sequence; here split into
  * SoA start[] and end[] arrays plus CSR offsets, or compressed with
- * APRIL_CODEC_VBYTE).  Allocates device memory owned by *out.  RAW copies are
- * asynchronous on hip_stream (the host lists must stay alive until the
- * stream has passed the copy); VBYTE encodes on the host and returns after
- * the copy.  Free with april_lists_free.
+ * APRIL_CODEC_VBYTE), and make their summaries (see april_filter_pairs).
+ * Allocates device memory owned by *out.  The work runs on hip_stream and is
+ * complete on return: the lists can be used on any stream, the host lists can
+ * be freed.  VBYTE encodes on the host.  Free with april_lists_free.
  */
 int april_lists_to_device(const april_lists_t *host, uint32_t codec, void *hip_stream,
                           april_lists_t **out);
@@ -496,7 +496,8 @@ int april_build_cells(const april_grid_t *grid, const double *xy, const uint64_t
 /* Upload host cells; free both with april_cells_free.  The device copy holds
  * each list as maximal runs of consecutive ids, [start, end), which the
  * polygon-linestring join streams like an A-list (a run meets an interval
- * exactly when one of its cells does).  Device cells cannot be exported. */
+ * exactly when one of its cells does), and summaries of them; complete on
+ * return, for any stream.  Device cells cannot be exported. */
 int april_cells_to_device(const april_cells_t *host, void *hip_stream, april_cells_t **out);
 /* Counts of linestrings and of cell ids. */
 int april_cells_info(const april_cells_t *cells, uint64_t *n_lines, uint64_t *n_ids);

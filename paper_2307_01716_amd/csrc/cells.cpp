@@ -63,6 +63,12 @@ extern "C" int april_cells_to_device(const april_cells_t *h, void *hip_stream, a
         april_cells_free(C);
         return rc;
     }
+    // (the copies from pageable memory have landed by now, the summaries may
+    // not have: a call on another stream would read them unwritten)
+    if (e = hipStreamSynchronize(s); e != hipSuccess) {
+        april_cells_free(C);
+        return fail(APRIL_E_HIP, std::string("cells upload: ") + hipGetErrorString(e));
+    }
     *out = C;
     return APRIL_OK;
 }

@@ -15,7 +15,13 @@ static int upload_summaries(const april_lists_t *h, april_lists_t *L, hipStream_
     const bool raw = L->codec == APRIL_CODEC_RAW;
     uint64_t longer = 0;
     for (uint64_t k = 0; k < h->n; k++) longer += h->off_a[k + 1] - h->off_a[k] >= (raw ? kExact : kVbyteSummaryMin);
-    if (raw) return launch_summaries(L, longer, L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s);
+    if (raw) {
+        // (waited for: the copies from pageable memory have landed by now, and
+        // a call on another stream would read summaries that are not written yet)
+        if (int rc = launch_summaries(L, longer, L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)) return rc;
+        APRIL_HIP_TRY(hipStreamSynchronize(s));
+        return APRIL_OK;
+    }
     if (!longer) return APRIL_OK;
     const uint64_t na = std::max<uint64_t>(L->n_a, 1), nf = std::max<uint64_t>(L->n_f, 1);
     void *tmp = nullptr;
