@@ -572,6 +572,16 @@ uint64_t vbyte_cache_offset() { return (kCtrBytes + 255) & ~uint64_t(255); }
 int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const uint32_t *d_r, const uint32_t *d_s,
                         uint64_t n_pairs, uint8_t *d_verdict, unsigned long long *counts,
                         const april_filter_opts_t &o, int cus, void *workspace, hipStream_t stream) {
+    // what can be refused is refused before a kernel writes anything
+    const uint32_t tile = o.tile ? o.tile : 512;
+    if (tile != 256 && tile != 512 && tile != 1024)
+        return fail(APRIL_E_INVALID, "compressed lists: tile must be 256, 512 or 1024");
+    // chunk: windows (up to 130 intervals each) in a join's first tile
+    if (o.chunk > 4) return fail(APRIL_E_INVALID, "compressed lists: chunk must be 0 to 4");
+    const uint64_t cache_bytes = vbyte_cache_bytes(cus);
+    if ((o.flags & APRIL_WS_DECODE_CACHE) &&
+        (!o.d_workspace || o.workspace_bytes < vbyte_cache_offset() + cache_bytes))
+        return fail(APRIL_E_INVALID, "workspace too small for the decode cache");
     CArgs a;
     a.Ar = clist(R, false);
     a.Fr = clist(R, true);
@@ -592,15 +602,12 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
     a.search_min = o.search_min ? o.search_min : 64;
     k_zero_ctrs<<<1, 64, 0, stream>>>(a.xhead);
     APRIL_HIP_TRY(hipGetLastError());
-    const uint32_t tile = o.tile ? o.tile : 512;
-    // chunk: windows (up to 130 intervals each) in a join's first tile
-    if (o.chunk > 4) return fail(APRIL_E_INVALID, "compressed lists: chunk must be 0 to 4");
     // (one by default: most joins of overlapping objects end within it)
     a.first_cap = std::min<uint32_t>(tile, 130u * (o.chunk ? o.chunk : 1u));
     const uint64_t blocks = uint64_t(cus) * kVbyteBlocksPerCu;
     a.grab = 64;
     a.screened = 0;
-    if ((tile == 256 || tile == 512 || tile == 1024) && can_screen(R, S, n_pairs)) {
+    if (can_screen(R, S, n_pairs)) {
         FilterArgs f{};
         f.Ar = {R->d.off_a, nullptr, nullptr};
         f.r = d_r;
@@ -628,11 +635,8 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
     // the cache 0.88, and 1.22 when the host waits for each call)
     a.cache_cap = kCacheCap;
     a.cache = nullptr;
-    const uint64_t cache_bytes = vbyte_cache_bytes(cus);
     bool own_cache = false;
     if (o.flags & APRIL_WS_DECODE_CACHE) {
-        if (!o.d_workspace || o.workspace_bytes < vbyte_cache_offset() + cache_bytes)
-            return fail(APRIL_E_INVALID, "workspace too small for the decode cache");
         if (!a.screened)
             a.cache = reinterpret_cast<uint32_t *>(static_cast<char *>(o.d_workspace) + vbyte_cache_offset());
     } else if (!a.screened && hipMallocAsync(reinterpret_cast<void **>(&a.cache), cache_bytes, stream) == hipSuccess) {
@@ -644,10 +648,7 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
     switch (tile) {
         case 256: k_filter_vbyte<256><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a); break;
         case 512: k_filter_vbyte<512><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a); break;
-        case 1024: k_filter_vbyte<1024><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a); break;
-        default:
-            if (own_cache) (void)hipFreeAsync(a.cache, stream);
-            return fail(APRIL_E_INVALID, "compressed lists: tile must be 256, 512 or 1024");
+        default: k_filter_vbyte<1024><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a); break;
     }
     const hipError_t e = hipGetLastError();
     if (own_cache) APRIL_HIP_TRY(hipFreeAsync(a.cache, stream));
