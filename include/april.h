@@ -276,7 +276,9 @@ int april_filter_workspace_size(uint64_t n_pairs, const april_filter_opts_t *opt
  * lists: 3.5 KiB for an A-list of 1,024 or more, none for shorter ones).  Calls
  * of 8,192 pairs or more, and all calls on long lists, first decide from the
  * summaries what they can (most pairs of overlapping or clearly separate
- * objects); the schedule then takes the pairs that are left.
+ * objects); the schedule then takes the pairs that are left.  Lists that were
+ * not validated are checked at upload; those that are not what
+ * april_lists_from_arrays asks for have no summaries and are not screened.
  *
  * Schedules (the verdicts are identical):
  *   APRIL_SCHED_PLAIN    one wavefront per pair; the three joins run as

@@ -461,6 +461,7 @@ int build_collection(const std::vector<LatticeGrid> &lg, GridOf gid, const april
     if (!L) return fail(APRIL_E_NOMEM, "out of host memory");
     try {
         L->grid = desc;
+        L->sound = true;
         L->partition_key = key;
         L->n = n;
         L->off_a.resize(n + 1);

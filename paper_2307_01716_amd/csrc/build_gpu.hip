@@ -1070,6 +1070,7 @@ int april::build_lists_gpu(const april_grid_t *grid, const double *xy, const uin
     L->n_f = n_f;
     L->device = dev;
     L->codec = APRIL_CODEC_RAW;
+    L->sound = true;
     L->max_len = uint32_t(std::min<uint64_t>(last[1], 0xfffffffeull));
     if (int rc = summaries ? launch_summaries(L, last[2], L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)
                            : APRIL_OK) {

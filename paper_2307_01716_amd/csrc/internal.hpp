@@ -83,6 +83,9 @@ struct april_lists {
     // object's A- or F-list (0xffffffff: not known), which tells the filter
     // whether any pair can reach its workgroup bin
     uint32_t max_len = 0xffffffffu;
+    // known to be what april_lists_from_arrays asks for (built, validated or
+    // checked at upload); only such lists are screened
+    bool sound = false;
     // host copy (empty for device lists)
     std::vector<uint64_t> off_a, off_f;
     std::vector<uint32_t> start_a, end_a, start_f, end_f;
@@ -197,6 +200,9 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
 int launch_summaries(april_lists_t *L, uint64_t longer, const uint32_t *as, const uint32_t *ae, const uint32_t *fs,
                      const uint32_t *fe, hipStream_t stream);
 int launch_line_summaries(april_cells_t *C, hipStream_t stream);
+// *bad (zero before the call) |= 1 unless the lists are what april_lists_from_arrays asks for.
+int launch_check_lists(uint64_t n, const uint64_t *off_a, const uint32_t *as, const uint32_t *ae, const uint64_t *off_f,
+                       const uint32_t *fs, const uint32_t *fe, unsigned int *bad, hipStream_t stream);
 // stats[0] = the most intervals in one list, stats[1] = A-lists of kExact intervals or more
 // (both zero before the call).
 int launch_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, unsigned long long *stats,

@@ -199,6 +199,7 @@ int april_lists_from_arrays(const april_grid_t *grid, uint64_t n, const uint64_t
     try {
         L->grid = *grid;
         L->n = n; L->n_a = na; L->n_f = nf;
+        L->sound = validate != 0;
         L->off_a.assign(off_a, off_a + n + 1);
         L->off_f.assign(off_f, off_f + n + 1);
         L->start_a.assign(start_a, start_a + na);
@@ -249,6 +250,7 @@ int april_lists_download(const april_lists_t *d, void *stream, april_lists_t **o
         L->grid = d->grid;
         L->partition_key = d->partition_key;
         L->n = d->n; L->n_a = d->n_a; L->n_f = d->n_f;
+        L->sound = d->sound;
         L->off_a.resize(d->n + 1);
         L->off_f.resize(d->n + 1);
         L->start_a.resize(d->n_a); L->end_a.resize(d->n_a);

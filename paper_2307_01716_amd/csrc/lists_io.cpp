@@ -294,6 +294,7 @@ int april_lists_load(const char *path, int validate, april_lists_t **out) {
     L->grid = grid;
     L->partition_key = key;
     L->n = n; L->n_a = na; L->n_f = nf;
+    L->sound = validate != 0;
     *out = L;
     return APRIL_OK;
 }

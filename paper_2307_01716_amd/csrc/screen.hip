@@ -3,10 +3,11 @@
 //
 // Every object of a device collection has a summary of 64 intervals, one per
 // lane of a wavefront, made once when the lists are uploaded or built:
-//   TF, lanes 0..31   its 32 longest F-intervals (those that lie inside an
-//                     A-interval, which APRIL's all do);
+//   TF, lanes 0..31   its 32 longest F-intervals, each inside an A-interval;
 //   H, lanes 32..63   its hull: the A-list with all but its 31 widest gaps
 //                     closed, so every A-interval lies in one of 32.
+// (Lists are sorted and disjoint and F lies inside A: those that were not
+// validated are checked at upload, and have no summaries where it is otherwise.)
 // Against the A-list of the other object, X, these give two one-sided tests:
 //   - a TF interval that overlaps A(X): that is an AF overlap, and, as it lies
 //     in an A-interval, an AA overlap too: Alg. 2 answers true hit;
@@ -166,7 +167,6 @@ struct SumLds {
     uint32_t sum[2 * kSumEntries];   // (start, end) pairs
     uint32_t coarse[kTable];
     uint32_t part[16][2];
-    uint32_t outside;                // some F-interval lies in no hull interval
 };
 
 // The hull of X.A with K gaps kept: hull interval i ends at the i-th kept gap
@@ -198,7 +198,6 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
     const uint32_t na = uint32_t(b.A.off[k + 1] - a0), nf = b.sample ? 0u : uint32_t(b.F.off[k + 1] - f0);
     const uint32_t *as = b.A.s + a0, *ae = b.A.e + a0, *fs = b.F.s + f0, *fe = b.F.e + f0;
     group_sync<W>();
-    if (tid == 0) l.outside = 0;
     for (uint32_t i = tid; i < 2 * kSumEntries; i += 64 * W) l.sum[i] = (i & 1) ? 0u : 0xffffffffu;
     if (slot != kNoSlot)
         for (uint32_t i = tid; i < kTable; i += 64 * W) l.coarse[i] = 0xffffffffu;
@@ -239,48 +238,12 @@ __device__ void summarize(const SumBuild &b, uint64_t k, uint32_t slot, SumLds &
         }, l.part, w, lane);
     }
     group_sync<W>();
-    // Within joins take an interval outside the hull for one outside F, so no
-    // F-interval may lie there (lists that were not validated may hold such):
-    // the last hull interval that starts at or below each one's start.
-    if (!b.sample) {
-        bool out = false;
-        for (uint32_t j = tid; j < nf; j += 64 * W) {
-            const uint32_t s = fs[j], *h = l.sum + kSumEntries;
-#pragma unroll
-            for (uint32_t step = kSumHalf / 2; step > 0; step >>= 1) h = h[2 * step] <= s ? h + 2 * step : h;
-            out |= h[0] > s || h[1] < fe[j];
-        }
-        if (__any(out) && lane == 0) l.outside = 1;
-        group_sync<W>();
-    }
-    const bool none = l.outside != 0;
-    // an F-interval counts only inside an A-interval (for the same reason): the
-    // first A-interval that ends above its start
-    auto in_a = [&](uint32_t s, uint32_t e) {
-        uint32_t lo = 0, hi = na;
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (ae[mid] > s) hi = mid;
-            else lo = mid + 1;
-        }
-        return lo < na && as[lo] <= s && ae[lo] >= e;
-    };
     if (w == 0) {
-        uint32_t s = l.sum[2 * lane], e = l.sum[2 * lane + 1];
-        if (lane < kSumHalf && e != 0 && !b.sample && (none || !in_a(s, e))) e = 0;
         const uint64_t at = b.by_slot ? slot : k;
-        b.sum[at * kSumEntries + lane] = (uint64_t(e) << 32) | s;
+        b.sum[at * kSumEntries + lane] = (uint64_t(l.sum[2 * lane + 1]) << 32) | l.sum[2 * lane];
     }
-    if (slot != kNoSlot) {
-        if (w == 0)
-            for (uint32_t i = 4 * kCoarse + lane; i < 5 * kCoarse; i += 64)
-                if (l.coarse[i] != 0xffffffffu && !in_a(l.coarse[i + kCoarse], l.coarse[i]))
-                    l.coarse[i] = l.coarse[i + kCoarse] = 0xffffffffu;
-        group_sync<W>();
+    if (slot != kNoSlot)
         for (uint32_t i = tid; i < kTable; i += 64 * W) b.coarse[uint64_t(slot) * kTable + i] = l.coarse[i];
-        // (the compressed join takes what lies outside the hull for outside F too)
-        if (none && b.by_slot && tid == 0) b.slot[k] = kNoSlot;
-    }
 }
 
 // Objects whose lists one wave summarizes; the others are queued.  Numbers
@@ -594,6 +557,32 @@ __global__ __launch_bounds__(kBlock, MODE == kLines ? 4 : 8) void k_screen(Scree
     }
 }
 
+// A wave per object: are its lists sorted, disjoint, of no empty interval, and
+// its F-intervals inside A-intervals?
+__global__ __launch_bounds__(kBlock) void k_check_lists(ListView A, ListView F, uint64_t n, unsigned int *bad) {
+    const uint32_t lane = threadIdx.x & 63, w = uniform(threadIdx.x >> 6);
+    const uint64_t waves = uint64_t(gridDim.x) * kWavesPerBlock;
+    bool wrong = false;
+    for (uint64_t k = uint64_t(blockIdx.x) * kWavesPerBlock + w; k < n; k += waves) {
+        const uint64_t a0 = A.off[k], a1 = A.off[k + 1], f1 = F.off[k + 1];
+        auto check = [&](const ListView &L, uint64_t t, uint64_t end) {
+            wrong |= L.s[t] >= L.e[t] || (t + 1 < end && L.e[t] > L.s[t + 1]);
+        };
+        for (uint64_t t = a0 + lane; t < a1; t += 64) check(A, t, a1);
+        for (uint64_t t = F.off[k] + lane; t < f1; t += 64) {
+            check(F, t, f1);
+            uint64_t lo = a0, hi = a1;   // the first A-interval that ends at or above F's end
+            while (lo < hi) {
+                const uint64_t mid = (lo + hi) >> 1;
+                if (A.e[mid] >= F.e[t]) hi = mid;
+                else lo = mid + 1;
+            }
+            wrong |= lo == a1 || A.s[lo] > F.s[t];
+        }
+    }
+    if (__any(wrong) && lane == 0) atomicOr(bad, 1u);
+}
+
 __global__ void k_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, unsigned long long *stats) {
     const uint32_t lane = threadIdx.x & 63;
     unsigned long long longest = 0, longer = 0;
@@ -618,6 +607,14 @@ int launch_list_stats(const uint64_t *off_a, const uint64_t *off_f, uint64_t n, 
                       hipStream_t stream) {
     k_list_stats<<<dim3(uint32_t(std::min<uint64_t>((n + 255) / 256, 256))), dim3(256), 0, stream>>>(off_a, off_f, n,
                                                                                                    stats);
+    APRIL_HIP_TRY(hipGetLastError());
+    return APRIL_OK;
+}
+
+int launch_check_lists(uint64_t n, const uint64_t *off_a, const uint32_t *as, const uint32_t *ae, const uint64_t *off_f,
+                       const uint32_t *fs, const uint32_t *fe, unsigned int *bad, hipStream_t stream) {
+    k_check_lists<<<dim3(uint32_t(std::min<uint64_t>((n + 3) / 4, 4096))), dim3(kBlock), 0, stream>>>(
+        {off_a, as, ae}, {off_f, fs, fe}, n, bad);
     APRIL_HIP_TRY(hipGetLastError());
     return APRIL_OK;
 }

@@ -8,6 +8,30 @@
 
 using namespace april;
 
+// Lists that were not validated are checked on the device.  Screening takes
+// lists for what april.h asks for; on others (F-intervals outside A, unsorted
+// or overlapping intervals) the joins may answer otherwise than the summaries
+// would, so those have none.
+static int check_sound(april_lists_t *L, const uint32_t *as, const uint32_t *ae, const uint32_t *fs,
+                       const uint32_t *fe, hipStream_t s) {
+    if (L->sound || L->n == 0) return APRIL_OK;
+    unsigned int *d_bad = nullptr, bad[2] = {0, 0};
+    if (hipMalloc(reinterpret_cast<void **>(&d_bad), sizeof(bad)) != hipSuccess) {
+        (void)hipGetLastError();
+        return APRIL_OK;   // not known: no summaries
+    }
+    hipError_t e = hipMemcpyAsync(d_bad, bad, sizeof(bad), hipMemcpyHostToDevice, s);
+    int rc = APRIL_OK;
+    if (e == hipSuccess) rc = launch_check_lists(L->n, L->d.off_a, as, ae, L->d.off_f, fs, fe, d_bad, s);
+    if (e == hipSuccess && !rc) e = hipMemcpyAsync(bad, d_bad, sizeof(bad), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess && !rc) e = hipStreamSynchronize(s);
+    (void)hipFree(d_bad);
+    if (rc) return rc;
+    if (e != hipSuccess) return fail(APRIL_E_HIP, std::string("upload: ") + hipGetErrorString(e));
+    L->sound = bad[0] == 0;
+    return APRIL_OK;
+}
+
 // The summaries of an uploaded collection.  Compressed lists are decoded on
 // the device for it, into memory that is given back; without room for that
 // they have none.
@@ -16,9 +40,11 @@ static int upload_summaries(const april_lists_t *h, april_lists_t *L, hipStream_
     uint64_t longer = 0;
     for (uint64_t k = 0; k < h->n; k++) longer += h->off_a[k + 1] - h->off_a[k] >= (raw ? kExact : kVbyteSummaryMin);
     if (raw) {
+        if (int rc = check_sound(L, L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)) return rc;
         // (waited for: the copies from pageable memory have landed by now, and
         // a call on another stream would read summaries that are not written yet)
-        if (int rc = launch_summaries(L, longer, L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)) return rc;
+        if (L->sound)
+            if (int rc = launch_summaries(L, longer, L->d.start_a, L->d.end_a, L->d.start_f, L->d.end_f, s)) return rc;
         APRIL_HIP_TRY(hipStreamSynchronize(s));
         return APRIL_OK;
     }
@@ -32,7 +58,8 @@ static int upload_summaries(const april_lists_t *h, april_lists_t *L, hipStream_
     uint32_t *as = static_cast<uint32_t *>(tmp), *ae = as + na, *fs = ae + na, *fe = fs + nf;
     int rc = launch_decode_lists(L, false, as, ae, s);
     if (!rc) rc = launch_decode_lists(L, true, fs, fe, s);
-    if (!rc) rc = launch_summaries(L, longer, as, ae, fs, fe, s);
+    if (!rc) rc = check_sound(L, as, ae, fs, fe, s);
+    if (!rc && L->sound) rc = launch_summaries(L, longer, as, ae, fs, fe, s);
     const hipError_t e = hipStreamSynchronize(s);
     (void)hipFree(tmp);
     if (!rc && e != hipSuccess) return fail(APRIL_E_HIP, std::string("summaries: ") + hipGetErrorString(e));
@@ -54,6 +81,7 @@ extern "C" int april_lists_to_device(const april_lists_t *h, uint32_t codec, voi
     L->n = h->n; L->n_a = h->n_a; L->n_f = h->n_f;
     L->device = dev;
     L->codec = codec;
+    L->sound = h->sound;
     uint64_t longest = 0;
     for (uint64_t k = 0; k < h->n; k++)
         longest = std::max({longest, h->off_a[k + 1] - h->off_a[k], h->off_f[k + 1] - h->off_f[k]});
