@@ -1,11 +1,12 @@
-"""Screened polygon-linestring calls: lists whose F-intervals lie outside A."""
+"""Polygon-linestring calls at the edges of screening's parts and lists of open
+pairs, and on lists whose F-intervals lie outside A."""
 
 import numpy as np
 import pytest
 
 import oracle
 from synth.grid import Grid
-from synth.intervals import ListSet, random_lists
+from synth.intervals import ListSet, random_lists, sub_lists
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +61,44 @@ def test_f_outside_a(sizes):
     v, counts = call(P, C, dev(p), dev(l))
     assert torch.equal(v, torch.cat([x[0] for x in parts]))
     assert counts == [sum(x) for x in zip(*(x[1] for x in parts))]
+
+
+@pytest.mark.parametrize("sizes", [[62, 63, 64, 255, 256, 257], [1, 40, 700, 2047, 2049, 5000]])
+def test_in_parts(sizes):
+    """More pairs than are screened at a time: the same ones over and over."""
+    print(f"[lines] parts {sizes}", flush=True)
+    rng = np.random.default_rng(50 + len(sizes) + sizes[0])
+    A = [random_lists(rng, sizes[k % len(sizes)], 0, IDS if k % 2 else max(16 * sizes[k % len(sizes)], IDS >> 4))
+         for k in range(24)]
+    P, LP = polygons(A, [sub_lists(rng, *a, p=0.3) for a in A])
+    C, LC = walks(rng, 24)
+    p, l = (rng.integers(0, 24, 9001).astype(np.uint32) for _ in range(2))
+    p.sort()
+    want = oracle.filter_linestrings(LP, LC, p, l)
+    assert set(np.unique(want)) == {0, 1, 2}
+    times = (1 << 24) // len(p) + 7
+    v, counts = call(P, C, dev(p).repeat(times), dev(l).repeat(times))
+    assert bool((v.view(times, -1) == torch.from_numpy(want).cuda()).all())
+    assert counts == (np.bincount(want, minlength=3) * times).tolist()
+
+
+@pytest.mark.parametrize("sizes, n", [([3, 40], 70_000), ([3], 1_100_000), ([600], 300_000), ([600], 600_000),
+                                      ([3, 600], 1_200_000)])
+def test_open_lists(sizes, n):
+    """Every pair is left open (no F-intervals, a cell that all meet): lists that
+    hold them all, and lists of either kind that overflow."""
+    print(f"[lines] open {sizes} {n}", flush=True)
+    rng = np.random.default_rng(n)
+    C, LC = walks(rng, 8)
+    cell = np.uint32(LC.ids[0])
+    none = (np.zeros(0, np.uint32), np.zeros(0, np.uint32))
+    A = []
+    for k in range(40):
+        m = sizes[k % len(sizes)]
+        s = np.unique(np.append(rng.choice(IDS // 8, m, replace=False).astype(np.uint32) * 8 + 1, cell))
+        A.append((s, s + np.uint32(1)))
+    P, _ = polygons(A, [none] * 40)
+    p = rng.integers(0, 40, n).astype(np.uint32)
+    v, counts = call(P, C, dev(p), dev(np.zeros(n, np.uint32)))
+    assert int((v != april.INDECISIVE).sum()) == 0
+    assert counts == [0, 0, n]
