@@ -222,7 +222,10 @@ int april_lists_load(const char *path, int validate, april_lists_t **out);
                                     earliest and latest wavefront end of its wave kernel, and the
                                     earliest and latest wavefront end of its workgroup-bin kernel
                                     (~0 and 0 when it does not run); a
-                                    kernel's latest end - earliest end is its tail */
+                                    kernel's latest end - earliest end is its tail.
+                                    Calls of more than 2^23 pairs are joined in parts
+                                    where they are screened: then the ends are those
+                                    of the last part's kernels */
 #define APRIL_WAVE_TIMES_OFFSET 24448u
 #define APRIL_WS_DECODE_CACHE 2u /* compressed lists: the workspace also holds the decode
                                     cache (april_filter_workspace_size counts it when this

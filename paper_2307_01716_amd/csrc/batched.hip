@@ -98,7 +98,7 @@ struct BatchArgs {
     unsigned int *qhead;         // queue entries taken by workgroups: qhead[k * kCtrStride]
     uint32_t *queue;             // XCD k's queue: queue[k * qcap ...]
     OpenLists open;              // screened: the open pairs (pairs null: found by a scan)
-    unsigned long long *times;   // APRIL_WAVE_TIMES: call start; first, last end of the wave
+    unsigned long long *times;   // APRIL_WAVE_TIMES: call start; first, last end of the last wave
                                  // kernel; first, last end of the workgroup kernel (or null)
 };
 
@@ -1108,6 +1108,14 @@ __global__ __launch_bounds__(kBlock) void k_wg(BatchArgs b) {
     if (b.times && lane == 0) wave_ended(b.times + 3);
 }
 
+// Has a list of open pairs been too short for its pairs?  Whole wave.
+__device__ __forceinline__ bool lists_full(const OpenLists &open, uint32_t xcds, uint32_t lane) {
+    const bool lng = lane >= kTilesCtr;   // (a lane for each list)
+    const uint32_t k = lane & (kTilesCtr - 1);
+    const uint32_t fill = k < xcds ? (lng ? open.long_fill : open.fill)[k * kCtrStride] : 0u;
+    return __any(fill > (lng ? open.long_cap : open.cap));
+}
+
 template <int TILE, int C, int MODE>
 // Register budget: 8 waves per SIMD where LDS allows it (TILE <= 256).
 // The hardware allocates SGPRs in blocks of 16, and above 80 SGPRs fewer
@@ -1119,13 +1127,8 @@ void k_batched(BatchArgs b) {
     __shared__ uint32_t lds_words[kWavesPerBlock * 4 * TILE];
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t w = uniform(threadIdx.x >> 6);
-    if (MODE != kMixedOrders && b.open.pairs) {
-        // the open pairs have been joined, unless a list was full
-        const bool lng = lane >= kTilesCtr;
-        const uint32_t k = lane & (kTilesCtr - 1);
-        const uint32_t fill = k < b.xcds ? (lng ? b.open.long_fill : b.open.fill)[k * kCtrStride] : 0u;
-        if (!__any(fill > (lng ? b.open.long_cap : b.open.cap))) return;
-    }
+    // the open pairs have been joined, unless a list was full
+    if (MODE != kMixedOrders && b.open.pairs && !lists_full(b.open, b.xcds, lane)) return;
     unsigned long long c_tn = 0, c_th = 0, c_ind = 0;
     const uint32_t xcds = b.xcds;
     const uint32_t my_xcd = blockIdx.x % xcds;
@@ -1393,7 +1396,8 @@ void k_open(BatchArgs b) {
         const unsigned long long v[3] = {c_tn, c_th, c_ind};
         if (lane == 0) add_totals(b.xhead, blockIdx.x * kWavesPerBlock + w, v, 3);
     }
-    if (b.times && lane == 0) wave_ended(b.times + 1);
+    // (where pairs are left to the kernel above, its waves end last)
+    if (b.times && !lists_full(b.open, xcds, lane) && lane == 0) wave_ended(b.times + 1);
 }
 
 template <int TILE, int C, int MODE = kAlg2>
@@ -1602,6 +1606,7 @@ static int screened_join(BatchArgs b, hipStream_t stream, uint64_t most, S scree
     if (int rc = open_lists(b, stream)) return rc;
     b.screened = 1;
     const FilterArgs a = b.f;
+    unsigned long long *const times = b.times;
     const uint64_t parts = b.open.pairs ? (a.n_pairs + most - 1) / most : 1;
     for (uint64_t k = 0; k < parts; k++) {
         const uint64_t lo = a.n_pairs / parts * k, hi = k + 1 < parts ? a.n_pairs / parts * (k + 1) : a.n_pairs;
@@ -1610,6 +1615,8 @@ static int screened_join(BatchArgs b, hipStream_t stream, uint64_t most, S scree
         b.f.verdict = a.verdict + lo;
         b.f.n_pairs = hi - lo;
         b.more = k + 1 < parts;
+        // (earliest and latest ends over several parts would be no kernel's tail)
+        b.times = b.more ? nullptr : times;
         if (k) {
             k_zero_lists<<<1, 2 * kMaxCtrs, 0, stream>>>(b.xhead, b.qfill);
             APRIL_HIP_TRY(hipGetLastError());
