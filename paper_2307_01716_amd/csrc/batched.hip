@@ -72,6 +72,8 @@ constexpr uint32_t kNone = 0xffffffffu;    // no resident object / no upper key 
 // Most pairs a wave takes at a time when they are screened (the offsets of
 // the open ones are kept as bytes).
 constexpr uint32_t kScreenGrab = 256;
+// And where more than a quarter of them are open, and near a range's end.
+constexpr uint32_t kDenseGrab = 32, kDenseTail = 8;
 
 // Turns of a wave, about, in a list of open pairs; most pairs a turn.
 constexpr uint32_t kListGrabs = 4, kListGrab = 16;
@@ -85,6 +87,7 @@ struct BatchArgs {
     uint32_t grab;               // pairs per grab (<= 64)
     uint32_t tail_grab;          // pairs per grab near a range's end
     uint64_t tail_pairs;         // "near the end": fewer pairs than this left
+    uint64_t dense_tail;         // the same for grabs of kDenseGrab
     uint32_t shift_r, shift_s;   // mixed orders: bits dropped from the finer side's A
     // workgroup bin (Alg. 2 only): pairs whose shorter object spans at least
     // wg_min intervals in a list (kNone: no workgroup bin)
@@ -1145,7 +1148,7 @@ void k_batched(BatchArgs b) {
 
     // ---- pairs in input order: each XCD drains its own contiguous range,
     // then helps the others
-    uint32_t grab = b.grab;
+    uint32_t grab = MODE != kMixedOrders && b.screened && !b.fixed ? kDenseGrab : b.grab;
     for (uint32_t k = 0; k < xcds; k++) {
         const uint32_t seg = (my_xcd + k) % xcds;
         const uint64_t lo = b.f.n_pairs * seg / xcds, hi = b.f.n_pairs * (seg + 1) / xcds;
@@ -1176,7 +1179,7 @@ void k_batched(BatchArgs b) {
             if (g0 >= hi) break;
             const uint64_t g1 = min(hi, g0 + grab);
             if (pb->fixed) grab = 0;
-            else if (hi - g1 < pb->tail_pairs) grab = pb->tail_grab;
+            else if (!pb->screened && hi - g1 < pb->tail_pairs) grab = pb->tail_grab;
             // Screened: the grab's open pairs (few of them) are collected first, as
             // offsets from g0, so that a round of the loop below has a pair for
             // most lanes.
@@ -1188,13 +1191,20 @@ void k_batched(BatchArgs b) {
                 wave_lds_sync();
 #pragma unroll
                 for (uint32_t q = 0; q < kScreenGrab; q += 64) {
-                    const bool open = q + lane < n_open && vb[q + lane] == kPending;
+                    const uint32_t was = q + lane < n_open ? vb[q + lane] : 0u;
+                    const bool open = was == kPending || was == kListed;
                     const uint64_t m = __ballot(open);
                     if (open) open_at[w][cnt + uint32_t(__popcll(m & ((1ull << lane) - 1)))] = uint8_t(q + lane);
                     cnt += uint32_t(__popcll(m));
                 }
                 wave_lds_sync();
                 n_open = cnt;
+                // where most pairs are open, grabs as of calls that are not screened
+                if (!pb->fixed) {
+                    const bool dense = 4 * n_open > uint32_t(g1 - g0);
+                    const bool tail = hi - g1 < (dense ? pb->dense_tail : pb->tail_pairs);
+                    grab = dense ? (tail ? kDenseTail : kDenseGrab) : tail ? pb->tail_grab : min(2 * grab, pb->grab);
+                }
             }
             for (uint32_t o0 = 0; o0 < n_open; o0 += 64) {
             const bool in = o0 + lane < n_open;
@@ -1308,6 +1318,10 @@ void k_open(BatchArgs b) {
     __shared__ uint32_t turns[2];
     if (threadIdx.x < 2) turns[threadIdx.x] = 0;
     __syncthreads();
+    // (a list was full: all pairs are left to k_batched, which has to read every
+    // verdict then anyway: of the 2.2M pairs of adjacent polygons in screen.hip
+    // the lists hold 0.8M, and both kernels took 1.50 ms, k_batched alone 1.36)
+    if (lists_full(b.open, xcds, lane)) return;
     // the long pairs' lists, then the others
     for (uint32_t half = 0; half < 2; half++) {
         uint32_t first, hi, grab, before;   // this part of all lists end to end; lane k: entries before XCD k's list
@@ -1396,8 +1410,7 @@ void k_open(BatchArgs b) {
         const unsigned long long v[3] = {c_tn, c_th, c_ind};
         if (lane == 0) add_totals(b.xhead, blockIdx.x * kWavesPerBlock + w, v, 3);
     }
-    // (where pairs are left to the kernel above, its waves end last)
-    if (b.times && !lists_full(b.open, xcds, lane) && lane == 0) wave_ended(b.times + 1);
+    if (b.times && lane == 0) wave_ended(b.times + 1);
 }
 
 template <int TILE, int C, int MODE = kAlg2>
@@ -1429,7 +1442,9 @@ int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
         bb.tail_grab = std::max(8u, bb.grab / 4);
     }
     // a range is near its end once its waves have about two full grabs each left
-    bb.tail_pairs = 2ull * bb.grab * kWavesPerBlock * ((blocks + b.xcds - 1) / b.xcds);
+    const uint64_t per_xcd = kWavesPerBlock * ((blocks + b.xcds - 1) / b.xcds);
+    bb.tail_pairs = 2ull * bb.grab * per_xcd;
+    bb.dense_tail = 2ull * kDenseGrab * per_xcd;
     if (MODE == kAlg2 && b.wg_min != kNone) {
         const uint64_t bin_blocks = std::min<uint64_t>((b.f.n_pairs + 255) / 256, uint64_t(cus) * 8);
         if (b.open.pairs) k_bin_open<<<dim3(32, b.xcds), dim3(256), 0, stream>>>(bb, TILE);
