@@ -1428,9 +1428,11 @@ int launch_tc(const BatchArgs &b, int cus, uint32_t waves, hipStream_t stream) {
     if (waves) blocks = std::max<uint64_t>(1, (waves + kWavesPerBlock - 1) / kWavesPerBlock);
     BatchArgs bb = b;
     if (b.fixed) {
-        // (at most kSmallCall pairs, so at most 8 or so a wave)
+        // at most kSmallCall pairs: 8 a wave on 256 CUs with 8 workgroups each, 16
+        // with 4 (512-interval tiles); never more than k_batched's list of a grab holds
         const uint64_t range = (b.f.n_pairs + b.xcds - 1) / b.xcds, per_xcd = std::max<uint64_t>(1, blocks / b.xcds);
         bb.fixed = uint32_t(std::max<uint64_t>(1, (range + per_xcd * kWavesPerBlock - 1) / (per_xcd * kWavesPerBlock)));
+        bb.fixed = std::min(bb.fixed, kScreenGrab);
         const uint64_t per_block = uint64_t(bb.fixed) * kWavesPerBlock;
         blocks = b.xcds * std::max<uint64_t>(1, (range + per_block - 1) / per_block);
         bb.grab = bb.fixed;

@@ -59,7 +59,8 @@ struct DeviceArrays {
 // Entries of an object's summary (screen.hip).
 constexpr uint32_t kSumEntries = 64;
 // A-lists of fewer intervals are screened against as they are; longer ones
-// have a coarse table of 3 KiB, three eighths of such lists (A and F) at most.
+// have a coarse table of 3 KiB: three eighths of such lists at most where the
+// F-list is as long, three quarters where there is none (thin polygons).
 constexpr uint32_t kExact = 512;
 // Compressed lists: objects of fewer A-intervals have neither summary nor
 // table (3.5 KiB; such a list and its F-list take about 4.8 KiB), so
