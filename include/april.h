@@ -304,7 +304,8 @@ int april_filter_workspace_size(uint64_t n_pairs, const april_filter_opts_t *opt
  *                        decode cache (64 KiB per wavefront, 512 MiB on 256
  *                        CUs) that keeps R objects of up to 4,096 intervals
  *                        per list decoded while consecutive pairs share
- *                        them.  With APRIL_WS_DECODE_CACHE the cache is the
+ *                        them (in calls that are screened: while many pairs
+ *                        that stay open do).  With APRIL_WS_DECODE_CACHE the cache is the
  *                        workspace's tail; else the call takes it from the
  *                        stream (stream-ordered), and when that allocation is
  *                        refused every pair decodes both objects (the

@@ -325,6 +325,13 @@ __device__ __forceinline__ void decode_all(const ListRef &X, uint32_t *xs, uint3
     }
 }
 
+// Screened calls decode an R object into the cache when so many of a grab's open
+// pairs share it; else each pair decodes only the blocks near the other object's
+// hull.  Adjacent polygons have up to 9 pairs each: 1.9M such pairs of 2,290
+// intervals take 22.9 ms by blocks and 31.3 through the cache.  R objects that
+// interleave with all of 48 others: 1.5M pairs of 4,000 intervals 46.6 and 32.6.
+constexpr uint32_t kCacheRun = 12;
+
 template <int TILE>
 __global__ __launch_bounds__(kBlock) void k_filter_vbyte(CArgs a) {
     __shared__ uint32_t lds[kWavesPerBlock][2 * TILE + 2 * 132];
@@ -350,10 +357,12 @@ __global__ __launch_bounds__(kBlock) void k_filter_vbyte(CArgs a) {
             const uint64_t g0 = lo + uniform(__shfl(got, 0));
             if (g0 >= hi) break;
             const uint32_t cnt = uint32_t(min<uint64_t>(a.grab, hi - g0));
-            uint64_t todo = __ballot(lane < cnt && (!a.screened || a.verdict[g0 + lane] == kPending));
+            const bool mine = lane < cnt && (!a.screened || a.verdict[g0 + lane] == kPending);
+            uint64_t todo = __ballot(mine);
+            const uint32_t r_lane = mine && a.screened && cap ? a.r[g0 + lane] : 0xffffffffu;
             while (todo) {
-                const uint64_t p = g0 + uint32_t(__builtin_ctzll(todo));
-                todo &= todo - 1;
+                const uint32_t at = uint32_t(__builtin_ctzll(todo));
+                const uint64_t p = g0 + at;
                 // the list arrays are read from the argument segment through a
                 // pointer the compiler cannot see through, so they hold no
                 // scalar registers between their uses
@@ -362,6 +371,7 @@ __global__ __launch_bounds__(kBlock) void k_filter_vbyte(CArgs a) {
                 const uint32_t r = uniform(a.r[p]), s = uniform(a.s[p]);
                 if (r >= a.n_r || s >= a.n_s) {
                     if (lane == 0) a.verdict[p] = APRIL_BAD_PAIR;
+                    todo &= todo - 1;
                     continue;
                 }
                 const uint32_t nar = uint32_t(a.Ar.off[r + 1] - a.Ar.off[r]);
@@ -369,7 +379,10 @@ __global__ __launch_bounds__(kBlock) void k_filter_vbyte(CArgs a) {
                 const uint32_t nas = uint32_t(a.As.off[s + 1] - a.As.off[s]);
                 const uint32_t nfs = uint32_t(a.Fs.off[s + 1] - a.Fs.off[s]);
                 uint8_t v;
-                if (max(nar, nfr) <= cap) {
+                const bool shared =
+                    !a.screened || r == cached || uint32_t(__popcll(__ballot(r_lane == r) & todo)) >= kCacheRun;
+                todo &= todo - 1;
+                if (max(nar, nfr) <= cap && shared) {
                     // R from the decode cache (decoded once while consecutive
                     // pairs share it), S streamed
                     if (r != cached) {
@@ -559,6 +572,8 @@ uint64_t vbyte_workspace_bytes() { return kCtrBytes; }
 // Intervals per list in a wave's decode cache (R objects with longer lists
 // decode per pair): 4 lists x 4 B x 4096 = 64 KiB per wave.
 constexpr uint32_t kCacheCap = 4096;
+// Fewest pairs for which a screened call allocates it.
+constexpr uint64_t kScreenedCache = 1ull << 22;
 // Blocks of the compressed filter's grid per CU.
 constexpr uint64_t kVbyteBlocksPerCu = 8;
 
@@ -623,27 +638,32 @@ int launch_filter_vbyte(const april_lists_t *R, const april_lists_t *S, const ui
         a.slot_s = S->d.slot;
         a.coarse_r = R->d.coarse;
         a.coarse_s = S->d.coarse;
-        // few pairs are left: four grabs per wave where there are enough
-        a.grab = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(8, n_pairs / (4 * blocks * kWavesPerBlock))));
     }
     // decode cache: cache_cap intervals per list for every wave of the grid,
     // from the caller's workspace (APRIL_WS_DECODE_CACHE) or stream-ordered;
     // without one (allocation refused) every pair decodes both objects.  Screened
-    // calls go without: two or three pairs of an R object are left, most of
-    // which end in its first tiles, and the 512 MiB are mapped anew after each
-    // synchronization (a partition of 8k x 8k objects: 0.77 ms a call, with
-    // the cache 0.88, and 1.22 when the host waits for each call)
+    // calls take what the caller gives, for R objects many of whose pairs are
+    // left (kCacheRun), but allocate one only when they are large: two or three
+    // pairs of an R object are left, most of which end in its first tiles, and
+    // the 512 MiB are mapped anew after each synchronization (0.35 ms a call)
     a.cache_cap = kCacheCap;
     a.cache = nullptr;
     bool own_cache = false;
     if (o.flags & APRIL_WS_DECODE_CACHE) {
-        if (!a.screened)
-            a.cache = reinterpret_cast<uint32_t *>(static_cast<char *>(o.d_workspace) + vbyte_cache_offset());
-    } else if (!a.screened && hipMallocAsync(reinterpret_cast<void **>(&a.cache), cache_bytes, stream) == hipSuccess) {
-        own_cache = true;
-    } else if (!a.screened) {
-        (void)hipGetLastError();
-        a.cache = nullptr;
+        a.cache = reinterpret_cast<uint32_t *>(static_cast<char *>(o.d_workspace) + vbyte_cache_offset());
+    } else if (!a.screened || n_pairs >= kScreenedCache) {
+        if (hipMallocAsync(reinterpret_cast<void **>(&a.cache), cache_bytes, stream) == hipSuccess) {
+            own_cache = true;
+        } else {
+            (void)hipGetLastError();
+            a.cache = nullptr;
+        }
+    }
+    // screened: few pairs are left, so four grabs per wave where there are enough
+    // (from 2^20 pairs on, room for the runs that the cache takes)
+    if (a.screened) {
+        const uint64_t per_wave = n_pairs / (blocks * kWavesPerBlock);
+        a.grab = uint32_t(std::min<uint64_t>(64, std::max<uint64_t>(a.cache && per_wave >= 128 ? 16 : 8, per_wave / 4)));
     }
     switch (tile) {
         case 256: k_filter_vbyte<256><<<dim3(uint32_t(blocks)), dim3(kBlock), 0, stream>>>(a); break;
