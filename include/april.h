@@ -116,8 +116,9 @@ int april_build_lists(const april_grid_t *grid, const double *xy, const uint64_t
  * april_build_lists(...), APRIL_CODEC_RAW).
  *   grid, xy, vtx_off, n_polys, flags  as for april_build_lists
  *   hip_stream  the stream the work runs on; the call returns when the lists
- *               are complete (it synchronizes the stream twice, to size the
- *               output) and frees its stream-ordered scratch
+ *               are complete, for any stream (it synchronizes hip_stream to
+ *               size its buffers and at the end), and frees its
+ *               stream-ordered scratch
  *   out         receives device-resident raw lists; free with april_lists_free
  * Errors: as april_build_lists (the first failing polygon is reported), and
  * APRIL_E_INVALID for n_polys >= 2^31, APRIL_E_HIP, APRIL_E_NODEV.

@@ -1,0 +1,75 @@
+"""Polygons of many blocks of 64 x 64 cells, whose empty blocks are left out,
+against the host builder, bit for bit: slivers, rings, combs and stars, about
+the number of blocks from which that is done, on grids that need 64-bit and
+128-bit products, with vertices on lines of blocks and anywhere."""
+
+import numpy as np
+import pytest
+
+from synth.polygons import LATTICE, PolygonSet
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_2307_01716_amd import april  # noqa: E402
+
+ORDER = 13
+TOP = (1 << ORDER) - 2.0   # cells
+
+
+def sliver(rng, length):
+    a = rng.uniform(0, 2 * np.pi) if rng.random() < 0.7 else rng.integers(0, 4) * np.pi / 2
+    d, p = np.array([np.cos(a), np.sin(a)]) * length / 2, np.array([-np.sin(a), np.cos(a)]) * rng.uniform(0.5, 70)
+    return np.array([-d - p, d - p, d + p, -d + p])
+
+
+def ring(rng, radius):
+    """An open ring, 1 to 40 cells wide."""
+    t, width = np.linspace(0, rng.uniform(3, 6.1), int(rng.integers(20, 300))), rng.uniform(1, 40)
+    u = np.stack([np.cos(t), np.sin(t)], 1)
+    return np.concatenate([radius * u, (radius - width) * u[::-1]])
+
+
+def comb(rng, size):
+    n = int(rng.integers(3, 40))
+    x = np.linspace(-size / 2, size / 2, 2 * n)
+    top = np.stack([np.repeat(x, 2), np.tile([-size / 2 + 20, size / 2, size / 2, -size / 2 + 20], n)], 1)
+    return np.concatenate([top[::-1], [[-size / 2, -size / 2], [size / 2, -size / 2]]])
+
+
+def star(rng, radius):
+    n = int(rng.integers(3, 700))
+    t = 2 * np.pi * np.arange(n) / n
+    r = radius * (1 - rng.uniform(0, 0.9) * rng.random(n))
+    return np.stack([r * np.cos(t), r * np.sin(t)], 1)
+
+
+# 16 x 16 blocks are 1,024 cells a side
+@pytest.mark.parametrize("kind", ["sliver", "ring", "comb", "star"])
+@pytest.mark.parametrize("w, quantum", [(1 << 14, 1), (1 << 14, 1 << 13), (1 << 21, 1), (1 << 10, 64 << 10), (8, 4)])
+def test_sparse(kind, w, quantum):
+    rng = np.random.default_rng(w % 1000 + quantum % 1000 + len(kind))
+    shapes = []
+    for size in (700, 960, 1000, 1024, 1090, 1500, 3000, 7800):
+        for _ in range(3):
+            s = {"sliver": lambda: sliver(rng, 1.2 * size), "ring": lambda: ring(rng, size / 2),
+                 "comb": lambda: comb(rng, size), "star": lambda: star(rng, size / 2)}[kind]()
+            lo, hi = s.min(0), s.max(0)
+            s *= min(1.0, (TOP - 4) / (hi - lo).max())
+            lo, hi = s.min(0), s.max(0)
+            c = 2 - lo + rng.random(2) * (TOP - 4 - (hi - lo))
+            if rng.random() < 0.4 and np.all(c + lo > 70):
+                c = np.floor(c / 64) * 64
+            v = np.round((s + c) * w / quantum) * quantum
+            v = np.clip(v, (1.001 * w // quantum + 1) * quantum, ((TOP + 0.999) * w // quantum - 1) * quantum)
+            keep = np.any(v != np.roll(v, 1, axis=0), axis=1)
+            if keep.sum() >= 3:
+                shapes.append(v[keep])
+    voff = np.concatenate([[0], np.cumsum([len(s) for s in shapes])]).astype(np.int64)
+    ps = PolygonSet(np.concatenate(shapes) * LATTICE, voff)
+    grid = (0.0, 0.0, float(w << ORDER) * LATTICE, ORDER)
+    print(f"[build rows] {kind}, cell {w}: {len(ps)} polygons, {len(ps.xy)} vertices", flush=True)
+    host = april.april_build_lists(grid, ps.xy, ps.voff, april.STRICT).export()
+    got = april.april_lists_download(april.april_build_lists_gpu(grid, ps.xy, ps.voff, april.STRICT)).export()
+    for name, x, y in zip(("offA", "sA", "eA", "offF", "sF", "eF"), host, got):
+        assert np.array_equal(x, y), name
