@@ -41,6 +41,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 KERNEL_SOURCES = {"k_batched": ["csrc/batched.hip", "csrc/device.hpp", "csrc/screen.hip"],
                   "k_filter_plain": ["csrc/filter.hip", "csrc/device.hpp", "csrc/screen.hip"],
                   "k_filter_vbyte": ["csrc/compressed.hip", "csrc/vbyte.hpp", "csrc/device.hpp", "csrc/screen.hip"]}
+HBM_PEAK_GBS = 8000.0
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 # Peak VALU issue rate of the device: 256 CUs x 4 SIMDs, each issuing one
 # wave64 VALU instruction every 4 cycles (16 lanes wide) at 2.4 GHz, i.e.
@@ -120,11 +121,12 @@ def _per_kernel(pmc_dir: str, counter: str, kernel: str):
     return got
 
 
-def traffic(fetch_dir: str, write_dir: str, kernel: str, copy_bytes: int = 1 << 30, parts=None):
+def traffic(fetch_dir: str, write_dir: str, kernel: str, copy_bytes: int = 1 << 30, parts=None, calls=None):
     """HBM bytes per launch of `kernel` from FETCH_SIZE / WRITE_SIZE runs, each
     scaled by the counter's reading for a copy of `copy_bytes` (which reads
     and writes copy_bytes).  With `parts` (kernel name prefixes), a launch is
-    one dispatch of each, and their per-dispatch averages are summed."""
+    one dispatch of each, and their per-dispatch averages are summed; with
+    `calls`, the run made that many launches of any number of dispatches."""
     kib = copy_bytes / 1024.0
     cf = _per_kernel(fetch_dir, "FETCH_SIZE", COPY_KERNEL)
     cw = _per_kernel(write_dir, "WRITE_SIZE", COPY_KERNEL)
@@ -139,10 +141,11 @@ def traffic(fetch_dir: str, write_dir: str, kernel: str, copy_bytes: int = 1 << 
     for part in parts or [kernel]:
         kf = _per_kernel(fetch_dir, "FETCH_SIZE", part)
         kw = _per_kernel(write_dir, "WRITE_SIZE", part)
-        per_part[part] = {"fetch_kib_raw": sum(kf) / len(kf), "write_kib_raw": sum(kw) / len(kw),
+        nf, nw = calls or len(kf), calls or len(kw)
+        per_part[part] = {"fetch_kib_raw": sum(kf) / nf, "write_kib_raw": sum(kw) / nw,
                           "dispatches": len(kf)}
-        fk += sum(kf) / len(kf)
-        wk += sum(kw) / len(kw)
+        fk += sum(kf) / nf
+        wk += sum(kw) / nw
         n = len(kf) if n is None else min(n, len(kf))
     fetch = fk * 1024.0 * f_factor
     write = wk * 1024.0 * w_factor
@@ -156,14 +159,15 @@ def traffic(fetch_dir: str, write_dir: str, kernel: str, copy_bytes: int = 1 << 
     return out
 
 
-def valu(pmc_dir: str, kernel: str, parts=None):
+def valu(pmc_dir: str, kernel: str, parts=None, calls=None):
     """VALU instructions (SQ_INSTS_VALU, wave64 instructions) per launch of
-    `kernel` (with `parts`: the sum of their per-dispatch averages)."""
+    `kernel` (with `parts`: the sum of their per-dispatch averages; with
+    `calls`: of all dispatches, over so many launches)."""
     total, n, per_part = 0.0, None, {}
     for part in parts or [kernel]:
         x = _per_kernel(pmc_dir, "SQ_INSTS_VALU", part)
-        per_part[part] = sum(x) / len(x)
-        total += sum(x) / len(x)
+        per_part[part] = sum(x) / (calls or len(x))
+        total += sum(x) / (calls or len(x))
         n = len(x) if n is None else min(n, len(x))
     out = {"insts_per_launch": total, "dispatches": n}
     if parts:
@@ -205,6 +209,21 @@ def read_valu(path: str, kernel: str, config: dict, pairs: int, kernel_ms: float
             "peak": VALU_ISSUE_PEAK, "unit": "wave64 VALU instructions/s", "frac": rate / VALU_ISSUE_PEAK}
 
 
+def roofline(ms: float, traffic, valu):
+    """The nearer of a call's two measured ceilings: HBM bytes (the traffic
+    record) over `ms` against HBM_PEAK_GBS, and vector issue (the VALU record).
+    Without records nothing is claimed.  Alg. 2's bytes are not part of it: a
+    screened call answers them without reading them."""
+    out = {"bound": None, "achieved": None, "peak": None, "unit": None, "frac": None, "traffic": traffic}
+    if traffic is not None:
+        rate = traffic / (ms / 1e3) / 1e9
+        out.update(bound="hbm", achieved=rate, peak=HBM_PEAK_GBS, unit="GB/s", frac=rate / HBM_PEAK_GBS)
+    if valu is not None and (out["frac"] is None or valu["frac"] > out["frac"]):
+        out.update(bound="valu_issue", achieved=valu["issue_rate"], peak=valu["peak"], unit=valu["unit"],
+                   frac=valu["frac"])
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     sub = ap.add_subparsers(dest="cmd", required=True)
@@ -214,6 +233,7 @@ def main():
     v.add_argument("--pmc", required=True, help="a --pmc SQ_INSTS_VALU output folder")
     v.add_argument("--kernel", default="k_batched")
     v.add_argument("--parts", default="")
+    v.add_argument("--calls", type=int, default=None)
     v.add_argument("--config", default="")
     v.add_argument("--pairs", type=int, required=True)
     v.add_argument("--command", default="")
@@ -224,6 +244,8 @@ def main():
     t.add_argument("--kernel", default="k_batched")
     t.add_argument("--parts", default="", help="kernel name prefixes of one launch, comma-separated "
                                                "(default: the kernel alone)")
+    t.add_argument("--calls", type=int, default=None, help="launches in the run, of any number of dispatches "
+                                                           "(default: a launch is one dispatch of each part)")
     t.add_argument("--config", default="")
     t.add_argument("--pairs", type=int, required=True)
     t.add_argument("--alg-bytes", type=int, default=0)
@@ -245,7 +267,7 @@ def main():
                           " ".join(f"{k}={x:.6g}" for k, x in sorted(v.items())))
     elif args.cmd == "valu":
         cfg = {k: int(x) for k, x in (kv.split("=") for kv in args.config.split(","))} if args.config else {}
-        va = valu(args.pmc, args.kernel, parts=[p for p in args.parts.split(",") if p] or None)
+        va = valu(args.pmc, args.kernel, parts=[p for p in args.parts.split(",") if p] or None, calls=args.calls)
         rec = {"kernel": args.kernel, "config": cfg, "pairs": args.pairs,
                "source_sha256": source_digest(args.kernel), "valu": va, "command": args.command}
         with open(args.out, "w") as f:
@@ -255,7 +277,7 @@ def main():
     else:
         cfg = {k: int(v) for k, v in (kv.split("=") for kv in args.config.split(","))} if args.config else {}
         tr = traffic(args.fetch, args.write, args.kernel,
-                     parts=[p for p in args.parts.split(",") if p] or None)
+                     parts=[p for p in args.parts.split(",") if p] or None, calls=args.calls)
         rec = {"kernel": args.kernel, "config": cfg, "pairs": args.pairs, "alg_bytes": args.alg_bytes,
                "source_sha256": source_digest(args.kernel), "traffic": tr, "command": args.command}
         with open(args.out, "w") as f:
