@@ -237,7 +237,7 @@ typedef struct {
     uint32_t flags;        /* APRIL_VALIDATE | APRIL_WS_DECODE_CACHE | APRIL_WAVE_TIMES */
     uint32_t waves;        /* resident wavefronts (0 = library default) */
     uint32_t tile;         /* batched: intervals per list kept in LDS per wavefront:
-                              128, 256 or 512 (0 = 256 when the two collections' A-lists
+                              128, 256 or 512 (0 = 256 when the A-lists of each collection
                               average at most 256 intervals, else 512; compressed lists:
                               256, 512, 1024, 0 = 512) */
     uint32_t chunk;        /* batched: streamed intervals per lane per step: 1, 2 or 4 (0 = 2);
@@ -265,10 +265,11 @@ typedef struct {
 
 /*
  * Device scratch a filter call may use: the batched schedule's work
- * counters and, for any schedule, the slots that sum d_counts (16 KiB,
- * whatever n_pairs and the schedule); with APRIL_WS_DECODE_CACHE in
- * opts->flags, plus the compressed filter's decode cache on the current
- * device.
+ * counters, the slots that sum d_counts, and 4 MiB of pair numbers (4 MiB +
+ * 32 KiB in all, whatever n_pairs and the schedule; calls of up to 65,536
+ * pairs mostly use none of it); with APRIL_WS_DECODE_CACHE in opts->flags,
+ * the counters (16 KiB) and the compressed filter's decode cache on the
+ * current device.
  */
 int april_filter_workspace_size(uint64_t n_pairs, const april_filter_opts_t *opts, uint64_t *bytes);
 
@@ -402,7 +403,10 @@ typedef struct april_server april_server_t;
 typedef struct {
     uint32_t mbr_grid;      /* cells per side of the uniform MBR index of S (0 = 1024) */
     uint32_t slots;         /* batches in flight at once, one stream each (0 = 3) */
-    uint64_t mem_budget;    /* device bytes for all slots' buffers (0 = 2 GiB) */
+    uint64_t mem_budget;    /* device bytes for all slots' buffers (0 = 2 GiB); beside
+                               them a quarter as much again at most is held by lists
+                               built on the GPU (see gpu_build_cells), and what their
+                               building takes while it runs */
     uint32_t max_batch;     /* queries per batch at most (0 = 8192) */
     uint32_t host_threads;  /* query-list builder threads (0 = host cores - 2) */
     uint32_t gpu_build_cells;   /* a query whose edges span about this many grid cells
@@ -437,8 +441,8 @@ typedef struct {
 /*
  * S_dev: device lists of S (borrowed: must outlive the server); s_boxes:
  * host float64 [n][4] MBRs of S, copied.  Allocates the MBR index and every
- * slot's buffers up front (no device allocation afterwards) and starts the
- * builder and dispatcher threads.
+ * slot's buffers up front (later only lists that are built on the GPU take
+ * device memory) and starts the builder and dispatcher threads.
  */
 int april_serve_create(const april_lists_t *S_dev, const double *s_boxes,
                        const april_serve_opts_t *opts, april_server_t **out);
@@ -469,8 +473,8 @@ void april_serve_destroy(april_server_t *server);
  * type, or lists of two grid orders.  One wavefront per pair; the same
  * verdict codes (APRIL_TN / APRIL_TH / APRIL_INDECISIVE, APRIL_BAD_PAIR for
  * an index out of range) and count layout as april_filter_pairs; device
- * pointers, asynchronous on `hip_stream` (a 16 KiB stream-ordered scratch
- * when d_counts is given).  Lists must be device-resident and raw. */
+ * pointers, asynchronous on `hip_stream` (calls of more than 65,536 pairs
+ * take a stream-ordered scratch of april_filter_workspace_size bytes).  Lists must be device-resident and raw. */
 
 /*
  * Within join (Sec. 4.3.2): is R[d_r[p]] within S[d_s[p]]?  AA-join first:
@@ -574,7 +578,8 @@ void april_polys_free(april_polys_t *polys);
  *              tested exactly (overwritten)
  * A pair with an id out of range gets APRIL_BAD_PAIR.  Device pointers,
  * asynchronous on `hip_stream` (a 16 KiB stream-ordered scratch holds the
- * work counters and the count sums).
+ * work counters and the count sums; 256 KiB more where polygons have many
+ * edges or lie far apart).
  * Errors: APRIL_E_INVALID (NULL collections or out array with n_pairs > 0,
  * n_pairs >= 2^32, collections on another device), APRIL_E_NOMEM (scratch),
  * APRIL_E_HIP.
