@@ -1698,7 +1698,7 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
         }
         return launch_t<512>(c, chunk, cus, o.waves, stream);
     };
-    if (!R || !S || !can_screen(R, S, a.n_pairs)) return join(b);
+    if (!R || !S || !can_screen_batched(R, S, a.n_pairs)) return join(b);
     return screened_join(b, stream, kChunkPairs, [&](const FilterArgs &f, const OpenLists &open) {
         return launch_screen(R, S, f, cus, workspace, stream, false, open);
     }, join);
@@ -1744,7 +1744,7 @@ int launch_batched_within(const FilterArgs &a, int cus, void *workspace, hipStre
         APRIL_HIP_TRY(hipGetLastError());
     }
     auto join = [&](const BatchArgs &c) { return launch_tc<256, 2, kWithinJoin>(c, cus, 0, stream); };
-    if (!can_screen(R, S, a.n_pairs)) return join(b);
+    if (!can_screen_batched(R, S, a.n_pairs)) return join(b);
     return screened_join(b, stream, kChunkPairs / 2, [&](const FilterArgs &f, const OpenLists &open) {
         return launch_screen(R, S, f, cus, workspace, stream, true, open);
     }, join);

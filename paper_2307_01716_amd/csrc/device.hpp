@@ -147,6 +147,7 @@ int launch_batched(const FilterArgs &a, const april_filter_opts_t &o, int cus, v
 
 // Screening (screen.hip): worth it, and possible, for a call's lists?
 bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs);
+bool can_screen_batched(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs);   // raw lists
 // Decide what the lists' summaries decide: verdicts of all pairs (kPending
 // where the join kernels have to look), and the decided pairs' counts into the
 // slots at `counters` (already cleared) when f.counts is set.  Of f only the

@@ -659,8 +659,24 @@ bool can_screen(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs
     return R->d.sum && S->d.sum && 2 * R->d.n_sums >= R->n && 2 * S->d.n_sums >= S->n;
 }
 
+// Batched calls of more than 2^21 pairs between lists of a few intervals (A-lists
+// of fewer than 6 on average on both sides): a look at a summary costs more than
+// such a join, most of which take a lane each.  8.6M pairs of lists of 3.4 on
+// average: batched 1.02 ms without screening and 1.29 with it, within 2.77 and
+// 3.62, 2.8M pairs with linestrings 0.72 and 1.05; 5.9 on average: 1.69 and 1.70,
+// 2.76 and 2.59, 0.71 and 0.80; 11: 2.39 and 1.45.  Smaller calls go by the lists
+// of open pairs, which are dealt out faster: 0.7M pairs of 3.4 0.23 and 0.15 ms.
+static bool cheap_joins(uint64_t intervals_r, uint64_t n_r, uint64_t intervals_s, uint64_t n_s, uint64_t n_pairs) {
+    return n_pairs > (1ull << 21) && intervals_r < 6 * n_r && intervals_s < 6 * n_s;
+}
+
+bool can_screen_batched(const april_lists_t *R, const april_lists_t *S, uint64_t n_pairs) {
+    return can_screen(R, S, n_pairs) && !cheap_joins(R->n_a, R->n, S->n_a, S->n, n_pairs);
+}
+
 bool can_screen_lines(const april_lists_t *P, const april_cells_t *L, uint64_t n_pairs) {
-    return (n_pairs >= kScreenMin || long_lists(P)) && P->d.sum && L->sum;
+    return (n_pairs >= kScreenMin || long_lists(P)) && P->d.sum && L->sum &&
+           !cheap_joins(P->n_a, P->n, L->n_runs, L->n, n_pairs);
 }
 
 template <int MODE>

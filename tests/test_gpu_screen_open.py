@@ -43,7 +43,7 @@ def stretches(rng, n, m):
 
 
 @pytest.mark.parametrize("kind", ["batched", "plain", "within", "lines"])
-@pytest.mark.parametrize("sizes", [[3, 40, 200], [20, 700]])
+@pytest.mark.parametrize("sizes", [[1, 3, 8], [3, 40, 200], [20, 700]])   # (the shortest: not screened at 2.6M)
 @pytest.mark.parametrize("n", [600_000, 2_600_000])
 def test_stretches(kind, sizes, n):
     print(f"[stretches] {kind} {sizes} {n}", flush=True)
