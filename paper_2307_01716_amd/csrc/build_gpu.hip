@@ -395,10 +395,20 @@ __global__ __launch_bounds__(kBlock) void k_block_rows(RowArgs a) {
             uint32_t got = 0;
             if (lane == 63) got = atomicAdd(&a.taken[i], upto);
             if (EMIT) {
-                uint64_t t = a.base[k] - a.item0 + uint32_t(__shfl(got, 63)) + (upto - n);
-                for (; need; need &= need - 1, t++)
-                    a.key[t] = ((k - a.first_poly) << (2 * a.g.border)) |
-                               hilbert_d(a.g.border, c.x0 + 32 * lane + uint32_t(__builtin_ctz(need)), c.y0 + row);
+                // a lane per block
+                const uint64_t at = a.base[k] - a.item0 + uint32_t(__shfl(got, 63));
+                wave_lds_sync();
+                if (lane < 32) {
+                    mark[lane] = need;
+                    cross[lane] = upto - n;
+                }
+                wave_lds_sync();
+                for (uint32_t b = lane; b < c.nx; b += 64) {
+                    const uint32_t word = mark[b >> 5], bit = 1u << (b & 31);
+                    if (word & bit)
+                        a.key[at + cross[b >> 5] + uint32_t(__popc(word & (bit - 1)))] =
+                            ((k - a.first_poly) << (2 * a.g.border)) | hilbert_d(a.g.border, c.x0 + b, c.y0 + row);
+                }
             }
         }
     }
