@@ -39,7 +39,7 @@
 // scratch, whose mapping and unmapping took up to 80 ms more in a call; now they
 // take 2.0 ms and 55 MB, and the whole call with a filter call behind it 5.0
 // ms, not 20.7 to 98.  k_items takes 0.65 ms to count and 1.04 to write, at
-// 0.9 of the VALU issue peak (783 instructions per item, 1,270 with the
+// 0.87 to 0.89 of the VALU issue peak (783 instructions per item, 1,270 with the
 // writing).  Blocks of 64 x 64 cells, because a wave then has one word of 64
 // cells per lane and one row of cells per lane; at scale a polygon has nine,
 // with 55 edge rows each, about one per lane.

@@ -33,9 +33,9 @@
 // a partition of 10k x 10k objects of 2,250 A-intervals 2.51 and 0.37 ms raw,
 // 8k x 8k 3.37 and 0.53 ms compressed; 40k x 40k with 300 complex objects a side
 // 1.99 and 0.45 ms; 100k x 100k within joins 0.95 and 0.43 ms, linestrings 0.93
-// and 0.30.  Making the summaries takes 0.8 ms for 200k objects.  The kernel issues 38
-// vector instructions per pair, 0.7 of the issue peak; two pairs' searches
-// side by side gained nothing at scale (0.42 ms).
+// and 0.30.  Making the summaries takes 0.7 ms for 200k objects.  The kernel issues 38
+// vector instructions per pair, at 0.63 to 0.68 of the issue peak; two pairs'
+// searches side by side gained nothing at scale (0.42 ms).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -115,7 +115,13 @@ def counters(pmc_dir: str):
 
 
 def _per_kernel(pmc_dir: str, counter: str, kernel: str):
-    got = [v[counter] for _, (n, v) in counters(pmc_dir).items() if n.startswith(kernel) and counter in v]
+    """Values of the kernel's dispatches; "name[a:b]" takes those from the a-th up
+    to the b-th (a run may use one kernel in two kinds of calls)."""
+    lo, hi = 0, None
+    if kernel.endswith("]"):
+        kernel, span = kernel[:-1].split("[")
+        lo, hi = (int(x) for x in span.split(":"))
+    got = [v[counter] for _, (n, v) in counters(pmc_dir).items() if n.startswith(kernel) and counter in v][lo:hi]
     if not got:
         raise ValueError(f"no {counter} for {kernel} in {pmc_dir}")
     return got

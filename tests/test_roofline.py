@@ -43,3 +43,15 @@ def test_calls_of_several_dispatches(tmp_path):
     t = profiling.traffic(str(tmp_path / "fetch"), str(tmp_path / "write"), "k_open", parts=["k_open"], calls=2)
     assert t["fetch_bytes"] == t["write_bytes"] == 2100 / 2 * 1024
     assert profiling.valu(str(tmp_path / "valu"), "k_open", parts=["k_open"], calls=2)["insts_per_launch"] == 1050
+
+
+def test_parts_of_the_dispatches(tmp_path):
+    os.makedirs(tmp_path / "valu")
+    with open(tmp_path / "valu" / "x_counter_collection.csv", "w", newline="") as f:
+        w = csv.DictWriter(f, fieldnames=["Dispatch_Id", "Kernel_Name", "Counter_Name", "Counter_Value"])
+        w.writeheader()
+        for d in range(5):
+            w.writerow({"Dispatch_Id": d, "Kernel_Name": "april::k_screen<0>(X)", "Counter_Name": "SQ_INSTS_VALU",
+                        "Counter_Value": 10 ** d})
+    got = profiling.valu(str(tmp_path / "valu"), "k_screen", parts=["k_screen[1:3]"], calls=2)
+    assert got["insts_per_launch"] == 110 / 2 and got["dispatches"] == 2
