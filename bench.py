@@ -66,7 +66,7 @@ def parse():
     ap.add_argument("--serve-objects", type=int, default=1_000_000)
     ap.add_argument("--gpu-build-cells", type=int, default=0,
                     help="served queries spanning this many grid cells or more are built on the GPU "
-                         "(0: library default 2^18; 4294967295: never)")
+                         "(0: library default 2^14; 4294967295: never)")
     ap.add_argument("--partitioned", action="store_true",
                     help="partitioned join, raw and compressed lists (own JSON line)")
     ap.add_argument("--part-objects", type=int, default=500_000)
