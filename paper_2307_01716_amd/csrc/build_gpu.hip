@@ -10,8 +10,8 @@
 //     (in place) and the checks (lattice, grid ring);
 //  2. one wave per 64 consecutive edges: their box; one wave per polygon:
 //     its extent in cells, which gives its blocks;
-//  3. every block of every polygon (of those of many blocks: every one that is
-//     not empty) is an item with the key (polygon, Hilbert id of the block); a
+//  3. every block of every polygon (of those of many blocks, where it pays: every
+//     one that is not empty) is an item with the key (polygon, Hilbert id of the block); a
 //     radix sort of these keys is the lists' order;
 //  4. one wave per item rasterizes it and counts the interval starts in it;
 //     whether an interval runs on from the block before or into the next one
@@ -244,15 +244,20 @@ __device__ __forceinline__ int64_t floor_w(int64_t v, const Geo &g) {   // floor
 
 // Polygons of this many blocks or more have an item only for the blocks that
 // are not empty (k_block_rows): a sliver across the grid has 2^18 blocks and an
-// edge in a thousand of them.  Such a call takes a further pass over the edges
-// and a further synchronization; with fewer blocks, empty ones included, slivers
+// edge in a thousand of them.  With fewer blocks, empty ones included, slivers
 // take half of what they took when every cell had a key.
 constexpr uint32_t kManyBlocks = 256;
+// That takes two further passes over their edges and a synchronization, 40 to 50
+// us, so it is done where such polygons have this many blocks together.  Without
+// and with it: a sliver of 5k blocks 340 and 352 us, of 20k 389 and 369, of 80k
+// 595 and 414; stars, of whose blocks a third are empty, 350 and 396 us at 2.5k
+// blocks, 523 and 569 at 40k, 1,280 and 1,253 at 160k.
+constexpr uint64_t kManyTotal = 1ull << 16;
 
 // One wave per polygon; item count of polygon k in items[k] (items[n] = 0).
-// Polygons of many blocks are listed, *n_many of them.
+// Polygons of many blocks are listed, found[0] of them with found[1] blocks.
 __global__ __launch_bounds__(256) void k_polygons(PolyArgs a, Blocks *blocks, uint64_t *items, uint32_t *many,
-                                                  uint32_t *n_many, unsigned long long *err) {
+                                                  unsigned long long *found, unsigned long long *err) {
     const uint32_t lane = threadIdx.x & 63;
     const uint64_t waves = uint64_t(gridDim.x) * (blockDim.x / 64);
     for (uint64_t k = uint64_t(blockIdx.x) * (blockDim.x / 64) + (threadIdx.x >> 6); k < a.n; k += waves) {
@@ -287,7 +292,10 @@ __global__ __launch_bounds__(256) void k_polygons(PolyArgs a, Blocks *blocks, ui
             c.ny = uint16_t((j1 >> 6) - (j0 >> 6) + 1);
             blocks[k] = c;
             items[k] = uint64_t(c.nx) * c.ny;
-            if (items[k] >= kManyBlocks) many[atomicAdd(n_many, 1u)] = uint32_t(k);
+            if (items[k] >= kManyBlocks) {
+                many[atomicAdd(found, 1ull)] = uint32_t(k);
+                atomicAdd(found + 1, (unsigned long long)items[k]);
+            }
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) items[a.n] = 0;
@@ -480,6 +488,7 @@ struct ItemArgs {
     const Blocks *blocks;
     const uint64_t *base;      // first item of polygon k (of all polygons)
     uint64_t first_poly, n_polys, item0, n_items;   // the group of polygons at work
+    uint32_t many;             // polygons of so many blocks: keys by k_block_rows
     uint64_t *key;             // (polygon - first_poly) << 2 border | Hilbert id of the block
     uint32_t *place;           // the block: x | y << 12 | state of the curve in it << 24
     uint32_t *info;
@@ -503,7 +512,7 @@ __global__ void k_item_keys(ItemArgs a) {
         else hi = mid;
     }
     const Blocks c = a.blocks[lo];
-    if (uint32_t(c.nx) * c.ny >= kManyBlocks) return;   // (k_block_rows)
+    if (uint32_t(c.nx) * c.ny >= a.many) return;   // (k_block_rows)
     const uint32_t i = uint32_t(a.item0 + t - a.base[lo]);
     a.key[t] = ((lo - a.first_poly) << (2 * a.g.border)) |
                hilbert_d(a.g.border, c.x0 + i % c.nx, c.y0 + i / c.nx);
@@ -1038,7 +1047,7 @@ int april::build_lists_gpu(const april_grid_t *grid, const double *xy, const uin
     EdgeBox *d_box = sc.get<EdgeBox>(n_boxes);
     uint32_t *d_distinct = sc.get<uint32_t>(n_boxes);
     Blocks *d_blocks = sc.get<Blocks>(n);
-    // err; bound of the cells; bad slot, longest list, long A-lists; polygons of many blocks
+    // err; bound of the cells; bad slot, longest list, long A-lists; polygons of many blocks, their blocks
     unsigned long long *d_small = sc.get<unsigned long long>(8);
     uint32_t *d_many = sc.get<uint32_t>(n), *d_taken = sc.get<uint32_t>(n);
     void *d_scan = sc.get<char>(scan_bytes);
@@ -1052,11 +1061,11 @@ int april::build_lists_gpu(const april_grid_t *grid, const double *xy, const uin
     PolyArgs pa{d_xy, d_voff, n, n_boxes, d_box, d_distinct, d_small + 1, g};
     k_edge_boxes<<<uint32_t(std::min<uint64_t>((n_boxes + 3) / 4, uint64_t(st->cus) * 8)), 256, 0, s>>>(pa);
     k_polygons<<<uint32_t(std::min<uint64_t>((n + 3) / 4, 16384)), 256, 0, s>>>(
-        pa, d_blocks, d_items, d_many, reinterpret_cast<uint32_t *>(d_small + 5), d_small);
+        pa, d_blocks, d_items, d_many, d_small + 5, d_small);
     BG_TRY(hipGetLastError());
     BG_TRY(hipcub::DeviceScan::ExclusiveSum(d_scan, scan_bytes, d_items, d_base, n + 1, s));
-    uint64_t h[6] = {0, 0}, items = 0;   // as d_small; items
-    BG_TRY(hipMemcpyAsync(h, d_small, 48, hipMemcpyDeviceToHost, s));
+    uint64_t h[7] = {0, 0}, items = 0;   // as d_small; items
+    BG_TRY(hipMemcpyAsync(h, d_small, 56, hipMemcpyDeviceToHost, s));
     BG_TRY(hipMemcpyAsync(&items, d_base + n, 8, hipMemcpyDeviceToHost, s));
     BG_TRY(hipStreamSynchronize(s));
     if (h[0] != ~0ull) {
@@ -1076,7 +1085,7 @@ int april::build_lists_gpu(const april_grid_t *grid, const double *xy, const uin
             return fail(APRIL_E_NOMEM, "more than 2^32 boundary-cell entries in one call: split the collection");
     }
 
-    // polygons of many blocks: items only where they are needed
+    // polygons of many blocks: items only where they are needed, if that pays
     RowArgs ra{};
     ra.xy = d_xy;
     ra.voff = d_voff;
@@ -1084,7 +1093,7 @@ int april::build_lists_gpu(const april_grid_t *grid, const double *xy, const uin
     ra.blocks = d_blocks;
     ra.many = d_many;
     ra.taken = d_taken;
-    ra.n_many = uint32_t(h[5]);
+    ra.n_many = h[6] >= kManyTotal ? uint32_t(h[5]) : 0u;
     ra.g = g;
     ra.base = d_base;
     const dim3 row_grid(std::min(ra.n_many, 1024u), kRowBlocks);
@@ -1138,6 +1147,7 @@ int april::build_lists_gpu(const april_grid_t *grid, const double *xy, const uin
     ia.base = d_base;
     ia.info = d_info;
     ia.place = d_place;
+    ia.many = ra.n_many ? kManyBlocks : ~0u;
     ia.g = g;
     ia.n = n;
     ia.ai = d_ai;

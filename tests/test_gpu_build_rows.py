@@ -44,14 +44,16 @@ def star(rng, radius):
     return np.stack([r * np.cos(t), r * np.sin(t)], 1)
 
 
-# 16 x 16 blocks are 1,024 cells a side
+# 16 x 16 blocks are 1,024 cells a side; of each size enough that the blocks are
+# left out (16), or too few (3)
+@pytest.mark.parametrize("each", [16, 3])
 @pytest.mark.parametrize("kind", ["sliver", "ring", "comb", "star"])
 @pytest.mark.parametrize("w, quantum", [(1 << 14, 1), (1 << 14, 1 << 13), (1 << 21, 1), (1 << 10, 64 << 10), (8, 4)])
-def test_sparse(kind, w, quantum):
+def test_sparse(kind, w, quantum, each):
     rng = np.random.default_rng(w % 1000 + quantum % 1000 + len(kind))
     shapes = []
     for size in (700, 960, 1000, 1024, 1090, 1500, 3000, 7800):
-        for _ in range(3):
+        for _ in range(each):
             s = {"sliver": lambda: sliver(rng, 1.2 * size), "ring": lambda: ring(rng, size / 2),
                  "comb": lambda: comb(rng, size), "star": lambda: star(rng, size / 2)}[kind]()
             lo, hi = s.min(0), s.max(0)
@@ -69,6 +71,28 @@ def test_sparse(kind, w, quantum):
     ps = PolygonSet(np.concatenate(shapes) * LATTICE, voff)
     grid = (0.0, 0.0, float(w << ORDER) * LATTICE, ORDER)
     print(f"[build rows] {kind}, cell {w}: {len(ps)} polygons, {len(ps.xy)} vertices", flush=True)
+    host = april.april_build_lists(grid, ps.xy, ps.voff, april.STRICT).export()
+    got = april.april_lists_download(april.april_build_lists_gpu(grid, ps.xy, ps.voff, april.STRICT)).export()
+    for name, x, y in zip(("offA", "sA", "eA", "offF", "sF", "eF"), host, got):
+        assert np.array_equal(x, y), name
+
+
+# rings of 128 x 128 blocks, four of which are as many as it takes
+@pytest.mark.parametrize("columns", [(128,), (128,) * 3 + (127,), (128,) * 4, (128,) * 4 + (16,), (16,) * 257, (16,) * 255])
+def test_how_many_blocks(columns):
+    rng = np.random.default_rng(len(columns) + columns[-1])
+    shapes = []
+    for nx in columns:
+        side = 64.0 * np.array([nx, 128 if nx > 16 else 16])
+        t, width = np.linspace(0.1, 5.5, 50), rng.uniform(3, 90)
+        u = np.stack([np.cos(t), np.sin(t)], 1)
+        s = np.concatenate([u * (side / 2 - 4), (u * (side / 2 - 4 - width))[::-1]])
+        s[0], s[len(t) // 2] = side / 2 - 3, 3 - side / 2   # (the whole of its blocks)
+        at = 64 * rng.integers(0, 127 - 15 if nx == 16 else 129 - nx, 2) * (1, nx == 16)
+        shapes.append(np.round((s + side / 2 + at) * (1 << 14)))
+    voff = np.concatenate([[0], np.cumsum([len(s) for s in shapes])]).astype(np.int64)
+    ps = PolygonSet(np.concatenate(shapes) * LATTICE, voff)
+    grid = (0.0, 0.0, float(1 << (14 + ORDER)) * LATTICE, ORDER)
     host = april.april_build_lists(grid, ps.xy, ps.voff, april.STRICT).export()
     got = april.april_lists_download(april.april_build_lists_gpu(grid, ps.xy, ps.voff, april.STRICT)).export()
     for name, x, y in zip(("offA", "sA", "eA", "offF", "sF", "eF"), host, got):
